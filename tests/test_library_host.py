@@ -431,3 +431,35 @@ def test_which_constants_a_plan_still_reads():
         B.clg_plan_reads_constant(plan.h, d.outputs[0])
     assert e.value.status == "UNKNOWN_ID"
     s.close()
+
+
+@pytest.mark.parametrize("width", [1, 62, 63, 64, 65, 130])
+def test_search_with_matches_that_span_many_positions(width):
+    """`width` parallel chains: the positions of one chain's operators lie `width` apart, so that a match spans one
+    or more words of the search's covered-operator windows; the first chain also has single-operator matches."""
+    d = wl.GraphDesc("wide")
+    x = d.input(np.zeros((1, 2, 4, 4), np.float32))
+    y = d.input(np.zeros((1, 3, 4, 4), np.float32))
+    w = d.const(np.zeros((2, 2, 3, 3), np.float32))
+    w0 = d.const(np.zeros((3, 3, 3, 3), np.float32))
+    b, b0 = d.const(np.zeros(2, np.float32)), d.const(np.zeros(3, np.float32))
+    convs = [d.op("conv2d", [x if i else y, w if i else w0], stride=(1, 1), pad=(1, 1), groups=1) for i in range(width)]
+    biases = [d.op("bias_add", [c, b if i else b0], axis=1) for i, c in enumerate(convs)]
+    for i, v in enumerate(biases):
+        d.mark_output(d.op("relu" if i else "tanh", [v]))
+    conv = P("conv2d", W, W)
+    reg = [("direct", P("relu", P("bias_add", conv, W))), ("igemm", P("relu", P("bias_add", conv, W))),
+           ("direct", P("tanh", P("bias_add", conv, W))), ("igemm_r16", P("bias_add", conv, W)), ("eltwise", P("tanh", W)),
+           ("eltwise", P("tanh", P("bias_add", W, W)))]
+    s = clg.Session(d, reg, device=None)
+    g = Graph(d)
+    oms = enumerate_matches(g, reg)
+    _same_matches(s.match(), oms)
+    for seed in range(3):
+        # tanh(bias_add(conv)) as one match or two; a relu chain has to be one match, so its partial matches are priced out
+        costs = wl.synthetic_costs(len(oms), seed, ties=seed == 2)
+        for i, m in enumerate(oms):
+            if reg[m.pattern][1][0] == "bias_add" and m.first != convs[0]:
+                costs[i] = B.COST_INF
+        assert s.search(costs, 7) == search.dp(g, reg, oms, costs, 7)
+    s.close()
