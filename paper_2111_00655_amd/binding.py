@@ -7,6 +7,7 @@ paper_2111_00655_amd.build); there is no fallback.
 from __future__ import annotations
 
 import ctypes as C
+import gc
 import os
 
 import numpy as np
@@ -32,6 +33,7 @@ ATTR_ID = {k: i for i, k in enumerate(("groups", "kernel_h", "kernel_w", "stride
 STATUS = {0: "OK", -1: "INVALID_ARG", -2: "SHAPE_MISMATCH", -3: "NO_KERNEL", -4: "NOT_A_COVER",
           -5: "OVERLAP", -6: "UNKNOWN_ID", -7: "WORKSPACE_TOO_SMALL", -8: "HIP_ERROR",
           -9: "OUT_OF_MEMORY", -10: "IO_ERROR", -11: "BUFFER_TOO_SMALL"}
+BUFFER_TOO_SMALL = -11
 F32, I32 = 0, 1
 
 
@@ -389,11 +391,23 @@ def clg_evolve(n, opts, rand, fitness):
 
 # ---- matches ------------------------------------------------------------------------
 def clg_match_all(ctx, g):
+    # one enumeration where the guess of its size holds (NasNet-A has 10 matches per node under twenty variant
+    # backends, ResNet-50 13), a second one into an array of the right size where it does not
     n = C.c_size_t()
-    _check(lib().clg_match_all(ctx, g, None, 0, C.byref(n)))
-    arr = (Match * max(n.value, 1))()
-    _check(lib().clg_match_all(ctx, g, arr, n.value, C.byref(n)))
-    return [arr[i] for i in range(n.value)]
+    arr = (Match * (16 * max(clg_graph_num_nodes(g), 1)))()
+    rc = lib().clg_match_all(ctx, g, arr, len(arr), C.byref(n))
+    if rc == BUFFER_TOO_SMALL:        # the array is too short: n holds the count
+        arr = (Match * n.value)()
+        rc = lib().clg_match_all(ctx, g, arr, n.value, C.byref(n))
+    _check(rc)
+    # thousands of small objects at once: without this the collector runs a score of times on the way
+    collecting = gc.isenabled()
+    gc.disable()
+    try:
+        return arr[:n.value]
+    finally:
+        if collecting:
+            gc.enable()
 
 
 # ---- measurer ------------------------------------------------------------------------

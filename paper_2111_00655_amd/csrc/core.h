@@ -57,12 +57,27 @@ struct Node {
     bool is_op() const { return kind >= 0; }
 };
 
+// A short list of graph values kept inside its owner: thousands of matches are enumerated at a time, and
+// three heap blocks each cost more than finding them.
+template <int CAP>
+struct IdList {
+    int32_t n = 0;
+    int32_t v[CAP];
+    size_t size() const { return (size_t)n; }
+    int32_t operator[](size_t i) const { return v[i]; }
+    int32_t *begin() { return v; }
+    int32_t *end() { return v + n; }
+    const int32_t *begin() const { return v; }
+    const int32_t *end() const { return v + n; }
+    void push_back(int32_t x) { v[n++] = x; }
+};
+
 struct MatchRec {
     int32_t pattern = 0, backend = 0, first = 0, sink = 0;
-    std::vector<int32_t> nodes;       // ascending node id
-    std::vector<int32_t> binding;     // op pattern nodes in pattern order
-    std::vector<int32_t> wild;        // graph value bound to each pattern node
-                                      // (all pattern nodes, wildcards included)
+    IdList<CLG_MAX_MATCH_NODES> nodes;      // ascending node id
+    IdList<CLG_MAX_MATCH_NODES> binding;    // op pattern nodes in pattern order
+    IdList<CLG_MAX_PATTERN_NODES> wild;     // graph value bound to each pattern node
+                                            // (all pattern nodes, wildcards included)
 };
 
 struct Context;
