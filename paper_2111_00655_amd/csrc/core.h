@@ -146,7 +146,7 @@ struct Operand {
 
 enum CallKind : int32_t {
     CALL_GEMM = 0, CALL_DIRECT_CONV, CALL_POOL, CALL_GAP, CALL_ROWWISE,
-    CALL_ELTWISE, CALL_LAYOUT, CALL_CONCAT, CALL_SEPCONV, CALL_ATTENTION
+    CALL_ELTWISE, CALL_LAYOUT, CALL_CONCAT, CALL_SEPCONV, CALL_ATTENTION, CALL_B3
 };
 
 struct KernelCall {
@@ -172,6 +172,7 @@ struct KernelCall {
     LayoutArgs layout{};
     ConcatArgs cat{};                                  // operands in epi_nodes[0..n)
     AttentionArgs att{};                               // a = q, b = k, c = v
+    B3Args b3{};                                       // a = x, b = weights (packed by the plan)
     SepConvArgs sep{};                                 // a = x, b = 1x1 weights (packed by the plan), c = depthwise weights
     KernelCall() { for (auto &e : epi_nodes) e = -1; }
 };

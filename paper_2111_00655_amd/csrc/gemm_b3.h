@@ -1,0 +1,491 @@
+// Contractions on the bf16 matrix cores with fp32 operands and fp32 results
+// ("b3": every operand as the exact sum of three bf16 values).
+//
+// gfx950's fp32 MFMA runs at 157 TFLOP/s, its bf16 MFMA at 2.5 PFLOP/s.  An fp32
+// number x has 24 significant bits, a bf16 has 8, and
+//     h = bf16(x), m = bf16(x - h), l = bf16(x - h - m)      (round to nearest)
+// holds x exactly (both differences are exact in fp32).  A product is then
+//     a b = ah bh + ah bm + am bh + am bm + ah bl + al bh    (+ am bl + al bm + al bl)
+// where every product of two bf16 values is exact in the fp32 accumulator's
+// format and the three terms left out are below 2^-23 |a b| together (2^-26 rms,
+// random in sign): less than what one rounding of a fp32 accumulation loses.
+// Against float64 the results are two to three times closer than the fp32 MFMA
+// kernels' own (3x3 convolution, K = 2304, two K-waves: 1.9e-7 of the result's norm
+// against 4.2e-7): the leading products have an accumulator of their own, which is
+// rounded once per 16 values of k instead of once per 2.  Six bf16 MFMAs of 32x32x16
+// take 192 cycles of a matrix core, eight fp32 MFMAs of 32x32x2 take 512: 417 instead
+// of 157 TFLOP/s.  An operand that is infinite, or
+// within 2^-9 of the largest float, gives NaN where a fp32 product chain would give an
+// infinity; magnitudes below 2^-110 lose their last bits (absolute error < 2^-126).
+//
+// Structure.  A wave owns 32 output rows (channels) and TN tiles of 32 output columns
+// (pixels); a workgroup has WM waves along the rows, WN along the columns and WK that
+// share a tile and split K.
+//  * Weights are constants: they are split and packed once per plan in the order in which a
+//    wave consumes them (32 rows x 16 values of k = three 1 KB planes, 16 bytes per lane), and
+//    are read straight into registers, R steps ahead.
+//  * The input is staged through LDS once per 16 * SC channels, double-buffered: a lane loads eight
+//    channels of one position (coalesced along the positions), splits them (5.5 vector
+//    instructions per value) and writes three 16-byte pieces.  The positions ("slots") are the
+//    input patch that the tile's output pixels touch, so a 3x3 filter loads and splits a value once
+//    instead of nine times; a tap is a constant offset into the patch, and padding is a slot
+//    that stays zero.
+//  * What a tile covers: a strip of TW output columns is walked row by row, image after
+//    image (or depth slice after depth slice), and a tile is BN consecutive pixels of
+//    that walk; small images share a tile, large ones are cut into strips so that the patch
+//    stays compact.
+//  * First layers have too few channels to fill the 16 values of k of an MFMA: their filter columns
+//    (and depth taps) are folded into the channel index (FOLD), with an offset table behind the
+//    packed weights.
+//  * Transposed convolution: the stride^2 sub-pixel phases are stride-1 convolutions over the
+//    same input patch; a phase is a further block of output rows with its own tap offset.
+#pragma once
+
+#include <utility>
+
+#include <hip/hip_runtime.h>
+
+#include "device_common.h"
+
+namespace clg {
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x2v __attribute__((ext_vector_type(2)));
+typedef float f32x16v __attribute__((ext_vector_type(16)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));        // 16 bytes at any float address
+
+template <int WM_, int WN_, int WK_, int TN_, int CW1_ = 2>
+struct B3Cfg {
+    static constexpr int WM = WM_, WN = WN_, WK = WK_, TN = TN_, CW1 = CW1_;
+    static constexpr int NW = WM * WN * WK, NT = NW * kWave;
+    static constexpr int BM = 32 * WM, BN = 32 * TN * WN;
+    static constexpr int RED = WK > 1 ? NW * TN * 16 * kWave * 4 : 0;      // bytes in which the K-waves meet
+};
+// (b3_shape in gemm_b3.hip lists the same numbers)
+using B3L = B3Cfg<4, 2, 1, 2, 4>;    // 128 x 128, eight waves
+using B3LM = B3Cfg<2, 2, 1, 2>;      // 64 x 128
+using B3M = B3Cfg<2, 1, 2, 2>;       // 64 x 64, two K-waves
+using B3S = B3Cfg<1, 1, 4, 2>;       // 32 x 64, four K-waves
+using B3SS = B3Cfg<1, 1, 4, 1>;      // 32 x 32, four K-waves
+using B3G = B3Cfg<1, 4, 1, 2>;       // 32 x 256: few output rows (grouped convolutions)
+using B3G2 = B3Cfg<1, 4, 1, 1>;      // 32 x 128
+
+// 16-channel blocks per K-wave and stage; registers sets of the weight stream (a set is loaded R - 1 steps ahead)
+template <class C, int TAPS>
+constexpr int b3_cw() { return TAPS == 1 ? C::CW1 : 1; }
+template <class C, int TAPS>
+constexpr int b3_ring() { return TAPS == 1 ? C::CW1 : (TAPS == 9 || TAPS == 3 ? 3 : 4); }
+// staging units (16 channels x 32 slots) per wave and stage of 1x1 filters and dense layers
+template <class C>
+constexpr int b3_units1() { return C::WK * C::CW1 * C::TN * C::WN / C::NW; }
+
+// n / d for d >= 2: m = floor(2^32 / d) + 1, one = 0; d = 1: m = 0, one = ~0
+__device__ __forceinline__ uint32_t b3_div(uint32_t n, const B3Div &d) { return __umulhi(n, d.m) + (n & d.one); }
+
+// One pair of values -> a 32-bit word of each plane.
+__device__ __forceinline__ void b3_split2(float a, float b, uint32_t &h, uint32_t &m, uint32_t &l) {
+    h = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2v{a, b}, bf16x2));
+    a -= __uint_as_float(h << 16);
+    b -= __uint_as_float(h & 0xffff0000u);
+    m = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2v{a, b}, bf16x2));
+    a -= __uint_as_float(m << 16);
+    b -= __uint_as_float(m & 0xffff0000u);
+    l = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2v{a, b}, bf16x2));
+}
+
+__device__ __forceinline__ float b3_finish(const EpiFast &ef, float v, float bias_v, float add_v) {
+    const int f = ef.flags;
+    if (f & EF_SCALE) v *= ef.scale;
+    v += bias_v;
+    v += add_v;
+    if (f & EF_RELU) v = v > 0.f ? v : 0.f;
+    else if (f & EF_GELU) v = gelu_erf(v);
+    else if (f & EF_TANH) v = tanhf(v);
+    return v;
+}
+
+// (the same mapping as the other tiled kernels': an XCD gets a contiguous range of tiles)
+__device__ __forceinline__ int b3_xcd_remap(int id, int n) {
+    const int q = n / 8, r = n % 8;
+    const int xcd = id % 8, idx = id / 8;
+    return xcd * q + (xcd < r ? xcd : r) + idx;
+}
+
+// f(0), f(1), ..., f(N - 1) with the index as a compile-time constant
+template <class F, int... I>
+__device__ __forceinline__ void b3_each(F &&f, std::integer_sequence<int, I...>) { (f(std::integral_constant<int, I>{}), ...); }
+template <int N, class F>
+__device__ __forceinline__ void b3_for(F &&f) { b3_each(f, std::make_integer_sequence<int, N>{}); }
+
+// LDS written by this workgroup is visible behind it; loads from memory stay in flight
+__device__ __forceinline__ void b3_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+// Loads through a buffer descriptor: a lane whose offset is kOut (beyond the buffer) gets zero.
+constexpr uint32_t kB3Out = 0x80000000u;
+
+template <class C, int TAPS, bool FOLD, bool DENSE, int UM>
+__global__ __launch_bounds__(C::NT, 2) void b3_kernel(B3Args p) {
+    constexpr int CW = b3_cw<C, TAPS>(), SC = C::WK * CW, Q = CW * TAPS, R = b3_ring<C, TAPS>();
+    constexpr int TN = C::TN, WK = C::WK;
+    static_assert(Q % R == 0, "the ring of weight registers must divide the steps of a stage");
+    extern __shared__ u32x4 b3_lds[];
+    const int tid = threadIdx.x;
+    const int lane = tid & (kWave - 1), half = lane >> 5, l32 = lane & 31;
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int wk = wave % WK, wn = (wave / WK) % C::WN, wm = wave / (WK * C::WN);
+
+    // tile -> (row group, column tile); the faster one is what neighbouring workgroups do not share
+    const int tile = b3_xcd_remap(blockIdx.x, gridDim.x);
+    const int t_hi = (int)b3_div((uint32_t)tile, p.d_tile), t_lo = tile - t_hi * p.tile_div;
+    const int mg = p.jmajor ? t_lo : t_hi, nt = p.jmajor ? t_hi : t_lo;
+    const int mt = min(mg * C::WM + wm, p.mtiles - 1);                     // packed row tile (all phases)
+    const bool m_live = mg * C::WM + wm < p.mtiles;
+    const int phase = p.phases > 1 ? mt / p.tiles_m : 0;
+    const int i0 = (mt - phase * p.tiles_m) * 32;
+    const int ph_a = p.phases > 1 ? phase / p.sw : 0, ph_b = p.phases > 1 ? phase - ph_a * p.sw : 0;
+    const int ks = blockIdx.z;
+    const int st_begin = ks * p.stages_per, st_end = min(p.stages, st_begin + p.stages_per);
+
+    const int strip = DENSE ? 0 : (int)b3_div((uint32_t)nt, p.d_strip);
+    const int j0 = (DENSE ? nt : nt - strip * p.tiles_strip) * C::BN;
+    // slots per 8-channel row of a plane (16-byte units), and one plane
+    const int S = TAPS == 1 ? (DENSE ? C::BN + 2 : C::BN) : p.slot_stride;
+    const int PL = 2 * SC * S;
+    int v0 = 0;
+    if constexpr (!DENSE) {
+        const uint32_t g = b3_div((uint32_t)j0, p.d_tw), im = b3_div(g, p.d_ho);
+        v0 = (int)im * p.rpi + ((int)g - (int)im * p.HO) * p.ly;
+    }
+
+    // ---- weights: this wave's stream, three planes of 64 lanes x 16 bytes per step
+    const u32x4 *Aw = reinterpret_cast<const u32x4 *>(p.w) + (((int64_t)mt * WK + wk) * p.stages + st_begin) * (Q * 3 * kWave);
+    const uint32_t lane_u = (uint32_t)lane;
+    u32x4 ar[R][3];
+#pragma unroll
+    for (int r = 0; r + 1 < R; ++r)
+#pragma unroll
+        for (int k = 0; k < 3; ++k) ar[r][k] = (Aw + (r * 3 + k) * kWave)[lane_u];
+    Aw += (R - 1) * 3 * kWave;
+
+    // ---- staging units of this wave: (16-channel block of the stage, 32 slots); a lane takes eight channels (its half).
+    // A wave short of units repeats the last one (the same values to the same place).
+    const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(p.x), (short)0, p.x_bytes, 0x00020000);
+    uint32_t off[UM];                                                      // byte offset, or kB3Out: the slot is padding
+    int ldsw[UM], c16l[UM];
+    int iwu[FOLD ? UM : 1], idu[FOLD ? UM : 1];
+#pragma unroll
+    for (int u = 0; u < UM; ++u) {
+        const int unit = TAPS == 1 ? wave + u * C::NW : min(wave + u * C::NW, p.units - 1);
+        if constexpr (DENSE) {
+            // 16 rows x 32 values of k: four lanes per row read 128 contiguous bytes
+            const int c32 = unit / (C::BN / 16), grp = unit % (C::BN / 16);
+            const int row = grp * 16 + (lane >> 2), part = lane & 3;
+            c16l[u] = c32 * 32 + part * 8;                                 // first k of the lane within the stage
+            off[u] = (uint32_t)min(j0 + row, p.Nrows - 1) * (uint32_t)p.ldx;
+            ldsw[u] = (c32 * 4 + part) * S + row;
+        } else {
+            const int c16 = TAPS == 1 ? unit / (C::BN / 32) : (int)b3_div((uint32_t)unit, p.d_g32);
+            const int grp = TAPS == 1 ? unit % (C::BN / 32) : unit - c16 * p.g32;
+            const int slot = grp * 32 + l32;
+            int im, ih, iw;
+            bool in;
+            if constexpr (TAPS == 1) {                                     // a slot is an output pixel
+                const uint32_t g = b3_div((uint32_t)(j0 + slot), p.d_tw);
+                im = (int)b3_div(g, p.d_ho);
+                ih = ((int)g - im * p.HO) * p.ys;
+                iw = (strip * p.TW + j0 + slot - (int)g * p.TW) * p.xs;
+                in = im < p.Nimg && iw < p.W;
+            } else {
+                const int r = (int)b3_div((uint32_t)slot, p.d_pw), x = slot - r * p.pw_slots;
+                const int v = v0 + r;
+                im = (int)b3_div((uint32_t)v, p.d_rpi);
+                ih = (v - im * p.rpi) * p.ys - p.ph;
+                iw = (strip * p.TW * p.lx + x) * p.xs - p.pwd;
+                in = im < p.Nimg && ih >= 0 && ih < p.H && ((FOLD && p.fold_w) || (iw >= 0 && iw < p.W));
+            }
+            int n = im, od = 0;
+            if (p.DO > 1) {
+                n = (int)b3_div((uint32_t)im, p.d_do);
+                od = im - n * p.DO;
+            }
+            const int id0 = od * p.sd - p.pd;
+            const int32_t o = (n * p.img_stride + id0 * p.HW + ih * p.W + iw) * 4;
+            if constexpr (FOLD) {
+                off[u] = (uint32_t)o;
+                iwu[u] = in ? iw : -(1 << 20);                             // a padding slot: no filter column reaches the input
+                idu[u] = id0;
+            } else {
+                off[u] = in ? (uint32_t)(o + half * 32 * p.cs) : kB3Out;
+            }
+            c16l[u] = c16;
+            ldsw[u] = (c16 * 2 + half) * S + slot;
+        }
+    }
+    const int cbase = (!DENSE && p.groups > 1) ? (int)b3_div((uint32_t)i0, p.d_cpgo) * p.cpg_in : 0;
+
+    float xv[UM][8];
+    auto load = [&](int u, int st_) {
+        const int st = min(st_, p.stages - 1);
+        if constexpr (DENSE) {
+            const int k = min(st * SC * 16 + c16l[u], p.K - 8);            // past the end: finite values that meet zero weights
+            const uint32_t o = (off[u] + (uint32_t)k) * 4;
+            const u32x4 a = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)o, 0, 0));
+            const u32x4 b = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)o, 16, 0));
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                xv[u][i] = __uint_as_float(a[i]);
+                xv[u][4 + i] = __uint_as_float(b[i]);
+            }
+        } else if constexpr (FOLD) {
+            const int2 *tab = reinterpret_cast<const int2 *>(p.table) + (st * SC + c16l[u]) * 16;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const int2 e0 = tab[i], e1 = tab[8 + i];
+                const int eo = half ? e1.x : e0.x, ek = half ? e1.y : e0.y;
+                const bool in = (uint32_t)(idu[u] + (ek & 0xffff)) < (uint32_t)p.D && (uint32_t)(iwu[u] + (ek >> 16)) < (uint32_t)p.W;
+                const uint32_t o = in ? off[u] + (uint32_t)eo : kB3Out;
+                xv[u][i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsrc, (int)o, 0, 0));
+            }
+        } else {
+            const int c = cbase + min(st * SC + c16l[u], p.nC - 1) * 16;   // past the last block: meets zero weights
+            const int so = c * p.cs * 4;
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                xv[u][i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsrc, (int)off[u], so + i * p.cs * 4, 0));
+        }
+    };
+    u32x4 pl[3];
+    // piece n of a stage's staging work: unit n / 4, pair n % 4; the last pair of a unit writes it and loads its next values
+    auto piece = [&](int n, int buf, int st_next) {
+        const int u = n / 4, i = n % 4;
+        uint32_t h, m, l;
+        b3_split2(xv[u][2 * i], xv[u][2 * i + 1], h, m, l);
+        pl[0][i] = h;
+        pl[1][i] = m;
+        pl[2][i] = l;
+        if (i == 3) {
+            u32x4 *dst = b3_lds + buf * 3 * PL + ldsw[u];
+#pragma unroll
+            for (int k = 0; k < 3; ++k) dst[k * PL] = pl[k];
+            load(u, st_next);
+        }
+    };
+#pragma unroll
+    for (int u = 0; u < UM; ++u) load(u, st_begin);
+
+    // ---- this lane's column of every tile: first slot
+    int sbase[TN];
+#pragma unroll
+    for (int t = 0; t < TN; ++t) {
+        const int jl = (wn * TN + t) * 32 + l32;
+        if constexpr (TAPS == 1) {
+            sbase[t] = jl + half * S;
+        } else {
+            const uint32_t jj = (uint32_t)min(j0 + jl, p.Ntot - 1);
+            const uint32_t g = b3_div(jj, p.d_tw), im = b3_div(g, p.d_ho);
+            const int oh = (int)g - (int)im * p.HO;
+            sbase[t] = ((int)im * p.rpi + oh * p.ly - v0) * p.pw_slots + ((int)jj - (int)g * p.TW) * p.lx + half * S;
+        }
+        sbase[t] += wk * CW * 2 * S;
+        if (TAPS == 4) {                                                   // where the phase's taps start in the common patch
+            const int dh = p.phe_max - (p.KHe - 1 - (ph_a + p.ph_t) / p.sh), dw = p.pwe_max - (p.KWe - 1 - (ph_b + p.pw_t) / p.sw);
+            sbase[t] += dh * p.pw_slots + dw;
+        }
+    }
+#pragma unroll
+    for (int n = 0; n < 4 * UM; ++n) piece(n, 0, st_begin + 1);
+
+    // Two accumulators per tile: the products of the leading planes, and the five small ones (2^-8 of them and
+    // less).  The large sum is then rounded once per 16 values of k.
+    f32x16v acc[TN], acs[TN];
+#pragma unroll
+    for (int t = 0; t < TN; ++t)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[t][r] = acs[t][r] = 0.f;
+
+    bf16x8 b[2][TN][3];
+    constexpr int KWt = TAPS == 9 ? 3 : (TAPS == 4 ? 2 : 1);
+    auto read_b = [&](int set, int q, int buf) {
+        const int tap = q % TAPS;
+        const int kh = TAPS == 8 ? min(tap, p.KHe - 1) : tap / KWt, kw = tap % KWt;
+        const int so = buf * 3 * PL + (q / TAPS) * 2 * S + (TAPS == 1 ? 0 : kh * p.pw_slots + kw);
+#pragma unroll
+        for (int t = 0; t < TN; ++t)
+#pragma unroll
+            for (int k = 0; k < 3; ++k) b[set][t][k] = reinterpret_cast<const bf16x8 *>(b3_lds)[k * PL + so + sbase[t]];
+    };
+    b3_barrier();
+    for (int st = st_begin; st < st_end; ++st) {
+        const int buf = (st - st_begin) & 1;
+        read_b(0, 0, buf);
+        b3_for<Q>([&](auto qc) {
+            constexpr int q = qc.value;
+            // the next step's input fragments and a later step's weights leave before this step's products
+            if constexpr (q + 1 < Q) read_b((q + 1) & 1, q + 1, buf);
+#pragma unroll
+            for (int k = 0; k < 3; ++k) ar[(q + R - 1) % R][k] = (Aw + k * kWave)[lane_u];      // (the stream is padded by R steps)
+            Aw += 3 * kWave;
+            __builtin_amdgcn_sched_barrier(0);
+            bf16x8 a[3];
+#pragma unroll
+            for (int k = 0; k < 3; ++k) a[k] = __builtin_bit_cast(bf16x8, ar[q % R][k]);
+            b3_for<6 * TN>([&](auto mc) {
+                constexpr int m = mc.value / TN, t = mc.value % TN;
+                constexpr int PA[6] = {0, 2, 0, 1, 1, 0}, PB[6] = {0, 0, 2, 1, 0, 1};
+                constexpr int SLOTS = 6 * TN * Q, PIECES = 4 * UM, slot = q * 6 * TN + mc.value;
+                constexpr int n0 = slot * PIECES / SLOTS, n1 = (slot + 1) * PIECES / SLOTS;
+                if constexpr (m == 0) acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[PA[m]], b[q & 1][t][PB[m]], acc[t], 0, 0, 0);
+                else acs[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[PA[m]], b[q & 1][t][PB[m]], acs[t], 0, 0, 0);
+                // staging work for the next stage, spread over the products of this one
+                b3_for<n1 - n0>([&](auto nc) { piece(n0 + nc.value, buf ^ 1, st + 2); });
+                __builtin_amdgcn_sched_barrier(0);
+            });
+        });
+        b3_barrier();
+    }
+
+    // ---- K-waves meet in LDS; every wave finishes its share of the tile's accumulator registers
+    constexpr int NR = TN * 16 / WK;                                       // values per lane to finish
+    float out[NR];
+    if constexpr (WK > 1) {
+        float *red = reinterpret_cast<float *>(b3_lds);
+        constexpr int PER = TN * 16 * kWave;
+#pragma unroll
+        for (int t = 0; t < TN; ++t)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) red[wave * PER + (t * 16 + r) * kWave + lane] = acc[t][r] + acs[t][r];
+        __syncthreads();
+        const int w0 = wave - wk;
+#pragma unroll
+        for (int n = 0; n < NR; ++n) {
+            float v = 0.f;
+#pragma unroll
+            for (int w = 0; w < WK; ++w) v += red[(w0 + w) * PER + (wk * NR + n) * kWave + lane];
+            out[n] = v;
+        }
+    } else {
+#pragma unroll
+        for (int t = 0; t < TN; ++t)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) out[t * 16 + r] = acc[t][r] + acs[t][r];
+    }
+    constexpr int ND = NR >= 16 ? NR / 16 : 1, NE = NR >= 16 ? 16 : NR;    // column tiles, registers of each
+    static_assert(NE % 4 == 0, "a lane finishes groups of four rows");
+#pragma unroll
+    for (int d = 0; d < ND; ++d) {
+        const int t = wk * NR / 16 + d, r0 = NR >= 16 ? 0 : (wk * NR) % 16;
+        const int j = j0 + (wn * TN + t) * 32 + l32;
+        int64_t ob = 0;
+        bool live = m_live;
+        if constexpr (DENSE) {
+            live = live && j < p.Nrows;
+            ob = (int64_t)j * p.ldy;
+        } else {
+            const uint32_t g = b3_div((uint32_t)j, p.d_tw), im = b3_div(g, p.d_ho);
+            const int oh = (int)g - (int)im * p.HO, ow = strip * p.TW + j - (int)g * p.TW;
+            live = live && j < p.Ntot && ow < p.WOe;
+            int n = (int)im, od = 0;
+            if (p.DO > 1) {
+                n = (int)b3_div(im, p.d_do);
+                od = (int)im - n * p.DO;
+            }
+            ob = (int64_t)n * p.ons + (int64_t)od * p.npix + (int64_t)(oh * p.os + ph_a) * p.WO + ow * p.os + ph_b;
+        }
+        // (tile rows of register r: 8 (r / 4) + 4 half + r % 4)
+#pragma unroll
+        for (int e4 = 0; e4 < NE; e4 += 4) {
+            const int i = i0 + 8 * ((r0 + e4) / 4) + 4 * half;
+            const float *o = out + d * NE + e4;
+            if constexpr (DENSE) {
+                if (!live || i >= p.Cout) continue;
+                const int64_t oo = ob + (p.cs_len ? (int64_t)(i / p.cs_len) * p.cs_stride + i % p.cs_len : i);
+                if (i + 3 < p.Cout) {
+                    f32x4u v;
+                    f32x4u bv = {0.f, 0.f, 0.f, 0.f}, av = {0.f, 0.f, 0.f, 0.f};
+                    if (p.ef.flags & EF_BIAS) bv = *reinterpret_cast<const f32x4u *>(p.ef.bias + i);
+                    if (p.ef.flags & EF_ADD) av = *reinterpret_cast<const f32x4u *>(p.ef.add + oo);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) v[e] = b3_finish(p.ef, o[e], bv[e], av[e]);
+                    *reinterpret_cast<f32x4u *>(p.y + oo) = v;
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        if (i + e < p.Cout)
+                            p.y[oo + e] = b3_finish(p.ef, o[e], (p.ef.flags & EF_BIAS) ? p.ef.bias[i + e] : 0.f,
+                                                    (p.ef.flags & EF_ADD) ? p.ef.add[oo + e] : 0.f);
+                }
+            } else {
+                float bv[4], av[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const bool w = live && i + e < p.Cout;
+                    const int64_t oo = ob + (int64_t)(i + e) * p.ocs;
+                    bv[e] = (w && p.splitk == 1 && (p.ef.flags & EF_BIAS)) ? p.ef.bias[i + e] : 0.f;
+                    av[e] = (w && p.splitk == 1 && (p.ef.flags & EF_ADD)) ? p.ef.add[oo] : 0.f;
+                }
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    if (!live || i + e >= p.Cout) continue;
+                    const int64_t oo = ob + (int64_t)(i + e) * p.ocs;
+                    if (p.splitk > 1) p.partial[(int64_t)ks * p.c_numel + oo] = o[e];
+                    else p.y[oo] = b3_finish(p.ef, o[e], bv[e], av[e]);
+                }
+            }
+        }
+    }
+}
+
+// host: launches one configuration (instantiated per filter class in gemm_b3_*.hip)
+template <int TAPS, bool FOLD, bool DENSE>
+int b3_launch_tile(const B3Args &a, hipStream_t s);
+
+template <class C, int TAPS, bool FOLD, bool DENSE, int UM>
+int b3_launch_um(const B3Args &a, hipStream_t s) {
+    const int S = TAPS == 1 ? (DENSE ? C::BN + 2 : C::BN) : a.slot_stride;
+    const size_t stage = (size_t)2 * 3 * 2 * C::WK * b3_cw<C, TAPS>() * S * 16;
+    const size_t lds = stage > (size_t)C::RED ? stage : (size_t)C::RED;
+    if (lds > 64 * 1024) {
+        static bool raised = false;          // more than 64 KB of dynamic LDS has to be allowed per kernel, once
+        if (!raised) {
+            const hipError_t e = hipFuncSetAttribute((const void *)b3_kernel<C, TAPS, FOLD, DENSE, UM>,
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+            if (e != hipSuccess) return (int)e;
+            raised = true;
+        }
+    }
+    hipLaunchKernelGGL((b3_kernel<C, TAPS, FOLD, DENSE, UM>), dim3((unsigned)(a.mgroups * a.ntiles), 1, (unsigned)a.splitk),
+                       dim3(C::NT), lds, s, a);
+    return (int)hipGetLastError();
+}
+
+template <class C, int TAPS, bool FOLD, bool DENSE>
+int b3_launch_one(const B3Args &a, hipStream_t s) {
+    if constexpr (TAPS == 1) {
+        return b3_launch_um<C, TAPS, FOLD, DENSE, b3_units1<C>()>(a, s);
+    } else {
+        const int um = (a.units + C::NW - 1) / C::NW;
+        if (um <= 2) return b3_launch_um<C, TAPS, FOLD, DENSE, 2>(a, s);
+        if (um <= 4) return b3_launch_um<C, TAPS, FOLD, DENSE, 4>(a, s);
+        if (um <= 6) return b3_launch_um<C, TAPS, FOLD, DENSE, 6>(a, s);
+        return (int)hipErrorInvalidValue;
+    }
+}
+
+#define CLG_B3_INSTANTIATE(TAPS, FOLD, DENSE)                                             \
+    template <>                                                                           \
+    int b3_launch_tile<TAPS, FOLD, DENSE>(const B3Args &a, hipStream_t s) {               \
+        switch (a.tile) {                                                                 \
+        case B3_L: return b3_launch_one<B3L, TAPS, FOLD, DENSE>(a, s);                    \
+        case B3_LM: return b3_launch_one<B3LM, TAPS, FOLD, DENSE>(a, s);                  \
+        case B3_M: return b3_launch_one<B3M, TAPS, FOLD, DENSE>(a, s);                    \
+        case B3_S: return b3_launch_one<B3S, TAPS, FOLD, DENSE>(a, s);                    \
+        case B3_SS: return b3_launch_one<B3SS, TAPS, FOLD, DENSE>(a, s);                  \
+        case B3_G: return b3_launch_one<B3G, TAPS, FOLD, DENSE>(a, s);                    \
+        case B3_G2: return b3_launch_one<B3G2, TAPS, FOLD, DENSE>(a, s);                  \
+        default: return (int)hipErrorInvalidValue;                                        \
+        }                                                                                 \
+    }
+
+}  // namespace clg

@@ -1,0 +1,361 @@
+// Planning, weight packing and dispatch of the split-operand contraction kernels (gemm_b3.h).
+#include <algorithm>
+
+#include "gemm_b3.h"
+
+namespace clg {
+
+template <> int b3_launch_tile<1, false, false>(const B3Args &a, hipStream_t s);
+template <> int b3_launch_tile<1, true, false>(const B3Args &a, hipStream_t s);
+template <> int b3_launch_tile<1, false, true>(const B3Args &a, hipStream_t s);
+template <> int b3_launch_tile<9, false, false>(const B3Args &a, hipStream_t s);
+template <> int b3_launch_tile<9, true, false>(const B3Args &a, hipStream_t s);
+template <> int b3_launch_tile<4, false, false>(const B3Args &a, hipStream_t s);
+template <> int b3_launch_tile<3, true, false>(const B3Args &a, hipStream_t s);
+template <> int b3_launch_tile<8, true, false>(const B3Args &a, hipStream_t s);
+
+namespace {
+
+struct TileShape { int wm, wn, wk, tn, cw1; };
+TileShape tile_shape(int t) {
+    switch (t) {
+    case B3_L: return {4, 2, 1, 2, 4};
+    case B3_LM: return {2, 2, 1, 2, 2};
+    case B3_M: return {2, 1, 2, 2, 2};
+    case B3_S: return {1, 1, 4, 2, 2};
+    case B3_SS: return {1, 1, 4, 1, 2};
+    case B3_G: return {1, 4, 1, 2, 2};
+    default: return {1, 4, 1, 1, 2};     // B3_G2
+    }
+}
+int tile_cw(int t, int taps) { return taps == 1 ? tile_shape(t).cw1 : 1; }
+
+int ceil_div(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
+
+// Division by multiply-high: exact for numerators up to `most` if most * d < 2^32.
+bool set_div(B3Div *m, int64_t d, int64_t most) {
+    if (d < 1 || most * d >= ((int64_t)1 << 32)) return false;
+    m->m = d == 1 ? 0u : (uint32_t)((((uint64_t)1 << 32) / (uint64_t)d) + 1);
+    m->one = d == 1 ? ~0u : 0u;
+    return true;
+}
+
+// Everything of the launch that depends on the tile; false: the tile does not take the problem.
+bool place(B3Args *a, int tile) {
+    const TileShape ts = tile_shape(tile);
+    const int nw = ts.wm * ts.wn * ts.wk, bn = 32 * ts.tn * ts.wn;
+    const int cw = tile_cw(tile, a->taps), sc = ts.wk * cw, um = a->taps == 1 ? sc * ts.tn * ts.wn / nw : 6;
+    a->tile = tile;
+    a->mgroups = ceil_div(a->mtiles, ts.wm);
+    if (a->groups > 1 && ts.wm != 1) return false;           // the row tiles of a workgroup share the staged channels
+    a->stages = ceil_div(a->nC, sc);
+    a->stages_per = a->stages;
+    a->splitk = 1;
+    bool ok = set_div(&a->d_g32, 1, 1);
+    if (a->dense) {
+        a->units = sc / 2 * (bn / 16);
+        a->g32 = 1;
+        a->slot_stride = bn + 2;                             // four k-parts of a row are written together: two slots of shift keep them in different banks
+        a->slots = bn;
+        a->ntiles = a->tiles_strip = ceil_div(a->Nrows, bn);
+    } else {
+        // strips: as few as possible, but narrow enough that the patch of a tile stays compact
+        double best = -1;
+        for (int ns = 1; ns <= a->WOe; ++ns) {
+            const int tw = ceil_div(a->WOe, ns);
+            if (ns > 1 && (tw < 4 || tw == ceil_div(a->WOe, ns - 1))) {
+                if (tw < 4) break;
+                continue;
+            }
+            // output rows a run of bn pixels touches; a step to the next image skips the rest of its patch rows
+            const int halo_h = a->KHe + a->phe_max;          // patch rows of one output row (phe_max: extra rows of the other phases)
+            const int halo_w = (a->fold_w ? 1 : a->KWe) + a->pwe_max;
+            const int rows = bn % tw == 0 ? bn / tw : ceil_div(bn - 1, tw) + 1;
+            const int cross = a->Nimg > 1 ? std::min(ceil_div(rows - 1, a->HO), a->Nimg - 1) : 0;
+            const int vrows = (rows - 1) * a->ly + cross * std::max(0, halo_h - a->ly) + halo_h;
+            const int pw = (tw - 1) * a->lx + halo_w;
+            const int slots = a->taps == 1 ? bn : vrows * pw, g32 = ceil_div(slots, 32), s = g32 * 32;
+            if (sc * g32 > um * nw || (int64_t)2 * 3 * 2 * sc * s * 16 > 150 * 1024) continue;
+            const int nst = ceil_div(a->WOe, tw);
+            const int64_t run = (int64_t)a->Nimg * a->HO * tw;
+            const double tiles = (double)nst * ceil_div(run, bn);
+            const double cost = tiles * (slots + 4.0 * bn);
+            if (best >= 0 && cost >= best) continue;
+            best = cost;
+            a->TW = tw;
+            a->Ntot = (int)run;
+            a->tiles_strip = ceil_div(run, bn);
+            a->ntiles = nst * a->tiles_strip;
+            a->rpi = (a->HO - 1) * a->ly + halo_h;
+            a->pw_slots = pw;
+            a->slots = slots;
+            a->slot_stride = s;
+            a->g32 = g32;
+            a->units = sc * g32;
+        }
+        if (best < 0) return false;
+        ok = ok && set_div(&a->d_tw, a->TW, (int64_t)a->Ntot + bn) && set_div(&a->d_strip, a->tiles_strip, a->ntiles) && set_div(&a->d_ho, a->HO, (int64_t)a->Ntot / a->TW + bn) &&
+             set_div(&a->d_pw, a->pw_slots, a->slots + 64) && set_div(&a->d_rpi, a->rpi, (int64_t)a->Nimg * a->rpi + a->slots) &&
+             set_div(&a->d_do, a->DO, a->Nimg + 64) && set_div(&a->d_cpgo, a->groups > 1 ? a->cpg_out : 1, a->Cout + 32);
+    }
+    ok = ok && set_div(&a->d_g32, a->g32, a->units + 64);
+    a->tile_div = a->jmajor ? a->mgroups : a->ntiles;
+    const int64_t wgs = (int64_t)a->mgroups * a->ntiles;
+    ok = ok && wgs < ((int64_t)1 << 31) && set_div(&a->d_tile, a->tile_div, wgs);
+    a->pack_steps = (int64_t)a->mtiles * ts.wk * a->stages * cw * a->taps + 4;      // the last wave's ring reads ahead
+    return ok;
+}
+
+}  // namespace
+
+bool b3_resolve(const GemmArgs &g, int tile, int epi_flags, int n_cus, B3Args *out) {
+    if (epi_flags & EF_GENERIC) return false;
+    B3Args a{};
+    a.epi = g.epi;
+    a.c_numel = g.c_numel;
+    if (g.c_numel >= ((int64_t)1 << 31)) return false;
+    a.phases = 1;
+    a.groups = 1;
+    a.taps = 1;
+    a.DO = a.D = a.KD = a.KWf = 1;
+    if (g.mode == GM_NT) {
+        if (g.batch != 1 || g.K % 16 || (int64_t)g.M * g.lda >= ((int64_t)1 << 29) || (g.cs_len && g.cs_len % 32)) return false;
+        a.dense = 1;
+        a.x_bytes = (int32_t)(((int64_t)(g.M - 1) * g.lda + g.K) * 4);
+        a.Cout = g.N;
+        a.Nrows = g.M;
+        a.K = g.K;
+        a.ldx = g.lda;
+        a.ldy = g.ldc;
+        a.ldb = g.ldb;
+        a.cs_len = g.cs_len;
+        a.cs_stride = g.cs_stride;
+        a.nC = ceil_div(g.K, 16);
+        a.Cf = g.K;
+        a.jmajor = g.M > g.N ? 1 : 0;
+    } else if (g.mode == GM_CONV || g.mode == GM_CONVT) {
+        const bool depth = g.D > 1 || g.KD > 1;
+        a.convt = g.mode == GM_CONVT;
+        a.Cin = g.Cin; a.KH = g.KH; a.KW = g.KW;
+        a.H = g.H; a.W = g.W; a.HW = g.H * g.W;
+        a.D = depth ? g.D : 1;
+        a.KD = depth ? g.KD : 1;
+        a.DO = depth ? g.DO : 1;
+        a.sd = depth ? g.sd : 1;
+        a.pd = depth ? g.pd : 0;
+        a.Nimg = g.Nimg * a.DO;
+        a.cs = a.D * a.HW;
+        if ((int64_t)g.Nimg * g.Cin * a.cs >= ((int64_t)1 << 29)) return false;      // 31-bit byte offsets
+        a.x_bytes = (int32_t)((int64_t)g.Nimg * g.Cin * a.cs * 4);
+        a.img_stride = g.Cin * a.cs;
+        a.groups = g.rf_groups > 1 ? g.rf_groups : 1;
+        a.Cout = g.Cout;
+        a.sh = g.sh; a.sw = g.sw;
+        a.KHe = g.KH; a.KWe = g.KW;
+        a.ph = g.ph; a.pwd = g.pw;
+        a.HO = g.HO; a.WOe = a.WO = g.WO;
+        a.os = 1;
+        int she = g.sh, swe = g.sw;
+        int cin = g.Cin;
+        if (a.convt) {
+            // phases as stride-1 convolutions over one common patch
+            if (depth || a.groups > 1 || g.sh != g.sw || g.KH % g.sh || g.KW % g.sw || g.HO % g.sh || g.WO % g.sw) return false;
+            a.phases = g.sh * g.sw;
+            a.KHe = g.KH / g.sh;
+            a.KWe = g.KW / g.sw;
+            a.ph_t = g.ph;
+            a.pw_t = g.pw;
+            int lo_h = 1 << 30, lo_w = 1 << 30;
+            a.phe_max = a.pwe_max = -(1 << 30);
+            for (int q = 0; q < g.sh; ++q) {
+                const int e = a.KHe - 1 - (q + g.ph) / g.sh, f = a.KWe - 1 - (q + g.pw) / g.sw;
+                lo_h = std::min(lo_h, e); lo_w = std::min(lo_w, f);
+                a.phe_max = std::max(a.phe_max, e); a.pwe_max = std::max(a.pwe_max, f);
+            }
+            if (lo_h < 0 || lo_w < 0) return false;
+            a.ph = a.phe_max;
+            a.pwd = a.pwe_max;
+            a.HO = g.HO / g.sh;
+            a.WOe = g.WO / g.sw;
+            a.os = g.sh;
+            she = swe = 1;
+            if (!(a.KHe == 2 && a.KWe == 2) || cin % 16) return false;
+            a.taps = 4;
+        } else {
+            if (a.groups > 1) {
+                if (depth || g.Cin % a.groups || g.Cout % a.groups) return false;
+                a.cpg_in = g.Cin / a.groups;
+                a.cpg_out = g.Cout / a.groups;
+                if (32 % a.cpg_out && a.cpg_out % 32) return false;
+                if (a.cpg_out < 32 && g.Cout % 32) return false;
+                cin = (a.cpg_out < 32 ? 32 / a.cpg_out : 1) * a.cpg_in;
+                if (cin % 16) return false;
+            }
+            const bool one = g.KH == 1 && g.KW == 1, three = g.KH == 3 && g.KW == 3;
+            if (one && (g.ph || g.pw)) return false;
+            a.fold = cin % 16 != 0 || a.KD > 1;
+            if (a.KD == 1 && a.pd != 0) return false;
+            if (one) {
+                a.taps = 1;
+            } else if (three && cin % 16 == 0) {
+                a.taps = 9;
+            } else if (three || (g.KH == 7 && g.KW <= 16)) {
+                // few channels: the filter columns are folded into the channel index, a step is a filter row
+                a.fold = a.fold_w = 1;
+                a.KWf = g.KW;
+                a.KWe = 1;
+                a.taps = three ? 3 : 8;
+            } else {
+                return false;
+            }
+            if (a.groups > 1 && a.fold) return false;
+        }
+        if (a.fold_w && cin * a.KD * a.KWf > 512) return false;      // (first layers; nothing wider is worth an offset table per value)
+        a.Cf = cin * a.KD * a.KWf;
+        a.nC = ceil_div(a.Cf, 16);
+        // slot geometry: with one filter row (column) only the rows (columns) that are read get slots
+        a.ys = a.KHe == 1 ? she : 1;
+        a.ly = a.KHe == 1 ? 1 : she;
+        const bool one_col = a.fold_w || a.KWe == 1;
+        a.xs = one_col ? swe : 1;
+        a.lx = one_col ? 1 : swe;
+        a.npix = (a.convt ? g.HO * g.WO : g.HO * g.WO);
+        a.ocs = a.DO * a.npix;
+        a.ons = g.Cout * a.ocs;
+        if ((int64_t)g.Cout * a.ocs >= ((int64_t)1 << 31)) return false;
+        a.jmajor = (int64_t)g.Nimg * g.Cin * a.cs > (int64_t)g.Cout * cin * g.KH * g.KW * a.KD ? 1 : 0;
+        if (!a.convt) a.phe_max = a.pwe_max = 0;
+        if ((int64_t)a.Nimg * a.HO * a.WOe > ((int64_t)1 << 28)) return false;
+    } else {
+        return false;
+    }
+    a.tiles_m = ceil_div(a.Cout, 32);
+    a.mtiles = a.tiles_m * a.phases;
+    if (tile != B3_NONE) {
+        if (!place(&a, tile)) return false;
+    } else {
+        // the largest tile that gives every compute unit a workgroup; row tiles no taller than the problem
+        const int wide[] = {B3_L, B3_LM, B3_M, B3_S, B3_SS}, narrow[] = {B3_G, B3_G2, B3_S, B3_SS};
+        const bool few_rows = a.mtiles == 1 || a.groups > 1;
+        bool found = false;
+        for (int n = 0; n < (few_rows ? 4 : 5); ++n) {
+            B3Args b = a;
+            const int t = few_rows ? narrow[n] : wide[n];
+            if (t == B3_L && a.mtiles < 4) continue;
+            if (!place(&b, t)) continue;
+            *out = b;
+            found = true;
+            if ((int64_t)b.mgroups * b.ntiles >= n_cus) break;
+        }
+        return found;
+    }
+    *out = a;
+    return true;
+}
+
+size_t b3_pack_bytes(const B3Args &a) {
+    return (size_t)a.pack_steps * 3 * kWave * 16 + (a.fold ? (size_t)a.stages * tile_shape(a.tile).wk * tile_cw(a.tile, a.taps) * 16 * 8 : 0);
+}
+
+size_t b3_scratch_bytes(const B3Args &a) { return a.splitk > 1 ? (size_t)a.splitk * (size_t)a.c_numel * sizeof(float) : 0; }
+
+namespace {
+
+// One thread per (step, lane): eight weights of row lane % 32, k = 16 * block + 8 * (lane / 32) + 0..7, in three planes.
+__global__ __launch_bounds__(256) void b3_pack_kernel(const float *w, u32x4 *dst, B3Args p, int wk_n, int cw) {
+    const int64_t d = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t step = d >> 6;
+    if (step >= p.pack_steps) return;
+    const int lane = (int)(d & 63);
+    const int64_t per_wave = (int64_t)p.stages * cw * p.taps;
+    const int64_t wave = step / per_wave;                    // (row tile, K-wave)
+    const int n = (int)(step - wave * per_wave);
+    const int tap = n % p.taps, blk = n / p.taps;            // block: stage * cw + c
+    const int wk = (int)(wave % wk_n);
+    const int64_t mt = wave / wk_n;
+    const int phase = (int)(mt / p.tiles_m);
+    const int i = (int)(mt - (int64_t)phase * p.tiles_m) * 32 + lane % 32;
+    const int c16 = (blk / cw) * wk_n * cw + wk * cw + blk % cw;
+    float v[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        const int c = c16 * 16 + (lane / 32) * 8 + e;
+        float x = 0.f;
+        if (mt < p.mtiles && i < p.Cout && c < p.Cf) {
+            if (p.dense) {
+                x = w[(int64_t)i * p.ldb + c];
+            } else if (p.convt) {
+                // w is [Cin][Cout][KH][KW]; tap u of the phase is kernel tap r + s * (KH/s - 1 - u)
+                const int a_h = phase / p.sw, a_w = phase - a_h * p.sw;
+                const int uh = tap / p.KWe, uw = tap - uh * p.KWe;
+                const int kh = (a_h + p.ph_t) % p.sh + p.sh * (p.KHe - 1 - uh), kw = (a_w + p.pw_t) % p.sw + p.sw * (p.KWe - 1 - uw);
+                x = w[(((int64_t)c * p.Cout + i) * p.KH + kh) * p.KW + kw];
+            } else {
+                const int kwf = c % p.KWf, kd = (c / p.KWf) % p.KD, cl = c / (p.KWf * p.KD);
+                const int kh = p.KWf > 1 || p.KW == 1 ? tap : tap / p.KW, kw = p.KWf > 1 ? kwf : (p.KW == 1 ? 0 : tap % p.KW);
+                if (kh < p.KH) {
+                    if (p.groups > 1) {
+                        const int ch = ((i / 32 * 32) / p.cpg_out) * p.cpg_in + cl, grp = i / p.cpg_out;
+                        if (ch / p.cpg_in == grp) x = w[(((int64_t)i * p.cpg_in + (ch - grp * p.cpg_in)) * p.KH + kh) * p.KW + kw];
+                    } else {
+                        x = w[((((int64_t)i * p.Cin + cl) * p.KD + kd) * p.KH + kh) * p.KW + kw];
+                    }
+                }
+            }
+        }
+        v[e] = x;
+    }
+    u32x4 pl[3];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        uint32_t h, m, l;
+        b3_split2(v[2 * e], v[2 * e + 1], h, m, l);
+        pl[0][e] = h;
+        pl[1][e] = m;
+        pl[2][e] = l;
+    }
+#pragma unroll
+    for (int k = 0; k < 3; ++k) dst[(step * 3 + k) * kWave + lane] = pl[k];
+}
+
+// Byte offset and tap of every folded channel (c * KD + kd) * KWf + kw; channels past the last one get a depth tap no input has.
+__global__ __launch_bounds__(256) void b3_table_kernel(int2 *dst, B3Args p, int n) {
+    const int c = blockIdx.x * blockDim.x + threadIdx.x;
+    if (c >= n) return;
+    const int kw = c % p.KWf, kd = (c / p.KWf) % p.KD, cl = c / (p.KWf * p.KD);
+    dst[c] = c < p.Cf ? make_int2((cl * p.cs + kd * p.HW + kw) * 4, kd | (kw << 16)) : make_int2(0, 0x7fff);
+}
+
+}  // namespace
+
+int launch_b3_pack(const B3Args &a, const float *w, void *dst, void *stream) {
+    const int64_t threads = a.pack_steps * kWave;
+    const int wk = tile_shape(a.tile).wk, cw = tile_cw(a.tile, a.taps);
+    hipLaunchKernelGGL(b3_pack_kernel, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, (hipStream_t)stream, w, (u32x4 *)dst, a, wk, cw);
+    int e = (int)hipGetLastError();
+    if (e || !a.fold) return e;
+    const int n = a.stages * wk * cw * 16;
+    hipLaunchKernelGGL(b3_table_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, (hipStream_t)stream,
+                       (int2 *)((char *)dst + (size_t)a.pack_steps * 3 * kWave * 16), a, n);
+    return (int)hipGetLastError();
+}
+
+int launch_b3(const B3Args &a_in, void *stream) {
+    B3Args a = a_in;
+    hipStream_t s = (hipStream_t)stream;
+    a.ef = make_epi_fast(a.epi);
+    if (a.ef.flags & EF_GENERIC) return (int)hipErrorInvalidValue;
+    a.table = (const int32_t *)((const char *)a.w + (size_t)a.pack_steps * 3 * kWave * 16);
+    int e;
+    if (a.dense) e = b3_launch_tile<1, false, true>(a, s);
+    else if (a.taps == 1) e = a.fold ? b3_launch_tile<1, true, false>(a, s) : b3_launch_tile<1, false, false>(a, s);
+    else if (a.taps == 9) e = a.fold ? b3_launch_tile<9, true, false>(a, s) : b3_launch_tile<9, false, false>(a, s);
+    else if (a.taps == 4) e = b3_launch_tile<4, false, false>(a, s);
+    else if (a.taps == 3) e = b3_launch_tile<3, true, false>(a, s);
+    else if (a.taps == 8) e = b3_launch_tile<8, true, false>(a, s);
+    else e = (int)hipErrorInvalidValue;
+    if (e || a.splitk <= 1) return e;
+    return launch_splitk_reduce(a.partial, a.y, a.c_numel, a.splitk, a.epi, stream);
+}
+
+}  // namespace clg

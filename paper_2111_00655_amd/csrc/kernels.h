@@ -231,6 +231,46 @@ struct AttentionArgs {
 bool attention_shape_ok(const AttentionArgs &a);       // d in {32, 64, 128}, Sk <= 512
 int launch_attention(const AttentionArgs &a, void *stream);
 
+// ---- contractions on the bf16 matrix cores, operands split exactly into three bf16 values (gemm_b3.h) ----
+enum B3Tile : int32_t { B3_NONE = 0, B3_L = 1, B3_LM = 2, B3_M = 3, B3_S = 4, B3_SS = 5, B3_G = 6, B3_G2 = 7 };
+struct B3Div { uint32_t m, one; };         // division by multiply-high: b3_div
+struct B3Args {
+    const float *x;                        // input, NCHW (or rows of a dense layer)
+    const void *w;                         // packed weights (b3_pack_bytes)
+    const int32_t *table;                  // FOLD: (offset, kd | kw << 16) per folded channel; lies behind the packed weights
+    float *y;
+    float *partial;                        // split-K partial sums [splitk][c_numel]
+    EpiFast ef;                            // filled by launch_b3 from epi
+    B3Div d_tile, d_strip, d_tw, d_ho, d_g32, d_pw, d_rpi, d_do, d_cpgo;
+    int32_t x_bytes;
+    int32_t tile_div, jmajor, mtiles, tiles_m, phases;      // packed row tiles: phases * tiles_m
+    int32_t mgroups, ntiles, tiles_strip;                   // grid.x = mgroups * ntiles
+    int32_t stages, stages_per, splitk;
+    int32_t slot_stride, slots, units, g32, pw_slots;       // patch: slots = rows * pw_slots
+    int32_t HO, WOe, TW, rpi, ly, lx, ys, xs;               // output rows / columns per phase; strip width; slot geometry
+    int32_t Nimg, Ntot, img_stride, HW, W, H, cs, ph, pwd;  // Nimg counts (image, output depth) pairs
+    int32_t D, DO, sd, pd, fold_w, nC;
+    int32_t groups, cpg_in;
+    int32_t KHe, KWe, sh, sw, ph_t, pw_t, phe_max, pwe_max;
+    int32_t Cout, WO, os, npix, ons, ocs;                   // output strides
+    int32_t Nrows, ldx, ldy, K, cs_len;                     // dense
+    int64_t cs_stride, c_numel;
+    // host side only
+    int32_t tile, taps, fold, dense;
+    int32_t Cin, KD, KH, KW, KWf, cpg_out, ldb, convt, Cf;
+    int64_t pack_steps;                                     // 3 KB steps of packed weights, padding included
+    Epilogue epi;
+};
+// Whether the kernel takes the problem `a` describes (its geometry as lower.cpp fills it before any
+// *_resolve call) under tile `tile`; fills *out.  B3_NONE as the tile: the largest one that gives every compute unit a workgroup.
+bool b3_resolve(const GemmArgs &a, int tile, int epi_flags, int n_cus, B3Args *out);
+size_t b3_pack_bytes(const B3Args &a);
+size_t b3_scratch_bytes(const B3Args &a);
+int launch_b3_pack(const B3Args &a, const float *w, void *dst, void *stream);
+int launch_b3(const B3Args &a, void *stream);
+// Adds split-K partial tiles in slice order and applies the fused tail.
+int launch_splitk_reduce(const float *partial, float *out, int64_t numel, int splitk, const Epilogue &epi, void *stream);
+
 // ---- concat: y[r][...] = x_0[r][...] x_1[r][...] ..., r < outer ---------------------------------
 struct ConcatArgs {
     int32_t n;                             // operands, at most 8

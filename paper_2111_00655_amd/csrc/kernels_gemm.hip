@@ -421,6 +421,12 @@ bool gemv_shape_ok(const GemmArgs &a, int epi_flags) {
            a.ldb % 4 == 0 && a.cs_len == 0 && !(epi_flags & EF_GENERIC);
 }
 
+int launch_splitk_reduce(const float *partial, float *out, int64_t numel, int splitk, const Epilogue &epi, void *stream) {
+    hipLaunchKernelGGL(splitk_reduce_kernel, dim3((unsigned)((numel + 255) / 256)), dim3(256), 0, (hipStream_t)stream,
+                       partial, out, numel, splitk, epi);
+    return (int)hipGetLastError();
+}
+
 int launch_gemm_region(const GemmArgs *members, int n, void *stream) {
     if (n < 2 || n > kMaxRegion) return (int)hipErrorInvalidValue;
     GemmArgs local[kMaxRegion];
@@ -438,9 +444,7 @@ int launch_gemm(const GemmArgs &a_in, void *stream) {
     if (a.rf_ts) {
         const int e = launch_rf_conv(a, s);
         if (e || a.splitk <= 1 || a.rf_convt) return e;      // (a transposed convolution's grid.z counts phases)
-        hipLaunchKernelGGL(splitk_reduce_kernel, dim3((unsigned)((a.c_numel + 255) / 256)), dim3(256), 0, s,
-                           a.partial, a.C, a.c_numel, a.splitk, a.epi);
-        return (int)hipGetLastError();
+        return launch_splitk_reduce(a.partial, a.C, a.c_numel, a.splitk, a.epi, stream);
     }
     if (a.gemv) {
         if (!al16(a.A) || !al16(a.B)) return (int)hipErrorInvalidValue;       // rows are read 16 bytes at a time
@@ -470,12 +474,7 @@ int launch_gemm(const GemmArgs &a_in, void *stream) {
     default: err = launch_mode<GM_CONVT>(a, s); break;
     }
     if (err) return err;
-    if (a.splitk > 1) {
-        hipLaunchKernelGGL(splitk_reduce_kernel, dim3((unsigned)((a.c_numel + 255) / 256)), dim3(256), 0, s,
-                           a.partial, a.C, a.c_numel, a.splitk, a.epi);
-        err = (int)hipGetLastError();
-    }
-    return err;
+    return a.splitk > 1 ? launch_splitk_reduce(a.partial, a.C, a.c_numel, a.splitk, a.epi, stream) : 0;
 }
 
 }  // namespace clg

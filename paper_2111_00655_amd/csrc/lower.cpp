@@ -261,6 +261,34 @@ int32_t add_step(const ChainView &cv, int t, bool as_anchor, Epilogue *e, int32_
 
 std::string shape_key(const Graph &g, int32_t v) { return g.nodes[v].shape.str(); }
 
+// The split-operand kernels (gemm_b3.h) as a backend's kernel for contractions with constant weights: the
+// large- and medium-tile backends and the automatic one run them wherever they take the shape; the three split-K
+// register-fed backends where the reduction needs no split across workgroups (`a` as their own resolve left it), where
+// they would otherwise repeat the kernel that their unsplit namesakes run.
+bool lower_b3(const Context &ctx, const Backend &be, const GemmArgs &a, const Epilogue &epi, const std::string &what, KernelCall *c) {
+    int tile;
+    switch (be.tile) {
+    case TILE_AUTO: tile = B3_NONE; break;
+    case TILE_L: tile = a.Cout > 64 || a.mode == GM_NT ? B3_L : B3_LM; break;
+    case TILE_M: tile = B3_M; break;
+    case TILE_R32: tile = B3_NONE; break;
+    case TILE_R16: tile = be.rf_waves ? B3_S : (a.rf_groups > 1 ? B3_G2 : B3_M); break;
+    default: return false;
+    }
+    if ((be.tile == TILE_R32 || be.tile == TILE_R16) && be.no_split) return false;
+    if (gemv_shape_ok(a, epi_fast_flags(epi))) return false;          // a handful of rows: streaming the weights once is the bound
+    B3Args b;
+    if (!b3_resolve(a, tile, epi_fast_flags(epi), ctx.n_cus, &b)) return false;
+    static const char *tn[] = {"", "m128n128", "m64n128", "m64n64", "m32n64", "m32n32", "m32n256", "m32n128"};
+    c->kind = CALL_B3;
+    c->b3 = b;
+    c->b3.epi = epi;
+    c->pack_bytes = b3_pack_bytes(b);
+    c->scratch_bytes = b3_scratch_bytes(b);
+    c->name = what + "_rfb3_" + tn[b.tile] + (b.dense ? "" : "_t" + std::to_string(b.taps)) + (b.fold ? "f" : "") + (b.cs_len ? "_split" : "");
+    return true;
+}
+
 }  // namespace
 
 int32_t lower_match(const Context &ctx, const Graph &g, int32_t match_id, KernelCall *out) {
@@ -536,7 +564,7 @@ int32_t lower_match(const Context &ctx, const Graph &g, int32_t match_id, Kernel
             GemmArgs &a = c.gemm;
             a.tile = be.tile;
             const bool want_rf = a.tile == TILE_R32 || a.tile == TILE_R16 || a.tile == TILE_R16X2;
-            bool rf = false;
+            bool rf = false, b3 = false;
             a.batch = 1;
             a.epi = epi;
             a.c_numel = ys.numel();
@@ -545,7 +573,6 @@ int32_t lower_match(const Context &ctx, const Graph &g, int32_t match_id, Kernel
                 a.M = (int)xs.d[0]; a.K = (int)xs.d[1]; a.N = (int)ws.d[0];
                 a.lda = a.K; a.ldb = a.K; a.ldc = a.N;
                 a.bias_on_row = 0;
-                c.name = "gemm_nt";
                 if (permuted) {
                     // [M, H*D] -> reshape [M, H, D] -> transpose (1, 0, 2) -> [H, M, D]
                     const Node &rs = g.nodes[cv.node(len - 2)], &tr = g.nodes[cv.node(len - 1)];
@@ -556,7 +583,9 @@ int32_t lower_match(const Context &ctx, const Graph &g, int32_t match_id, Kernel
                     a.cs_len = (int)rs.shape.d[2];
                     a.cs_stride = (int64_t)a.M * rs.shape.d[2];
                 }
-                if (want_rf && g.nodes[wb].kind == NODE_CONST)
+                c.name = "gemm_nt";
+                b3 = g.nodes[wb].kind == NODE_CONST && lower_b3(ctx, be, a, epi, "dense", &c);
+                if (!b3 && want_rf && g.nodes[wb].kind == NODE_CONST)
                     rf = rf_resolve_dense(&a, a.tile == TILE_R32 ? 32 : 16, epi_fast_flags(epi), ctx.n_cus, rfw,
                                            a.tile == TILE_R16X2 ? 2 : 1);
                 if (rf) c.pack_bytes = rf_pack_bytes(a);
@@ -596,10 +625,18 @@ int32_t lower_match(const Context &ctx, const Graph &g, int32_t match_id, Kernel
                 a.rf_groups = 1;
                 if ((int64_t)a.Nimg * a.DO > 65535) return fail(CLG_NO_KERNEL, "conv3d: too many (image, depth) slices");
                 if (a.KD == 1 && a.pd != 0) return fail(CLG_NO_KERNEL, "conv3d: depth padding needs more than one depth tap");
+                const GemmArgs geo = a;
                 rf = rf_resolve(&a, a.tile == TILE_R32 ? 32 : 16, epi_fast_flags(epi), ctx.n_cus, rfw, !be.no_split);
-                if (!rf) return fail(CLG_NO_KERNEL, "conv3d: the register-fed kernel does not take this shape or tail");
-                c.pack_bytes = rf_pack_bytes(a);
-                c.name = "conv3d";
+                if (rf && a.splitk == 1 && lower_b3(ctx, be, geo, epi, "conv3d", &c)) {
+                    rf = false;
+                    b3 = true;
+                    a = geo;
+                }
+                if (!rf && !b3) return fail(CLG_NO_KERNEL, "conv3d: the register-fed kernel does not take this shape or tail");
+                if (rf) {
+                    c.pack_bytes = rf_pack_bytes(a);
+                    c.name = "conv3d";
+                }
             } else if (k0 == CLG_OP_CONV2D) {
                 const int G = anchor.attrs.groups > 0 ? anchor.attrs.groups : 1;
                 if (G != 1 && !want_rf)
@@ -611,18 +648,26 @@ int32_t lower_match(const Context &ctx, const Graph &g, int32_t match_id, Kernel
                 a.HO = (int)ys.d[2]; a.WO = (int)ys.d[3];
                 a.bias_on_row = 1;
                 c.gemm_swap = true;
-                // register-fed kernel: needs constant weights (re-packed once) and a common-form tail
-                if (want_rf && g.nodes[wb].kind == NODE_CONST) {
+                // register-fed kernels: need constant weights (re-packed once) and a common-form tail
+                if (g.nodes[wb].kind == NODE_CONST) {
                     a.mode = GM_CONV;
                     a.M = a.Cout; a.N = a.Nimg * a.HO * a.WO; a.K = a.Cin * a.KH * a.KW;
                     a.lda = a.K;
                     a.rf_groups = G;
-                    rf = rf_resolve(&a, a.tile == TILE_R32 ? 32 : 16, epi_fast_flags(epi), ctx.n_cus, rfw, !be.no_split);
+                    const GemmArgs geo = a;
+                    rf = want_rf && rf_resolve(&a, a.tile == TILE_R32 ? 32 : 16, epi_fast_flags(epi), ctx.n_cus, rfw, !be.no_split);
+                    if ((!want_rf || (rf && a.splitk == 1)) && lower_b3(ctx, be, geo, epi, "conv", &c)) {
+                        rf = false;
+                        b3 = true;
+                        a = geo;
+                    }
                 }
-                if (G != 1 && !rf)
+                if (G != 1 && !rf && !b3)
                     return fail(CLG_NO_KERNEL, "the register-fed conv runs %d groups only with constant weights, a common-form "
                                 "tail and channels per group that divide, or are a multiple of, the tile edge", G);
-                if (rf) {
+                if (b3) {
+                    // geometry and packed weights are in c.b3
+                } else if (rf) {
                     c.pack_bytes = rf_pack_bytes(a);
                 } else if (a.KH == 1 && a.KW == 1 && a.sh == 1 && a.sw == 1 && a.ph == 0 && a.pw == 0) {
                     // 1x1 stride-1 convolution is a plain GEMM per image: W[Cout,Cin] * X[Cin,H*W]
@@ -636,7 +681,7 @@ int32_t lower_match(const Context &ctx, const Graph &g, int32_t match_id, Kernel
                     a.M = a.Cout; a.N = a.Nimg * a.HO * a.WO; a.K = a.Cin * a.KH * a.KW;
                     a.lda = a.K;
                 }
-                c.name = "conv_igemm";
+                if (!b3) c.name = "conv_igemm";
             } else {
                 a.mode = GM_CONVT;
                 a.Nimg = (int)xs.d[0]; a.Cin = (int)xs.d[1]; a.H = (int)xs.d[2]; a.W = (int)xs.d[3];
@@ -651,17 +696,20 @@ int32_t lower_match(const Context &ctx, const Graph &g, int32_t match_id, Kernel
                 a.K = a.Cin * (a.KH / a.sh) * (a.KW / a.sw);
                 a.bias_on_row = 1;
                 c.gemm_swap = true;
-                c.name = "convt_igemm";
-                if (want_rf && g.nodes[wb].kind == NODE_CONST)
+                b3 = g.nodes[wb].kind == NODE_CONST && lower_b3(ctx, be, a, epi, "convt", &c);
+                if (!b3) c.name = "convt_igemm";
+                if (!b3 && want_rf && g.nodes[wb].kind == NODE_CONST)
                     rf = rf_resolve_convt(&a, a.tile == TILE_R32 ? 32 : 16, epi_fast_flags(epi), ctx.n_cus, rfw);
                 if (rf) c.pack_bytes = rf_pack_bytes(a);
             }
             macs = (double)a.batch * a.M * a.N * a.K;
-            if (rf && a.rf_groups > 1) macs /= a.rf_groups;
+            if ((rf || b3) && a.rf_groups > 1) macs /= a.rf_groups;
             if ((double)a.M * a.N > 2.0e9 || a.K < 1) return fail(CLG_NO_KERNEL, "GEMM dimensions out of range");
-            c.kind = CALL_GEMM;
             c.bound = 0;
-            if (rf) {
+            if (!b3) c.kind = CALL_GEMM;
+            if (b3) {
+                c.gemm_swap = false;
+            } else if (rf) {
                 c.scratch_bytes = gemm_scratch_bytes(a);
                 c.name = (a.rf_tapk == -1 ? "dense_rf" + std::to_string(a.rf_ts) + (a.rf_nb == 2 ? "x2" : "")
                                           : std::string((a.rf_convt || a.rf_d2s) ? "convt_rf" : (a.D > 1 ? "conv3d_rf" : "conv_rf")) + std::to_string(a.rf_ts) + "_t" +

@@ -508,6 +508,7 @@ int32_t measure_plan(Plan &p, const void *const *inputs, void *const *outputs, v
 
 int32_t pack_weights(const KernelCall &c, const void *w, void *dst, void *stream) {
     const int err = c.kind == CALL_SEPCONV ? launch_sepconv_pack(c.sep, (const float *)w, (float *)dst, stream)
+                    : c.kind == CALL_B3    ? launch_b3_pack(c.b3, (const float *)w, dst, stream)
                                            : launch_rf_pack(c.gemm, (const float *)w, (float *)dst, stream);
     if (err != 0) return fail(CLG_HIP_ERROR, "weight packing launch failed: %s", hipGetErrorString((hipError_t)err));
     return CLG_OK;
@@ -544,6 +545,14 @@ int32_t launch_call(const KernelCall &c, const void *a, const void *b, const voi
         const int32_t rc = bind_gemm(c, a, b, out, epi_ptrs, scratch, packed, &k);
         if (rc != CLG_OK) return rc;
         err = launch_gemm(k, stream);
+        break;
+    }
+    case CALL_B3: {
+        if (!packed) return fail(CLG_INVALID_ARG, "%s needs packed weights, none were prepared", c.name.c_str());
+        B3Args k = c.b3;
+        k.x = (const float *)a; k.w = packed; k.y = (float *)out; k.partial = (float *)scratch;
+        k.epi = bind(c.b3.epi);
+        err = launch_b3(k, stream);
         break;
     }
     case CALL_DIRECT_CONV: {
