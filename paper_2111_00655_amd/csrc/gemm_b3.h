@@ -34,9 +34,10 @@
 //    image (or depth slice after depth slice), and a tile is BN consecutive pixels of
 //    that walk; small images share a tile, large ones are cut into strips so that the patch
 //    stays compact.
-//  * First layers have too few channels to fill the 16 values of k of an MFMA: their filter columns
-//    (and depth taps) are folded into the channel index (FOLD), with an offset table behind the
-//    packed weights.
+//  * First layers have too few channels to fill the 16 values of k of an MFMA: they have a kernel of
+//    their own (gemm_b3_first.hip), which takes eight neighbouring pixels of an input row as k.
+//  * 3-D: a tile's walk passes depth slice after depth slice; the depth taps of a channel block are
+//    stages of their own, one input plane each (DEPTH).
 //  * Transposed convolution: the stride^2 sub-pixel phases are stride-1 convolutions over the
 //    same input patch; a phase is a further block of output rows with its own tap offset.
 #pragma once
@@ -54,7 +55,6 @@ typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x2v __attribute__((ext_vector_type(2)));
 typedef float f32x16v __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));        // 16 bytes at any float address
 
 template <int WM_, int WN_, int WK_, int TN_, int CW1_ = 2>
 struct B3Cfg {
@@ -76,7 +76,7 @@ using B3G2 = B3Cfg<1, 4, 1, 1>;      // 32 x 128
 template <class C, int TAPS>
 constexpr int b3_cw() { return TAPS == 1 ? C::CW1 : 1; }
 template <class C, int TAPS>
-constexpr int b3_ring() { return TAPS == 1 ? C::CW1 : (TAPS == 9 || TAPS == 3 ? 3 : 4); }
+constexpr int b3_ring() { return TAPS == 1 ? C::CW1 : (TAPS == 9 ? 3 : 4); }
 // staging units (16 channels x 32 slots) per wave and stage of 1x1 filters and dense layers
 template <class C>
 constexpr int b3_units1() { return C::WK * C::CW1 * C::TN * C::WN / C::NW; }
@@ -95,15 +95,23 @@ __device__ __forceinline__ void b3_split2(float a, float b, uint32_t &h, uint32_
     l = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2v{a, b}, bf16x2));
 }
 
-__device__ __forceinline__ float b3_finish(const EpiFast &ef, float v, float bias_v, float add_v) {
-    const int f = ef.flags;
-    if (f & EF_SCALE) v *= ef.scale;
-    v += bias_v;
-    v += add_v;
-    if (f & EF_RELU) v = v > 0.f ? v : 0.f;
-    else if (f & EF_GELU) v = gelu_erf(v);
-    else if (f & EF_TANH) v = tanhf(v);
-    return v;
+// The fused tail on a lane's N finished values at once.  (Tests of the flags value by value, with the bodies of erff
+// and tanhf in between, made 31 KB of code and cost 4 us at the end of a workgroup.)
+template <int N>
+__device__ __forceinline__ void b3_tail(const EpiFast &ef, float (&v)[N], const float (&bv)[N], const float (&av)[N]) {
+    const float scale = (ef.flags & EF_SCALE) ? ef.scale : 1.f;
+#pragma unroll
+    for (int n = 0; n < N; ++n) v[n] = v[n] * scale + bv[n] + av[n];
+    if (ef.flags & EF_RELU) {
+#pragma unroll
+        for (int n = 0; n < N; ++n) v[n] = v[n] > 0.f ? v[n] : 0.f;
+    } else if (ef.flags & EF_GELU) {
+#pragma unroll
+        for (int n = 0; n < N; ++n) v[n] = gelu_erf(v[n]);
+    } else if (ef.flags & EF_TANH) {
+#pragma unroll
+        for (int n = 0; n < N; ++n) v[n] = tanhf(v[n]);
+    }
 }
 
 // (the same mapping as the other tiled kernels': an XCD gets a contiguous range of tiles)
@@ -125,7 +133,7 @@ __device__ __forceinline__ void b3_barrier() { asm volatile("s_waitcnt lgkmcnt(0
 // Loads through a buffer descriptor: a lane whose offset is kOut (beyond the buffer) gets zero.
 constexpr uint32_t kB3Out = 0x80000000u;
 
-template <class C, int TAPS, bool FOLD, bool DENSE, int UM>
+template <class C, int TAPS, bool DEPTH, bool DENSE, int UM>
 __global__ __launch_bounds__(C::NT, 2) void b3_kernel(B3Args p) {
     constexpr int CW = b3_cw<C, TAPS>(), SC = C::WK * CW, Q = CW * TAPS, R = b3_ring<C, TAPS>();
     constexpr int TN = C::TN, WK = C::WK;
@@ -174,7 +182,7 @@ __global__ __launch_bounds__(C::NT, 2) void b3_kernel(B3Args p) {
     const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(p.x), (short)0, p.x_bytes, 0x00020000);
     uint32_t off[UM];                                                      // byte offset, or kB3Out: the slot is padding
     int ldsw[UM], c16l[UM];
-    int iwu[FOLD ? UM : 1], idu[FOLD ? UM : 1];
+    int idu[DEPTH ? UM : 1];
 #pragma unroll
     for (int u = 0; u < UM; ++u) {
         const int unit = TAPS == 1 ? wave + u * C::NW : min(wave + u * C::NW, p.units - 1);
@@ -203,7 +211,7 @@ __global__ __launch_bounds__(C::NT, 2) void b3_kernel(B3Args p) {
                 im = (int)b3_div((uint32_t)v, p.d_rpi);
                 ih = (v - im * p.rpi) * p.ys - p.ph;
                 iw = (strip * p.TW * p.lx + x) * p.xs - p.pwd;
-                in = im < p.Nimg && ih >= 0 && ih < p.H && ((FOLD && p.fold_w) || (iw >= 0 && iw < p.W));
+                in = im < p.Nimg && ih >= 0 && ih < p.H && iw >= 0 && iw < p.W;
             }
             int n = im, od = 0;
             if (p.DO > 1) {
@@ -212,13 +220,8 @@ __global__ __launch_bounds__(C::NT, 2) void b3_kernel(B3Args p) {
             }
             const int id0 = od * p.sd - p.pd;
             const int32_t o = (n * p.img_stride + id0 * p.HW + ih * p.W + iw) * 4;
-            if constexpr (FOLD) {
-                off[u] = (uint32_t)o;
-                iwu[u] = in ? iw : -(1 << 20);                             // a padding slot: no filter column reaches the input
-                idu[u] = id0;
-            } else {
-                off[u] = in ? (uint32_t)(o + half * 32 * p.cs) : kB3Out;
-            }
+            off[u] = in ? (uint32_t)(o + half * 32 * p.cs) : kB3Out;
+            if constexpr (DEPTH) idu[u] = id0;
             c16l[u] = c16;
             ldsw[u] = (c16 * 2 + half) * S + slot;
         }
@@ -238,16 +241,15 @@ __global__ __launch_bounds__(C::NT, 2) void b3_kernel(B3Args p) {
                 xv[u][i] = __uint_as_float(a[i]);
                 xv[u][4 + i] = __uint_as_float(b[i]);
             }
-        } else if constexpr (FOLD) {
-            const int2 *tab = reinterpret_cast<const int2 *>(p.table) + (st * SC + c16l[u]) * 16;
+        } else if constexpr (DEPTH) {
+            // block: (16 channels, depth tap); a plane before or behind the volume is zero
+            const int blk = min(st * SC + c16l[u], p.nC - 1), c16 = (int)b3_div((uint32_t)blk, p.d_kd), kd = blk - c16 * p.KD;
+            const int so = c16 * 16 * p.cs * 4;
+            const bool in = off[u] != kB3Out && (uint32_t)(idu[u] + kd) < (uint32_t)p.D;
+            const uint32_t o = in ? off[u] + (uint32_t)(kd * p.HW * 4) : kB3Out;      // (off may lie in front of the volume)
 #pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const int2 e0 = tab[i], e1 = tab[8 + i];
-                const int eo = half ? e1.x : e0.x, ek = half ? e1.y : e0.y;
-                const bool in = (uint32_t)(idu[u] + (ek & 0xffff)) < (uint32_t)p.D && (uint32_t)(iwu[u] + (ek >> 16)) < (uint32_t)p.W;
-                const uint32_t o = in ? off[u] + (uint32_t)eo : kB3Out;
-                xv[u][i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsrc, (int)o, 0, 0));
-            }
+            for (int i = 0; i < 8; ++i)
+                xv[u][i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsrc, (int)o, so + i * p.cs * 4, 0));
         } else {
             const int c = cbase + min(st * SC + c16l[u], p.nC - 1) * 16;   // past the last block: meets zero weights
             const int so = c * p.cs * 4;
@@ -305,25 +307,25 @@ __global__ __launch_bounds__(C::NT, 2) void b3_kernel(B3Args p) {
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[t][r] = acs[t][r] = 0.f;
 
-    bf16x8 b[2][TN][3];
+    bf16x8 b[TN][3];
     constexpr int KWt = TAPS == 9 ? 3 : (TAPS == 4 ? 2 : 1);
-    auto read_b = [&](int set, int q, int buf) {
+    auto read_b = [&](int q, int buf) {
         const int tap = q % TAPS;
-        const int kh = TAPS == 8 ? min(tap, p.KHe - 1) : tap / KWt, kw = tap % KWt;
+        const int kh = tap / KWt, kw = tap % KWt;
         const int so = buf * 3 * PL + (q / TAPS) * 2 * S + (TAPS == 1 ? 0 : kh * p.pw_slots + kw);
 #pragma unroll
         for (int t = 0; t < TN; ++t)
 #pragma unroll
-            for (int k = 0; k < 3; ++k) b[set][t][k] = reinterpret_cast<const bf16x8 *>(b3_lds)[k * PL + so + sbase[t]];
+            for (int k = 0; k < 3; ++k) b[t][k] = reinterpret_cast<const bf16x8 *>(b3_lds)[k * PL + so + sbase[t]];
     };
     b3_barrier();
     for (int st = st_begin; st < st_end; ++st) {
         const int buf = (st - st_begin) & 1;
-        read_b(0, 0, buf);
         b3_for<Q>([&](auto qc) {
             constexpr int q = qc.value;
-            // the next step's input fragments and a later step's weights leave before this step's products
-            if constexpr (q + 1 < Q) read_b((q + 1) & 1, q + 1, buf);
+            // a later step's weights leave before this step's products.  (Input fragments read a step ahead as well
+            // cost 24 more registers and with them the third wave of a SIMD: 1x1 64 -> 256 at 56x56, batch 32, 53 instead of 44 us.)
+            read_b(q, buf);
 #pragma unroll
             for (int k = 0; k < 3; ++k) ar[(q + R - 1) % R][k] = (Aw + k * kWave)[lane_u];      // (the stream is padded by R steps)
             Aw += 3 * kWave;
@@ -336,8 +338,8 @@ __global__ __launch_bounds__(C::NT, 2) void b3_kernel(B3Args p) {
                 constexpr int PA[6] = {0, 2, 0, 1, 1, 0}, PB[6] = {0, 0, 2, 1, 0, 1};
                 constexpr int SLOTS = 6 * TN * Q, PIECES = 4 * UM, slot = q * 6 * TN + mc.value;
                 constexpr int n0 = slot * PIECES / SLOTS, n1 = (slot + 1) * PIECES / SLOTS;
-                if constexpr (m == 0) acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[PA[m]], b[q & 1][t][PB[m]], acc[t], 0, 0, 0);
-                else acs[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[PA[m]], b[q & 1][t][PB[m]], acs[t], 0, 0, 0);
+                if constexpr (m == 0) acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[PA[m]], b[t][PB[m]], acc[t], 0, 0, 0);
+                else acs[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[PA[m]], b[t][PB[m]], acs[t], 0, 0, 0);
                 // staging work for the next stage, spread over the products of this one
                 b3_for<n1 - n0>([&](auto nc) { piece(n0 + nc.value, buf ^ 1, st + 2); });
                 __builtin_amdgcn_sched_barrier(0);
@@ -371,77 +373,109 @@ __global__ __launch_bounds__(C::NT, 2) void b3_kernel(B3Args p) {
 #pragma unroll
             for (int r = 0; r < 16; ++r) out[t * 16 + r] = acc[t][r] + acs[t][r];
     }
+    // Every operand of the fused tail is loaded before the first result is stored, and stores go through a buffer
+    // descriptor: what lies outside the output gets an offset that is dropped, so there is no branch per value.
     constexpr int ND = NR >= 16 ? NR / 16 : 1, NE = NR >= 16 ? 16 : NR;    // column tiles, registers of each
     static_assert(NE % 4 == 0, "a lane finishes groups of four rows");
+    const int r0 = NR >= 16 ? 0 : (wk * NR) % 16;                          // (tile row of register r: 8 (r / 4) + 4 half + r % 4)
+    const bool tail = p.splitk == 1;
+    const int flags = tail ? p.ef.flags : 0;
+    const auto ydst = __builtin_amdgcn_make_buffer_rsrc(tail ? p.y : p.partial + (int64_t)ks * p.c_numel, (short)0, (int)(p.c_numel * 4), 0x00020000);
+    const auto rsum = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(p.ef.add), (short)0, (int)(p.c_numel * 4), 0x00020000);
+    const auto rbias = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(p.ef.bias), (short)0, p.Cout * 4, 0x00020000);
+    uint32_t ob[ND];
 #pragma unroll
     for (int d = 0; d < ND; ++d) {
-        const int t = wk * NR / 16 + d, r0 = NR >= 16 ? 0 : (wk * NR) % 16;
+        const int t = wk * NR / 16 + d;
         const int j = j0 + (wn * TN + t) * 32 + l32;
-        int64_t ob = 0;
-        bool live = m_live;
         if constexpr (DENSE) {
-            live = live && j < p.Nrows;
-            ob = (int64_t)j * p.ldy;
+            ob[d] = m_live && j < p.Nrows ? (uint32_t)(j * p.ldy + 4 * half) * 4 : kB3Out;
         } else {
             const uint32_t g = b3_div((uint32_t)j, p.d_tw), im = b3_div(g, p.d_ho);
             const int oh = (int)g - (int)im * p.HO, ow = strip * p.TW + j - (int)g * p.TW;
-            live = live && j < p.Ntot && ow < p.WOe;
             int n = (int)im, od = 0;
             if (p.DO > 1) {
                 n = (int)b3_div(im, p.d_do);
                 od = (int)im - n * p.DO;
             }
-            ob = (int64_t)n * p.ons + (int64_t)od * p.npix + (int64_t)(oh * p.os + ph_a) * p.WO + ow * p.os + ph_b;
-        }
-        // (tile rows of register r: 8 (r / 4) + 4 half + r % 4)
-#pragma unroll
-        for (int e4 = 0; e4 < NE; e4 += 4) {
-            const int i = i0 + 8 * ((r0 + e4) / 4) + 4 * half;
-            const float *o = out + d * NE + e4;
-            if constexpr (DENSE) {
-                if (!live || i >= p.Cout) continue;
-                const int64_t oo = ob + (p.cs_len ? (int64_t)(i / p.cs_len) * p.cs_stride + i % p.cs_len : i);
-                if (i + 3 < p.Cout) {
-                    f32x4u v;
-                    f32x4u bv = {0.f, 0.f, 0.f, 0.f}, av = {0.f, 0.f, 0.f, 0.f};
-                    if (p.ef.flags & EF_BIAS) bv = *reinterpret_cast<const f32x4u *>(p.ef.bias + i);
-                    if (p.ef.flags & EF_ADD) av = *reinterpret_cast<const f32x4u *>(p.ef.add + oo);
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) v[e] = b3_finish(p.ef, o[e], bv[e], av[e]);
-                    *reinterpret_cast<f32x4u *>(p.y + oo) = v;
-                } else {
-#pragma unroll
-                    for (int e = 0; e < 4; ++e)
-                        if (i + e < p.Cout)
-                            p.y[oo + e] = b3_finish(p.ef, o[e], (p.ef.flags & EF_BIAS) ? p.ef.bias[i + e] : 0.f,
-                                                    (p.ef.flags & EF_ADD) ? p.ef.add[oo + e] : 0.f);
-                }
-            } else {
-                float bv[4], av[4];
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const bool w = live && i + e < p.Cout;
-                    const int64_t oo = ob + (int64_t)(i + e) * p.ocs;
-                    bv[e] = (w && p.splitk == 1 && (p.ef.flags & EF_BIAS)) ? p.ef.bias[i + e] : 0.f;
-                    av[e] = (w && p.splitk == 1 && (p.ef.flags & EF_ADD)) ? p.ef.add[oo] : 0.f;
-                }
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    if (!live || i + e >= p.Cout) continue;
-                    const int64_t oo = ob + (int64_t)(i + e) * p.ocs;
-                    if (p.splitk > 1) p.partial[(int64_t)ks * p.c_numel + oo] = o[e];
-                    else p.y[oo] = b3_finish(p.ef, o[e], bv[e], av[e]);
-                }
-            }
+            const uint32_t o = (uint32_t)(n * p.ons + od * p.npix + (oh * p.os + ph_a) * p.WO + ow * p.os + ph_b + 4 * half * p.ocs) * 4;
+            ob[d] = m_live && j < p.Ntot && ow < p.WOe ? o : kB3Out;
         }
     }
+    const int left = p.Cout - i0 - 4 * half;                               // rows of the tile this lane half may store, from its first one
+    float bv[NR], av[NR];
+#pragma unroll
+    for (int n = 0; n < NR; ++n) bv[n] = av[n] = 0.f;
+    if (flags & EF_BIAS) {
+#pragma unroll
+        for (int e = 0; e < NE; ++e) {
+            const float v = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rbias, (i0 + 4 * half) * 4, (8 * ((r0 + e) / 4) + (r0 + e) % 4) * 4, 0));
+#pragma unroll
+            for (int d = 0; d < ND; ++d) bv[d * NE + e] = v;
+        }
+    }
+    const int cbase_y = DENSE ? (p.cs_len ? (i0 / p.cs_len) * (int)p.cs_stride + i0 % p.cs_len : i0) : 0;
+    if constexpr (DENSE) {
+        if (p.Cout % 4 == 0) {                                             // four rows of the tile = 16 contiguous bytes
+            if (flags & EF_ADD) {
+#pragma unroll
+                for (int d = 0; d < ND; ++d)
+#pragma unroll
+                    for (int e = 0; e < NE; e += 4) {
+                        const int rr = 8 * ((r0 + e) / 4);
+                        const u32x4 v = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rsum, (int)(rr < left ? ob[d] : kB3Out), (cbase_y + rr) * 4, 0));
+#pragma unroll
+                        for (int f = 0; f < 4; ++f) av[d * NE + e + f] = __uint_as_float(v[f]);
+                    }
+            }
+            b3_tail<NR>(EpiFast{flags, p.ef.scale, nullptr, nullptr}, out, bv, av);
+#pragma unroll
+            for (int d = 0; d < ND; ++d)
+#pragma unroll
+                for (int e = 0; e < NE; e += 4) {
+                    const int rr = 8 * ((r0 + e) / 4);
+                    u32x4 v;
+#pragma unroll
+                    for (int f = 0; f < 4; ++f) v[f] = __float_as_uint(out[d * NE + e + f]);
+                    // (the offset all in the lane register: with a scalar offset the four data registers were overwritten by the
+                    // next vector instruction while the store still read them - the compiler inserts a wait only without one)
+                    __builtin_amdgcn_raw_buffer_store_b128(v, ydst, (int)((rr < left ? ob[d] : kB3Out) + (uint32_t)(cbase_y + rr) * 4u), 0, 0);
+                }
+            return;
+        }
+    }
+    const int rstep = DENSE ? 1 : p.ocs;
+    if (flags & EF_ADD) {
+#pragma unroll
+        for (int d = 0; d < ND; ++d)
+#pragma unroll
+            for (int e = 0; e < NE; ++e) {
+                const int rr = 8 * ((r0 + e) / 4) + (r0 + e) % 4;
+                av[d * NE + e] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsum, (int)(rr < left ? ob[d] : kB3Out),
+                                                                                      (DENSE ? cbase_y + rr : (i0 + rr) * rstep) * 4, 0));
+            }
+    }
+    b3_tail<NR>(EpiFast{flags, p.ef.scale, nullptr, nullptr}, out, bv, av);
+#pragma unroll
+    for (int d = 0; d < ND; ++d)
+#pragma unroll
+        for (int e = 0; e < NE; ++e) {
+            const int rr = 8 * ((r0 + e) / 4) + (r0 + e) % 4;
+            __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(out[d * NE + e]), ydst, (int)(rr < left ? ob[d] : kB3Out),
+                                                  (DENSE ? cbase_y + rr : (i0 + rr) * rstep) * 4, 0);
+        }
 }
 
-// host: launches one configuration (instantiated per filter class in gemm_b3_*.hip)
-template <int TAPS, bool FOLD, bool DENSE>
+// gemm_b3_first.hip: first layers (few input channels)
+bool first_resolve(const GemmArgs &g, B3Args *out);
+int launch_b3_first_pack(const B3Args &a, const float *w, void *dst, hipStream_t s);
+int launch_b3_first(const B3Args &a, hipStream_t s);
+
+// host: launches one configuration (instantiated per filter class in gemm_b3_point / _nine / _depth / _phase.hip)
+template <int TAPS, bool DEPTH, bool DENSE>
 int b3_launch_tile(const B3Args &a, hipStream_t s);
 
-template <class C, int TAPS, bool FOLD, bool DENSE, int UM>
+template <class C, int TAPS, bool DEPTH, bool DENSE, int UM>
 int b3_launch_um(const B3Args &a, hipStream_t s) {
     const int S = TAPS == 1 ? (DENSE ? C::BN + 2 : C::BN) : a.slot_stride;
     const size_t stage = (size_t)2 * 3 * 2 * C::WK * b3_cw<C, TAPS>() * S * 16;
@@ -449,41 +483,41 @@ int b3_launch_um(const B3Args &a, hipStream_t s) {
     if (lds > 64 * 1024) {
         static bool raised = false;          // more than 64 KB of dynamic LDS has to be allowed per kernel, once
         if (!raised) {
-            const hipError_t e = hipFuncSetAttribute((const void *)b3_kernel<C, TAPS, FOLD, DENSE, UM>,
+            const hipError_t e = hipFuncSetAttribute((const void *)b3_kernel<C, TAPS, DEPTH, DENSE, UM>,
                                                      hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
             if (e != hipSuccess) return (int)e;
             raised = true;
         }
     }
-    hipLaunchKernelGGL((b3_kernel<C, TAPS, FOLD, DENSE, UM>), dim3((unsigned)(a.mgroups * a.ntiles), 1, (unsigned)a.splitk),
+    hipLaunchKernelGGL((b3_kernel<C, TAPS, DEPTH, DENSE, UM>), dim3((unsigned)(a.mgroups * a.ntiles), 1, (unsigned)a.splitk),
                        dim3(C::NT), lds, s, a);
     return (int)hipGetLastError();
 }
 
-template <class C, int TAPS, bool FOLD, bool DENSE>
+template <class C, int TAPS, bool DEPTH, bool DENSE>
 int b3_launch_one(const B3Args &a, hipStream_t s) {
     if constexpr (TAPS == 1) {
-        return b3_launch_um<C, TAPS, FOLD, DENSE, b3_units1<C>()>(a, s);
+        return b3_launch_um<C, TAPS, DEPTH, DENSE, b3_units1<C>()>(a, s);
     } else {
         const int um = (a.units + C::NW - 1) / C::NW;
-        if (um <= 2) return b3_launch_um<C, TAPS, FOLD, DENSE, 2>(a, s);
-        if (um <= 4) return b3_launch_um<C, TAPS, FOLD, DENSE, 4>(a, s);
-        if (um <= 6) return b3_launch_um<C, TAPS, FOLD, DENSE, 6>(a, s);
+        if (um <= 2) return b3_launch_um<C, TAPS, DEPTH, DENSE, 2>(a, s);
+        if (um <= 4) return b3_launch_um<C, TAPS, DEPTH, DENSE, 4>(a, s);
+        if (um <= 6) return b3_launch_um<C, TAPS, DEPTH, DENSE, 6>(a, s);
         return (int)hipErrorInvalidValue;
     }
 }
 
-#define CLG_B3_INSTANTIATE(TAPS, FOLD, DENSE)                                             \
+#define CLG_B3_INSTANTIATE(TAPS, DEPTH, DENSE)                                             \
     template <>                                                                           \
-    int b3_launch_tile<TAPS, FOLD, DENSE>(const B3Args &a, hipStream_t s) {               \
+    int b3_launch_tile<TAPS, DEPTH, DENSE>(const B3Args &a, hipStream_t s) {               \
         switch (a.tile) {                                                                 \
-        case B3_L: return b3_launch_one<B3L, TAPS, FOLD, DENSE>(a, s);                    \
-        case B3_LM: return b3_launch_one<B3LM, TAPS, FOLD, DENSE>(a, s);                  \
-        case B3_M: return b3_launch_one<B3M, TAPS, FOLD, DENSE>(a, s);                    \
-        case B3_S: return b3_launch_one<B3S, TAPS, FOLD, DENSE>(a, s);                    \
-        case B3_SS: return b3_launch_one<B3SS, TAPS, FOLD, DENSE>(a, s);                  \
-        case B3_G: return b3_launch_one<B3G, TAPS, FOLD, DENSE>(a, s);                    \
-        case B3_G2: return b3_launch_one<B3G2, TAPS, FOLD, DENSE>(a, s);                  \
+        case B3_L: return b3_launch_one<B3L, TAPS, DEPTH, DENSE>(a, s);                    \
+        case B3_LM: return b3_launch_one<B3LM, TAPS, DEPTH, DENSE>(a, s);                  \
+        case B3_M: return b3_launch_one<B3M, TAPS, DEPTH, DENSE>(a, s);                    \
+        case B3_S: return b3_launch_one<B3S, TAPS, DEPTH, DENSE>(a, s);                    \
+        case B3_SS: return b3_launch_one<B3SS, TAPS, DEPTH, DENSE>(a, s);                  \
+        case B3_G: return b3_launch_one<B3G, TAPS, DEPTH, DENSE>(a, s);                    \
+        case B3_G2: return b3_launch_one<B3G2, TAPS, DEPTH, DENSE>(a, s);                  \
         default: return (int)hipErrorInvalidValue;                                        \
         }                                                                                 \
     }

@@ -6,13 +6,10 @@
 namespace clg {
 
 template <> int b3_launch_tile<1, false, false>(const B3Args &a, hipStream_t s);
-template <> int b3_launch_tile<1, true, false>(const B3Args &a, hipStream_t s);
 template <> int b3_launch_tile<1, false, true>(const B3Args &a, hipStream_t s);
 template <> int b3_launch_tile<9, false, false>(const B3Args &a, hipStream_t s);
 template <> int b3_launch_tile<9, true, false>(const B3Args &a, hipStream_t s);
 template <> int b3_launch_tile<4, false, false>(const B3Args &a, hipStream_t s);
-template <> int b3_launch_tile<3, true, false>(const B3Args &a, hipStream_t s);
-template <> int b3_launch_tile<8, true, false>(const B3Args &a, hipStream_t s);
 
 namespace {
 
@@ -69,7 +66,7 @@ bool place(B3Args *a, int tile) {
             }
             // output rows a run of bn pixels touches; a step to the next image skips the rest of its patch rows
             const int halo_h = a->KHe + a->phe_max;          // patch rows of one output row (phe_max: extra rows of the other phases)
-            const int halo_w = (a->fold_w ? 1 : a->KWe) + a->pwe_max;
+            const int halo_w = a->KWe + a->pwe_max;
             const int rows = bn % tw == 0 ? bn / tw : ceil_div(bn - 1, tw) + 1;
             const int cross = a->Nimg > 1 ? std::min(ceil_div(rows - 1, a->HO), a->Nimg - 1) : 0;
             const int vrows = (rows - 1) * a->ly + cross * std::max(0, halo_h - a->ly) + halo_h;
@@ -96,7 +93,7 @@ bool place(B3Args *a, int tile) {
         if (best < 0) return false;
         ok = ok && set_div(&a->d_tw, a->TW, (int64_t)a->Ntot + bn) && set_div(&a->d_strip, a->tiles_strip, a->ntiles) && set_div(&a->d_ho, a->HO, (int64_t)a->Ntot / a->TW + bn) &&
              set_div(&a->d_pw, a->pw_slots, a->slots + 64) && set_div(&a->d_rpi, a->rpi, (int64_t)a->Nimg * a->rpi + a->slots) &&
-             set_div(&a->d_do, a->DO, a->Nimg + 64) && set_div(&a->d_cpgo, a->groups > 1 ? a->cpg_out : 1, a->Cout + 32);
+             set_div(&a->d_do, a->DO, a->Nimg + 64) && set_div(&a->d_kd, a->KD, a->nC) && set_div(&a->d_cpgo, a->groups > 1 ? a->cpg_out : 1, a->Cout + 32);
     }
     ok = ok && set_div(&a->d_g32, a->g32, a->units + 64);
     a->tile_div = a->jmajor ? a->mgroups : a->ntiles;
@@ -110,14 +107,15 @@ bool place(B3Args *a, int tile) {
 
 bool b3_resolve(const GemmArgs &g, int tile, int epi_flags, int n_cus, B3Args *out) {
     if (epi_flags & EF_GENERIC) return false;
+    if (first_resolve(g, out)) return true;
     B3Args a{};
     a.epi = g.epi;
     a.c_numel = g.c_numel;
-    if (g.c_numel >= ((int64_t)1 << 31)) return false;
+    if (g.c_numel >= ((int64_t)1 << 29)) return false;                   // 31-bit byte offsets
     a.phases = 1;
     a.groups = 1;
     a.taps = 1;
-    a.DO = a.D = a.KD = a.KWf = 1;
+    a.DO = a.D = a.KD = 1;
     if (g.mode == GM_NT) {
         if (g.batch != 1 || g.K % 16 || (int64_t)g.M * g.lda >= ((int64_t)1 << 29) || (g.cs_len && g.cs_len % 32)) return false;
         a.dense = 1;
@@ -193,36 +191,22 @@ bool b3_resolve(const GemmArgs &g, int tile, int epi_flags, int n_cus, B3Args *o
             }
             const bool one = g.KH == 1 && g.KW == 1, three = g.KH == 3 && g.KW == 3;
             if (one && (g.ph || g.pw)) return false;
-            a.fold = cin % 16 != 0 || a.KD > 1;
-            if (a.KD == 1 && a.pd != 0) return false;
-            if (one) {
-                a.taps = 1;
-            } else if (three && cin % 16 == 0) {
-                a.taps = 9;
-            } else if (three || (g.KH == 7 && g.KW <= 16)) {
-                // few channels: the filter columns are folded into the channel index, a step is a filter row
-                a.fold = a.fold_w = 1;
-                a.KWf = g.KW;
-                a.KWe = 1;
-                a.taps = three ? 3 : 8;
-            } else {
-                return false;
-            }
-            if (a.groups > 1 && a.fold) return false;
+            if (a.KD == 1 ? a.pd != 0 : !three) return false;
+            if (a.groups == 1 && cin % 16 && cin < 64) return false;          // mostly padding (first layers: first_resolve)
+            a.taps = one ? 1 : 9;
+            if (!one && !three) return false;
         }
-        if (a.fold_w && cin * a.KD * a.KWf > 512) return false;      // (first layers; nothing wider is worth an offset table per value)
-        a.Cf = cin * a.KD * a.KWf;
-        a.nC = ceil_div(a.Cf, 16);
+        a.Cf = cin;
+        a.nC = ceil_div(cin, 16) * a.KD;
         // slot geometry: with one filter row (column) only the rows (columns) that are read get slots
         a.ys = a.KHe == 1 ? she : 1;
         a.ly = a.KHe == 1 ? 1 : she;
-        const bool one_col = a.fold_w || a.KWe == 1;
+        const bool one_col = a.KWe == 1;
         a.xs = one_col ? swe : 1;
         a.lx = one_col ? 1 : swe;
-        a.npix = (a.convt ? g.HO * g.WO : g.HO * g.WO);
+        a.npix = g.HO * g.WO;
         a.ocs = a.DO * a.npix;
         a.ons = g.Cout * a.ocs;
-        if ((int64_t)g.Cout * a.ocs >= ((int64_t)1 << 31)) return false;
         a.jmajor = (int64_t)g.Nimg * g.Cin * a.cs > (int64_t)g.Cout * cin * g.KH * g.KW * a.KD ? 1 : 0;
         if (!a.convt) a.phe_max = a.pwe_max = 0;
         if ((int64_t)a.Nimg * a.HO * a.WOe > ((int64_t)1 << 28)) return false;
@@ -253,9 +237,7 @@ bool b3_resolve(const GemmArgs &g, int tile, int epi_flags, int n_cus, B3Args *o
     return true;
 }
 
-size_t b3_pack_bytes(const B3Args &a) {
-    return (size_t)a.pack_steps * 3 * kWave * 16 + (a.fold ? (size_t)a.stages * tile_shape(a.tile).wk * tile_cw(a.tile, a.taps) * 16 * 8 : 0);
-}
+size_t b3_pack_bytes(const B3Args &a) { return (size_t)a.pack_steps * 3 * kWave * 16; }
 
 size_t b3_scratch_bytes(const B3Args &a) { return a.splitk > 1 ? (size_t)a.splitk * (size_t)a.c_numel * sizeof(float) : 0; }
 
@@ -275,7 +257,8 @@ __global__ __launch_bounds__(256) void b3_pack_kernel(const float *w, u32x4 *dst
     const int64_t mt = wave / wk_n;
     const int phase = (int)(mt / p.tiles_m);
     const int i = (int)(mt - (int64_t)phase * p.tiles_m) * 32 + lane % 32;
-    const int c16 = (blk / cw) * wk_n * cw + wk * cw + blk % cw;
+    const int b = (blk / cw) * wk_n * cw + wk * cw + blk % cw;         // block of 16 channels (and depth tap)
+    const int c16 = b / p.KD, kd = b - c16 * p.KD;
     float v[8];
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
@@ -290,17 +273,11 @@ __global__ __launch_bounds__(256) void b3_pack_kernel(const float *w, u32x4 *dst
                 const int uh = tap / p.KWe, uw = tap - uh * p.KWe;
                 const int kh = (a_h + p.ph_t) % p.sh + p.sh * (p.KHe - 1 - uh), kw = (a_w + p.pw_t) % p.sw + p.sw * (p.KWe - 1 - uw);
                 x = w[(((int64_t)c * p.Cout + i) * p.KH + kh) * p.KW + kw];
+            } else if (p.groups > 1) {
+                const int ch = ((i / 32 * 32) / p.cpg_out) * p.cpg_in + c, grp = i / p.cpg_out;
+                if (ch / p.cpg_in == grp) x = w[((int64_t)i * p.cpg_in + (ch - grp * p.cpg_in)) * p.taps + tap];
             } else {
-                const int kwf = c % p.KWf, kd = (c / p.KWf) % p.KD, cl = c / (p.KWf * p.KD);
-                const int kh = p.KWf > 1 || p.KW == 1 ? tap : tap / p.KW, kw = p.KWf > 1 ? kwf : (p.KW == 1 ? 0 : tap % p.KW);
-                if (kh < p.KH) {
-                    if (p.groups > 1) {
-                        const int ch = ((i / 32 * 32) / p.cpg_out) * p.cpg_in + cl, grp = i / p.cpg_out;
-                        if (ch / p.cpg_in == grp) x = w[(((int64_t)i * p.cpg_in + (ch - grp * p.cpg_in)) * p.KH + kh) * p.KW + kw];
-                    } else {
-                        x = w[((((int64_t)i * p.Cin + cl) * p.KD + kd) * p.KH + kh) * p.KW + kw];
-                    }
-                }
+                x = w[(((int64_t)i * p.Cin + c) * p.KD + kd) * p.taps + tap];
             }
         }
         v[e] = x;
@@ -318,25 +295,13 @@ __global__ __launch_bounds__(256) void b3_pack_kernel(const float *w, u32x4 *dst
     for (int k = 0; k < 3; ++k) dst[(step * 3 + k) * kWave + lane] = pl[k];
 }
 
-// Byte offset and tap of every folded channel (c * KD + kd) * KWf + kw; channels past the last one get a depth tap no input has.
-__global__ __launch_bounds__(256) void b3_table_kernel(int2 *dst, B3Args p, int n) {
-    const int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= n) return;
-    const int kw = c % p.KWf, kd = (c / p.KWf) % p.KD, cl = c / (p.KWf * p.KD);
-    dst[c] = c < p.Cf ? make_int2((cl * p.cs + kd * p.HW + kw) * 4, kd | (kw << 16)) : make_int2(0, 0x7fff);
-}
-
 }  // namespace
 
 int launch_b3_pack(const B3Args &a, const float *w, void *dst, void *stream) {
+    if (a.tile == B3_FIRST) return launch_b3_first_pack(a, w, dst, (hipStream_t)stream);
     const int64_t threads = a.pack_steps * kWave;
-    const int wk = tile_shape(a.tile).wk, cw = tile_cw(a.tile, a.taps);
-    hipLaunchKernelGGL(b3_pack_kernel, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, (hipStream_t)stream, w, (u32x4 *)dst, a, wk, cw);
-    int e = (int)hipGetLastError();
-    if (e || !a.fold) return e;
-    const int n = a.stages * wk * cw * 16;
-    hipLaunchKernelGGL(b3_table_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, (hipStream_t)stream,
-                       (int2 *)((char *)dst + (size_t)a.pack_steps * 3 * kWave * 16), a, n);
+    hipLaunchKernelGGL(b3_pack_kernel, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, (hipStream_t)stream, w, (u32x4 *)dst, a,
+                       tile_shape(a.tile).wk, tile_cw(a.tile, a.taps));
     return (int)hipGetLastError();
 }
 
@@ -345,14 +310,12 @@ int launch_b3(const B3Args &a_in, void *stream) {
     hipStream_t s = (hipStream_t)stream;
     a.ef = make_epi_fast(a.epi);
     if (a.ef.flags & EF_GENERIC) return (int)hipErrorInvalidValue;
-    a.table = (const int32_t *)((const char *)a.w + (size_t)a.pack_steps * 3 * kWave * 16);
     int e;
+    if (a.tile == B3_FIRST) return launch_b3_first(a, s);
     if (a.dense) e = b3_launch_tile<1, false, true>(a, s);
-    else if (a.taps == 1) e = a.fold ? b3_launch_tile<1, true, false>(a, s) : b3_launch_tile<1, false, false>(a, s);
-    else if (a.taps == 9) e = a.fold ? b3_launch_tile<9, true, false>(a, s) : b3_launch_tile<9, false, false>(a, s);
+    else if (a.taps == 1) e = b3_launch_tile<1, false, false>(a, s);
+    else if (a.taps == 9) e = a.KD > 1 ? b3_launch_tile<9, true, false>(a, s) : b3_launch_tile<9, false, false>(a, s);
     else if (a.taps == 4) e = b3_launch_tile<4, false, false>(a, s);
-    else if (a.taps == 3) e = b3_launch_tile<3, true, false>(a, s);
-    else if (a.taps == 8) e = b3_launch_tile<8, true, false>(a, s);
     else e = (int)hipErrorInvalidValue;
     if (e || a.splitk <= 1) return e;
     return launch_splitk_reduce(a.partial, a.y, a.c_numel, a.splitk, a.epi, stream);

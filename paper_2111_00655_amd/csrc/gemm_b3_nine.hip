@@ -3,5 +3,4 @@
 
 namespace clg {
 CLG_B3_INSTANTIATE(9, false, false)
-CLG_B3_INSTANTIATE(9, true, false)
 }  // namespace clg

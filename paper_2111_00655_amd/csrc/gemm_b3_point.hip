@@ -3,6 +3,5 @@
 
 namespace clg {
 CLG_B3_INSTANTIATE(1, false, false)
-CLG_B3_INSTANTIATE(1, true, false)
 CLG_B3_INSTANTIATE(1, false, true)
 }  // namespace clg

@@ -232,16 +232,15 @@ bool attention_shape_ok(const AttentionArgs &a);       // d in {32, 64, 128}, Sk
 int launch_attention(const AttentionArgs &a, void *stream);
 
 // ---- contractions on the bf16 matrix cores, operands split exactly into three bf16 values (gemm_b3.h) ----
-enum B3Tile : int32_t { B3_NONE = 0, B3_L = 1, B3_LM = 2, B3_M = 3, B3_S = 4, B3_SS = 5, B3_G = 6, B3_G2 = 7 };
+enum B3Tile : int32_t { B3_NONE = 0, B3_L = 1, B3_LM = 2, B3_M = 3, B3_S = 4, B3_SS = 5, B3_G = 6, B3_G2 = 7, B3_FIRST = 8 };
 struct B3Div { uint32_t m, one; };         // division by multiply-high: b3_div
 struct B3Args {
     const float *x;                        // input, NCHW (or rows of a dense layer)
     const void *w;                         // packed weights (b3_pack_bytes)
-    const int32_t *table;                  // FOLD: (offset, kd | kw << 16) per folded channel; lies behind the packed weights
     float *y;
     float *partial;                        // split-K partial sums [splitk][c_numel]
     EpiFast ef;                            // filled by launch_b3 from epi
-    B3Div d_tile, d_strip, d_tw, d_ho, d_g32, d_pw, d_rpi, d_do, d_cpgo;
+    B3Div d_tile, d_strip, d_tw, d_ho, d_g32, d_pw, d_rpi, d_do, d_cpgo, d_kd;
     int32_t x_bytes;
     int32_t tile_div, jmajor, mtiles, tiles_m, phases;      // packed row tiles: phases * tiles_m
     int32_t mgroups, ntiles, tiles_strip;                   // grid.x = mgroups * ntiles
@@ -249,15 +248,17 @@ struct B3Args {
     int32_t slot_stride, slots, units, g32, pw_slots;       // patch: slots = rows * pw_slots
     int32_t HO, WOe, TW, rpi, ly, lx, ys, xs;               // output rows / columns per phase; strip width; slot geometry
     int32_t Nimg, Ntot, img_stride, HW, W, H, cs, ph, pwd;  // Nimg counts (image, output depth) pairs
-    int32_t D, DO, sd, pd, fold_w, nC;
+    int32_t D, DO, sd, pd, KD, nC;                          // nC: blocks of 16 channels, times KD
     int32_t groups, cpg_in;
     int32_t KHe, KWe, sh, sw, ph_t, pw_t, phe_max, pwe_max;
     int32_t Cout, WO, os, npix, ons, ocs;                   // output strides
     int32_t Nrows, ldx, ldy, K, cs_len;                     // dense
     int64_t cs_stride, c_numel;
+    // first layers (gemm_b3_first.hip)
+    int32_t TH, tiles_x, tiles_y, prow, pxw, cps, steps;
     // host side only
-    int32_t tile, taps, fold, dense;
-    int32_t Cin, KD, KH, KW, KWf, cpg_out, ldb, convt, Cf;
+    int32_t tile, taps, dense;
+    int32_t Cin, KH, KW, cpg_out, ldb, convt, Cf;           // Cf: channels (per group of an m-tile), or K of a dense layer
     int64_t pack_steps;                                     // 3 KB steps of packed weights, padding included
     Epilogue epi;
 };

@@ -279,13 +279,13 @@ bool lower_b3(const Context &ctx, const Backend &be, const GemmArgs &a, const Ep
     if (gemv_shape_ok(a, epi_fast_flags(epi))) return false;          // a handful of rows: streaming the weights once is the bound
     B3Args b;
     if (!b3_resolve(a, tile, epi_fast_flags(epi), ctx.n_cus, &b)) return false;
-    static const char *tn[] = {"", "m128n128", "m64n128", "m64n64", "m32n64", "m32n32", "m32n256", "m32n128"};
+    static const char *tn[] = {"", "m128n128", "m64n128", "m64n64", "m32n64", "m32n32", "m32n256", "m32n128", "first"};
     c->kind = CALL_B3;
     c->b3 = b;
     c->b3.epi = epi;
     c->pack_bytes = b3_pack_bytes(b);
     c->scratch_bytes = b3_scratch_bytes(b);
-    c->name = what + "_rfb3_" + tn[b.tile] + (b.dense ? "" : "_t" + std::to_string(b.taps)) + (b.fold ? "f" : "") + (b.cs_len ? "_split" : "");
+    c->name = what + "_rfb3_" + tn[b.tile] + (b.dense ? "" : "_t" + std::to_string(b.taps)) + (b.cs_len ? "_split" : "");
     return true;
 }
 

@@ -1,0 +1,106 @@
+"""The contractions on the bf16 matrix cores with exactly split fp32 operands, at the sizes where
+they can go wrong: tile remainders in every direction, tiles that span images and strips, channel counts that
+are no multiple of a block, fewer stages than K-waves, strides, depth taps, phases, first layers.  Against float64, with a
+bar below what fp32 accumulation in one chain leaves (a lost or doubled product plane is 1e-3 and more)."""
+import numpy as np
+import pytest
+
+import workloads as wl
+from workloads.patterns import P, W
+import paper_2111_00655_amd as clg
+
+pytestmark = pytest.mark.gpu
+
+# the backends that run these kernels: tiles 128x128 / 64x128, 64x64, automatic, and the split-K ones without a split
+BACKENDS = ("igemm_l", "igemm_m", "igemm", "igemm_r32_sk", "igemm_r16_sk", "igemm_r16_sk_w4")
+
+# kind, images, in, out channels, spatial, filter, stride, pad, groups
+CASES = [
+    ("conv2d", 1, 64, 128, (16, 16), (1, 1), (1, 1), (0, 0), 1),
+    ("conv2d", 3, 72, 130, (7, 9), (1, 1), (1, 1), (0, 0), 1),
+    ("conv2d", 5, 128, 33, (13, 13), (1, 1), (2, 2), (0, 0), 1),
+    ("conv2d", 2, 200, 64, (1, 1), (1, 1), (1, 1), (0, 0), 1),
+    ("conv2d", 1, 64, 64, (57, 61), (3, 3), (1, 1), (1, 1), 1),
+    ("conv2d", 4, 64, 96, (7, 7), (3, 3), (1, 1), (1, 1), 1),
+    ("conv2d", 2, 80, 40, (15, 11), (3, 3), (2, 2), (1, 1), 1),
+    ("conv2d", 1, 64, 65, (3, 200), (3, 3), (1, 2), (0, 1), 1),
+    ("conv2d", 3, 128, 128, (14, 10), (3, 3), (1, 1), (1, 1), 32),
+    ("conv2d", 2, 64, 64, (9, 9), (3, 3), (2, 2), (1, 1), 2),
+    ("conv2d", 1, 3, 64, (45, 51), (7, 7), (2, 2), (3, 3), 1),
+    ("conv2d", 2, 3, 35, (33, 30), (3, 3), (2, 2), (1, 1), 1),
+    ("conv2d", 1, 4, 16, (9, 64), (1, 8), (1, 2), (0, 0), 1),
+    ("conv3d", 1, 64, 70, (5, 9, 7), (3, 3, 3), (1, 1, 1), (1, 1, 1), 1),
+    ("conv3d", 2, 32, 64, (4, 8, 8), (3, 3, 3), (2, 2, 2), (1, 1, 1), 1),
+    ("conv3d", 1, 64, 64, (3, 6, 5), (1, 1, 1), (2, 2, 2), (0, 0, 0), 1),
+    ("conv3d", 1, 3, 40, (8, 44, 47), (7, 7, 7), (1, 2, 2), (3, 3, 3), 1),
+    ("conv2d_transpose", 3, 64, 70, (5, 7), (4, 4), (2, 2), (1, 1), 1),
+    ("conv2d_transpose", 1, 32, 24, (9, 4), (4, 4), (2, 2), (0, 0), 1),
+    ("dense", 129, 768, 192, None, None, None, None, 1),
+    ("dense", 33, 48, 70, None, None, None, None, 1),
+    ("dense", 9, 3072, 130, None, None, None, None, 1),
+]
+
+
+@pytest.mark.parametrize("tail", [(), ("bias_add", "add", "relu"), ("bias_add", "tanh")], ids=lambda t: "+".join(t) or "none")
+@pytest.mark.parametrize("ci", range(len(CASES)))
+def test_split_operand_contractions_against_float64(ci, tail):
+    import torch
+    F = torch.nn.functional
+    kind, n, cin, cout, sp, k, s, p, g = CASES[ci]
+    r = np.random.default_rng([31, ci])
+
+    def f32(*shape, scale=1.0):
+        return (r.standard_normal(shape) * scale).astype(np.float32)
+
+    d = wl.GraphDesc("b3")
+    if kind == "dense":
+        x, w = f32(n, cin), f32(cout, cin, scale=cin ** -0.5)
+        ref = torch.from_numpy(x).double() @ torch.from_numpy(w).double().T
+        y = d.op("dense", [d.input(x), d.const(w)])
+    else:
+        x = f32(n, cin, *sp)
+        wshape = (cin, cout, *k) if kind == "conv2d_transpose" else (cout, cin // g, *k)
+        w = f32(*wshape, scale=(cin // g * float(np.prod(k))) ** -0.5)
+        f = {"conv2d": F.conv2d, "conv3d": F.conv3d, "conv2d_transpose": F.conv_transpose2d}[kind]
+        grouped = {"groups": g} if kind == "conv2d" else {}
+        ref = f(torch.from_numpy(x).double(), torch.from_numpy(w).double(), stride=s, padding=p, **grouped)
+        y = d.op(kind, [d.input(x), d.const(w)], stride=s, pad=p, **grouped)
+    ref = ref.numpy()
+    pat = P(kind, W, W)
+    for op in tail:
+        if op == "bias_add":
+            b = f32(cout)
+            ref = ref + b.astype(np.float64).reshape((1, -1) + (1,) * (ref.ndim - 2))
+            y = d.op("bias_add", [y, d.const(b)], axis=1)
+            pat = P("bias_add", pat, W)
+        elif op == "add":
+            a = f32(*ref.shape)
+            ref = ref + a
+            y = d.op("add", [y, d.input(a)])
+            pat = P("add", pat, W)
+        else:
+            ref = np.maximum(ref, 0) if op == "relu" else np.tanh(ref)
+            y = d.op(op, [y])
+            pat = P(op, pat)
+    d.mark_output(y)
+    ran = set()
+    for be in BACKENDS:
+        sess = clg.Session(d, [(be, pat)], device=0)
+        full = [i for i, m in enumerate(sess.match()) if m.n_nodes == len(d.op_nodes())]
+        try:
+            plan = sess.compile(full)
+        except clg.ClgError as e:
+            assert e.status == "NO_KERNEL", str(e)
+            sess.close()
+            continue
+        name = plan.kernels()[0]["name"]
+        got, again = plan.run()[0], plan.run()[0]
+        sess.close()
+        if "_rfb3_" not in name:
+            continue
+        ran.add(name)
+        assert np.array_equal(got, again), (be, name, "not deterministic")
+        err = np.linalg.norm(got - ref) / np.linalg.norm(ref)
+        worst = np.abs(got - ref).max() / np.abs(ref).max()
+        assert err < 1e-6 and worst < 4e-6, (be, name, err, worst)
+    assert ran, (CASES[ci], "no backend ran the split-operand kernels")
