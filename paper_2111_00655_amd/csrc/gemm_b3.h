@@ -14,9 +14,10 @@
 // against 4.2e-7): the leading products have an accumulator of their own, which is
 // rounded once per 16 values of k instead of once per 2.  Six bf16 MFMAs of 32x32x16
 // take 192 cycles of a matrix core, eight fp32 MFMAs of 32x32x2 take 512: 417 instead
-// of 157 TFLOP/s.  An operand that is infinite, or
-// within 2^-9 of the largest float, gives NaN where a fp32 product chain would give an
-// infinity; magnitudes below 2^-110 lose their last bits (absolute error < 2^-126).
+// of 157 TFLOP/s.  Infinities and NaN pass through the leading planes as through a fp32 product chain, and
+// a sum of theirs that is not finite is the result (b3_sum: the small planes of an infinity are NaN); what meets
+// a padded weight is zero, so they reach no other output.  An operand within 2^-9 of the largest float rounds to
+// an infinity; magnitudes below 2^-110 lose their last bits (absolute error < 2^-126).
 //
 // Structure.  A wave owns 32 output rows (channels) and TN tiles of 32 output columns
 // (pixels); a workgroup has WM waves along the rows, WN along the columns and WK that
@@ -94,6 +95,9 @@ __device__ __forceinline__ void b3_split2(float a, float b, uint32_t &h, uint32_
     b -= __uint_as_float(m & 0xffff0000u);
     l = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2v{a, b}, bf16x2));
 }
+
+// The leading products' sum and the small ones'.
+__device__ __forceinline__ float b3_sum(float lead, float small) { return __builtin_isfinite(lead) ? lead + small : lead; }
 
 // The fused tail on a lane's N finished values at once.  (Tests of the flags value by value, with the bodies of erff
 // and tanhf in between, made 31 KB of code and cost 4 us at the end of a workgroup.)
@@ -228,12 +232,14 @@ __global__ __launch_bounds__(C::NT, 2) void b3_kernel(B3Args p) {
     }
     const int cbase = (!DENSE && p.groups > 1) ? (int)b3_div((uint32_t)i0, p.d_cpgo) * p.cpg_in : 0;
 
+    // blocks (and depth taps) in which this lane's eight channels exist; the others are zero, as their weights are
+    const int blk_end = DENSE ? 0 : ((p.Cf - half * 8 + 15) >> 4) * (DEPTH ? p.KD : 1);
     float xv[UM][8];
     auto load = [&](int u, int st_) {
         const int st = min(st_, p.stages - 1);
         if constexpr (DENSE) {
-            const int k = min(st * SC * 16 + c16l[u], p.K - 8);            // past the end: finite values that meet zero weights
-            const uint32_t o = (off[u] + (uint32_t)k) * 4;
+            const int k = st * SC * 16 + c16l[u];
+            const uint32_t o = k < p.K ? (off[u] + (uint32_t)k) * 4 : kB3Out;
             const u32x4 a = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)o, 0, 0));
             const u32x4 b = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)o, 16, 0));
 #pragma unroll
@@ -244,18 +250,19 @@ __global__ __launch_bounds__(C::NT, 2) void b3_kernel(B3Args p) {
         } else if constexpr (DEPTH) {
             // block: (16 channels, depth tap); a plane before or behind the volume is zero
             const int blk = min(st * SC + c16l[u], p.nC - 1), c16 = (int)b3_div((uint32_t)blk, p.d_kd), kd = blk - c16 * p.KD;
-            const int so = c16 * 16 * p.cs * 4;
-            const bool in = off[u] != kB3Out && (uint32_t)(idu[u] + kd) < (uint32_t)p.D;
+            const int so = c16 * 16 * p.cs * 4;                            // (within the buffer: the bounds check subtracts it from the size)
+            const bool in = off[u] != kB3Out && st * SC + c16l[u] < blk_end && (uint32_t)(idu[u] + kd) < (uint32_t)p.D;
             const uint32_t o = in ? off[u] + (uint32_t)(kd * p.HW * 4) : kB3Out;      // (off may lie in front of the volume)
 #pragma unroll
             for (int i = 0; i < 8; ++i)
                 xv[u][i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsrc, (int)o, so + i * p.cs * 4, 0));
         } else {
-            const int c = cbase + min(st * SC + c16l[u], p.nC - 1) * 16;   // past the last block: meets zero weights
-            const int so = c * p.cs * 4;
+            const int c = cbase + min(st * SC + c16l[u], p.nC - 1) * 16;
+            const int so = c * p.cs * 4;                                   // (within the buffer: the bounds check subtracts it from the size)
+            const uint32_t o = st * SC + c16l[u] < blk_end ? off[u] : kB3Out;
 #pragma unroll
             for (int i = 0; i < 8; ++i)
-                xv[u][i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsrc, (int)off[u], so + i * p.cs * 4, 0));
+                xv[u][i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsrc, (int)o, so + i * p.cs * 4, 0));
         }
     };
     u32x4 pl[3];
@@ -357,7 +364,7 @@ __global__ __launch_bounds__(C::NT, 2) void b3_kernel(B3Args p) {
 #pragma unroll
         for (int t = 0; t < TN; ++t)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) red[wave * PER + (t * 16 + r) * kWave + lane] = acc[t][r] + acs[t][r];
+            for (int r = 0; r < 16; ++r) red[wave * PER + (t * 16 + r) * kWave + lane] = b3_sum(acc[t][r], acs[t][r]);
         __syncthreads();
         const int w0 = wave - wk;
 #pragma unroll
@@ -371,7 +378,7 @@ __global__ __launch_bounds__(C::NT, 2) void b3_kernel(B3Args p) {
 #pragma unroll
         for (int t = 0; t < TN; ++t)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) out[t * 16 + r] = acc[t][r] + acs[t][r];
+            for (int r = 0; r < 16; ++r) out[t * 16 + r] = b3_sum(acc[t][r], acs[t][r]);
     }
     // Every operand of the fused tail is loaded before the first result is stored, and stores go through a buffer
     // descriptor: what lies outside the output gets an offset that is dropped, so there is no branch per value.

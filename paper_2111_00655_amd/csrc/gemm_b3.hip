@@ -192,7 +192,7 @@ bool b3_resolve(const GemmArgs &g, int tile, int epi_flags, int n_cus, B3Args *o
             const bool one = g.KH == 1 && g.KW == 1, three = g.KH == 3 && g.KW == 3;
             if (one && (g.ph || g.pw)) return false;
             if (a.KD == 1 ? a.pd != 0 : !three) return false;
-            if (a.groups == 1 && cin % 16 && cin < 64) return false;          // mostly padding (first layers: first_resolve)
+            if (a.groups == 1 && cin % 16 && (cin < 64 || cin % 8)) return false;      // mostly padding (first layers: first_resolve); a lane's eight channels exist or do not
             a.taps = one ? 1 : 9;
             if (!one && !three) return false;
         }

@@ -5,7 +5,7 @@
 // bound the register-fed kernel: 7x7 stride 2, 3 -> 64 channels at 224x224 and batch 32 took 206 us, for
 // 7.6 GFLOP and 122 MB.  Here k runs along an input row: for a fixed (channel, depth tap, filter row)
 // the eight values x[2 ow - pad .. + 7] are eight consecutive bf16 in LDS, which a lane reads with one
-// 16-byte load at a 4-byte aligned address; columns past the filter's width meet zero weights.
+// 16-byte load at a 4-byte aligned address; columns past the filter's width are cleared.
 // An MFMA takes two such rows (one per lane half).  A workgroup copies the input patch of its 128 (256) output
 // pixels once, split into the three planes; the patch is 2.5 times its output in values, so the split costs
 // little, and the kernel is bound by its stores (64 channels of output per 3 of input).
@@ -121,22 +121,29 @@ __global__ __launch_bounds__(256, 2) void b3_first_kernel(B3Args p) {
         if (st + 1 < p.stages) load(st + 1);
         b3_barrier();
         const uint32_t *P0 = b3_patch + buf * 3 * PL;
-        // filter rows 2 q and 2 q + 1 of the stage, as (plane, row); past the last one: its weights are zero
+        // filter rows 2 q and 2 q + 1 of the stage, as (plane, row); past the last one: cleared, as its weights are
         int kh0 = 0, r0 = 0, kh1 = 1, r1 = 1;
         if (p.KHe == 1) {
             kh1 = 0;
             r1 = p.prow;
         }
         const int last = (p.cps - 1) * p.prow + p.KHe - 1;
+        // columns past the filter and rows past the last one are cleared: an infinity among them would be NaN times a zero weight
+        u32x4 cols;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) cols[e] = 2 * e + 1 < p.KWe ? ~0u : (2 * e < p.KWe ? 0xffffu : 0u);
         auto step = [&](auto sc) {
             constexpr int s = sc.value;
-            const int ro = (half ? min(r1, last) : min(r0, last)) * words;
+            const int row = half ? r1 : r0, ro = min(row, last) * words;
+            u32x4 keep;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) keep[e] = row <= last ? cols[e] : 0u;
             bf16x8 b[TN][3], a[3];
 #pragma unroll
             for (int t = 0; t < TN; ++t)
 #pragma unroll
                 for (int k = 0; k < 3; ++k)
-                    b[t][k] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4a *>(P0 + k * PL + sbase[t] + ro));
+                    b[t][k] = __builtin_bit_cast(bf16x8, (u32x4)*reinterpret_cast<const u32x4a *>(P0 + k * PL + sbase[t] + ro) & keep);
 #pragma unroll
             for (int k = 0; k < 3; ++k) ar[(s + kRing - 1) % kRing][k] = (Aw + k * kWave)[lane_u];
             Aw += 3 * kWave;
@@ -168,7 +175,7 @@ __global__ __launch_bounds__(256, 2) void b3_first_kernel(B3Args p) {
     const int left = p.Cout - i0 - 4 * half;
 #pragma unroll
     for (int n = 0; n < TN * 16; ++n) {
-        out[n] = acc[n / 16][n % 16] + acs[n / 16][n % 16];
+        out[n] = b3_sum(acc[n / 16][n % 16], acs[n / 16][n % 16]);
         bv[n] = av[n] = 0.f;
     }
     if (p.ef.flags & EF_BIAS) {

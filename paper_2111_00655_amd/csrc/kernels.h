@@ -249,7 +249,7 @@ struct B3Args {
     int32_t HO, WOe, TW, rpi, ly, lx, ys, xs;               // output rows / columns per phase; strip width; slot geometry
     int32_t Nimg, Ntot, img_stride, HW, W, H, cs, ph, pwd;  // Nimg counts (image, output depth) pairs
     int32_t D, DO, sd, pd, KD, nC;                          // nC: blocks of 16 channels, times KD
-    int32_t groups, cpg_in;
+    int32_t groups, cpg_in, Cf;                             // Cf: channels (per group of an m-tile), or K of a dense layer
     int32_t KHe, KWe, sh, sw, ph_t, pw_t, phe_max, pwe_max;
     int32_t Cout, WO, os, npix, ons, ocs;                   // output strides
     int32_t Nrows, ldx, ldy, K, cs_len;                     // dense
@@ -258,7 +258,7 @@ struct B3Args {
     int32_t TH, tiles_x, tiles_y, prow, pxw, cps, steps;
     // host side only
     int32_t tile, taps, dense;
-    int32_t Cin, KH, KW, cpg_out, ldb, convt, Cf;           // Cf: channels (per group of an m-tile), or K of a dense layer
+    int32_t Cin, KH, KW, cpg_out, ldb, convt;
     int64_t pack_steps;                                     // 3 KB steps of packed weights, padding included
     Epilogue epi;
 };

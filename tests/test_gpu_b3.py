@@ -104,3 +104,59 @@ def test_split_operand_contractions_against_float64(ci, tail):
         worst = np.abs(got - ref).max() / np.abs(ref).max()
         assert err < 1e-6 and worst < 4e-6, (be, name, err, worst)
     assert ran, (CASES[ci], "no backend ran the split-operand kernels")
+
+
+@pytest.mark.parametrize("ci", [i for i, c in enumerate(CASES) if c[8] <= 2])      # (a block of 16 channels spans narrower groups)
+def test_infinities_and_nan_reach_the_outputs_they_belong_to(ci):
+    """Infinite and NaN inputs: the same outputs are infinite, of the same sign, or NaN as in float64, and the others are right."""
+    import torch
+    F = torch.nn.functional
+    kind, n, cin, cout, sp, k, s, p, g = CASES[ci]
+    r = np.random.default_rng([37, ci])
+    d = wl.GraphDesc("b3_nonfinite")
+    x = r.standard_normal((n, cin, *sp) if sp else (n, cin)).astype(np.float32)
+    at = r.choice(x.size, 4, replace=False)                  # the last value of the first image among them: next to a padded block
+    at[0] = x.size // n - 1
+    x.reshape(-1)[at] = [np.inf, -np.inf, np.inf, np.nan]
+    if kind == "dense":
+        w = (r.standard_normal((cout, cin)) * cin ** -0.5).astype(np.float32)
+        y = d.op("dense", [d.input(x), d.const(w)])
+        ref = np.stack([[np.sum(a * b) for b in w.astype(np.float64)] for a in x.astype(np.float64)])
+    else:
+        wshape = (cin, cout, *k) if kind == "conv2d_transpose" else (cout, cin // g, *k)
+        w = (r.standard_normal(wshape) * (cin // g * float(np.prod(k))) ** -0.5).astype(np.float32)
+        f = {"conv2d": F.conv2d, "conv3d": F.conv3d, "conv2d_transpose": F.conv_transpose2d}[kind]
+        grouped = {"groups": g} if kind == "conv2d" else {}
+
+        def conv(a, b):
+            return f(torch.from_numpy(a).double(), torch.from_numpy(b).double(), stride=s, padding=p, **grouped).numpy()
+
+        # which outputs an infinity of either sign reaches, from the products' signs
+        y = d.op(kind, [d.input(x), d.const(w)], stride=s, pad=p, **grouped)
+        up, down, bad = np.float32(x == np.inf), np.float32(x == -np.inf), np.float32(np.isnan(x))
+        wu, wd = np.float32(w > 0), np.float32(w < 0)
+        pos = conv(up, wu) + conv(down, wd) > 0.5
+        neg = conv(up, wd) + conv(down, wu) > 0.5
+        ref = conv(np.where(np.isfinite(x), x, 0).astype(np.float32), w)
+        ref = np.where(pos, np.where(neg, np.nan, np.inf), np.where(neg, -np.inf, ref))
+        ref = np.where(conv(bad, np.ones_like(w)) > 0.5, np.nan, ref)
+    d.mark_output(y)
+    finite, ran = np.isfinite(ref), 0
+    for be in BACKENDS:
+        sess = clg.Session(d, [(be, P(kind, W, W))], device=0)
+        sess.match()
+        try:
+            plan = sess.compile([0])
+        except clg.ClgError as e:
+            assert e.status == "NO_KERNEL", str(e)
+            sess.close()
+            continue
+        name, got = plan.kernels()[0]["name"], plan.run()[0]
+        sess.close()
+        if "_rfb3_" not in name:
+            continue
+        ran += 1
+        np.testing.assert_array_equal(got[~finite], ref[~finite].astype(np.float32), err_msg=f"{be} {name}")
+        assert np.isfinite(got[finite]).all(), (be, name, "a value that is not finite where none belongs")
+        assert np.abs(got[finite] - ref[finite]).max(initial=0) < 4e-6 * max(1.0, np.abs(ref[finite]).max(initial=0)), (be, name)
+    assert ran
