@@ -5,14 +5,21 @@
 // round trip through memory; at batch 1 and sequence 128 (BERT-base, paper Sec. 5.1) each of them
 // is a few microseconds of mostly launch.
 //
-// A workgroup (4 waves) owns 16 query rows of one head.  Scores: the 16 x Sk block is cut into
-// 16 x 16 tiles (v_mfma_f32_16x16x4_f32, contraction over d), a tile per wave and round; q and k are
-// both read 16 bytes per lane along d: lane (slot s, row r) takes elements 16g + 4s .. + 3 of its row
-// for the four MFMAs of group g - the order of the contraction index does not matter as long as both
-// operands use the same one.  The scaled scores go to LDS; each wave then normalises four rows
-// (sixteen lanes per row: max, exp, sum); the probabilities stay in LDS and are the A operand of the
-// second product (read 16 bytes per lane, the same index order), v is the B operand, 4 bytes per lane
-// along d.  Nothing but q, k, v and the result touches memory.
+// A workgroup of eight waves owns 16 (32) query rows of one head.  Scores: the block is cut into 16 x 16 tiles
+// (v_mfma_f32_16x16x4_f32, contraction over d); q and k are both read 16 bytes per lane along d: lane
+// (slot s, row r) takes elements 16g + 4s .. + 3 of its row for the four MFMAs of group g - the order of
+// the contraction index does not matter as long as both operands use the same one.  The scaled scores go
+// to LDS; the waves share out the rows of the softmax (max, exp, sum); the probabilities stay in
+// LDS and are the A operand of the second product (read 16 bytes per lane, the same index order).
+// Nothing but q, k, v and the result touches memory.
+//
+// What bounds it is latency and the L1: some 5 us of matrix work at most, and k and v pass through a compute unit's L1
+// once per workgroup.  So a wave keeps the same keys in both products, loads all its rows of k and of v at once
+// before the first MFMA, and reads v 16 bytes per lane as well: the columns of d are dealt out so that a lane's four
+// neighbouring ones belong to four column tiles.  Every wave has a partial result of all columns; they meet in LDS.
+// Twelve heads of 64, before (four waves, v read 4 bytes per lane behind the softmax) and now: 16 keys 3.9, 3.75 us; 128 keys
+// 6.2, 5.5; 256 keys 10.6, 8.0; 389 keys 19.9, 16.8; 512 keys 23.9, 18.8.  (Sixteen waves and two column tiles of v per
+// wave: 5.4 us at 128 keys, 11.2 at 256, 18.4 at 389.)
 #include <algorithm>
 
 #include <hip/hip_runtime.h>
@@ -23,6 +30,9 @@
 namespace clg {
 
 namespace {
+
+// LDS written by this workgroup is visible behind it; loads from memory stay in flight
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 
@@ -47,157 +57,203 @@ __device__ __forceinline__ float row16_sum(float v) {
     return v + dpp_peer<0x140>(v);
 }
 
-constexpr int kRows = 16;          // query rows per workgroup
+constexpr int kRows = 16;          // query rows of a tile
 constexpr int kMaxKeys = 512;
-constexpr int kVPre = 8;           // key groups whose v operands a wave loads ahead
+constexpr int kWaves = 8;
+constexpr int kCUs = 256;          // compute units of an MI355X
 
-// D16 = head size / 16.  MAXT = score tiles per wave the code is unrolled for: 2 (up to 128 keys) or
-// 8 (up to 512); the short form is a third of the code, and a kernel of a few microseconds that starts
-// with a cold instruction cache feels its length.
-template <int D16, int MAXT>
-__global__ __launch_bounds__(256) void attention_kernel(AttentionArgs a) {
-    constexpr int kMaxTiles = MAXT;
-    extern __shared__ float lds[];                           // [16][ldp]: scores, then probabilities
+// D16 = head size / 16; MAXT = key tiles per wave (kWaves * MAXT tiles cover the keys); RT = row tiles; CS = column
+// splits of the second product.
+template <int D16, int MAXT, int RT, int CS>
+__global__ __launch_bounds__(kWaves * kWave) void attention_kernel(AttentionArgs a) {
+    constexpr int ROWS = kRows * RT, d = D16 * 16, ldr = d + 4;
+    constexpr int KS = kWaves / CS, VT = D16 / CS;           // key splits of the second product, column tiles of a wave
+    constexpr int VG = MAXT * CS;                            // key tiles of a wave in it
+    constexpr int VEC = VT < 4 ? VT : 4, NV = VT / VEC;      // columns of d per load of v, loads per row
+    static_assert(kWaves % CS == 0 && D16 % CS == 0, "the waves share out the column tiles");
+    constexpr int LPR = kWave * kWaves / ROWS;               // lanes per row of the softmax
+    constexpr int CPL = kWaves * MAXT * 16 / LPR;            // columns per lane
+    typedef float vecv __attribute__((ext_vector_type(VEC)));
+    typedef float vecu __attribute__((ext_vector_type(VEC), aligned(4)));      // (v may lie at any address of a float)
+    extern __shared__ float lds[];                           // [ROWS][ldp]: scores, then probabilities; then [KS][ROWS][ldr]: partial results
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r = lane & 15, s = lane >> 4;
-    const int h = blockIdx.y, q0 = blockIdx.x * kRows;
-    constexpr int d = D16 * 16;
-    const int nct = (a.Sk + 15) / 16;                        // key tiles = key groups of the second product
+    const int h = blockIdx.y, q0 = blockIdx.x * ROWS;
+    const int nct = (a.Sk + 15) / 16;                        // key tiles
     const int ldp = nct * 16 + 4;
     const float *Q = a.q + (int64_t)h * a.Sq * d;
     const float *K = a.k + (int64_t)h * a.Sk * d;
     const float *V = a.v + (int64_t)h * a.Sk * d;
 
-    // ---- scores: tile t = wave + 4u of this wave
-    const float4 *qp = reinterpret_cast<const float4 *>(Q + (int64_t)min(q0 + r, a.Sq - 1) * d) + s;
-    float4 qa[D16];
+    // ---- all loads: key tiles wave, wave + kWaves, ... of this wave (past the end: the last key row, not used)
+    float4 qa[RT][D16], kb[MAXT][D16];
 #pragma unroll
-    for (int g = 0; g < D16; ++g) qa[g] = qp[4 * g];
-    // two tiles per round: their k rows are loaded together (one memory latency per round, tiles past
-    // the end re-read the last key row and are not stored), and their MFMA chains are interleaved
-    floatx4 acc[kMaxTiles];
+    for (int t = 0; t < RT; ++t) {
+        const float4 *qp = reinterpret_cast<const float4 *>(Q + (int64_t)min(q0 + 16 * t + r, a.Sq - 1) * d) + s;
 #pragma unroll
-    for (int u = 0; u < kMaxTiles; u += 2) {
-        acc[u] = floatx4{0.f, 0.f, 0.f, 0.f};
-        acc[u + 1] = floatx4{0.f, 0.f, 0.f, 0.f};
-        const int t0 = wave + 4 * u, t1 = t0 + 4;
-        if (t0 < nct) {                                      // uniform over the wave
-            const float4 *kp0 = reinterpret_cast<const float4 *>(K + (int64_t)min(t0 * 16 + r, a.Sk - 1) * d) + s;
-            const float4 *kp1 = reinterpret_cast<const float4 *>(K + (int64_t)min(t1 * 16 + r, a.Sk - 1) * d) + s;
-            float4 kb0[D16], kb1[D16];
-#pragma unroll
-            for (int g = 0; g < D16; ++g) {
-                kb0[g] = kp0[4 * g];
-                kb1[g] = kp1[4 * g];
-            }
-#pragma unroll
-            for (int g = 0; g < D16; ++g) {
-                acc[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(qa[g].x, kb0[g].x, acc[u], 0, 0, 0);
-                acc[u + 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(qa[g].x, kb1[g].x, acc[u + 1], 0, 0, 0);
-                acc[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(qa[g].y, kb0[g].y, acc[u], 0, 0, 0);
-                acc[u + 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(qa[g].y, kb1[g].y, acc[u + 1], 0, 0, 0);
-                acc[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(qa[g].z, kb0[g].z, acc[u], 0, 0, 0);
-                acc[u + 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(qa[g].z, kb1[g].z, acc[u + 1], 0, 0, 0);
-                acc[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(qa[g].w, kb0[g].w, acc[u], 0, 0, 0);
-                acc[u + 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(qa[g].w, kb1[g].w, acc[u + 1], 0, 0, 0);
-            }
-        }
+        for (int g = 0; g < D16; ++g) qa[t][g] = qp[4 * g];
     }
-    // v operands of the first key groups of this wave's first output tile: in flight during the softmax
-    const int vt = wave;                                     // output tile (16 columns of d) of this wave, first round
-    float vb[kVPre][4];
-    if (vt < D16) {
 #pragma unroll
-        for (int g = 0; g < kVPre; ++g)
+    for (int u = 0; u < MAXT; ++u) {
+        const float4 *kp = reinterpret_cast<const float4 *>(K + (int64_t)min((wave + kWaves * u) * 16 + r, a.Sk - 1) * d) + s;
+#pragma unroll
+        for (int g = 0; g < D16; ++g) kb[u][g] = kp[4 * g];
+    }
+    // (heads of 128 leave no registers for v before the scores are done)
+    constexpr bool EARLY_V = D16 <= 4;
+    const int ks = wave / CS, c0 = wave % CS * VT * 16;      // key tiles ks, ks + KS, ... and first column in the second product
+    vecv vb[VG][4][NV];                                      // row 4s + q of the tile, columns c0 + 16 VEC c + VEC r ..
+    auto load_v = [&] {
+#pragma unroll
+        for (int u = 0; u < VG; ++u)
 #pragma unroll
             for (int q = 0; q < 4; ++q)
-                vb[g][q] = g < nct ? V[(int64_t)min(16 * g + 4 * s + q, a.Sk - 1) * d + vt * 16 + r] : 0.f;
+#pragma unroll
+                for (int c = 0; c < NV; ++c)
+                    vb[u][q][c] = *reinterpret_cast<const vecu *>(V + (int64_t)min((ks + KS * u) * 16 + 4 * s + q, a.Sk - 1) * d + c0 + 16 * VEC * c + VEC * r);
+    };
+    if constexpr (EARLY_V) {
+        load_v();
+        __builtin_amdgcn_sched_barrier(0);                   // every load leaves before the first MFMA waits
     }
-    // accumulator g of a lane: row 4s + g, column r of the tile
+    // ---- scores; accumulator g of a lane: row 4s + g, column r of the tile
 #pragma unroll
-    for (int u = 0; u < kMaxTiles; ++u) {
-        const int t = wave + 4 * u;
-        if (t < nct) {
-            const int col = t * 16 + r;
+    for (int u = 0; u < MAXT; ++u) {
+        const int kt = wave + kWaves * u;
+        if (kt < nct) {                                      // uniform over the wave
+            floatx4 acc[RT][2];                              // even and odd groups of d apart: shorter chains
 #pragma unroll
-            for (int g = 0; g < 4; ++g) lds[(4 * s + g) * ldp + col] = col < a.Sk ? acc[u][g] * a.scale : -INFINITY;
+            for (int t = 0; t < RT; ++t) acc[t][0] = acc[t][1] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int g = 0; g < D16; g += 2)
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+#pragma unroll
+                    for (int e = 0; e < 2; ++e)
+#pragma unroll
+                        for (int t = 0; t < RT; ++t)
+                            acc[t][e] = __builtin_amdgcn_mfma_f32_16x16x4f32((&qa[t][g + e].x)[q], (&kb[u][g + e].x)[q], acc[t][e], 0, 0, 0);
+            const int col = kt * 16 + r;
+#pragma unroll
+            for (int t = 0; t < RT; ++t)
+#pragma unroll
+                for (int g = 0; g < 4; ++g)
+                    lds[(16 * t + 4 * s + g) * ldp + col] = col < a.Sk ? (acc[t][0][g] + acc[t][1][g]) * a.scale : -INFINITY;
         }
     }
-    __syncthreads();
+    if constexpr (!EARLY_V) load_v();
+    lds_barrier();                                           // (LDS only: the v operands stay in flight)
 
-    // ---- softmax: this wave's four rows at once, sixteen lanes (one slot s) per row, a lane takes the
-    // columns r, r + 16, ...; the reductions stay within 16 lanes (four exchange steps instead of six,
-    // and one pass instead of four)
+    // ---- softmax: LPR lanes per row, a lane takes the columns c, c + LPR, ...
     {
-        float *row = lds + (4 * wave + s) * ldp;
-        float v[4 * kMaxTiles];                                            // 4 * MAXT >= nct
+        const int c = tid % LPR, cols = nct * 16;
+        float *row = lds + tid / LPR * ldp;
+        float v[CPL];
         float mx = -INFINITY;
 #pragma unroll
-        for (int i = 0; i < 4 * kMaxTiles; ++i) {
-            v[i] = i < nct ? row[r + 16 * i] : -INFINITY;
+        for (int i = 0; i < CPL; ++i) {
+            v[i] = c + LPR * i < cols ? row[c + LPR * i] : -INFINITY;
             mx = fmaxf(mx, v[i]);
         }
         mx = row16_max(mx);
+#pragma unroll
+        for (int o = 16; o < LPR; o *= 2) mx = fmaxf(mx, __shfl_xor(mx, o));
         float sum = 0.f;
 #pragma unroll
-        for (int i = 0; i < 4 * kMaxTiles; ++i) {
-            v[i] = i < nct ? __expf(v[i] - mx) : 0.f;                     // exp(-inf) = 0 for the padded columns
+        for (int i = 0; i < CPL; ++i) {
+            v[i] = c + LPR * i < cols ? __expf(v[i] - mx) : 0.f;           // exp(-inf) = 0 for the padded columns
             sum += v[i];
         }
         sum = row16_sum(sum);
+#pragma unroll
+        for (int o = 16; o < LPR; o *= 2) sum += __shfl_xor(sum, o);
         const float inv = 1.0f / sum;
 #pragma unroll
-        for (int i = 0; i < 4 * kMaxTiles; ++i)
-            if (i < nct) row[r + 16 * i] = v[i] * inv;
+        for (int i = 0; i < CPL; ++i)
+            if (c + LPR * i < cols) row[c + LPR * i] = v[i] * inv;
     }
-    __syncthreads();
+    lds_barrier();
 
-    // ---- out tile = P[16 x Sk] V[Sk x 16]; A operand from LDS (row r), 16 bytes per lane
-    for (int t = wave; t < D16; t += 4) {
-        // two accumulators, even and odd key groups: half as long a chain of dependent MFMAs
-        floatx4 o = {0.f, 0.f, 0.f, 0.f}, o2 = {0.f, 0.f, 0.f, 0.f};
-        const float *prow = lds + r * ldp + 4 * s;
-        int g = 0;
-        if (t == vt) {                                       // the key groups whose v operands are already in registers
+    // ---- P[ROWS x keys of this wave] V[keys x d]; A operand from LDS (row r), 16 bytes per lane
+    floatx4 o[RT][VT];
 #pragma unroll
-            for (int gg = 0; gg < kVPre; gg += 2) {
-                if (gg < nct) {
-                    const float4 pa = *reinterpret_cast<const float4 *>(prow + 16 * gg);
-                    float4 pb = make_float4(0.f, 0.f, 0.f, 0.f);
-                    if (gg + 1 < nct) pb = *reinterpret_cast<const float4 *>(prow + 16 * (gg + 1));
-                    o = __builtin_amdgcn_mfma_f32_16x16x4f32(pa.x, vb[gg][0], o, 0, 0, 0);
-                    o2 = __builtin_amdgcn_mfma_f32_16x16x4f32(pb.x, vb[gg + 1][0], o2, 0, 0, 0);
-                    o = __builtin_amdgcn_mfma_f32_16x16x4f32(pa.y, vb[gg][1], o, 0, 0, 0);
-                    o2 = __builtin_amdgcn_mfma_f32_16x16x4f32(pb.y, vb[gg + 1][1], o2, 0, 0, 0);
-                    o = __builtin_amdgcn_mfma_f32_16x16x4f32(pa.z, vb[gg][2], o, 0, 0, 0);
-                    o2 = __builtin_amdgcn_mfma_f32_16x16x4f32(pb.z, vb[gg + 1][2], o2, 0, 0, 0);
-                    o = __builtin_amdgcn_mfma_f32_16x16x4f32(pa.w, vb[gg][3], o, 0, 0, 0);
-                    o2 = __builtin_amdgcn_mfma_f32_16x16x4f32(pb.w, vb[gg + 1][3], o2, 0, 0, 0);
-                }
-            }
-            g = min(nct, kVPre);
-        }
-        for (; g < nct; ++g) {
-            const float4 pa = *reinterpret_cast<const float4 *>(prow + 16 * g);
-            float b[4];
+    for (int t = 0; t < RT; ++t)
 #pragma unroll
-            for (int q = 0; q < 4; ++q) b[q] = V[(int64_t)min(16 * g + 4 * s + q, a.Sk - 1) * d + t * 16 + r];
-            o = __builtin_amdgcn_mfma_f32_16x16x4f32(pa.x, b[0], o, 0, 0, 0);
-            o = __builtin_amdgcn_mfma_f32_16x16x4f32(pa.y, b[1], o, 0, 0, 0);
-            o = __builtin_amdgcn_mfma_f32_16x16x4f32(pa.z, b[2], o, 0, 0, 0);
-            o = __builtin_amdgcn_mfma_f32_16x16x4f32(pa.w, b[3], o, 0, 0, 0);
-        }
+        for (int n = 0; n < VT; ++n) o[t][n] = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int g = 0; g < 4; ++g) o[g] += o2[g];
+    for (int u = 0; u < VG; ++u) {
+        const int kt = ks + KS * u;
+        if (kt < nct) {
+            float4 pa[RT];
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {
-            const int qi = q0 + 4 * s + g;
-            if (qi >= a.Sq) continue;
-            const int64_t off = a.merge ? ((int64_t)qi * a.B + h) * d + t * 16 + r : ((int64_t)h * a.Sq + qi) * d + t * 16 + r;
-            a.y[off] = o[g];
+            for (int t = 0; t < RT; ++t) pa[t] = *reinterpret_cast<const float4 *>(lds + (16 * t + r) * ldp + 16 * kt + 4 * s);
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+#pragma unroll
+                for (int t = 0; t < RT; ++t)
+#pragma unroll
+                    for (int n = 0; n < VT; ++n)
+                        o[t][n] = __builtin_amdgcn_mfma_f32_16x16x4f32((&pa[t].x)[q], vb[u][q][n / VEC][n % VEC], o[t][n], 0, 0, 0);
         }
     }
+    lds_barrier();                                           // the probabilities have been read: their place holds the partial results now
+#pragma unroll
+    for (int t = 0; t < RT; ++t)
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+#pragma unroll
+            for (int c = 0; c < NV; ++c) {
+                vecv w;
+#pragma unroll
+                for (int e = 0; e < VEC; ++e) w[e] = o[t][c * VEC + e][g];
+                *reinterpret_cast<vecv *>(lds + (ks * ROWS + 16 * t + 4 * s + g) * ldr + c0 + 16 * VEC * c + VEC * r) = w;
+            }
+    lds_barrier();
+#pragma unroll
+    for (int e = tid; e < ROWS * d; e += kWaves * kWave) {
+        const int row = e / d, col = e % d, qi = q0 + row;
+        float v = 0.f;
+#pragma unroll
+        for (int k = 0; k < KS; ++k) v += lds[(k * ROWS + row) * ldr + col];
+        if (qi < a.Sq) a.y[a.merge ? ((int64_t)qi * a.B + h) * d + col : ((int64_t)h * a.Sq + qi) * d + col] = v;
+    }
+}
+
+template <int D16, int MAXT, int RT, int CS>
+int launch_one(const AttentionArgs &a, hipStream_t s) {
+    constexpr int ROWS = kRows * RT;
+    const size_t lds = (size_t)ROWS * std::max((a.Sk + 15) / 16 * 16 + 4, kWaves / CS * (D16 * 16 + 4)) * sizeof(float);
+    if (lds > 64 * 1024) {
+        static bool raised = false;          // more than 64 KB of dynamic LDS has to be allowed per kernel, once
+        if (!raised) {
+            const hipError_t e = hipFuncSetAttribute((const void *)attention_kernel<D16, MAXT, RT, CS>,
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+            if (e != hipSuccess) return (int)e;
+            raised = true;
+        }
+    }
+    const dim3 grid((unsigned)((a.Sq + ROWS - 1) / ROWS), (unsigned)a.B);
+    hipLaunchKernelGGL((attention_kernel<D16, MAXT, RT, CS>), grid, dim3(kWaves * kWave), lds, s, a);
+    return (int)hipGetLastError();
+}
+
+// Up to 128 keys a wave takes one column tile of the result (a short second product: adding eight partial results would be
+// the longer part); beyond, its keys' part of all of them (two column splits: 17.1 instead of 16.8 us at 389 keys).  From 385 keys on a compute unit's registers hold one workgroup, below two: more of
+// them than that would be a second round, and two row tiles share each load of k and v (389 keys, twelve heads: 18.4
+// instead of 22.3 us).  (Heads of 128 have no
+// registers for a second row tile.)
+template <int D16>
+int launch_heads(const AttentionArgs &a, hipStream_t s) {
+    const int tiles = (a.Sk + 15) / 16;
+    const int64_t groups = (int64_t)((a.Sq + kRows - 1) / kRows) * a.B;
+    if (tiles <= kWaves) return launch_one<D16, 1, 1, D16>(a, s);
+    if (tiles <= 2 * kWaves) return launch_one<D16, 2, 1, 1>(a, s);
+    if constexpr (D16 <= 4) {
+        if (tiles <= 3 * kWaves && groups > 2 * kCUs) return launch_one<D16, 3, 2, 1>(a, s);
+        if (tiles > 3 * kWaves && groups > kCUs) return launch_one<D16, 4, 2, 1>(a, s);
+    }
+    return tiles <= 3 * kWaves ? launch_one<D16, 3, 1, 1>(a, s) : launch_one<D16, 4, 1, 1>(a, s);
 }
 
 }  // namespace
@@ -211,14 +267,8 @@ int launch_attention(const AttentionArgs &a, void *stream) {
     if (!attention_shape_ok(a)) return (int)hipErrorInvalidValue;
     for (const void *p : {(const void *)a.q, (const void *)a.k})
         if (((uintptr_t)p & 15) != 0) return (int)hipErrorInvalidValue;        // rows are read 16 bytes at a time
-    const dim3 grid((unsigned)((a.Sq + kRows - 1) / kRows), (unsigned)a.B);
-    const int nct = (a.Sk + 15) / 16;
-    const size_t lds = (size_t)kRows * (nct * 16 + 4) * sizeof(float);
-    void (*kern)(AttentionArgs);
-    if (a.Sk <= 128) kern = a.d == 32 ? attention_kernel<2, 2> : (a.d == 64 ? attention_kernel<4, 2> : attention_kernel<8, 2>);
-    else kern = a.d == 32 ? attention_kernel<2, 8> : (a.d == 64 ? attention_kernel<4, 8> : attention_kernel<8, 8>);
-    hipLaunchKernelGGL(kern, grid, dim3(256), lds, (hipStream_t)stream, a);
-    return (int)hipGetLastError();
+    hipStream_t s = (hipStream_t)stream;
+    return a.d == 32 ? launch_heads<2>(a, s) : (a.d == 64 ? launch_heads<4>(a, s) : launch_heads<8>(a, s));
 }
 
 }  // namespace clg
