@@ -99,25 +99,6 @@ __device__ __forceinline__ void b3_split2(float a, float b, uint32_t &h, uint32_
 // The leading products' sum and the small ones'.
 __device__ __forceinline__ float b3_sum(float lead, float small) { return __builtin_isfinite(lead) ? lead + small : lead; }
 
-// The fused tail on a lane's N finished values at once.  (Tests of the flags value by value, with the bodies of erff
-// and tanhf in between, made 31 KB of code and cost 4 us at the end of a workgroup.)
-template <int N>
-__device__ __forceinline__ void b3_tail(const EpiFast &ef, float (&v)[N], const float (&bv)[N], const float (&av)[N]) {
-    const float scale = (ef.flags & EF_SCALE) ? ef.scale : 1.f;
-#pragma unroll
-    for (int n = 0; n < N; ++n) v[n] = v[n] * scale + bv[n] + av[n];
-    if (ef.flags & EF_RELU) {
-#pragma unroll
-        for (int n = 0; n < N; ++n) v[n] = v[n] > 0.f ? v[n] : 0.f;
-    } else if (ef.flags & EF_GELU) {
-#pragma unroll
-        for (int n = 0; n < N; ++n) v[n] = gelu_erf(v[n]);
-    } else if (ef.flags & EF_TANH) {
-#pragma unroll
-        for (int n = 0; n < N; ++n) v[n] = tanhf(v[n]);
-    }
-}
-
 // (the same mapping as the other tiled kernels': an XCD gets a contiguous range of tiles)
 __device__ __forceinline__ int b3_xcd_remap(int id, int n) {
     const int q = n / 8, r = n % 8;
@@ -435,7 +416,7 @@ __global__ __launch_bounds__(C::NT, 2) void b3_kernel(B3Args p) {
                         for (int f = 0; f < 4; ++f) av[d * NE + e + f] = __uint_as_float(v[f]);
                     }
             }
-            b3_tail<NR>(EpiFast{flags, p.ef.scale, nullptr, nullptr}, out, bv, av);
+            fused_tail<NR>(EpiFast{flags, p.ef.scale, nullptr, nullptr}, out, bv, av);
 #pragma unroll
             for (int d = 0; d < ND; ++d)
 #pragma unroll
@@ -462,7 +443,7 @@ __global__ __launch_bounds__(C::NT, 2) void b3_kernel(B3Args p) {
                                                                                       (DENSE ? cbase_y + rr : (i0 + rr) * rstep) * 4, 0));
             }
     }
-    b3_tail<NR>(EpiFast{flags, p.ef.scale, nullptr, nullptr}, out, bv, av);
+    fused_tail<NR>(EpiFast{flags, p.ef.scale, nullptr, nullptr}, out, bv, av);
 #pragma unroll
     for (int d = 0; d < ND; ++d)
 #pragma unroll

@@ -193,7 +193,7 @@ __global__ __launch_bounds__(256, 2) void b3_first_kernel(B3Args p) {
             av[n] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsum, (int)(rr < left ? ob[n / 16] : kB3Out), (i0 + rr) * p.ocs * 4, 0));
         }
     }
-    b3_tail<TN * 16>(p.ef, out, bv, av);
+    fused_tail<TN * 16>(p.ef, out, bv, av);
 #pragma unroll
     for (int n = 0; n < TN * 16; ++n) {
         const int rr = 8 * (n % 16 / 4) + n % 4;

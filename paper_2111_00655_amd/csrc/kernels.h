@@ -264,13 +264,12 @@ struct B3Args {
 };
 // Whether the kernel takes the problem `a` describes (its geometry as lower.cpp fills it before any
 // *_resolve call) under tile `tile`; fills *out.  B3_NONE as the tile: the largest one that gives every compute unit a workgroup.
-bool b3_resolve(const GemmArgs &a, int tile, int epi_flags, int n_cus, B3Args *out);
+// split: K may be split across workgroups (partial tiles in scratch, a second kernel adds them).
+bool b3_resolve(const GemmArgs &a, int tile, int epi_flags, int n_cus, bool split, B3Args *out);
 size_t b3_pack_bytes(const B3Args &a);
 size_t b3_scratch_bytes(const B3Args &a);
 int launch_b3_pack(const B3Args &a, const float *w, void *dst, void *stream);
 int launch_b3(const B3Args &a, void *stream);
-// Adds split-K partial tiles in slice order and applies the fused tail.
-int launch_splitk_reduce(const float *partial, float *out, int64_t numel, int splitk, const Epilogue &epi, void *stream);
 
 // ---- concat: y[r][...] = x_0[r][...] x_1[r][...] ..., r < outer ---------------------------------
 struct ConcatArgs {

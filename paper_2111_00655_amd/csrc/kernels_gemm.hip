@@ -421,7 +421,7 @@ bool gemv_shape_ok(const GemmArgs &a, int epi_flags) {
            a.ldb % 4 == 0 && a.cs_len == 0 && !(epi_flags & EF_GENERIC);
 }
 
-int launch_splitk_reduce(const float *partial, float *out, int64_t numel, int splitk, const Epilogue &epi, void *stream) {
+static int launch_splitk_reduce(const float *partial, float *out, int64_t numel, int splitk, const Epilogue &epi, void *stream) {
     hipLaunchKernelGGL(splitk_reduce_kernel, dim3((unsigned)((numel + 255) / 256)), dim3(256), 0, (hipStream_t)stream,
                        partial, out, numel, splitk, epi);
     return (int)hipGetLastError();

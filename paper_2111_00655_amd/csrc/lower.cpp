@@ -262,10 +262,11 @@ int32_t add_step(const ChainView &cv, int t, bool as_anchor, Epilogue *e, int32_
 std::string shape_key(const Graph &g, int32_t v) { return g.nodes[v].shape.str(); }
 
 // The split-operand kernels (gemm_b3.h) as a backend's kernel for contractions with constant weights: the
-// large- and medium-tile backends and the automatic one run them wherever they take the shape; the three split-K
+// large- and medium-tile backends (with K split across workgroups where the tiles would leave most of the chip idle) and
+// the automatic one run them wherever they take the shape; the three split-K
 // register-fed backends where the reduction needs no split across workgroups (`a` as their own resolve left it), where
 // they would otherwise repeat the kernel that their unsplit namesakes run.
-bool lower_b3(const Context &ctx, const Backend &be, const GemmArgs &a, const Epilogue &epi, const std::string &what, KernelCall *c) {
+bool lower_b3(const Context &ctx, const Backend &be, const GemmArgs &a, const Epilogue &epi, const std::string &what, KernelCall *c, bool split = false) {
     int tile;
     switch (be.tile) {
     case TILE_AUTO: tile = B3_NONE; break;
@@ -278,14 +279,15 @@ bool lower_b3(const Context &ctx, const Backend &be, const GemmArgs &a, const Ep
     if ((be.tile == TILE_R32 || be.tile == TILE_R16) && be.no_split) return false;
     if (gemv_shape_ok(a, epi_fast_flags(epi))) return false;          // a handful of rows: streaming the weights once is the bound
     B3Args b;
-    if (!b3_resolve(a, tile, epi_fast_flags(epi), ctx.n_cus, &b)) return false;
+    if (!b3_resolve(a, tile, epi_fast_flags(epi), ctx.n_cus, split || be.tile == TILE_L || be.tile == TILE_M, &b)) return false;
     static const char *tn[] = {"", "m128n128", "m64n128", "m64n64", "m32n64", "m32n32", "m32n256", "m32n128", "first"};
     c->kind = CALL_B3;
     c->b3 = b;
     c->b3.epi = epi;
     c->pack_bytes = b3_pack_bytes(b);
     c->scratch_bytes = b3_scratch_bytes(b);
-    c->name = what + "_rfb3_" + tn[b.tile] + (b.dense ? "" : "_t" + std::to_string(b.taps)) + (b.cs_len ? "_split" : "");
+    c->name = what + "_rfb3_" + tn[b.tile] + (b.dense ? "" : "_t" + std::to_string(b.taps)) + (b.cs_len ? "_split" : "") +
+              (b.splitk > 1 ? "_k" + std::to_string(b.splitk) : "");
     return true;
 }
 
@@ -627,7 +629,9 @@ int32_t lower_match(const Context &ctx, const Graph &g, int32_t match_id, Kernel
                 if (a.KD == 1 && a.pd != 0) return fail(CLG_NO_KERNEL, "conv3d: depth padding needs more than one depth tap");
                 const GemmArgs geo = a;
                 rf = rf_resolve(&a, a.tile == TILE_R32 ? 32 : 16, epi_fast_flags(epi), ctx.n_cus, rfw, !be.no_split);
-                if (rf && a.splitk == 1 && lower_b3(ctx, be, geo, epi, "conv3d", &c)) {
+                // (the tiled backends, whose K may be split, do not run 3-D convolutions: the 16x16 split-K one does it for them)
+                const bool split = a.tile == TILE_R16 && !rfw;
+                if (rf && (a.splitk == 1 || split) && lower_b3(ctx, be, geo, epi, "conv3d", &c, split)) {
                     rf = false;
                     b3 = true;
                     a = geo;
