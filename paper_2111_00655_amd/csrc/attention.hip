@@ -239,10 +239,10 @@ int launch_one(const AttentionArgs &a, hipStream_t s) {
 }
 
 // Up to 128 keys a wave takes one column tile of the result (a short second product: adding eight partial results would be
-// the longer part); beyond, its keys' part of all of them (two column splits: 17.1 instead of 16.8 us at 389 keys).  From 385 keys on a compute unit's registers hold one workgroup, below two: more of
-// them than that would be a second round, and two row tiles share each load of k and v (389 keys, twelve heads: 18.4
-// instead of 22.3 us).  (Heads of 128 have no
-// registers for a second row tile.)
+// the longer part); beyond, all columns of its own keys (two column splits: 17.1 instead of 16.8 us at 389 keys).  From
+// 385 keys on a compute unit's registers hold one workgroup, below two: more of them than that would be a second
+// round, and two row tiles share each load of k and v (389 keys, twelve heads, sixteen waves: 18.4 instead of 22.3 us).
+// Heads of 128 have no registers for a second row tile.
 template <int D16>
 int launch_heads(const AttentionArgs &a, hipStream_t s) {
     const int tiles = (a.Sk + 15) / 16;

@@ -119,7 +119,7 @@ __device__ __forceinline__ void b3_barrier() { asm volatile("s_waitcnt lgkmcnt(0
 constexpr uint32_t kB3Out = 0x80000000u;
 
 template <class C, int TAPS, bool DEPTH, bool DENSE, int UM>
-__global__ __launch_bounds__(C::NT, 2) void b3_kernel(B3Args p) {
+__device__ __forceinline__ void b3_body(const B3Args &p) {
     constexpr int CW = b3_cw<C, TAPS>(), SC = C::WK * CW, Q = CW * TAPS, R = b3_ring<C, TAPS>();
     constexpr int TN = C::TN, WK = C::WK;
     static_assert(Q % R == 0, "the ring of weight registers must divide the steps of a stage");
@@ -454,6 +454,21 @@ __global__ __launch_bounds__(C::NT, 2) void b3_kernel(B3Args p) {
         }
 }
 
+template <class C, int TAPS, bool DEPTH, bool DENSE, int UM>
+__global__ __launch_bounds__(C::NT, 2) void b3_kernel(B3Args p) { b3_body<C, TAPS, DEPTH, DENSE, UM>(p); }
+
+// Dense layers of one shape and tail, one per blockIdx.y (a transformer's q, k and v: 84 tiles each at 389 rows, too few alone).
+template <class C, int UM>
+__global__ __launch_bounds__(C::NT, 2) void b3_dense_multi_kernel(B3Args p, B3Region r) {
+    const int k = blockIdx.y;
+    p.x = r.x[k];
+    p.w = r.w[k];
+    p.y = r.y[k];
+    p.ef.bias = r.bias[k];
+    p.ef.add = r.add[k];
+    b3_body<C, 1, false, true, UM>(p);
+}
+
 // gemm_b3_first.hip: first layers (few input channels)
 bool first_resolve(const GemmArgs &g, B3Args *out);
 int launch_b3_first_pack(const B3Args &a, const float *w, void *dst, hipStream_t s);
@@ -468,6 +483,16 @@ int b3_launch_um(const B3Args &a, hipStream_t s) {
     const int S = TAPS == 1 ? (DENSE ? C::BN + 2 : C::BN) : a.slot_stride;
     const size_t stage = (size_t)2 * 3 * 2 * C::WK * b3_cw<C, TAPS>() * S * 16;
     const size_t lds = stage > (size_t)C::RED ? stage : (size_t)C::RED;
+    if constexpr (DENSE) {
+        if (a.region) {
+            if (lds > 64 * 1024) {
+                const hipError_t e = hipFuncSetAttribute((const void *)b3_dense_multi_kernel<C, UM>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+                if (e != hipSuccess) return (int)e;
+            }
+            hipLaunchKernelGGL((b3_dense_multi_kernel<C, UM>), dim3((unsigned)(a.mgroups * a.ntiles), (unsigned)a.region->n, 1), dim3(C::NT), lds, s, a, *a.region);
+            return (int)hipGetLastError();
+        }
+    }
     if (lds > 64 * 1024) {
         static bool raised = false;          // more than 64 KB of dynamic LDS has to be allowed per kernel, once
         if (!raised) {

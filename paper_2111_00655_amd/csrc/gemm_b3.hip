@@ -252,6 +252,43 @@ bool b3_resolve(const GemmArgs &g, int tile, int epi_flags, int n_cus, bool spli
     return true;
 }
 
+bool b3_region_resolve(const GemmArgs *m, int n, int n_cus, B3Args *out) {
+    if (n < 2 || n > kMaxB3Region) return false;
+    const GemmArgs &a = m[0];
+    for (int k = 1; k < n; ++k) {
+        const GemmArgs &b = m[k];
+        if (b.mode != a.mode || b.M != a.M || b.N != a.N || b.K != a.K || b.lda != a.lda || b.ldb != a.ldb || b.ldc != a.ldc || b.batch != a.batch ||
+            b.c_numel != a.c_numel || b.cs_len != a.cs_len || b.cs_stride != a.cs_stride || b.epi.n != a.epi.n)
+            return false;
+        for (int s = 0; s < a.epi.n; ++s)
+            if (b.epi.s[s].op != a.epi.s[s].op || b.epi.s[s].scalar != a.epi.s[s].scalar) return false;
+    }
+    // 64 x 64 tiles once the members have them for 9/16 of the compute units, four-wave 32 x 32 ones before.  Two layers of BERT-base,
+    // us with q, k, v on the fp32 register-fed region, on 64 x 64 and on 32 x 32 tiles: 128 rows 99.0, 106.8, 98.3; 200 rows
+    // 132.2, 133.8, 130.8; 256 rows 139.2, 138.0, 140.7; 320 rows 152.1, 144.7, 149.4; 389 rows 202.4, 190.2, 195.6.
+    const int tile = (int64_t)n * a.M * a.N >= (int64_t)64 * 64 * (n_cus * 9 / 16) ? B3_M : B3_SS;
+    return a.mode == GM_NT && b3_resolve(a, tile, epi_fast_flags(a.epi), n_cus, false, out) && out->dense;
+}
+
+int launch_b3_region(const B3Args *members, int n, void *stream) {
+    if (n < 2 || n > kMaxB3Region) return (int)hipErrorInvalidValue;
+    B3Args a = members[0];
+    B3Region r{};
+    r.n = n;
+    for (int k = 0; k < n; ++k) {
+        const EpiFast ef = make_epi_fast(members[k].epi);
+        if (ef.flags & EF_GENERIC) return (int)hipErrorInvalidValue;
+        r.x[k] = members[k].x;
+        r.w[k] = members[k].w;
+        r.y[k] = members[k].y;
+        r.bias[k] = ef.bias;
+        r.add[k] = ef.add;
+        a.ef = ef;
+    }
+    a.region = &r;
+    return b3_launch_tile<1, false, true>(a, (hipStream_t)stream);
+}
+
 size_t b3_pack_bytes(const B3Args &a) { return (size_t)a.pack_steps * 3 * kWave * 16; }
 
 size_t b3_scratch_bytes(const B3Args &a) { return a.splitk > 1 ? (size_t)a.splitk * (size_t)a.c_numel * sizeof(float) : 0; }

@@ -260,7 +260,17 @@ struct B3Args {
     int32_t tile, taps, dense;
     int32_t Cin, KH, KW, cpg_out, ldb, convt;
     int64_t pack_steps;                                     // 3 KB steps of packed weights, padding included
+    const struct B3Region *region;                          // siblings in the same launch (launch_b3_region)
     Epilogue epi;
+};
+// Dense layers of one shape and tail in one launch: what differs between them, by blockIdx.y.
+constexpr int kMaxB3Region = 4;
+struct B3Region {
+    const float *x[kMaxB3Region];
+    const void *w[kMaxB3Region];
+    float *y[kMaxB3Region];
+    const float *bias[kMaxB3Region], *add[kMaxB3Region];
+    int32_t n;
 };
 // Whether the kernel takes the problem `a` describes (its geometry as lower.cpp fills it before any
 // *_resolve call) under tile `tile`; fills *out.  B3_NONE as the tile: the largest one that gives every compute unit a workgroup.
@@ -270,6 +280,9 @@ size_t b3_pack_bytes(const B3Args &a);
 size_t b3_scratch_bytes(const B3Args &a);
 int launch_b3_pack(const B3Args &a, const float *w, void *dst, void *stream);
 int launch_b3(const B3Args &a, void *stream);
+// The kernel of `n` dense layers of one shape and tail in one launch; members differ in pointers only.
+bool b3_region_resolve(const GemmArgs *members, int n, int n_cus, B3Args *out);
+int launch_b3_region(const B3Args *members, int n, void *stream);
 
 // ---- concat: y[r][...] = x_0[r][...] x_1[r][...] ..., r < outer ---------------------------------
 struct ConcatArgs {

@@ -261,6 +261,12 @@ int32_t add_step(const ChainView &cv, int t, bool as_anchor, Epilogue *e, int32_
 
 std::string shape_key(const Graph &g, int32_t v) { return g.nodes[v].shape.str(); }
 
+// Dense layers of fewer rows stay with the fp32 kernels: streaming the weights is their bound, and three bf16 planes are 1.5
+// times the bytes.  Timed alone, with its weights in the memory-side cache, a layer of 128 rows looks the same either way; all of
+// BERT-base at 128 rows takes 664 us with one of its layers on these kernels and 624 without; at 160 rows there is no difference,
+// at 230 rows 870 against 895.
+constexpr int kB3DenseRows = 160;
+
 // The split-operand kernels (gemm_b3.h) as a backend's kernel for contractions with constant weights: the
 // large- and medium-tile backends (with K split across workgroups where the tiles would leave most of the chip idle) and
 // the automatic one run them wherever they take the shape; the three split-K
@@ -278,6 +284,7 @@ bool lower_b3(const Context &ctx, const Backend &be, const GemmArgs &a, const Ep
     }
     if ((be.tile == TILE_R32 || be.tile == TILE_R16) && be.no_split) return false;
     if (gemv_shape_ok(a, epi_fast_flags(epi))) return false;          // a handful of rows: streaming the weights once is the bound
+    if (a.mode == GM_NT && a.M < kB3DenseRows) return false;
     B3Args b;
     if (!b3_resolve(a, tile, epi_fast_flags(epi), ctx.n_cus, split || be.tile == TILE_L || be.tile == TILE_M, &b)) return false;
     static const char *tn[] = {"", "m128n128", "m64n128", "m64n64", "m32n64", "m32n32", "m32n256", "m32n128", "first"};

@@ -52,12 +52,13 @@ std::vector<int32_t> operands_of(const KernelCall &c) {
 // ---- regions (the graph-level backend, paper Sec. 4.3) -------------------------------------------
 // Which several-problems-per-launch kernel could run the call beside siblings of the same class
 // (0: none): 1 register-fed dense, 2 register-fed 1x1 convolution, 3 thread-per-output kernels
-// (depthwise convolution with its unrolled-tap kernel, window pools), 100 and up separable convolutions.
-enum RegionClass { RC_NONE = 0, RC_DENSE = 1, RC_CONV1X1 = 2, RC_PLANE = 3, RC_SEPCONV = 100 };
+// (depthwise convolution with its unrolled-tap kernel, window pools), 4 split-operand dense, 100 and up separable convolutions.
+enum RegionClass { RC_NONE = 0, RC_DENSE = 1, RC_CONV1X1 = 2, RC_PLANE = 3, RC_DENSE_B3 = 4, RC_SEPCONV = 100 };
 int region_class(const KernelCall &c) {
     if (c.kind == CALL_SEPCONV) return RC_SEPCONV + sepconv_region_key(c.sep);      // one class per kernel instantiation
     if (c.kind == CALL_DIRECT_CONV) return depthwise_fast_ok(c.dconv) ? RC_PLANE : RC_NONE;
     if (c.kind == CALL_POOL) return plane_region_pool_ok(c.pool) ? RC_PLANE : RC_NONE;
+    if (c.kind == CALL_B3) return c.b3.dense && c.b3.splitk == 1 ? RC_DENSE_B3 : RC_NONE;
     if (c.kind != CALL_GEMM || !c.gemm.rf_ts || c.gemm.splitk != 1 || !c.pack_bytes) return RC_NONE;
     const GemmArgs &a = c.gemm;
     if (a.rf_tapk == -1) return RC_DENSE;
@@ -83,6 +84,27 @@ bool relower_for(const Context &ctx, const KernelCall &leader, const KernelCall 
     return out->scratch_bytes == 0 && rf_same_launch_shape(leader.gemm, a);
 }
 
+// Dense siblings of one shape and tail with enough rows for its tiles run on the split-operand kernel inside a region, whatever
+// kernel each would use alone (figures: b3_region_resolve; below 160 rows see
+// kB3DenseRows in lower.cpp).
+constexpr int kB3RegionRows = 160;
+bool dense_region_b3(const Context &ctx, std::vector<KernelCall> *fused) {
+    const size_t n = fused->size();
+    if (n > kMaxB3Region) return false;
+    GemmArgs m[kMaxB3Region];
+    for (size_t k = 0; k < n; ++k) m[k] = (*fused)[k].gemm;
+    B3Args b;
+    if (m[0].M < kB3RegionRows || !b3_region_resolve(m, (int)n, ctx.n_cus, &b)) return false;
+    for (size_t k = 0; k < n; ++k) {
+        KernelCall &c = (*fused)[k];
+        c.kind = CALL_B3;
+        c.b3 = b;
+        c.b3.epi = m[k].epi;
+        c.pack_bytes = b3_pack_bytes(b);
+    }
+    return true;
+}
+
 // Finds the regions of a freshly lowered kernel sequence and moves every member next to its region's
 // first one (a member only moves forward past kernels it does not depend on, so the order stays
 // topological).  Greedy and deterministic: scanning in order, a kernel of a fusable kind opens a
@@ -100,7 +122,7 @@ void find_regions(const Context &ctx, const Graph &g, Plan *plan) {
         const int cls = region_class(calls[i]);
         if (reg_of[i] >= 0 || cls == RC_NONE) continue;
         std::vector<int32_t> cand{(int32_t)i};
-        const size_t cap = cls == RC_PLANE ? (size_t)kMaxPlaneRegion : (cls >= RC_SEPCONV ? (size_t)kMaxSepRegion : (size_t)kMaxRegion);
+        const size_t cap = cls == RC_PLANE ? (size_t)kMaxPlaneRegion : (cls >= RC_SEPCONV ? (size_t)kMaxSepRegion : (cls == RC_DENSE_B3 ? (size_t)kMaxB3Region : (size_t)kMaxRegion));
         for (size_t j = i + 1; j < nc && cand.size() < cap; ++j) {
             if (reg_of[j] >= 0 || region_class(calls[j]) != cls) continue;
             bool free = true;
@@ -121,6 +143,8 @@ void find_regions(const Context &ctx, const Graph &g, Plan *plan) {
             }
         }
         if (f.members.size() < 2 || f.members[0] != (int32_t)i) continue;     // the opener must be in (else try from the next kernel)
+        const bool b3 = (cls == RC_DENSE || cls == RC_DENSE_B3) && dense_region_b3(ctx, &f.fused);
+        if (cls == RC_DENSE_B3 && !b3) continue;
         for (int32_t c : f.members) reg_of[c] = (int32_t)found.size();
         found.push_back(std::move(f));
     }
@@ -334,7 +358,7 @@ int32_t compile_plan(Context &ctx, Graph &g, const int32_t *ids, size_t n, Plan 
         for (Region &r : plan->regions)
             for (size_t k = 0; k < r.members.size(); ++k) {
                 const KernelCall &own = plan->calls[(size_t)r.members[k]], &fc = r.fused[k];
-                if (fc.gemm.rf_ts == own.gemm.rf_ts && fc.gemm.rf_wgk == own.gemm.rf_wgk && fc.pack_bytes == own.pack_bytes) continue;
+                if (fc.kind == own.kind && fc.kind != CALL_B3 && fc.gemm.rf_ts == own.gemm.rf_ts && fc.gemm.rf_wgk == own.gemm.rf_wgk && fc.pack_bytes == own.pack_bytes) continue;
                 const void *w = g.nodes[fc.b_node].dev_ptr;
                 if (hipMalloc(&r.packed[k], fc.pack_bytes) != hipSuccess) {
                     (void)hipGetLastError();
@@ -693,8 +717,10 @@ int32_t execute_plan(Plan &p, const void *const *inputs, void *const *outputs, v
         if (fuse && p.region_of[i] >= 0 && p.handed[i]) {
             const Region &r = p.regions[(size_t)p.region_of[i]];
             const bool sep = c.kind == CALL_SEPCONV;
-            const bool plane = c.kind != CALL_GEMM && !sep;          // a region of thread-per-output kernels
+            const bool b3 = r.fused[0].kind == CALL_B3;
+            const bool plane = c.kind != CALL_GEMM && !sep && !b3;   // a region of thread-per-output kernels
             GemmArgs members[kMaxRegion];
+            B3Args bmembers[kMaxB3Region];
             SepConvArgs smembers[kMaxSepRegion];
             PlaneMultiArgs &pm = p.plane_args;           // (part of the plan: nothing this large goes on the stack per call)
             size_t idx[kMaxPlaneRegion];
@@ -729,6 +755,13 @@ int32_t execute_plan(Plan &p, const void *const *inputs, void *const *outputs, v
                         for (int s = 0; s < k2.epi.n; ++s) k2.epi.s[s].ptr = (const float *)fepi[s];
                         pm.kind[nm] = k2.mode == 0 ? 10 : 11;
                     }
+                } else if (b3) {
+                    if (!r.packed[k]) rc = fail(CLG_INVALID_ARG, "%s needs packed weights, none were prepared", fc.name.c_str());
+                    B3Args &k2 = bmembers[nm];
+                    k2 = fc.b3;
+                    k2.x = (const float *)ptr_of(fc.a_node); k2.w = r.packed[k];
+                    k2.y = (float *)const_cast<void *>(ptr_of(fc.out_node));
+                    for (int s = 0; s < k2.epi.n; ++s) k2.epi.s[s].ptr = (const float *)fepi[s];
                 } else {
                     const void *pk = r.packed[k] ? r.packed[k] : p.packed[ci];
                     rc = bind_gemm(fc, ptr_of(fc.a_node), ptr_of(fc.b_node), const_cast<void *>(ptr_of(fc.out_node)), fepi,
@@ -742,7 +775,8 @@ int32_t execute_plan(Plan &p, const void *const *inputs, void *const *outputs, v
                 if (kernel_ns) (void)hipEventRecord(ev[2 * i], (hipStream_t)stream);
                 pm.n = nm;
                 const int err = sep ? launch_sepconv_region(smembers, nm, stream)
-                                    : (plane ? launch_plane_region(pm, stream) : launch_gemm_region(members, nm, stream));
+                                    : (plane ? launch_plane_region(pm, stream)
+                                             : (b3 ? launch_b3_region(bmembers, nm, stream) : launch_gemm_region(members, nm, stream)));
                 if (kernel_ns) (void)hipEventRecord(ev[2 * i + 1], (hipStream_t)stream);
                 if (err != 0) rc = fail(CLG_HIP_ERROR, "launch of the region around %s failed: %s", c.name.c_str(),
                                         hipGetErrorString((hipError_t)err));

@@ -35,9 +35,9 @@ CASES = [
     ("conv3d", 1, 3, 40, (8, 44, 47), (7, 7, 7), (1, 2, 2), (3, 3, 3), 1),
     ("conv2d_transpose", 3, 64, 70, (5, 7), (4, 4), (2, 2), (1, 1), 1),
     ("conv2d_transpose", 1, 32, 24, (9, 4), (4, 4), (2, 2), (0, 0), 1),
-    ("dense", 129, 768, 192, None, None, None, None, 1),
-    ("dense", 33, 48, 70, None, None, None, None, 1),
-    ("dense", 9, 3072, 130, None, None, None, None, 1),
+    ("dense", 161, 768, 192, None, None, None, None, 1),
+    ("dense", 160, 48, 70, None, None, None, None, 1),
+    ("dense", 197, 3072, 130, None, None, None, None, 1),
 ]
 
 

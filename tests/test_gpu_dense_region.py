@@ -1,0 +1,45 @@
+"""Dense siblings of one shape in one launch of the split-operand kernel: both tiles, ragged rows, two to four members, the
+head split, tails; fused and apart against float64 with the bar of the single kernels."""
+import numpy as np
+import pytest
+
+import workloads as wl
+from workloads.patterns import P, W
+import paper_2111_00655_amd as clg
+
+pytestmark = pytest.mark.gpu
+
+# members, rows, in, out, heads of the head split (0: none), backend of the single kernels
+CASES = [(3, 389, 768, 768, 12, "igemm_r16"), (3, 161, 768, 768, 12, "igemm_r16"), (2, 163, 64, 96, 0, "igemm_r32"),
+         (4, 512, 128, 768, 0, "igemm"), (3, 300, 128, 640, 0, "igemm_r32_sk"), (3, 160, 48, 70, 0, "igemm")]
+
+
+@pytest.mark.parametrize("case", CASES)
+def test_dense_siblings_in_one_launch(case):
+    n, rows, cin, cout, heads, backend = case
+    r = np.random.default_rng([61, *case[:5]])
+    d = wl.GraphDesc("dense_region")
+    x = r.standard_normal((rows, cin)).astype(np.float32)
+    xin, refs = d.input(x), []
+    pat = P("bias_add", P("dense", W, W), W)
+    for _ in range(n):
+        w, b = (r.standard_normal(s).astype(np.float32) * np.float32(cin ** -0.5) for s in ((cout, cin), (cout,)))
+        y = d.op("bias_add", [d.op("dense", [xin, d.const(w)]), d.const(b)], axis=1)
+        ref = x.astype(np.float64) @ w.astype(np.float64).T + b
+        if heads:
+            y = d.op("transpose", [d.op("reshape", [y], dims=(rows, heads, cout // heads))], dims=(1, 0, 2))
+            ref = ref.reshape(rows, heads, -1).transpose(1, 0, 2)
+        d.mark_output(y)
+        refs.append(ref)
+    if heads:
+        pat = P("transpose", P("reshape", pat))
+    sess = clg.Session(d, [(backend, pat)], device=0)
+    per = len(d.op_nodes()) // n
+    plan = sess.compile([i for i, m in enumerate(sess.match()) if m.n_nodes == per])
+    assert plan.n_kernels == n and len(set(plan.regions())) == 1 and plan.regions()[0] >= 0, "the siblings are one region"
+    for digits in ([1] * n, [0] * n, [1] * n, [1, 1] + [0] * (n - 2)):
+        plan.set_handover(digits, 1)
+        for got, ref in zip(plan.run(), refs):
+            err = np.linalg.norm(got - ref) / np.linalg.norm(ref)
+            assert err < 1e-6, (case, digits, err)
+    sess.close()
