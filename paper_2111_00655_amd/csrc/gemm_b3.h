@@ -28,10 +28,11 @@
 // share a tile and split K.
 //  * Weights are constants: they are split and packed once per plan in the order in which a
 //    wave consumes them (32 rows x 16 values of k = three 1 KB planes, 16 bytes per lane), and
-//    are read straight into registers, R steps ahead.
+//    are read straight into registers, R - 1 steps ahead.
 //  * The input is staged through LDS once per 16 * SC channels, double-buffered: a lane loads eight
 //    channels of one position (coalesced along the positions), splits them (5.5 vector
-//    instructions per value) and writes three 16-byte pieces.  The positions ("slots") are the
+//    instructions per value) and writes three 16-byte pieces.  A wave that shares its rows and columns with no other one stages for itself, without
+//    barriers, and a 1x1 filter's unit then is a fragment as it is (DIRECT).  The positions ("slots") are the
 //    input patch that the tile's output pixels touch, so a 3x3 filter loads and splits a value once
 //    instead of nine times; a tap is a constant offset into the patch, and padding is a slot
 //    that stays zero.
@@ -69,23 +70,45 @@ struct B3Cfg {
     static constexpr int NW = WM * WN * WK, NT = NW * kWave;
     static constexpr int BM = 32 * WM, BN = 32 * TN * WN;
     static constexpr int RED = WK > 1 ? NW * TN * 16 * kWave * 4 : 0;      // bytes in which the K-waves meet
+    static constexpr bool PRIV = WM == 1 && WN == 1;                       // a wave stages what it alone reads: no barrier in the loop
 };
 using B3L = B3Cfg<4, 2, 1, 2, 4>;    // 128 x 128, eight waves
 using B3LM = B3Cfg<2, 2, 1, 2>;      // 64 x 128
 using B3M = B3Cfg<2, 1, 2, 2>;       // 64 x 64, two K-waves
+using B3M8 = B3Cfg<2, 1, 4, 2, 1>;   // 64 x 64, four K-waves (1x1 filters and dense layers)
 using B3S = B3Cfg<1, 1, 4, 2>;       // 32 x 64, four K-waves
 using B3SS = B3Cfg<1, 1, 4, 1>;      // 32 x 32, four K-waves
 using B3G = B3Cfg<1, 4, 1, 2>;       // 32 x 256: few output rows (grouped convolutions)
 using B3G2 = B3Cfg<1, 4, 1, 1>;      // 32 x 128
 
-// 16-channel blocks per K-wave and stage; registers sets of the weight stream (a set is loaded R - 1 steps ahead)
+// A wave of S and SS tiles is alone with its rows and columns and stages for itself.  For 1x1 filters its staging unit (a lane: eight channels of one position)
+// already is the fragment that it multiplies, so nothing goes through LDS (DIRECT); otherwise it does, in order and without barriers.
+template <class C, int TAPS, bool DENSE>
+constexpr bool b3_direct() { return C::PRIV && TAPS == 1 && !DENSE; }
+// 16-channel blocks per K-wave and stage
+template <class C, int TAPS, bool DENSE>
+constexpr int b3_cw() { return TAPS != 1 || b3_direct<C, TAPS, DENSE>() ? 1 : C::CW1; }
+// Register sets of the weight stream (a set is loaded R - 1 steps ahead), of the input (loaded D stages ahead of its split) and of
+// input fragments (BB = 2: read a step ahead).  Deeper rings gave nothing (128x128 tiles, R = 8 and D = 2, 46 -> 51 us) or cost waves
+// (32x32 tiles, R = 8 and D = 4, 9.4 -> 10.9 us): what a compute unit waits for is its own instruction stream and the L1, not a single load.
 template <class C, int TAPS>
-constexpr int b3_cw() { return TAPS == 1 ? C::CW1 : 1; }
+constexpr int b3_ring() { return TAPS == 9 ? 3 : (TAPS == 4 || C::PRIV || C::BM == 128 ? 4 : 2); }
+template <class C, int TAPS, bool DENSE>
+constexpr int b3_deep() { return b3_direct<C, TAPS, DENSE>() ? 2 : 1; }
 template <class C, int TAPS>
-constexpr int b3_ring() { return TAPS == 1 ? C::CW1 : (TAPS == 9 ? 3 : 4); }
+constexpr int b3_ahead() {
+    if (C::PRIV) return TAPS != 1 && C::TN > 1 ? 1 : 2;
+    return C::BM == 128 && TAPS != 9 ? 2 : 1;
+}
+// Stages per turn of the loop: every ring is back where it was.
+constexpr int b3_turn(int q, int r, int d, int bb) {
+    int u = 1;
+    while (u * q % r || u % d || u * q % bb) ++u;
+    return u;
+}
 // staging units (16 channels x 32 slots) per wave and stage of 1x1 filters and dense layers
-template <class C>
-constexpr int b3_units1() { return C::WK * C::CW1 * C::TN * C::WN / C::NW; }
+template <class C, bool DENSE>
+constexpr int b3_units1() { return C::WK * b3_cw<C, 1, DENSE>() * C::TN * C::WN / C::NW; }
 
 // Division by multiply-high, n / d for d >= 2: m = floor(2^32 / d) + 1, one = 0; d = 1: m = 0, one = ~0.  Exact for numerators
 // up to `most` if most * d < 2^32, which b3_set_div checks.
@@ -108,7 +131,17 @@ __device__ __forceinline__ void b3_split2(float a, float b, uint32_t &h, uint32_
     l = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2v{a, b}, bf16x2));
 }
 
-// The same for constant operands, which are split once: a finite value that would round to an infinity has the largest finite
+// One plane of a pair: the word of it, and what it leaves out in place of the pair.
+__device__ __forceinline__ void b3_take(float &a, float &b, uint32_t &w) {
+    w = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2v{a, b}, bf16x2));
+    a -= __uint_as_float(w << 16);
+    b -= __uint_as_float(w & 0xffff0000u);
+}
+// The staging split in pieces that a wave puts between its products: a plane of a pair each, and the four pairs of a unit take turns
+// (the steps of one pair depend on each other).  The ninth is the last plane of all four.
+constexpr int kB3Pieces = 9;
+
+// One pair of constant operands, which are split once, into all planes: a finite value that would round to an infinity has the largest finite
 // bf16 as its leading plane (what is left then has 16 bits, as elsewhere).
 __device__ __forceinline__ void b3_split2_full(float a, float b, uint32_t &h, uint32_t &m, uint32_t &l) {
     constexpr float most = 0x1.fep127f;
@@ -168,9 +201,11 @@ constexpr uint32_t kB3Out = 0x80000000u;
 
 template <class C, int TAPS, bool DEPTH, bool DENSE, int UM>
 __device__ __forceinline__ void b3_body(const B3Args &p) {
-    constexpr int CW = b3_cw<C, TAPS>(), SC = C::WK * CW, Q = CW * TAPS, R = b3_ring<C, TAPS>();
+    constexpr int CW = b3_cw<C, TAPS, DENSE>(), SC = C::WK * CW, Q = CW * TAPS;
+    constexpr int R = b3_ring<C, TAPS>(), D = b3_deep<C, TAPS, DENSE>(), BB = b3_ahead<C, TAPS>(), U = b3_turn(Q, R, D, BB);
     constexpr int TN = C::TN, WK = C::WK;
-    static_assert(Q % R == 0, "the ring of weight registers must divide the steps of a stage");
+    constexpr bool PRIV = C::PRIV, DIRECT = b3_direct<C, TAPS, DENSE>();
+    static_assert(DIRECT || BB == 1 || Q > 1, "staging ends a step before the stage does");
     extern __shared__ u32x4 b3_lds[];
     const int tid = threadIdx.x;
     const int lane = tid & (kWave - 1), half = lane >> 5, l32 = lane & 31;
@@ -200,18 +235,25 @@ __device__ __forceinline__ void b3_body(const B3Args &p) {
         v0 = (int)im * p.rpi + ((int)g - (int)im * p.HO) * p.ly;
     }
 
-    // ---- weights: this wave's stream, three planes of 64 lanes x 16 bytes per step
-    const u32x4 *Aw = reinterpret_cast<const u32x4 *>(p.w) + (((int64_t)mt * WK + wk) * p.stages + st_begin) * (Q * 3 * kWave);
-    const uint32_t lane_u = (uint32_t)lane;
+    // ---- weights: this wave's stream, three planes of 64 lanes x 16 bytes per step, through a buffer descriptor that ends where the stream does: what a
+    // ring reads ahead of the last step is zero and costs no traffic (with four steps per wave it would be a good part of it).  As loads from a
+    // scalar pointer the same kernels took 1024 -> 512 at 14x14, batch 32, 50.8 instead of 43.0 us, dense 768 -> 3072 on 389 rows 20.6 instead of 19.8.
+    constexpr int STEP = 3 * kWave * 16;
+    const int64_t w_first = (((int64_t)mt * WK + wk) * p.stages + st_begin) * (Q * STEP);
+    const auto wsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(reinterpret_cast<const char *>(p.w)) + w_first, (short)0,
+                                                        (st_end - st_begin) * (Q * STEP), 0x00020000);
+    uint32_t wo = (uint32_t)lane * 16;
     u32x4 ar[R][3];
+    auto load_w = [&](int set) {
 #pragma unroll
-    for (int r = 0; r + 1 < R; ++r)
+        for (int k = 0; k < 3; ++k) ar[set][k] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(wsrc, (int)wo, k * (kWave * 16), 0));
+        wo += STEP;
+    };
 #pragma unroll
-        for (int k = 0; k < 3; ++k) ar[r][k] = (Aw + (r * 3 + k) * kWave)[lane_u];
-    Aw += (R - 1) * 3 * kWave;
+    for (int r = 0; r + 1 < R; ++r) load_w(r);
 
     // ---- staging units of this wave: (16-channel block of the stage, 32 slots); a lane takes eight channels (its half).
-    // A wave short of units repeats the last one (the same values to the same place).
+    // A wave short of units repeats the last one (the same values to the same place); PRIV: the units of the wave's own blocks.
     const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(p.x), (short)0, p.x_bytes, 0x00020000);
     uint32_t off[UM];                                                      // byte offset, or kB3Out: the slot is padding
     int ldsw[UM], c16l[UM];
@@ -221,14 +263,14 @@ __device__ __forceinline__ void b3_body(const B3Args &p) {
         const int unit = TAPS == 1 ? wave + u * C::NW : min(wave + u * C::NW, p.units - 1);
         if constexpr (DENSE) {
             // 16 rows x 32 values of k: four lanes per row read 128 contiguous bytes
-            const int c32 = unit / (C::BN / 16), grp = unit % (C::BN / 16);
+            const int c32 = PRIV ? wk * (CW / 2) + u / (C::BN / 16) : unit / (C::BN / 16), grp = (PRIV ? u : unit) % (C::BN / 16);
             const int row = grp * 16 + (lane >> 2), part = lane & 3;
             c16l[u] = c32 * 32 + part * 8;                                 // first k of the lane within the stage
             off[u] = (uint32_t)min(j0 + row, p.Nrows - 1) * (uint32_t)p.ldx;
             ldsw[u] = (c32 * 4 + part) * S + row;
         } else {
-            const int c16 = TAPS == 1 ? unit / (C::BN / 32) : (int)b3_div((uint32_t)unit, p.d_g32);
-            const int grp = TAPS == 1 ? unit % (C::BN / 32) : unit - c16 * p.g32;
+            const int c16 = PRIV ? wk * CW : (TAPS == 1 ? unit / (C::BN / 32) : (int)b3_div((uint32_t)unit, p.d_g32));
+            const int grp = PRIV ? (TAPS == 1 ? u : min(u, p.g32 - 1)) : (TAPS == 1 ? unit % (C::BN / 32) : unit - c16 * p.g32);
             const int slot = grp * 32 + l32;
             int im, ih, iw;
             bool in;
@@ -262,13 +304,15 @@ __device__ __forceinline__ void b3_body(const B3Args &p) {
     const int cbase = (!DENSE && p.groups > 1) ? (int)b3_div((uint32_t)i0, p.d_cpgo) * p.cpg_in : 0;
 
     // blocks (and depth taps) in which this lane's eight channels exist; the others are zero, as their weights are
-    const int blk_end = DENSE ? 0 : ((p.Cf - half * 8 + 15) >> 4) * (DEPTH ? p.KD : 1);
-    float xv[UM][8];
-    auto load = [&](int u, int st_) {
-        const int st = min(st_, p.stages - 1);
+    // (nor is anything read of a stage behind this workgroup's last one)
+    const int blk_end = DENSE ? 0 : min(((p.Cf - half * 8 + 15) >> 4) * (DEPTH ? p.KD : 1), st_end * SC);
+    const int k_end = DENSE ? min(p.K, st_end * SC * 16) : 0;
+    float xs[D][UM][8];
+    auto load = [&](int set, int u, int st) {
+        float (&xv)[UM][8] = xs[set];
         if constexpr (DENSE) {
             const int k = st * SC * 16 + c16l[u];
-            const uint32_t o = k < p.K ? (off[u] + (uint32_t)k) * 4 : kB3Out;
+            const uint32_t o = k < k_end ? (off[u] + (uint32_t)k) * 4 : kB3Out;
             const u32x4 a = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)o, 0, 0));
             const u32x4 b = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)o, 16, 0));
 #pragma unroll
@@ -279,39 +323,50 @@ __device__ __forceinline__ void b3_body(const B3Args &p) {
         } else if constexpr (DEPTH) {
             // block: (16 channels, depth tap); a plane before or behind the volume is zero
             const int blk = min(st * SC + c16l[u], p.nC - 1), c16 = (int)b3_div((uint32_t)blk, p.d_kd), kd = blk - c16 * p.KD;
-            const int so = c16 * 16 * p.cs * 4;                            // (within the buffer: the bounds check subtracts it from the size)
+            const uint32_t so = (uint32_t)(c16 * 16 * p.cs) * 4;
             const bool in = off[u] != kB3Out && st * SC + c16l[u] < blk_end && (uint32_t)(idu[u] + kd) < (uint32_t)p.D;
-            const uint32_t o = in ? off[u] + (uint32_t)(kd * p.HW * 4) : kB3Out;      // (off may lie in front of the volume)
+            const uint32_t o = in ? off[u] + so + (uint32_t)(kd * p.HW * 4) : kB3Out;      // (off may lie in front of the volume)
 #pragma unroll
             for (int i = 0; i < 8; ++i)
-                xv[u][i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsrc, (int)o, so + i * p.cs * 4, 0));
+                xv[u][i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsrc, (int)o, i * p.cs * 4, 0));
         } else {
             const int c = cbase + min(st * SC + c16l[u], p.nC - 1) * 16;
-            const int so = c * p.cs * 4;                                   // (within the buffer: the bounds check subtracts it from the size)
-            const uint32_t o = st * SC + c16l[u] < blk_end ? off[u] : kB3Out;
+            const uint32_t so = (uint32_t)(c * p.cs) * 4;                  // (kB3Out + so is outside as well: the buffer has less than 2 GB)
+            const uint32_t o = (off[u] + so) | (st * SC + c16l[u] < blk_end ? 0u : kB3Out);
 #pragma unroll
             for (int i = 0; i < 8; ++i)
-                xv[u][i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsrc, (int)o, so + i * p.cs * 4, 0));
+                xv[u][i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsrc, (int)o, i * p.cs * 4, 0));
         }
     };
-    u32x4 pl[3];
-    // piece n of a stage's staging work: unit n / 4, pair n % 4; the last pair of a unit writes it and loads its next values
-    auto piece = [&](int n, int buf, int st_next) {
-        const int u = n / 4, i = n % 4;
-        uint32_t h, m, l;
-        b3_split2(xv[u][2 * i], xv[u][2 * i + 1], h, m, l);
-        pl[0][i] = h;
-        pl[1][i] = m;
-        pl[2][i] = l;
-        if (i == 3) {
-            u32x4 *dst = b3_lds + buf * 3 * PL + ldsw[u];
+    bf16x8 b[BB][TN][3];
+    uint32_t pl_w[3][4];
+    // piece i of the staging work of unit u, input set `set`; the last one writes the unit to LDS buffer `buf` (DIRECT: it is the fragment
+    // of column tile u in fragment set `buf`) and loads its next values
+    auto piece = [&](int set, int u, int i, int buf, int st_next) {
+        float (&xv)[8] = xs[set][u];
+        if (i < 8) {
+            b3_take(xv[2 * (i & 3)], xv[2 * (i & 3) + 1], pl_w[i >> 2][i & 3]);
+        } else {
 #pragma unroll
-            for (int k = 0; k < 3; ++k) dst[k * PL] = pl[k];
-            load(u, st_next);
+            for (int n = 0; n < 4; ++n) pl_w[2][n] = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2v{xv[2 * n], xv[2 * n + 1]}, bf16x2));
+            u32x4 pl[3];
+#pragma unroll
+            for (int k = 0; k < 3; ++k) pl[k] = u32x4{pl_w[k][0], pl_w[k][1], pl_w[k][2], pl_w[k][3]};
+            if constexpr (DIRECT) {
+#pragma unroll
+                for (int k = 0; k < 3; ++k) b[buf][u][k] = __builtin_bit_cast(bf16x8, pl[k]);
+            } else {
+                u32x4 *dst = b3_lds + buf * 3 * PL + ldsw[u];
+#pragma unroll
+                for (int k = 0; k < 3; ++k) dst[k * PL] = pl[k];
+            }
+            load(set, u, st_next);
         }
     };
 #pragma unroll
-    for (int u = 0; u < UM; ++u) load(u, st_begin);
+    for (int d = 0; d < D; ++d)
+#pragma unroll
+        for (int u = 0; u < UM; ++u) load(d, u, st_begin + d);
 
     // ---- this lane's column of every tile: first slot
     int sbase[TN];
@@ -333,7 +388,7 @@ __device__ __forceinline__ void b3_body(const B3Args &p) {
         }
     }
 #pragma unroll
-    for (int n = 0; n < 4 * UM; ++n) piece(n, 0, st_begin + 1);
+    for (int n = 0; n < kB3Pieces * UM; ++n) piece(0, n / kB3Pieces, n % kB3Pieces, 0, st_begin + D);
 
     // Two accumulators per tile: the products of the leading planes, and the five small ones (2^-8 of them and
     // less).  The large sum is then rounded once per 16 values of k.
@@ -343,45 +398,62 @@ __device__ __forceinline__ void b3_body(const B3Args &p) {
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[t][r] = acs[t][r] = 0.f;
 
-    bf16x8 b[TN][3];
     constexpr int KWt = TAPS == 9 ? 3 : (TAPS == 4 ? 2 : 1);
-    auto read_b = [&](int q, int buf) {
+    auto read_b = [&](int set, int q, int buf) {
         const int tap = q % TAPS;
         const int kh = tap / KWt, kw = tap % KWt;
         const int so = buf * 3 * PL + (q / TAPS) * 2 * S + (TAPS == 1 ? 0 : kh * p.pw_slots + kw);
 #pragma unroll
         for (int t = 0; t < TN; ++t)
 #pragma unroll
-            for (int k = 0; k < 3; ++k) b[t][k] = reinterpret_cast<const bf16x8 *>(b3_lds)[k * PL + so + sbase[t]];
+            for (int k = 0; k < 3; ++k) b[set][t][k] = reinterpret_cast<const bf16x8 *>(b3_lds)[k * PL + so + sbase[t]];
     };
-    lds_barrier();
-    for (int st = st_begin; st < st_end; ++st) {
-        const int buf = (st - st_begin) & 1;
-        b3_for<Q>([&](auto qc) {
-            constexpr int q = qc.value;
-            // a later step's weights leave before this step's products.  (Input fragments read a step ahead as well
-            // cost 24 more registers and with them the third wave of a SIMD: 1x1 64 -> 256 at 56x56, batch 32, 53 instead of 44 us.)
-            read_b(q, buf);
-#pragma unroll
-            for (int k = 0; k < 3; ++k) ar[(q + R - 1) % R][k] = (Aw + k * kWave)[lane_u];      // (the stream is padded by R steps)
-            Aw += 3 * kWave;
-            __builtin_amdgcn_sched_barrier(0);
-            bf16x8 a[3];
-#pragma unroll
-            for (int k = 0; k < 3; ++k) a[k] = __builtin_bit_cast(bf16x8, ar[q % R][k]);
-            b3_for<6 * TN>([&](auto mc) {
-                constexpr int m = mc.value / TN, t = mc.value % TN;
-                constexpr int PA[6] = {0, 2, 0, 1, 1, 0}, PB[6] = {0, 0, 2, 1, 0, 1};
-                constexpr int SLOTS = 6 * TN * Q, PIECES = 4 * UM, slot = q * 6 * TN + mc.value;
-                constexpr int n0 = slot * PIECES / SLOTS, n1 = (slot + 1) * PIECES / SLOTS;
-                if constexpr (m == 0) acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[PA[m]], b[t][PB[m]], acc[t], 0, 0, 0);
-                else acs[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[PA[m]], b[t][PB[m]], acs[t], 0, 0, 0);
-                // staging work for the next stage, spread over the products of this one
-                b3_for<n1 - n0>([&](auto nc) { piece(n0 + nc.value, buf ^ 1, st + 2); });
+    if constexpr (!PRIV) lds_barrier();
+    if constexpr (!DIRECT && BB > 1) read_b(0, 0, 0);
+    for (int st0 = st_begin; st0 < st_end; st0 += U) {                     // (a turn may end behind the last stage: weights and inputs are zero there)
+        b3_for<U>([&](auto uc) {
+            constexpr int u = uc.value;
+            const int st = st0 + u, buf = (st - st_begin) & 1;
+            b3_for<Q>([&](auto qc) {
+                constexpr int q = qc.value, g = u * Q + q, cur = g % BB, nxt = (g + 1) % BB;
+                // Input fragments, and a later step's weights, leave before this step's products.  With a second set of fragments the next step's
+                // leave now, the next stage's first ones behind the barrier that ends its staging, one step before this stage
+                // ends.  That set pays where its registers cost no resident wave: 128x128 tiles (1024 -> 512 at 14x14, batch 32, 47 -> 44 us) and the PRIV ones;
+                // not on 64-row tiles, which lose the third wave of a SIMD (64 -> 256 at 56x56, batch 32, 44 -> 53 us).
+                if constexpr (!DIRECT) {
+                    if constexpr (BB == 1) {
+                        read_b(0, q, buf);
+                    } else if constexpr (q + 1 < Q) {
+                        read_b(nxt, q + 1, buf);
+                    } else {
+                        if constexpr (!PRIV) lds_barrier();
+                        read_b(nxt, 0, buf ^ 1);
+                    }
+                }
+                load_w((g + R - 1) % R);
                 __builtin_amdgcn_sched_barrier(0);
+                bf16x8 a[3];
+#pragma unroll
+                for (int k = 0; k < 3; ++k) a[k] = __builtin_bit_cast(bf16x8, ar[g % R][k]);
+                b3_for<6 * TN>([&](auto mc) {
+                    constexpr int m = mc.value / TN, t = mc.value % TN;
+                    constexpr int PA[6] = {0, 2, 0, 1, 1, 0}, PB[6] = {0, 0, 2, 1, 0, 1};
+                    if constexpr (m == 0) acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[PA[m]], b[cur][t][PB[m]], acc[t], 0, 0, 0);
+                    else acs[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[PA[m]], b[cur][t][PB[m]], acs[t], 0, 0, 0);
+                    // staging work for the next stage, spread over the products of this one (BB = 2: of all steps but the last)
+                    constexpr int SLOTS = 6 * TN * (BB > 1 && !DIRECT ? Q - 1 : Q), PIECES = kB3Pieces * UM, slot = q * 6 * TN + mc.value;
+                    if constexpr (slot < SLOTS) {
+                        constexpr int n0 = slot * PIECES / SLOTS, n1 = (slot + 1) * PIECES / SLOTS;
+                        b3_for<n1 - n0>([&](auto nc) {
+                            constexpr int n = n0 + nc.value;
+                            piece((u + 1) % D, n / kB3Pieces, n % kB3Pieces, DIRECT ? nxt : buf ^ 1, st + 1 + D);
+                        });
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                });
             });
+            if constexpr (!PRIV && BB == 1) lds_barrier();
         });
-        lds_barrier();
     }
 
     // ---- K-waves meet in LDS; every wave finishes its share of the tile's accumulator registers
@@ -390,6 +462,7 @@ __device__ __forceinline__ void b3_body(const B3Args &p) {
     if constexpr (WK > 1) {
         float *red = reinterpret_cast<float *>(b3_lds);
         constexpr int PER = TN * 16 * kWave;
+        if constexpr (PRIV ? !DIRECT : BB > 1) __syncthreads();        // (some wave's fragments may still be on their way out of the same LDS)
 #pragma unroll
         for (int t = 0; t < TN; ++t)
 #pragma unroll
@@ -585,7 +658,7 @@ int b3_launch_tile(const B3Args &a, hipStream_t s);
 template <class C, int TAPS, bool DEPTH, bool DENSE, int UM>
 int b3_launch_um(const B3Args &a, hipStream_t s) {
     const int S = TAPS == 1 ? (DENSE ? C::BN + 2 : C::BN) : a.slot_stride;
-    const size_t stage = (size_t)2 * 3 * 2 * C::WK * b3_cw<C, TAPS>() * S * 16;
+    const size_t stage = b3_direct<C, TAPS, DENSE>() ? 0 : (size_t)2 * 3 * 2 * C::WK * b3_cw<C, TAPS, DENSE>() * S * 16;
     const size_t lds = stage > (size_t)C::RED ? stage : (size_t)C::RED;
     if constexpr (DENSE && (std::is_same_v<C, B3M> || std::is_same_v<C, B3SS>)) {        // the tiles of regions (b3_region_resolve), 51 KB of LDS each
         if (a.region) {
@@ -607,7 +680,7 @@ int b3_launch_um(const B3Args &a, hipStream_t s) {
 template <class C, int TAPS, bool DEPTH, bool DENSE>
 int b3_launch_one(const B3Args &a, hipStream_t s) {
     if constexpr (TAPS == 1) {
-        return b3_launch_um<C, TAPS, DEPTH, DENSE, b3_units1<C>()>(a, s);
+        return b3_launch_um<C, TAPS, DEPTH, DENSE, b3_units1<C, DENSE>()>(a, s);
     } else {
         const int um = (a.units + C::NW - 1) / C::NW;
         if (um <= 2) return b3_launch_um<C, TAPS, DEPTH, DENSE, 2>(a, s);
@@ -624,6 +697,9 @@ int b3_launch_one(const B3Args &a, hipStream_t s) {
         case B3_L: return b3_launch_one<B3L, TAPS, DEPTH, DENSE>(a, s);                    \
         case B3_LM: return b3_launch_one<B3LM, TAPS, DEPTH, DENSE>(a, s);                  \
         case B3_M: return b3_launch_one<B3M, TAPS, DEPTH, DENSE>(a, s);                    \
+        case B3_M8:                                                                       \
+            if constexpr (TAPS == 1) return b3_launch_one<B3M8, TAPS, DEPTH, DENSE>(a, s); \
+            else return (int)hipErrorInvalidValue;                                        \
         case B3_S: return b3_launch_one<B3S, TAPS, DEPTH, DENSE>(a, s);                    \
         case B3_SS: return b3_launch_one<B3SS, TAPS, DEPTH, DENSE>(a, s);                  \
         case B3_G: return b3_launch_one<B3G, TAPS, DEPTH, DENSE>(a, s);                    \

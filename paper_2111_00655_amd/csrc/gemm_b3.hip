@@ -21,13 +21,18 @@ TileShape tile_shape(int t) {
     case B3_L: return shape_of<B3L>();
     case B3_LM: return shape_of<B3LM>();
     case B3_M: return shape_of<B3M>();
+    case B3_M8: return shape_of<B3M8>();
     case B3_S: return shape_of<B3S>();
     case B3_SS: return shape_of<B3SS>();
     case B3_G: return shape_of<B3G>();
     default: return shape_of<B3G2>();
     }
 }
-int tile_cw(int t, int taps) { return taps == 1 ? tile_shape(t).cw1 : 1; }
+// 16-channel blocks per K-wave and stage (as b3_cw)
+int tile_cw(int t, int taps, bool dense) {
+    const TileShape s = tile_shape(t);
+    return taps != 1 || (s.wm == 1 && s.wn == 1 && !dense) ? 1 : s.cw1;
+}
 
 int ceil_div(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
 
@@ -36,7 +41,7 @@ int ceil_div(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
 bool place(B3Args *a, int tile, int split_cus = 0) {
     const TileShape ts = tile_shape(tile);
     const int nw = ts.wm * ts.wn * ts.wk, bn = 32 * ts.tn * ts.wn;
-    const int cw = tile_cw(tile, a->taps), sc = ts.wk * cw, um = a->taps == 1 ? sc * ts.tn * ts.wn / nw : 6;
+    const int cw = tile_cw(tile, a->taps, a->dense), sc = ts.wk * cw, um = a->taps == 1 ? sc * ts.tn * ts.wn / nw : 6;
     a->tile = tile;
     a->mgroups = ceil_div(a->mtiles, ts.wm);
     if (a->groups > 1 && ts.wm != 1) return false;           // the row tiles of a workgroup share the staged channels
@@ -108,7 +113,7 @@ bool place(B3Args *a, int tile, int split_cus = 0) {
             a->splitk = ceil_div(a->stages, a->stages_per);
         }
     }
-    a->pack_steps = (int64_t)a->mtiles * ts.wk * a->stages * cw * a->taps + 4;      // the last wave's ring reads ahead
+    a->pack_steps = (int64_t)a->mtiles * ts.wk * a->stages * cw * a->taps + 4;      // (and four steps of zeros; no kernel reads behind its stream)
     return ok;
 }
 
@@ -224,6 +229,17 @@ bool b3_resolve(const GemmArgs &g, int tile, int epi_flags, int n_cus, bool spli
     }
     a.tiles_m = ceil_div(a.Cout, 32);
     a.mtiles = a.tiles_m * a.phases;
+    if (tile == B3_M && split && a.taps == 1) {
+        // No more 64 x 64 tiles than compute units: eight waves each, since four leave a SIMD one wave, which hides nothing (us, four and eight waves,
+        // five images: 256 -> 64 at 50x50, 196 tiles, 9.2 and 7.9; 256 -> 1024 at 13x13, 224 tiles, 9.9 and 8.3; 2048 -> 512 at 7x7, 32 tiles and K split, 14.1 and
+        // 11.3; dense 768 -> 3072 on 200 rows, 192 tiles, 14.0 and 11.9).  Where units get several workgroups the smaller one
+        // is better (64 -> 256 at 50x50, 784 tiles, 13.7 and 21; dense 768 -> 3072 on 389 rows, 336 tiles, 20.4 and 22.3).
+        B3Args b = a;
+        if (place(&b, B3_M8, n_cus) && (int64_t)b.mgroups * b.ntiles <= n_cus) {
+            *out = b;
+            return true;
+        }
+    }
     if (tile != B3_NONE) {
         if (!place(&a, tile, split ? n_cus : 0)) return false;
     } else {
@@ -399,7 +415,7 @@ int launch_b3_pack(const B3Args &a, const float *w, void *dst, void *stream) {
     if (a.tile == B3_FIRST) return launch_b3_first_pack(a, w, dst, (hipStream_t)stream);
     const int64_t threads = a.pack_steps * kWave;
     hipLaunchKernelGGL(b3_pack_kernel, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, (hipStream_t)stream, w, (u32x4 *)dst, a,
-                       tile_shape(a.tile).wk, tile_cw(a.tile, a.taps));
+                       tile_shape(a.tile).wk, tile_cw(a.tile, a.taps, a.dense));
     return (int)hipGetLastError();
 }
 
