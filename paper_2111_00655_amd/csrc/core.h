@@ -210,6 +210,7 @@ struct Plan {
     std::vector<Region> regions;
     std::vector<int32_t> region_of;        // call -> index into regions, -1 none
     std::vector<char> fuse_mark;           // per call, scratch of an execution: 1 launched with its region, 2 carried its region
+    std::vector<std::vector<int32_t>> ahead;   // call -> later calls whose packed weights it reads ahead
     size_t workspace_bytes = 0;
     // concurrent lanes: kernels of independent branches go to different HIP streams
     int32_t max_lanes = 1;                 // 1 = everything on the caller's stream (default: see clg_plan_set_lanes)
@@ -230,7 +231,7 @@ struct Plan {
 
 // `packed`: the re-packed weights when c.pack_bytes != 0 (see pack_weights), else ignored.
 int32_t launch_call(const KernelCall &c, const void *a, const void *b, const void *c3,
-                    void *out, const void *const *epi_ptrs, void *scratch, const void *packed, void *stream);
+                    void *out, const void *const *epi_ptrs, void *scratch, const void *packed, void *stream, const Ahead *ahead = nullptr);
 // The kernel arguments of a CALL_GEMM call with every pointer bound.
 int32_t bind_gemm(const KernelCall &c, const void *a, const void *b, void *out, const void *const *epi_ptrs,
                   void *scratch, const void *packed, GemmArgs *k);

@@ -84,6 +84,21 @@ __device__ __forceinline__ float wave_sum_dpp(float v) {
             __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 48)));
 }
 
+// Thread `t` of `n` of a kernel's read-ahead workgroups: a word of every n-th piece, eight in flight.
+__device__ __forceinline__ void read_ahead(const Ahead &a, uint32_t t, uint32_t n) {
+    for (int s = 0; s < a.n; ++s) {
+        const uint32_t *p = reinterpret_cast<const uint32_t *>(a.p[s]);
+        const uint32_t lines = a.lines[s];
+        for (uint32_t i = t; i < lines; i += 8 * n) {
+            uint32_t v[8];
+#pragma unroll
+            for (uint32_t k = 0; k < 8; ++k) v[k] = p[(uint64_t)min(i + k * n, lines - 1) * (kAheadLine / 4)];
+#pragma unroll
+            for (uint32_t k = 0; k < 8; ++k) asm volatile("" ::"v"(v[k]));
+        }
+    }
+}
+
 __device__ __forceinline__ float wave_max(float v) {
 #pragma unroll
     for (int m = kWave / 2; m >= 1; m >>= 1) v = fmaxf(v, __shfl_xor(v, m, kWave));

@@ -216,6 +216,16 @@ struct SepMultiArgs {
 int sepconv_region_key(const SepConvArgs &a);
 int launch_sepconv_region(const SepConvArgs *members, int n, void *stream);
 
+// ---- reading ahead -----------------------------------------------------------------------------
+// Packed weights of later kernels that workgroups behind a kernel's own ones read without using them, so that those kernels find them in
+// the memory-side cache (plan.cpp: plan_read_ahead says when).
+constexpr int kMaxAhead = 4, kAheadLine = 64;
+struct Ahead {
+    const void *p[kMaxAhead];
+    uint32_t lines[kMaxAhead];             // pieces of kAheadLine bytes
+    int32_t n;
+};
+
 // ---- scaled-dot-product attention in one kernel (attention.hip) -----------------------------
 // y[h] = softmax(scale * q[h] k[h]^T) v[h]; q [B][Sq][d], k and v [B][Sk][d]; y [B][Sq][d], or with
 // merge = 1 the heads side by side: [Sq][B*d].
@@ -227,6 +237,7 @@ struct AttentionArgs {
     int32_t B, Sq, Sk, d;
     float scale;
     int32_t merge;
+    Ahead ahead;
 };
 bool attention_shape_ok(const AttentionArgs &a);       // d in {32, 64, 128}, Sk <= 512
 int launch_attention(const AttentionArgs &a, void *stream);
@@ -317,7 +328,9 @@ struct RowwiseArgs {
     int32_t tab_rows[3];
     const float *tab[3];
     const int32_t *gid[3];
+    Ahead ahead;                           // read by the one-round-trip layer norm only (rowwise_reads_ahead)
 };
+bool rowwise_reads_ahead(const RowwiseArgs &a);        // the shape is that kernel's (pointer alignment aside)
 
 // ---- elementwise chain / gather --------------------------------------------------------------
 struct EltwiseArgs {

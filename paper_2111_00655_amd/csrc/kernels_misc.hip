@@ -207,7 +207,8 @@ __global__ __launch_bounds__(256) void rowwise_block_kernel(RowwiseArgs a) {
 template <int V4>
 __global__ __launch_bounds__(64) void ln_wave_kernel(RowwiseArgs a, EpiFast ef) {
     const int lane = threadIdx.x;
-    const int row = blockIdx.x;
+    const int first = gridDim.x - a.rows, row = (int)blockIdx.x - first;
+    if (row < 0) return read_ahead(a.ahead, (uint32_t)(blockIdx.x * kWave + lane), first * kWave);
     const int len4 = a.len >> 2;
     const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
     float4 v[V4], t1[V4], t2[V4], ga[V4], be[V4];
@@ -267,9 +268,13 @@ __global__ __launch_bounds__(64) void ln_wave_kernel(RowwiseArgs a, EpiFast ef) 
     }
 }
 
+bool rowwise_reads_ahead(const RowwiseArgs &a) {
+    return a.mode == 1 && a.len % 4 == 0 && a.len <= 256 * 8 && a.len >= 64 && a.rows <= 4096;
+}
+
 // Whether the one-round-trip layer norm takes these arguments; fills *ef with the prologue's common form.
 static bool ln_wave_ok(const RowwiseArgs &a, EpiFast *ef) {
-    if (a.mode != 1 || a.len % 4 || a.len > 256 * 8 || a.len < 64 || a.rows > 65535 * 16) return false;
+    if (!rowwise_reads_ahead(a)) return false;
     auto al = [](const void *p) { return ((uintptr_t)p & 15) == 0; };
     if (!al(a.y) || !al(a.gamma) || !al(a.beta)) return false;
     ef->flags = 0;
@@ -324,12 +329,14 @@ int launch_rowwise(const RowwiseArgs &a, void *stream) {
     const int items = (a.len + kWave - 1) / kWave;
     hipStream_t s = (hipStream_t)stream;
     EpiFast ef{};
-    if (a.rows <= 4096 && ln_wave_ok(a, &ef)) {                    // layer norm in one memory round trip
+    if (ln_wave_ok(a, &ef)) {                                      // layer norm in one memory round trip
         const int v4 = (a.len / 4 + kWave - 1) / kWave;
-        if (v4 <= 1) hipLaunchKernelGGL(ln_wave_kernel<1>, dim3(a.rows), dim3(kWave), 0, s, a, ef);
-        else if (v4 <= 2) hipLaunchKernelGGL(ln_wave_kernel<2>, dim3(a.rows), dim3(kWave), 0, s, a, ef);
-        else if (v4 <= 4) hipLaunchKernelGGL(ln_wave_kernel<4>, dim3(a.rows), dim3(kWave), 0, s, a, ef);
-        else hipLaunchKernelGGL(ln_wave_kernel<8>, dim3(a.rows), dim3(kWave), 0, s, a, ef);
+        // (read-ahead waves first, so that theirs are the first loads to leave: behind the rows all of BERT-base, 200 rows, took 797 instead of 785 us)
+        const dim3 waves(a.rows + (a.ahead.n ? 256 : 0));
+        if (v4 <= 1) hipLaunchKernelGGL(ln_wave_kernel<1>, waves, dim3(kWave), 0, s, a, ef);
+        else if (v4 <= 2) hipLaunchKernelGGL(ln_wave_kernel<2>, waves, dim3(kWave), 0, s, a, ef);
+        else if (v4 <= 4) hipLaunchKernelGGL(ln_wave_kernel<4>, waves, dim3(kWave), 0, s, a, ef);
+        else hipLaunchKernelGGL(ln_wave_kernel<8>, waves, dim3(kWave), 0, s, a, ef);
         return (int)hipGetLastError();
     }
     if (a.n_gather) return (int)hipErrorInvalidValue;              // only the kernel above gathers

@@ -218,6 +218,61 @@ size_t plan_num_launches(const Plan &p) {
     return n;
 }
 
+// Which kernels read the packed weights of later ones ahead.  A network whose weights fit the memory-side cache (256 MB) finds them there pass
+// after pass; a larger one streams them from HBM (BERT-base: 340 MB), and each of its dense layers then takes 1.3 - 3.5 us longer than with its
+// weights in that cache.  Layer norms and attention leave most of the chip idle: workgroups of theirs read (64 bytes apart, nothing is
+// kept) what later kernels will stream.
+//  * How much: attention 2.4 MB per microsecond it takes itself (4 + flops / 37 GFLOP per ms on 12 heads of 64), a layer norm 16 MB, which make it
+//    1 us longer; more makes it longer than the dense layers gain (BERT-base, 389 rows: 14 MB more in a layer norm 1102 instead of 1077 us).
+//  * Where: attention with room for all that lies before the kernel after next that could read ahead takes all of it (389 rows: 1077 us, with
+//    a share in the layer norm 1099, without any 1123); otherwise the nearest one before that has room (256 rows: 795, attention first 820, without 864).
+//  * From 96 rows on: below, everything takes a few microseconds and reading ahead prolongs what it hides in (us without and with, all of BERT-base: 16 rows 435
+//    and 436 - 459, 64 rows 509 and 506 - 528, 128 rows 649 and 623).
+static void plan_read_ahead(Plan *plan) {
+    constexpr int64_t kMemorySideCache = (int64_t)256 << 20, kWorthIt = 1 << 20;
+    constexpr int kRows = 96, kReach = 8;
+    const size_t nc = plan->calls.size();
+    int64_t total = 0;
+    for (const KernelCall &c : plan->calls) total += (int64_t)c.pack_bytes;
+    plan->ahead.clear();
+    if (total <= kMemorySideCache) return;
+    plan->ahead.assign(nc, {});
+    std::vector<int64_t> room(nc, 0);
+    for (size_t i = 0; i < nc; ++i) {
+        const KernelCall &c = plan->calls[i];
+        const AttentionArgs &a = c.att;
+        if (c.kind == CALL_ATTENTION && a.Sq >= kRows) room[i] = (int64_t)(2.4e6 * (4.0 + 4.0 * a.B * a.Sq * a.Sk * a.d / 37e6));
+        if (c.kind == CALL_ROWWISE && c.row.rows >= kRows && rowwise_reads_ahead(c.row)) room[i] = 16000000;
+    }
+    std::vector<char> placed(nc, 0);
+    auto place = [&](size_t i, size_t j) {
+        room[i] -= (int64_t)plan->calls[j].pack_bytes;
+        plan->ahead[i].push_back((int32_t)j);
+        placed[j] = 1;
+    };
+    for (size_t i = 0; i < nc; ++i) {
+        if (plan->calls[i].kind != CALL_ATTENTION || !room[i]) continue;
+        int64_t sum = 0;
+        std::vector<size_t> all;
+        for (size_t j = i + 1, hosts = 0; j < nc && j <= i + kReach && hosts < 2; ++j) {
+            if (room[j]) ++hosts;
+            if ((int64_t)plan->calls[j].pack_bytes < kWorthIt) continue;
+            sum += (int64_t)plan->calls[j].pack_bytes;
+            all.push_back(j);
+        }
+        if (sum <= room[i] && all.size() <= (size_t)kMaxAhead)
+            for (size_t j : all) place(i, j);
+    }
+    for (size_t j = 0; j < nc; ++j) {
+        if (placed[j] || (int64_t)plan->calls[j].pack_bytes < kWorthIt) continue;
+        for (size_t i = j; i-- > 0 && j - i <= kReach;)
+            if (room[i] >= (int64_t)plan->calls[j].pack_bytes && plan->ahead[i].size() < (size_t)kMaxAhead) {
+                place(i, j);
+                break;
+            }
+    }
+}
+
 int32_t compile_plan(Context &ctx, Graph &g, const int32_t *ids, size_t n, Plan *plan) {
     g.finalize();
     if (!g.matched) return fail(CLG_INVALID_ARG, "clg_match_all has not been called on this graph");
@@ -395,6 +450,7 @@ int32_t compile_plan(Context &ctx, Graph &g, const int32_t *ids, size_t n, Plan 
             }
         if (any && hipStreamSynchronize(nullptr) != hipSuccess)
             return fail(CLG_HIP_ERROR, "weight packing failed: %s", hipGetErrorString(hipGetLastError()));
+        plan_read_ahead(plan);
     }
     return CLG_OK;
 }
@@ -581,7 +637,7 @@ int32_t bind_gemm(const KernelCall &c, const void *a, const void *b, void *out, 
 }
 
 int32_t launch_call(const KernelCall &c, const void *a, const void *b, const void *c3, void *out,
-                    const void *const *epi_ptrs, void *scratch, const void *packed, void *stream) {
+                    const void *const *epi_ptrs, void *scratch, const void *packed, void *stream, const Ahead *ahead) {
     auto bind = [&](Epilogue e) {
         for (int s = 0; s < e.n; ++s) e.s[s].ptr = (const float *)epi_ptrs[s];
         return e;
@@ -626,6 +682,7 @@ int32_t launch_call(const KernelCall &c, const void *a, const void *b, const voi
             k.gid[t] = (const int32_t *)epi_ptrs[3 + t];
         }
         if (k.n_gather) k.x = nullptr;
+        if (ahead) k.ahead = *ahead;
         err = launch_rowwise(k, stream);
         break;
     }
@@ -653,6 +710,7 @@ int32_t launch_call(const KernelCall &c, const void *a, const void *b, const voi
     case CALL_ATTENTION: {
         AttentionArgs k = c.att;
         k.q = (const float *)a; k.k = (const float *)b; k.v = (const float *)c3; k.y = (float *)out;
+        if (ahead) k.ahead = *ahead;
         err = launch_attention(k, stream);
         break;
     }
@@ -730,9 +788,29 @@ int32_t execute_plan(Plan &p, const void *const *inputs, void *const *outputs, v
     auto stream_of = [&](size_t i) -> void * {
         return (lanes && p.lane[i] > 0) ? p.side_streams[(size_t)p.lane[i] - 1] : stream;
     };
+    const bool fuse = p.max_lanes <= 1 && !p.handed.empty() && !p.regions.empty();
+    Ahead ahead;
+    auto ahead_of = [&](size_t i, Ahead *out) -> const Ahead * {
+        if (p.ahead.empty() || p.ahead[i].empty()) return nullptr;
+        out->n = 0;
+        for (int32_t j : p.ahead[i]) {
+            const void *w = p.packed[(size_t)j];
+            size_t bytes = p.calls[(size_t)j].pack_bytes;
+            if (fuse && p.region_of[(size_t)j] >= 0 && p.handed[(size_t)j]) {
+                const Region &r = p.regions[(size_t)p.region_of[(size_t)j]];
+                for (size_t k = 0; k < r.members.size(); ++k)
+                    if (r.members[k] == j && r.packed[k]) {
+                        w = r.packed[k];
+                        bytes = r.fused[k].pack_bytes;
+                    }
+            }
+            out->p[out->n] = w;
+            out->lines[out->n++] = (uint32_t)(bytes / kAheadLine);
+        }
+        return out;
+    };
     int32_t rc = CLG_OK;
     // regions: with one lane, the handed-over members of a region (two or more) go out as one launch
-    const bool fuse = p.max_lanes <= 1 && !p.handed.empty() && !p.regions.empty();
     std::vector<char> &done = p.fuse_mark;             // sized at compile time: nothing is allocated here
     if (fuse) std::fill(done.begin(), done.end(), 0);
     for (size_t i = 0; i < p.calls.size() && rc == CLG_OK; ++i) {
@@ -825,7 +903,7 @@ int32_t execute_plan(Plan &p, const void *const *inputs, void *const *outputs, v
         if (kernel_ns && !p.elided[i]) (void)hipEventRecord(ev[2 * i], (hipStream_t)stream);
         if (!p.elided[i])                                // an aliased concatenation: its operands are already in place
             rc = launch_call(c, ptr_of(c.a_node), ptr_of(c.b_node), ptr_of(c.c_node),
-                             const_cast<void *>(ptr_of(c.out_node)), epi, scratch, p.packed[i], st);
+                             const_cast<void *>(ptr_of(c.out_node)), epi, scratch, p.packed[i], st, ahead_of(i, &ahead));
         if (kernel_ns && !p.elided[i]) (void)hipEventRecord(ev[2 * i + 1], (hipStream_t)stream);
         if (lanes && p.signals[i] && rc == CLG_OK && hipEventRecord((hipEvent_t)p.events[i], (hipStream_t)st) != hipSuccess)
             rc = fail(CLG_HIP_ERROR, "hipEventRecord failed");
