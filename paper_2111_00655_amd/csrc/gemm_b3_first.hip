@@ -48,14 +48,17 @@ __global__ __launch_bounds__(256, 2) void b3_first_kernel(B3Args p) {
     const int oy0 = ty * p.TH, ox0 = tx * p.TW;
     const int id0 = od * p.sd - p.pd, ih0 = oy0 * p.sh - p.ph, iw0 = ox0 * p.sw - p.pwd;
 
-    const u32x4 *Aw = reinterpret_cast<const u32x4 *>(p.w) + (int64_t)mt * p.stages * p.steps * 3 * kWave;
-    const uint32_t lane_u = (uint32_t)lane;
+    const int w_bytes = p.stages * p.steps * (3 * kWave * 16);
+    const auto wsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(reinterpret_cast<const char *>(p.w)) + (int64_t)mt * w_bytes, (short)0, w_bytes, 0x00020000);
+    uint32_t wo = (uint32_t)lane * 16;
     u32x4 ar[kRing][3];
+    auto load_w = [&](int set) {
 #pragma unroll
-    for (int r = 0; r + 1 < kRing; ++r)
+        for (int k = 0; k < 3; ++k) ar[set][k] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(wsrc, (int)wo, k * (kWave * 16), 0));
+        wo += 3 * kWave * 16;
+    };
 #pragma unroll
-        for (int k = 0; k < 3; ++k) ar[r][k] = (Aw + (r * 3 + k) * kWave)[lane_u];
-    Aw += (kRing - 1) * 3 * kWave;
+    for (int r = 0; r + 1 < kRing; ++r) load_w(r);
 
     // ---- patch: item = pair of neighbouring columns of a row (channel of the stage or depth tap, input row)
     const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(p.x), (short)0, p.x_bytes, 0x00020000);
@@ -128,25 +131,18 @@ __global__ __launch_bounds__(256, 2) void b3_first_kernel(B3Args p) {
             r1 = p.prow;
         }
         const int last = (p.cps - 1) * p.prow + p.KHe - 1;
-        // columns past the filter and rows past the last one are cleared: an infinity among them would be NaN times a zero weight
-        u32x4 cols;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) cols[e] = 2 * e + 1 < p.KWe ? ~0u : (2 * e < p.KWe ? 0xffffu : 0u);
+        // (Columns past the filter and rows past the last one meet zero weights and are multiplied as they are.  An infinity or NaN among them makes the result a
+        // NaN, and such results are computed again below; clearing them took two dozen instructions for twelve MFMAs.)
         auto step = [&](auto sc) {
             constexpr int s = sc.value;
-            const int row = half ? r1 : r0, ro = min(row, last) * words;
-            u32x4 keep;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) keep[e] = row <= last ? cols[e] : 0u;
+            const int ro = min(half ? r1 : r0, last) * words;
             bf16x8 b[TN][3], a[3];
 #pragma unroll
             for (int t = 0; t < TN; ++t)
 #pragma unroll
                 for (int k = 0; k < 3; ++k)
-                    b[t][k] = __builtin_bit_cast(bf16x8, (u32x4)*reinterpret_cast<const u32x4a *>(P0 + k * PL + sbase[t] + ro) & keep);
-#pragma unroll
-            for (int k = 0; k < 3; ++k) ar[(s + kRing - 1) % kRing][k] = (Aw + k * kWave)[lane_u];
-            Aw += 3 * kWave;
+                    b[t][k] = __builtin_bit_cast(bf16x8, (u32x4)*reinterpret_cast<const u32x4a *>(P0 + k * PL + sbase[t] + ro));
+            load_w((s + kRing - 1) % kRing);
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int k = 0; k < 3; ++k) a[k] = __builtin_bit_cast(bf16x8, ar[s][k]);
