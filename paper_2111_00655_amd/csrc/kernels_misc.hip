@@ -8,6 +8,7 @@
 // is read once and written once, with consecutive lanes on consecutive
 // addresses; anything elementwise rides along in registers.
 #include <algorithm>
+#include <type_traits>
 
 #include <hip/hip_runtime.h>
 
@@ -651,7 +652,33 @@ __device__ __forceinline__ void window_pool_body(const PoolArgs &a, const uint32
     const float *xp = a.x + (int64_t)nc * a.D * a.H * a.W;
     float acc = AVG ? 0.f : -INFINITY;
     int cnt = 0;
-    for (int kd = 0; kd < a.KD; ++kd) {
+    // 3x3 windows (planes of a 3x3x3 one): all loads at once, from clamped addresses, and taken or not in the order of the loops below.  One after the
+    // other, each behind its test, they made the kernel nine round trips long: 3x3 stride 2 over 112x112, 64 channels, 4.35 us instead of
+    // 3.44, batch 32 52 instead of 36 (155 MB).
+    auto planes = [&](auto kds) {
+        constexpr int KD = decltype(kds)::value;
+        float v[KD][9];
+        bool in[KD][9];
+#pragma unroll
+        for (int kd = 0; kd < KD; ++kd)
+#pragma unroll
+            for (int t = 0; t < 9; ++t) {
+                const int id = od * a.sd - a.pd + kd, ih = oh * a.sh - a.ph + t / 3, iw = ow * a.sw - a.pw + t % 3;
+                in[kd][t] = id >= 0 && id < a.D && ih >= 0 && ih < a.H && iw >= 0 && iw < a.W;
+                v[kd][t] = xp[(uint32_t)((min(max(id, 0), a.D - 1) * a.H + min(max(ih, 0), a.H - 1)) * a.W + min(max(iw, 0), a.W - 1))];
+            }
+#pragma unroll
+        for (int kd = 0; kd < KD; ++kd)
+#pragma unroll
+            for (int t = 0; t < 9; ++t) {
+                acc = !in[kd][t] ? acc : (AVG ? acc + v[kd][t] : fmaxf(acc, v[kd][t]));
+                cnt += in[kd][t] ? 1 : 0;
+            }
+    };
+    const bool three = a.KH == 3 && a.KW == 3;
+    if (three && a.KD == 1) planes(std::integral_constant<int, 1>{});
+    else if (three && a.KD == 3) planes(std::integral_constant<int, 3>{});
+    else for (int kd = 0; kd < a.KD; ++kd) {
         const int id = od * a.sd - a.pd + kd;
         if (id < 0 || id >= a.D) continue;
         for (int kh = 0; kh < a.KH; ++kh) {
@@ -733,8 +760,20 @@ __global__ __launch_bounds__(256) void global_avg_pool_kernel(PoolArgs a) {
     if (nc >= a.NC) return;
     const int hw = a.H * a.W;
     const float *xp = a.x + (int64_t)nc * hw;
-    float sum = 0.f;
-    for (int i = lane; i < hw; i += kWave) sum += xp[i];
+    float sum = lane < hw ? xp[lane] : 0.f;
+    if (hw > kWave) {
+        // eight loads in flight (one at a time a 32x32 image is sixteen round trips long: 6.6 us inside a network, 3.2 back to back)
+        float part[8] = {sum, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+        for (int i = lane + kWave; i < hw; i += 8 * kWave) {
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                const int o = i + k * kWave;
+                const float v = xp[min(o, hw - 1)];
+                part[k] += o < hw ? v : 0.f;
+            }
+        }
+        sum = ((part[0] + part[1]) + (part[2] + part[3])) + ((part[4] + part[5]) + (part[6] + part[7]));
+    }
     sum = wave_sum(sum);
     if (lane == 0) a.y[nc] = sum / (float)hw;
 }

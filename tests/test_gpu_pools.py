@@ -1,0 +1,48 @@
+"""Pools where their kernels branch: 3x3 and 3x3x3 windows (all loads at once) over images smaller than a window, windows that hang over every edge, other windows beside them;
+global averages of one wave's lanes, one more, and more than eight rounds of loads.  Against the oracle: maxima are the same values, averages of n terms agree to n roundings."""
+import numpy as np
+import pytest
+
+import workloads as wl
+from workloads.patterns import P, W
+import paper_2111_00655_amd as clg
+from oracle.graph import Graph
+
+pytestmark = pytest.mark.gpu
+
+WINDOWS = [((2, 3, 1, 1), 3, 1, 1), ((1, 2, 2, 5), 3, 2, 1), ((3, 5, 14, 9), 3, 3, 0), ((1, 4, 33, 31), 3, 2, 1), ((2, 2, 7, 8), 2, 2, 0), ((1, 3, 9, 9), 5, 1, 2),
+           ((1, 2, 1, 1, 1), 3, 1, 1), ((2, 3, 5, 4, 7), 3, 2, 1), ((1, 2, 4, 6, 5), 2, 2, 0)]
+
+
+@pytest.mark.parametrize("avg", [False, True], ids=["max", "avg"])
+@pytest.mark.parametrize("case", WINDOWS, ids=str)
+def test_window_pools(case, avg):
+    shape, k, st, pad = case
+    n = len(shape) - 2
+    if avg and n == 3:
+        pytest.skip("no 3-D average window pool")
+    d = wl.GraphDesc("pool")
+    x = d.input(np.random.default_rng(len(shape) * 100 + k).standard_normal(shape).astype(np.float32))
+    kind = "avg_pool2d" if avg else f"max_pool{n}d"
+    d.mark_output(d.op(kind, [x], kernel=(k,) * n, stride=(st,) * n, pad=(pad,) * n))
+    s = clg.Session(d, [("direct", P(kind, W))], device=0)
+    s.match()
+    got, ref = s.compile([0]).run()[0], Graph(d).run()[0]
+    s.close()
+    if avg:
+        np.testing.assert_allclose(got, ref, rtol=0, atol=k * k * 2.0 ** -24 * 4)
+    else:
+        np.testing.assert_array_equal(got, ref)
+
+
+@pytest.mark.parametrize("hw", [(1, 1), (7, 7), (8, 8), (5, 13), (24, 24), (31, 33), (90, 77)])
+def test_global_average(hw):
+    d = wl.GraphDesc("gap")
+    x = d.input(np.random.default_rng(hw[1]).standard_normal((3, 5) + hw).astype(np.float32))
+    d.mark_output(d.op("global_avg_pool2d", [x]))
+    s = clg.Session(d, [("direct", P("global_avg_pool2d", W))], device=0)
+    s.match()
+    got, ref = s.compile([0]).run()[0], Graph(d).run()[0]
+    s.close()
+    # sums of hw terms of size one, rounded once per addition of a lane's and the lanes' partial sums
+    np.testing.assert_allclose(got, ref, rtol=0, atol=4 * 2.0 ** -24 * (hw[0] * hw[1]) ** 0.5)
