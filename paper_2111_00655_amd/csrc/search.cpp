@@ -14,8 +14,8 @@
 // makes the answer a pure function of the inputs.
 //
 // What it costs: the number of (sub-placement, distinct operator set) pairs -
-// NasNet-A with its separable convolutions operator by operator: 60 000 stored
-// sub-placements.
+// NasNet-A with its separable convolutions operator by operator: 53 000 stored
+// sub-placements, 119 000 pairs.
 //  * Matches of one frontier node that cover the same operators (the same
 //    pattern under every kernel-variant backend) differ in cost only: the
 //    cheapest (the earliest among equals) stands for all of them.
@@ -25,7 +25,11 @@
 //  * Sets are found by hash: every operator has a random 64-bit number, a set's
 //    hash is the XOR of its members', so extending a set by a match costs one
 //    XOR; equality is decided on the windows, never on the hash.
-// 120 - 230 ms -> 4 ms on that network (8-CPU host).
+//  * The loops over a window's words have a constant length up to four words,
+//    which leaves a pair without inner loops: 3.6 -> 3.1 ms on that network
+//    (three words, 8-CPU host).  Wider windows take the same code with a length
+//    read at run time.
+// 120 - 230 ms before sets were windows.
 #include <algorithm>
 
 #include "core.h"
@@ -76,24 +80,13 @@ void placement_of(const std::vector<Sub> &subs, int32_t idx, int32_t extra,
     std::reverse(out->begin(), out->end());
 }
 
-}  // namespace
-
-int32_t search_dp(Graph &g, size_t, const int64_t *cost, int64_t eps,
-                  std::vector<int32_t> *chosen, int64_t *total) {
-    g.finalize();
+// W: words of a window where the compiler is to know them, 0: `any_words`.
+template <int W>
+int32_t search(Graph &g, size_t any_words, const int64_t *cost, int64_t eps,
+               std::vector<int32_t> *chosen, int64_t *total) {
+    const size_t words = W ? (size_t)W : any_words;
     const int n = (int)g.order.size();
     const size_t n_matches = g.matches.size();
-    for (size_t i = 0; i < n_matches; ++i)
-        if (cost[i] < 0) return fail(CLG_INVALID_ARG, "negative cost for match %zu", i);
-    if (eps < 0) return fail(CLG_INVALID_ARG, "negative eps");
-
-    // A set whose lowest uncovered position is f holds no position above f + span: every match in it starts at
-    // or below f.  Its window starts at word f / 64 of the bit string and is `words` long; one spare word
-    // lets a window that is moved to a later frontier be read past its end.
-    int span = 0;
-    for (const MatchRec &m : g.matches)
-        for (int32_t v : m.nodes) span = std::max(span, g.rank[v] - g.rank[m.first]);
-    const size_t words = (size_t)(span + 63) / 64 + 1;
     std::vector<uint64_t> key((size_t)n);                 // random number of each position
     for (int r = 0; r < n; ++r) key[(size_t)r] = mix((uint64_t)r);
 
@@ -211,6 +204,29 @@ int32_t search_dp(Graph &g, size_t, const int64_t *cost, int64_t eps,
     placement_of(subs, full, -1, chosen);
     *total = subs[(size_t)full].cost;
     return CLG_OK;
+}
+
+}  // namespace
+
+int32_t search_dp(Graph &g, size_t, const int64_t *cost, int64_t eps,
+                  std::vector<int32_t> *chosen, int64_t *total) {
+    g.finalize();
+    for (size_t i = 0; i < g.matches.size(); ++i)
+        if (cost[i] < 0) return fail(CLG_INVALID_ARG, "negative cost for match %zu", i);
+    if (eps < 0) return fail(CLG_INVALID_ARG, "negative eps");
+
+    // A set whose lowest uncovered position is f holds no position above f + span: every match in it starts at
+    // or below f.  Its window starts at word f / 64 of the bit string and is `words` long; one spare word
+    // lets a window that is moved to a later frontier be read past its end.
+    int span = 0;
+    for (const MatchRec &m : g.matches)
+        for (int32_t v : m.nodes) span = std::max(span, g.rank[v] - g.rank[m.first]);
+    const size_t words = (size_t)(span + 63) / 64 + 1;
+    if (words == 1) return search<1>(g, words, cost, eps, chosen, total);
+    if (words == 2) return search<2>(g, words, cost, eps, chosen, total);
+    if (words == 3) return search<3>(g, words, cost, eps, chosen, total);
+    if (words == 4) return search<4>(g, words, cost, eps, chosen, total);
+    return search<0>(g, words, cost, eps, chosen, total);
 }
 
 }  // namespace clg

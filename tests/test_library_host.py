@@ -463,3 +463,34 @@ def test_search_with_matches_that_span_many_positions(width):
                 costs[i] = B.COST_INF
         assert s.search(costs, 7) == search.dp(g, reg, oms, costs, 7)
     s.close()
+
+
+@pytest.mark.parametrize("width, depth", [(3, 1), (66, 2), (96, 3), (97, 3)])
+def test_search_windows_of_one_word_and_at_the_edge_of_the_constant_lengths(width, depth):
+    """Matches of `depth` operators that lie `width` positions apart: windows of 1 word (no match spans two
+    positions), 3, 4 (the last length known to the compiler) and 5 (the general code) words."""
+    span = width * (depth - 1)
+    assert (span + 63) // 64 + 1 == {3: 1, 66: 3, 96: 4, 97: 5}[width]
+    d = wl.GraphDesc("windows")
+    x = d.input(np.zeros((2, 8), np.float32))
+    ops = ("relu", "tanh", "relu")
+    for _ in range(width):
+        v = x
+        for op in ops[:depth]:
+            v = d.op(op, [v])
+        d.mark_output(v)
+    whole = W
+    for op in ops[:depth]:
+        whole = P(op, whole)
+    reg = [("eltwise", P(op, W)) for op in dict.fromkeys(ops[:depth])] + ([("eltwise", whole)] if depth > 1 else [])
+    s = clg.Session(d, reg, device=None)
+    oms = enumerate_matches(Graph(d), reg)
+    _same_matches(s.match(), oms)
+    for seed in range(2):
+        costs = wl.synthetic_costs(len(oms), seed, ties=bool(seed))
+        chains = {min(m.nodes) for m in oms if len(m.nodes) > 1 and min(m.nodes) < 4 * depth}      # a few chains have both covers (a small state space)
+        for i, m in enumerate(oms):
+            if depth > 1 and len(m.nodes) > 1 and min(m.nodes) not in chains:
+                costs[i] = B.COST_INF
+        assert s.search(costs, 5) == search.dp(Graph(d), reg, oms, costs, 5)
+    s.close()
