@@ -102,8 +102,8 @@ bool place(B3Args *a, int tile, int split_cus = 0) {
     // Too few tiles for half of the compute units (deep layers, short sequences): K is split across workgroups and a
     // second kernel adds the partial tiles and applies the fused tail.  The 64 x 64 tile gives two workgroups to a compute
     // unit (four waves leave half of each SIMD's time to memory latency), the others one.  A split keeps two stages
-    // or more: a single one has nothing to load behind its products.  Dense 3072 -> 768 on 389 rows 25.5 -> 21 us
-    // (32 x 32 tiles before), 3x3 512 -> 512 on five 7x7 images 21.6 -> 15.7, 3x3x3 256 -> 256 on 4x7x7 17.8 -> 14.9; below some
+    // or more: a single one has nothing to load behind its products.  Dense 3072 -> 768 on 389 rows 25.5 -> 19.0 us
+    // (32 x 32 tiles before), 3x3 512 -> 512 on five 7x7 images 21.6 -> 15.1, 3x3x3 256 -> 256 on 2x7x7 20.9 -> 11.9; below some
     // 10 us the best unsplit tile wins, and is a candidate of its own.
     if (split_cus && wgs * 2 <= split_cus && !a->cs_len) {
         const int64_t want = (tile == B3_M ? 2 : 1) * split_cus / wgs;
@@ -311,27 +311,39 @@ size_t b3_scratch_bytes(const B3Args &a) { return a.splitk > 1 ? (size_t)a.split
 namespace {
 
 // Adds split-K partial tiles in slice order and applies the fused tail, V consecutive values per thread (four where they
-// share a channel, or have four neighbouring ones).
-template <int V>
-__global__ __launch_bounds__(256) void b3_reduce_kernel(const float *partial, float *y, uint32_t numel, int splitk, EpiFast ef,
-                                                        uint32_t inner, uint32_t channels) {
-    const uint32_t i = (blockIdx.x * 256u + threadIdx.x) * V;
+// share a channel, or have four neighbouring ones).  A slice is at most 2 MB and in some XCD's L2, so the bound is the latency of the
+// loads: F slices' leave together, from workgroups of one wave, which reach four times as many compute units as 256 threads do (all
+// of a 512 -> 512 layer on 4x4 is 32 KB).  Layer and reduction, us, with 256 threads and four slices, one wave and eight, one wave and
+// 16: 3x3x3 512 -> 512 on 1x4x4 (16 slices) 15.0, 14.2, 13.8; 256 -> 256 on 2x7x7 (12) 12.6, 12.3, 11.9; 128 -> 128 on 4x14x14 (6) 13.9,
+// 13.5, 13.6; 3x3 512 -> 512 on five 7x7 (8) 15.5, 15.1, 15.4; 1x1 2048 -> 512 on those (8) 11.4, 11.1, 11.2.
+constexpr int kReduceThreads = kWave;
+template <int V, int F>
+__global__ __launch_bounds__(kReduceThreads) void b3_reduce_kernel(const float *partial, float *y, uint32_t numel, int splitk, EpiFast ef,
+                                                                   uint32_t inner, uint32_t channels) {
+    const uint32_t i = (blockIdx.x * (uint32_t)kReduceThreads + threadIdx.x) * V;
     if (i >= numel) return;
     typedef float vec __attribute__((ext_vector_type(V)));
     auto at = [](const float *p, uint32_t o) { return *reinterpret_cast<const vec *>(p + o); };
     vec bv = 0.f, av = 0.f, sum = 0.f;
-    if (ef.flags & EF_BIAS) {
-        if (inner == 1) bv = at(ef.bias, i % channels);
-        else bv = ef.bias[i / inner % channels];
+    const auto parts = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(partial), (short)0, (int)(splitk * numel * 4), 0x00020000);
+    for (int k = 0; k < splitk; k += F) {
+        vec v[F];
+#pragma unroll
+        for (int e = 0; e < F; ++e) {               // (behind the last slice: beyond the buffer, zero)
+            const int o = (int)(((uint32_t)(k + e) * numel + i) * 4u);
+            if constexpr (V == 4) v[e] = __builtin_bit_cast(vec, __builtin_amdgcn_raw_buffer_load_b128(parts, o, 0, 0));
+            else v[e] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(parts, o, 0, 0));
+        }
+        if (k == 0) {
+            if (ef.flags & EF_BIAS) {
+                if (inner == 1) bv = at(ef.bias, i % channels);
+                else bv = ef.bias[i / inner % channels];
+            }
+            if (ef.flags & EF_ADD) av = at(ef.add, i);
+        }
+#pragma unroll
+        for (int e = 0; e < F; ++e) sum += v[e];
     }
-    if (ef.flags & EF_ADD) av = at(ef.add, i);
-    int k = 0;
-    for (; k + 4 <= splitk; k += 4) {                        // four loads in flight
-        const float *p = partial + (int64_t)k * numel;
-        const vec a = at(p, i), b = at(p + numel, i), c = at(p + 2 * (int64_t)numel, i), d = at(p + 3 * (int64_t)numel, i);
-        sum = sum + a + b + c + d;
-    }
-    for (; k < splitk; ++k) sum += at(partial + (int64_t)k * numel, i);
     float v[V], b[V], a[V];
 #pragma unroll
     for (int e = 0; e < V; ++e) {
@@ -352,8 +364,9 @@ int launch_b3_reduce(const B3Args &a, hipStream_t s) {
     bool four = n % 4 == 0 && (!bias || (inner == 1 ? c % 4 == 0 : inner % 4 == 0));
     for (const void *p : {(const void *)a.partial, (const void *)a.y, (const void *)a.ef.add, (const void *)(inner == 1 ? a.ef.bias : nullptr)})
         four = four && ((uintptr_t)p & 15) == 0;
-    if (four) hipLaunchKernelGGL(b3_reduce_kernel<4>, dim3((n / 4 + 255) / 256), dim3(256), 0, s, a.partial, a.y, n, a.splitk, a.ef, inner, c);
-    else hipLaunchKernelGGL(b3_reduce_kernel<1>, dim3((n + 255) / 256), dim3(256), 0, s, a.partial, a.y, n, a.splitk, a.ef, inner, c);
+    const uint32_t per = (uint32_t)kReduceThreads * (four ? 4 : 1);
+    const auto kernel = a.splitk > 8 ? (four ? b3_reduce_kernel<4, 16> : b3_reduce_kernel<1, 16>) : (four ? b3_reduce_kernel<4, 8> : b3_reduce_kernel<1, 8>);
+    hipLaunchKernelGGL(kernel, dim3((n + per - 1) / per), dim3(kReduceThreads), 0, s, a.partial, a.y, n, a.splitk, a.ef, inner, c);
     return (int)hipGetLastError();
 }
 
