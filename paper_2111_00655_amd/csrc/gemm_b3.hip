@@ -22,6 +22,7 @@ TileShape tile_shape(int t) {
     case B3_LM: return shape_of<B3LM>();
     case B3_M: return shape_of<B3M>();
     case B3_M8: return shape_of<B3M8>();
+    case B3_M12: return shape_of<B3M12>();
     case B3_S: return shape_of<B3S>();
     case B3_SS: return shape_of<B3SS>();
     case B3_G: return shape_of<B3G>();
@@ -237,6 +238,15 @@ bool b3_resolve(const GemmArgs &g, int tile, int epi_flags, int n_cus, bool spli
         B3Args b = a;
         if (place(&b, B3_M8, n_cus) && (int64_t)b.mgroups * b.ntiles <= n_cus) {
             *out = b;
+            return true;
+        }
+        // Dense layers with more than that, but no more 96 x 64 tiles than compute units: every unit has one tile and one round, of 12 waves, where
+        // some would have two of the small ones and others one (us, 64 x 64 tiles, 96 x 64 ones of six and of 12 waves: 768 -> 3072 on 389 rows, 336 and
+        // 224 tiles, 19.9, 18.0 and 16.0, on 353 rows 19.4, 17.0 and 15.5; 768 -> 4096 on 300 rows 19.8, 18.0 and 16.0; 1024 -> 3072 on 384 rows 24.0, 22.9
+        // and 20.2; 768 -> 2048 on 700 rows 20.4, 18.6 and 17.5).  1x1 filters, whose loads are short of registers: 256 -> 1024 on six 14x14 12.1, 12.9.
+        B3Args c = a;
+        if (a.dense && place(&c, B3_M12) && (int64_t)c.mgroups * c.ntiles <= n_cus) {
+            *out = c;
             return true;
         }
     }

@@ -243,7 +243,7 @@ bool attention_shape_ok(const AttentionArgs &a);       // d in {32, 64, 128}, Sk
 int launch_attention(const AttentionArgs &a, void *stream);
 
 // ---- contractions on the bf16 matrix cores, operands split exactly into three bf16 values (gemm_b3.h) ----
-enum B3Tile : int32_t { B3_NONE = 0, B3_L = 1, B3_LM = 2, B3_M = 3, B3_S = 4, B3_SS = 5, B3_G = 6, B3_G2 = 7, B3_FIRST = 8, B3_M8 = 9 };
+enum B3Tile : int32_t { B3_NONE = 0, B3_L = 1, B3_LM = 2, B3_M = 3, B3_S = 4, B3_SS = 5, B3_G = 6, B3_G2 = 7, B3_FIRST = 8, B3_M8 = 9, B3_M12 = 10 };
 struct B3Div { uint32_t m, one; };         // division by multiply-high: b3_div
 struct B3Args {
     const float *x;                        // input, NCHW (or rows of a dense layer)

@@ -293,7 +293,7 @@ bool lower_b3(const Context &ctx, const Backend &be, const GemmArgs &a, const Ep
     if (!(be.tile == TILE_R32 && b3_resolve(a, B3_FIRST, flags, ctx.n_cus, false, &b)) &&
         !b3_resolve(a, tile, flags, ctx.n_cus, tile == B3_M, &b))
         return false;
-    static const char *tn[] = {"", "m128n128", "m64n128", "m64n64", "m32n64", "m32n32", "m32n256", "m32n128", "first", "m64n64w8"};
+    static const char *tn[] = {"", "m128n128", "m64n128", "m64n64", "m32n64", "m32n32", "m32n256", "m32n128", "first", "m64n64w8", "m96n64w12"};
     c->kind = CALL_B3;
     c->b3 = b;
     c->b3.epi = epi;
