@@ -661,8 +661,13 @@ int b3_launch_um(const B3Args &a, hipStream_t s) {
     const int S = TAPS == 1 ? (DENSE ? C::BN + 2 : C::BN) : a.slot_stride;
     const size_t stage = b3_direct<C, TAPS, DENSE>() ? 0 : (size_t)2 * 3 * 2 * C::WK * b3_cw<C, TAPS, DENSE>() * S * 16;
     const size_t lds = stage > (size_t)C::RED ? stage : (size_t)C::RED;
-    if constexpr (DENSE && (std::is_same_v<C, B3M> || std::is_same_v<C, B3SS>)) {        // the tiles of regions (b3_region_resolve), 51 KB of LDS each
+    if constexpr (DENSE && (std::is_same_v<C, B3M> || std::is_same_v<C, B3M8> || std::is_same_v<C, B3M12> || std::is_same_v<C, B3SS>)) {        // the tiles of regions (b3_region_resolve)
         if (a.region) {
+            if (lds > 64 * 1024) {
+                static LdsLimit limit;
+                const hipError_t e = limit.raise((const void *)b3_dense_multi_kernel<C, UM>);
+                if (e != hipSuccess) return (int)e;
+            }
             hipLaunchKernelGGL((b3_dense_multi_kernel<C, UM>), dim3((unsigned)(a.mgroups * a.ntiles), (unsigned)a.region->n, 1), dim3(C::NT), lds, s, a, *a.region);
             return (int)hipGetLastError();
         }

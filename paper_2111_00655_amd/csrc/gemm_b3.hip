@@ -291,8 +291,17 @@ bool b3_region_resolve(const GemmArgs *m, int n, int n_cus, B3Args *out) {
     // 64 x 64 tiles once the members have them for 9/16 of the compute units, four-wave 32 x 32 ones before.  Two layers of BERT-base,
     // us with q, k, v on the fp32 register-fed region, on 64 x 64 and on 32 x 32 tiles: 128 rows 99.0, 106.8, 98.3; 200 rows
     // 132.2, 133.8, 130.8; 256 rows 139.2, 138.0, 140.7; 320 rows 152.1, 144.7, 149.4; 389 rows 202.4, 190.2, 195.6.
+    // With no more 64 x 64 tiles, or else 96 x 64 ones, than compute units, the members get those of eight or twelve waves, as a layer alone does
+    // (b3_resolve).  All of BERT-base, us, its q, k and v on four waves per tile and on these: 256 rows 816 and 793, 320 rows 911 and 888, 389 rows
+    // 1105 and 1086 (252 tiles of 64 x 64), 512 rows 1267 and 1222 (288 of them, 192 of 96 x 64).  With 64 x 64 tiles from 5/16 of the units on: 160
+    // rows 657 -> 677, 200 rows 792 -> 785.
     const int tile = (int64_t)n * a.M * a.N >= (int64_t)64 * 64 * (n_cus * 9 / 16) ? B3_M : B3_SS;
-    return a.mode == GM_NT && b3_resolve(a, tile, epi_fast_flags(a.epi), n_cus, false, out) && out->dense;
+    if (a.mode != GM_NT) return false;
+    if (tile == B3_M) {
+        for (int t : {B3_M8, B3_M12})
+            if (b3_resolve(a, t, epi_fast_flags(a.epi), n_cus, false, out) && out->dense && (int64_t)n * out->mgroups * out->ntiles <= n_cus) return true;
+    }
+    return b3_resolve(a, tile, epi_fast_flags(a.epi), n_cus, false, out) && out->dense;
 }
 
 int launch_b3_region(const B3Args *members, int n, void *stream) {
