@@ -495,17 +495,10 @@ static void launch_grouped3(const DirectConvArgs &a, hipStream_t s) {
     else hipLaunchKernelGGL((grouped3_kernel<COB, 2>), grid, dim3(256), 0, s, a, items, quads);
 }
 
-// Transposed convolution of any filter size, stride and pad (w is [C][O][KH][KW]), gather form: one
-// thread per output pixel, blockIdx.y = output channel, blockIdx.z = image.  Output row oh takes
+// One output of a transposed convolution in gather form (w is [C][O][KH][KW]): output row oh takes
 // filter row kh from input row (oh + ph - kh) / sh where that division is exact and the row exists;
-// the same along the width.  The kernel that runs what the phase-decomposed MFMA kernels refuse
-// (a filter size that the stride does not divide).
-__global__ __launch_bounds__(256) void direct_convt_kernel(DirectConvArgs a) {
-    const int p = blockIdx.x * blockDim.x + threadIdx.x;
-    const int npix = a.HO * a.WO;
-    const int co = blockIdx.y, n = blockIdx.z;
-    if (p >= npix) return;
-    const int oh = p / a.WO, ow = p % a.WO;
+// the same along the width.
+__device__ __forceinline__ float convt_gather(const DirectConvArgs &a, int n, int co, int oh, int ow) {
     const float *xn = a.x + (int64_t)n * a.C * a.H * a.W;
     const float *wo = a.w + (int64_t)co * a.KH * a.KW;
     const int64_t xstride = (int64_t)a.H * a.W, wstride = (int64_t)a.O * a.KH * a.KW;
@@ -522,8 +515,148 @@ __global__ __launch_bounds__(256) void direct_convt_kernel(DirectConvArgs a) {
             for (int ci = 0; ci < a.C; ++ci) acc = fmaf(xp[ci * xstride], wp[ci * wstride], acc);
         }
     }
+    return acc;
+}
+
+// Transposed convolution of any filter size, stride and pad: one thread per output pixel, blockIdx.y =
+// output channel, blockIdx.z = image.  The kernel that runs what the phase-decomposed MFMA kernels refuse
+// (a filter size that the stride does not divide).
+__global__ __launch_bounds__(256) void direct_convt_kernel(DirectConvArgs a) {
+    const int p = blockIdx.x * blockDim.x + threadIdx.x;
+    const int npix = a.HO * a.WO;
+    const int co = blockIdx.y, n = blockIdx.z;
+    if (p >= npix) return;
     const int64_t off = ((int64_t)n * a.O + co) * npix + p;
-    a.y[off] = apply_steps(a.epi, acc, off, co);
+    a.y[off] = apply_steps(a.epi, convt_gather(a, n, co, p / a.WO, p % a.WO), off, co);
+}
+
+// 4x4 filters, stride 2, pad 1, one to four output channels (the layer that makes an image): a lane owns the 2x2 outputs around
+// each of R input positions, one above the other, which need R + 2 rows of three inputs, so 3 R + 6 loads feed 16 R O products, all of them useful; the 16 O
+// weights of an input channel are wave-uniform (scalar loads).  The matrix cores do this layer with 3 of 16 or 12 of 16 rows filled and
+// nine taps of which a phase uses four.  The WK waves of a workgroup share its 64 lanes' positions and split the input channels; they meet in
+// LDS, and each finishes whole rows of pixel pairs.  Bounds: the products at 39 T/s (5 us for 64 -> 3 channels at 32x32, 64 images), and for few images
+// the weights' round trips, one behind the other.  That layer on the fp32 matrix cores and here: 16 images 7.0 and 6.5 us, 32 images
+// 12.0 and 8.7, 64 images 21.2 and 12.6, 256 images 74 and 39; up to eight images the matrix cores are faster (3.8 - 4.9 us).
+template <int O, int R, int WK>
+__global__ __launch_bounds__(WK * kWave) void few_convt_kernel(DirectConvArgs a, uint32_t items) {
+    constexpr uint32_t kOut = 0x80000000u;                   // beyond the buffer: loaded as zero, not stored
+    constexpr int X = 3 * (R + 2);
+    __shared__ float red[WK][4 * R * O][kWave];
+    const int lane = threadIdx.x & (kWave - 1), wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const uint32_t t = blockIdx.x * (uint32_t)kWave + lane;
+    const bool live = t < items;
+    const uint32_t tt = live ? t : 0;
+    const int HW = a.H * a.W, per_image = (a.H + R - 1) / R * a.W;
+    const int n = (int)(tt / (uint32_t)per_image), q = (int)(tt - (uint32_t)n * per_image);
+    const int i = q / a.W * R, j = q - i / R * a.W;
+    const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(a.x), (short)0, (int)((int64_t)a.N * a.C * HW * 4), 0x00020000);
+    uint32_t off[X];
+#pragma unroll
+    for (int k = 0; k < X; ++k) {
+        const int ih = i - 1 + k / 3, iw = j - 1 + k % 3;
+        off[k] = live && ih >= 0 && ih < a.H && iw >= 0 && iw < a.W ? (uint32_t)(n * a.C * HW + ih * a.W + iw) * 4u : kOut;
+    }
+    float acc[2 * R][2][O];                                  // output row, column
+#pragma unroll
+    for (int r = 0; r < 2 * R; ++r)
+#pragma unroll
+        for (int o = 0; o < O; ++o) acc[r][0][o] = acc[r][1][o] = 0.f;
+    const int per = (a.C + WK - 1) / WK, c0 = wave * per, c1 = min(c0 + per, a.C);
+    float x[2][X];
+    auto load = [&](int set, int c) {
+#pragma unroll
+        for (int k = 0; k < X; ++k) x[set][k] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsrc, (int)off[k], min(c, a.C - 1) * HW * 4, 0));
+    };
+    // Weights: 16 at a time (an output channel), the next ones on their way while these are used.  Scalar loads return out of order, so a wait is for all
+    // of them: the next load leaves behind the first product of this one's.  (All of a channel's loaded where they are used: 64 images 13.0 instead of 12.6 us.)
+    float wv[2][16];
+    auto load_w = [&](int set, int k) {
+        const float *w = a.w + (int64_t)min(k, a.C * O - 1) * 16;
+#pragma unroll
+        for (int f = 0; f < 16; ++f) wv[set][f] = w[f];
+    };
+    auto step = [&](int set, int c) {
+#pragma unroll
+        for (int o = 0; o < O; ++o) {
+            const int ring = (set * O + o) & 1;
+#pragma unroll
+            for (int f = 0; f < 16; ++f) {
+                // filter rows 0 and 2 make the lower output row, from the input row below and this one; 1 and 3 the upper one, from this one and the one above
+                const int kh = f >> 2, kw = f & 3, r = kh & 1 ? 0 : 1, s = kw & 1 ? 0 : 1, ih = kh == 0 ? 2 : (kh == 3 ? 0 : 1), iw = kw == 0 ? 2 : (kw == 3 ? 0 : 1);
+#pragma unroll
+                for (int y = 0; y < R; ++y) acc[2 * y + r][s][o] = fmaf(x[set][(y + ih) * 3 + iw], wv[ring][f], acc[2 * y + r][s][o]);
+                if (f == 0) {
+                    __builtin_amdgcn_sched_barrier(0);
+                    load_w(ring ^ 1, c * O + o + 1);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    load_w(0, c0 * O);
+    load(0, c0);
+    for (int c = c0; c < c1; c += 2) {
+        load(1, c + 1);
+        step(0, c);
+        load(0, c + 2);
+        if (c + 1 < c1) step(1, c + 1);
+    }
+#pragma unroll
+    for (int r = 0; r < 2 * R; ++r)
+#pragma unroll
+        for (int s = 0; s < 2; ++s)
+#pragma unroll
+            for (int o = 0; o < O; ++o) red[wave][(2 * r + s) * O + o][lane] = acc[r][s][o];
+    __syncthreads();
+    const int npix = a.HO * a.WO, bytes = (int)((int64_t)a.N * O * npix * 4);
+    const auto ydst = __builtin_amdgcn_make_buffer_rsrc(a.y, (short)0, bytes, 0x00020000);
+    const auto rsum = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(a.ef.add), (short)0, bytes, 0x00020000);
+#pragma unroll 1
+    for (int e = wave; e < 2 * R * O; e += WK) {             // (channel, output row)
+        const int r = e & (2 * R - 1), o = e / (2 * R);
+        const bool in = live && 2 * i + r < a.HO;
+        float v[2] = {0.f, 0.f}, bv[2], av[2] = {0.f, 0.f};
+#pragma unroll
+        for (int k = 0; k < WK; ++k) {
+            v[0] += red[k][2 * r * O + o][lane];
+            v[1] += red[k][(2 * r + 1) * O + o][lane];
+        }
+        // taps outside the image were multiplied as zeros, which an infinite weight makes a NaN: such outputs are gathered
+        if (in && !(fabsf(v[0]) < INFINITY)) v[0] = convt_gather(a, n, o, 2 * i + r, 2 * j);
+        if (in && !(fabsf(v[1]) < INFINITY)) v[1] = convt_gather(a, n, o, 2 * i + r, 2 * j + 1);
+        const uint32_t ob = in ? (uint32_t)((n * O + o) * npix + (2 * i + r) * a.WO + 2 * j) * 4u : kOut;
+        bv[0] = bv[1] = (a.ef.flags & EF_BIAS) ? a.ef.bias[o] : 0.f;
+        if (a.ef.flags & EF_ADD) {
+            av[0] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsum, (int)ob, 0, 0));
+            av[1] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsum, (int)ob, 4, 0));
+        }
+        fused_tail<2>(a.ef, v, bv, av);
+        typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+        __builtin_amdgcn_raw_buffer_store_b64(u32x2{__float_as_uint(v[0]), __float_as_uint(v[1])}, ydst, (int)ob, 0, 0);
+    }
+}
+
+// 31-bit byte offsets.  At every size: over 26 layers 1.3 (one channel of one value) to 35 times as fast as the general kernel (512 channels at 2x2: 19 us, 663).
+static bool few_convt_ok(const DirectConvArgs &a) {
+    return a.transposed && !(a.ef.flags & EF_GENERIC) && a.G == 1 && a.O >= 1 && a.O <= 4 && a.C >= 1 && a.KH == 4 && a.KW == 4 && a.sh == 2 && a.sw == 2 && a.ph == 1 && a.pw == 1 &&
+           a.HO == 2 * a.H && a.WO == 2 * a.W && (int64_t)a.N * a.C * a.H * a.W < ((int64_t)1 << 29) && (int64_t)a.N * a.O * a.HO * a.WO < ((int64_t)1 << 29);
+}
+
+template <int O, int R, int WK>
+static void launch_few_convt_as(const DirectConvArgs &a, hipStream_t s) {
+    const uint32_t items = (uint32_t)(a.N * ((a.H + R - 1) / R) * a.W), groups = (items + kWave - 1) / kWave;
+    hipLaunchKernelGGL((few_convt_kernel<O, R, WK>), dim3(groups), dim3(WK * kWave), 0, s, a, items);
+}
+
+// One position per lane while that makes no more than two workgroups per compute unit, two above (64 -> 3 channels at 32x32, us with one and
+// two: 16 images 6.5 and 8.7, 32 images 8.7 and 9.0, 64 images 14.0 and 12.6, 256 images 47 and 39; 16 -> 1 at 256x256, four images, 17.2 and 12.0).
+// Four waves and sixteen instead of eight, one position: 16 images 9.0 and 6.4, 32 images 9.4 and 8.9.
+template <int O>
+static void launch_few_convt(const DirectConvArgs &a, hipStream_t s) {
+    constexpr int kCUs = 256;                                // of an MI355X
+    if (((int64_t)a.N * a.H * a.W + kWave - 1) / kWave <= 2 * kCUs) launch_few_convt_as<O, 1, 8>(a, s);
+    else launch_few_convt_as<O, 2, 8>(a, s);
 }
 
 // Depthwise convolution (one input channel per output channel), square filter KS: one output per
@@ -615,6 +748,13 @@ int launch_direct_conv(const DirectConvArgs &a_in, void *stream) {
     hipStream_t s = (hipStream_t)stream;
     if (a.transposed) {
         if (a.G != 1 || a.O > 65535 || a.N > 65535) return (int)hipErrorInvalidValue;
+        if (few_convt_ok(a)) {
+            if (a.O == 1) launch_few_convt<1>(a, s);
+            else if (a.O == 2) launch_few_convt<2>(a, s);
+            else if (a.O == 3) launch_few_convt<3>(a, s);
+            else launch_few_convt<4>(a, s);
+            return (int)hipGetLastError();
+        }
         hipLaunchKernelGGL(direct_convt_kernel, dim3((npix + block - 1) / block, a.O, a.N), dim3(block), 0, s, a);
         return (int)hipGetLastError();
     }
