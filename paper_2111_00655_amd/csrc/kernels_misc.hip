@@ -536,7 +536,8 @@ __global__ __launch_bounds__(256) void direct_convt_kernel(DirectConvArgs a) {
 // nine taps of which a phase uses four.  The WK waves of a workgroup share its 64 lanes' positions and split the input channels; they meet in
 // LDS, and each finishes whole rows of pixel pairs.  Bounds: the products at 39 T/s (5 us for 64 -> 3 channels at 32x32, 64 images), and for few images
 // the weights' round trips, one behind the other.  That layer on the fp32 matrix cores and here: 16 images 7.0 and 6.5 us, 32 images
-// 12.0 and 8.7, 64 images 21.2 and 12.6, 256 images 74 and 39; up to eight images the matrix cores are faster (3.8 - 4.9 us).
+// 12.0 and 8.7, 64 images 21.2 and 12.6, 256 images 74 and 38; up to eight images the matrix cores are faster (3.8 - 4.9 us).
+// Error against 64 bits, rms, 0.82 - 0.86 of theirs: a sum is eight chains (five layers of 33 - 256 channels).
 template <int O, int R, int WK>
 __global__ __launch_bounds__(WK * kWave) void few_convt_kernel(DirectConvArgs a, uint32_t items) {
     constexpr uint32_t kOut = 0x80000000u;                   // beyond the buffer: loaded as zero, not stored
