@@ -32,9 +32,10 @@ def data(n, cin, cout, hw, seed):
 
 
 # (images, channels in, out, (height, width), tail): one position; a workgroup's 64 positions exactly, one more; fewer channels than
-# waves, channels that the waves cannot share evenly; more workgroups than compute units (the four-wave kernel on many channels)
+# waves, channels that the waves cannot share evenly; more than 512 workgroups of one position per lane: two, at odd and even heights
 CASES = [(1, 1, 1, (1, 1), ""), (1, 64, 3, (8, 8), "bt"), (1, 33, 3, (5, 13), "bt"), (2, 3, 2, (1, 65), "br"), (1, 40, 4, (7, 9), "ba"),
-         (3, 17, 4, (65, 1), "b"), (1, 100, 1, (16, 16), "bar"), (17, 33, 3, (31, 33), "bt"), (5, 64, 2, (64, 64), "b")]
+         (3, 17, 4, (65, 1), "b"), (1, 100, 1, (16, 16), "bar"), (17, 33, 3, (31, 33), "bt"), (34, 33, 3, (31, 33), "bt"),
+         (35, 5, 4, (31, 33), "ba"), (33, 6, 1, (32, 32), ""), (9, 64, 2, (64, 64), "b")]
 
 
 @pytest.mark.parametrize("n,cin,cout,hw,tail", CASES)
@@ -52,8 +53,9 @@ def test_against_64_bits(n, cin, cout, hw, tail):
     np.testing.assert_array_less(abs(got - ref), 4 * cin * 2.0 ** -24 * mag + 8 * 2.0 ** -24 * (1 + abs(ref)))
 
 
-def test_infinities_stay_where_their_taps_are():
-    x, w, _ = data(2, 5, 3, (4, 6), 8)
+@pytest.mark.parametrize("n,hw", [(2, (4, 6)), (34, (31, 33))])
+def test_infinities_stay_where_their_taps_are(n, hw):
+    x, w, _ = data(n, 5, 3, hw, 8)
     x[0, 2, 0, 0], x[1, 1, 3, 5], w[3, 1, 0, 2], w[4, 2, 3, 3] = np.inf, np.nan, np.inf, -np.inf
     got = run(x, w)
     ref = F.conv_transpose2d(torch.from_numpy(x).double(), torch.from_numpy(w).double(), stride=2, padding=1).numpy()
