@@ -494,3 +494,17 @@ def test_search_windows_of_one_word_and_at_the_edge_of_the_constant_lengths(widt
                 costs[i] = B.COST_INF
         assert s.search(costs, 5) == search.dp(Graph(d), reg, oms, costs, 5)
     s.close()
+
+
+def test_weight_streams_of_split_operand_kernels_fit_one_buffer_descriptor():
+    """A wave of a 32x32 tile reads four taps of every fourth block of 16 channels, 12288 bytes each, through a 31-bit descriptor: 174762 of them
+    fit, and layers with more channels go to the fp32 kernels (with the size taken modulo 2^32 most weights read as zero)."""
+    for blocks, split_operand in ((174762, True), (174763, False), (24 << 14, False)):
+        cin = 64 * blocks
+        d = wl.GraphDesc("long_stream")
+        d.mark_output(d.op("conv2d_transpose", [d.input(np.zeros((1, cin, 1, 1), np.float32)), d.const(np.zeros((cin, 1, 4, 4), np.float32))],
+                           stride=(2, 2), pad=(1, 1)))
+        s = clg.Session(d, [("igemm_r32_sk", P("conv2d_transpose", W, W))], device=None)
+        s.match()
+        assert ("_rfb3_" in s.compile([0]).kernels()[0]["name"]) == split_operand, cin
+        s.close()
