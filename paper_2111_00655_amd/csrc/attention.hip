@@ -21,6 +21,7 @@
 // 6.1 and 5.35; 256 keys 10.5 and 7.8; 389 keys 19.6 and 16.5; 512 keys 23.7 and 18.7.  (Sixteen waves with two column tiles of v per
 // wave took 5.4, 11.2 and 18.4 at 128, 256 and 389 keys.)
 #include <algorithm>
+#include <type_traits>
 
 #include <hip/hip_runtime.h>
 
@@ -62,8 +63,9 @@ constexpr int kCUs = 256;          // compute units of an MI355X
 
 // D16 = head size / 16; MAXT = key tiles per wave (kWaves * MAXT tiles cover the keys); RT = row tiles; CS = column
 // splits of the second product.
-template <int D16, int MAXT, int RT, int CS>
-__global__ __launch_bounds__(kWaves * kWave) void attention_kernel(AttentionArgs a) {
+// R: Ahead (workgroups behind the heads read ahead) or NoAhead.
+template <int D16, int MAXT, int RT, int CS, class R>
+__global__ __launch_bounds__(kWaves * kWave) void attention_kernel(AttentionArgs a, R ra) {
     constexpr int ROWS = kRows * RT, d = D16 * 16, ldr = d + 4;
     constexpr int KS = kWaves / CS, VT = D16 / CS;           // key splits of the second product, column tiles of a wave
     constexpr int VG = MAXT * CS;                            // key tiles of a wave in it
@@ -78,8 +80,11 @@ __global__ __launch_bounds__(kWaves * kWave) void attention_kernel(AttentionArgs
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r = lane & 15, s = lane >> 4;
     const int h = blockIdx.y, q0 = blockIdx.x * ROWS;
-    if (h >= a.B)                                            // a workgroup behind the heads
-        return read_ahead(a.ahead, (blockIdx.x + gridDim.x * (h - a.B)) * (kWaves * kWave) + tid, gridDim.x * (gridDim.y - a.B) * (kWaves * kWave));
+    if constexpr (std::is_same_v<R, Ahead>) {
+        asm volatile("" ::"s"(a.q), "s"(a.k), "s"(a.v), "s"(a.y), "s"(a.Sq), "s"(a.Sk));      // (loaded with a.B, not behind the branch on it)
+        if (h >= a.B)
+            return read_ahead(ra, (blockIdx.x + gridDim.x * (h - a.B)) * (kWaves * kWave) + tid, gridDim.x * (gridDim.y - a.B) * (kWaves * kWave));
+    }
     const int nct = (a.Sk + 15) / 16;                        // key tiles
     const int ldp = nct * 16 + 4;
     const float *Q = a.q + (int64_t)h * a.Sq * d;
@@ -220,22 +225,28 @@ __global__ __launch_bounds__(kWaves * kWave) void attention_kernel(AttentionArgs
     }
 }
 
-template <int D16, int MAXT, int RT, int CS>
-int launch_one(const AttentionArgs &a, hipStream_t s) {
+template <int D16, int MAXT, int RT, int CS, class R>
+int launch_as(const AttentionArgs &a, const R &r, dim3 grid, hipStream_t s) {
     constexpr int ROWS = kRows * RT;
     const size_t lds = (size_t)ROWS * std::max((a.Sk + 15) / 16 * 16 + 4, kWaves / CS * (D16 * 16 + 4)) * sizeof(float);
     if (lds > 64 * 1024) {
         static LdsLimit limit;
-        const hipError_t e = limit.raise((const void *)attention_kernel<D16, MAXT, RT, CS>);
+        const hipError_t e = limit.raise((const void *)attention_kernel<D16, MAXT, RT, CS, R>);
         if (e != hipSuccess) return (int)e;
     }
+    hipLaunchKernelGGL((attention_kernel<D16, MAXT, RT, CS, R>), grid, dim3(kWaves * kWave), lds, s, a, r);
+    return (int)hipGetLastError();
+}
+
+template <int D16, int MAXT, int RT, int CS>
+int launch_one(const AttentionArgs &a, const Ahead *ahead, hipStream_t s) {
+    constexpr int ROWS = kRows * RT;
     const unsigned tiles = (unsigned)((a.Sq + ROWS - 1) / ROWS), own = tiles * (unsigned)a.B;
     // Reading ahead: at most 64 workgroups, last, and only on compute units that have none of the others (one in the way of those
     // made all of BERT-base on 512 rows 7 % slower).
-    const unsigned idle = own < (unsigned)kCUs && a.ahead.n ? std::min((unsigned)kCUs - own, 64u) : 0;
-    const dim3 grid(tiles, (unsigned)a.B + idle / tiles);
-    hipLaunchKernelGGL((attention_kernel<D16, MAXT, RT, CS>), grid, dim3(kWaves * kWave), lds, s, a);
-    return (int)hipGetLastError();
+    const unsigned idle = own < (unsigned)kCUs && ahead && ahead->n ? std::min((unsigned)kCUs - own, 64u) : 0;
+    if (idle / tiles) return launch_as<D16, MAXT, RT, CS>(a, *ahead, dim3(tiles, (unsigned)a.B + idle / tiles), s);
+    return launch_as<D16, MAXT, RT, CS>(a, NoAhead{}, dim3(tiles, (unsigned)a.B), s);
 }
 
 // Up to 128 keys a wave takes one column tile of the result (a short second product: adding eight partial results would be
@@ -244,16 +255,16 @@ int launch_one(const AttentionArgs &a, hipStream_t s) {
 // row tiles, us: 389 keys, heads of 64, 20.4 and 16.5, heads of 32 10.9 and 10.1; 512 keys 23.2 and 18.7).  Heads of 128 have no
 // registers for a second row tile.
 template <int D16>
-int launch_heads(const AttentionArgs &a, hipStream_t s) {
+int launch_heads(const AttentionArgs &a, const Ahead *r, hipStream_t s) {
     const int tiles = (a.Sk + 15) / 16;
     const int64_t groups = (int64_t)((a.Sq + kRows - 1) / kRows) * a.B;
-    if (tiles <= kWaves) return launch_one<D16, 1, 1, D16>(a, s);
-    if (tiles <= 2 * kWaves) return launch_one<D16, 2, 1, 1>(a, s);
+    if (tiles <= kWaves) return launch_one<D16, 1, 1, D16>(a, r, s);
+    if (tiles <= 2 * kWaves) return launch_one<D16, 2, 1, 1>(a, r, s);
     if constexpr (D16 <= 4) {
-        if (tiles <= 3 * kWaves && groups > 2 * kCUs) return launch_one<D16, 3, 2, 1>(a, s);
-        if (tiles > 3 * kWaves && groups > kCUs) return launch_one<D16, 4, 2, 1>(a, s);
+        if (tiles <= 3 * kWaves && groups > 2 * kCUs) return launch_one<D16, 3, 2, 1>(a, r, s);
+        if (tiles > 3 * kWaves && groups > kCUs) return launch_one<D16, 4, 2, 1>(a, r, s);
     }
-    return tiles <= 3 * kWaves ? launch_one<D16, 3, 1, 1>(a, s) : launch_one<D16, 4, 1, 1>(a, s);
+    return tiles <= 3 * kWaves ? launch_one<D16, 3, 1, 1>(a, r, s) : launch_one<D16, 4, 1, 1>(a, r, s);
 }
 
 }  // namespace
@@ -263,12 +274,12 @@ bool attention_shape_ok(const AttentionArgs &a) {
            (a.d == 32 || a.d == 64 || a.d == 128) && (int64_t)a.Sq * a.d < ((int64_t)1 << 31);
 }
 
-int launch_attention(const AttentionArgs &a, void *stream) {
+int launch_attention(const AttentionArgs &a, const Ahead *ahead, void *stream) {
     if (!attention_shape_ok(a)) return (int)hipErrorInvalidValue;
     for (const void *p : {(const void *)a.q, (const void *)a.k})
         if (((uintptr_t)p & 15) != 0) return (int)hipErrorInvalidValue;        // rows are read 16 bytes at a time
     hipStream_t s = (hipStream_t)stream;
-    return a.d == 32 ? launch_heads<2>(a, s) : (a.d == 64 ? launch_heads<4>(a, s) : launch_heads<8>(a, s));
+    return a.d == 32 ? launch_heads<2>(a, ahead, s) : (a.d == 64 ? launch_heads<4>(a, ahead, s) : launch_heads<8>(a, ahead, s));
 }
 
 }  // namespace clg

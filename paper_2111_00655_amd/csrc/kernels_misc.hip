@@ -205,11 +205,16 @@ __global__ __launch_bounds__(256) void rowwise_block_kernel(RowwiseArgs a) {
 // [bias] [residual add] in front (the common form of a fused prologue), or is the sum of two or three
 // gathered table rows (an embedding).  Same arithmetic as above: mean, biased variance of the centred
 // values, scale and shift.  len % 4 == 0, len <= 256 * V4, all pointers 16-byte aligned.
-template <int V4>
-__global__ __launch_bounds__(64) void ln_wave_kernel(RowwiseArgs a, EpiFast ef) {
+// R: Ahead (the first kAheadWaves workgroups read ahead; a constant, so that the others wait for nothing to know that they do not) or NoAhead.
+constexpr int kAheadWaves = 256;
+template <int V4, class R>
+__global__ __launch_bounds__(64) void ln_wave_kernel(RowwiseArgs a, EpiFast ef, R ra) {
     const int lane = threadIdx.x;
-    const int first = gridDim.x - a.rows, row = (int)blockIdx.x - first;
-    if (row < 0) return read_ahead(a.ahead, (uint32_t)(blockIdx.x * kWave + lane), first * kWave);
+    int row = blockIdx.x;
+    if constexpr (std::is_same_v<R, Ahead>) {
+        row -= kAheadWaves;
+        if (row < 0) return read_ahead(ra, (uint32_t)(blockIdx.x * kWave + lane), kAheadWaves * kWave);
+    }
     const int len4 = a.len >> 2;
     const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
     float4 v[V4], t1[V4], t2[V4], ga[V4], be[V4];
@@ -324,20 +329,25 @@ __global__ __launch_bounds__(256) void rowwise_long_kernel(RowwiseArgs a) {
     }
 }
 
-int launch_rowwise(const RowwiseArgs &a, void *stream) {
+template <class R>
+static void launch_ln_wave(const RowwiseArgs &a, const EpiFast &ef, const R &r, int waves, hipStream_t s) {
+    const int v4 = (a.len / 4 + kWave - 1) / kWave;
+    if (v4 <= 1) hipLaunchKernelGGL((ln_wave_kernel<1, R>), dim3(waves), dim3(kWave), 0, s, a, ef, r);
+    else if (v4 <= 2) hipLaunchKernelGGL((ln_wave_kernel<2, R>), dim3(waves), dim3(kWave), 0, s, a, ef, r);
+    else if (v4 <= 4) hipLaunchKernelGGL((ln_wave_kernel<4, R>), dim3(waves), dim3(kWave), 0, s, a, ef, r);
+    else hipLaunchKernelGGL((ln_wave_kernel<8, R>), dim3(waves), dim3(kWave), 0, s, a, ef, r);
+}
+
+int launch_rowwise(const RowwiseArgs &a, const Ahead *ahead, void *stream) {
     const int block = 256, rows_per_block = block / kWave;
     const dim3 grid((a.rows + rows_per_block - 1) / rows_per_block);
     const int items = (a.len + kWave - 1) / kWave;
     hipStream_t s = (hipStream_t)stream;
     EpiFast ef{};
     if (ln_wave_ok(a, &ef)) {                                      // layer norm in one memory round trip
-        const int v4 = (a.len / 4 + kWave - 1) / kWave;
         // (read-ahead waves first, so that theirs are the first loads to leave: behind the rows all of BERT-base, 200 rows, took 797 instead of 785 us)
-        const dim3 waves(a.rows + (a.ahead.n ? 256 : 0));
-        if (v4 <= 1) hipLaunchKernelGGL(ln_wave_kernel<1>, waves, dim3(kWave), 0, s, a, ef);
-        else if (v4 <= 2) hipLaunchKernelGGL(ln_wave_kernel<2>, waves, dim3(kWave), 0, s, a, ef);
-        else if (v4 <= 4) hipLaunchKernelGGL(ln_wave_kernel<4>, waves, dim3(kWave), 0, s, a, ef);
-        else hipLaunchKernelGGL(ln_wave_kernel<8>, waves, dim3(kWave), 0, s, a, ef);
+        if (ahead && ahead->n) launch_ln_wave(a, ef, *ahead, a.rows + kAheadWaves, s);
+        else launch_ln_wave(a, ef, NoAhead{}, a.rows, s);
         return (int)hipGetLastError();
     }
     if (a.n_gather) return (int)hipErrorInvalidValue;              // only the kernel above gathers

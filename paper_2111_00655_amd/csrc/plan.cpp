@@ -682,8 +682,7 @@ int32_t launch_call(const KernelCall &c, const void *a, const void *b, const voi
             k.gid[t] = (const int32_t *)epi_ptrs[3 + t];
         }
         if (k.n_gather) k.x = nullptr;
-        if (ahead) k.ahead = *ahead;
-        err = launch_rowwise(k, stream);
+        err = launch_rowwise(k, ahead, stream);
         break;
     }
     case CALL_ELTWISE: {
@@ -710,8 +709,7 @@ int32_t launch_call(const KernelCall &c, const void *a, const void *b, const voi
     case CALL_ATTENTION: {
         AttentionArgs k = c.att;
         k.q = (const float *)a; k.k = (const float *)b; k.v = (const float *)c3; k.y = (float *)out;
-        if (ahead) k.ahead = *ahead;
-        err = launch_attention(k, stream);
+        err = launch_attention(k, ahead, stream);
         break;
     }
     case CALL_CONCAT: {
