@@ -513,6 +513,12 @@ int32_t clg_plan_measure(clg_plan *plan, const void *const *inputs,
                          const clg_measure_opts *opts, int64_t *ns);
 int32_t clg_plan_num_launches(const clg_plan *plan, size_t *n);
 int32_t clg_plan_region_of(const clg_plan *plan, size_t index, int32_t *region);
+/* Reading ahead: where a plan's packed weights exceed the memory-side cache, layer
+ * norms and attention carry workgroups that read later kernels' weights.  bytes:
+ * packed weights that kernel `index` reads ahead; workgroups: how many of its launch
+ * do it.  Both 0 where it reads nothing ahead. */
+int32_t clg_plan_read_ahead(const clg_plan *plan, size_t index, size_t *bytes,
+                            int32_t *workgroups);
 int32_t clg_search_graph_level(clg_plan *plan, const void *const *inputs,
                                void *const *outputs, void *workspace,
                                size_t workspace_bytes, void *stream,

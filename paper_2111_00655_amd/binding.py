@@ -153,6 +153,7 @@ SYMBOLS = {
     "clg_plan_reads_constant": (C.c_int32, [_P, C.c_int32, _i32p, C.POINTER(C.c_size_t)]),
     "clg_plan_num_launches": (C.c_int32, [_P, C.POINTER(C.c_size_t)]),
     "clg_plan_region_of": (C.c_int32, [_P, C.c_size_t, _i32p]),
+    "clg_plan_read_ahead": (C.c_int32, [_P, C.c_size_t, C.POINTER(C.c_size_t), _i32p]),
     "clg_execute": (C.c_int32, [_P, C.POINTER(_P), C.POINTER(_P), _P, C.c_size_t, _P]),
     "clg_execute_static": (C.c_int32, [_P, C.POINTER(_P), C.POINTER(_P), _P]),
     "clg_execute_timed": (C.c_int32, [_P, C.POINTER(_P), C.POINTER(_P), _P, C.c_size_t, _P, _i64p, C.c_size_t]),
@@ -535,6 +536,13 @@ def clg_plan_region_of(plan, index):
     r = C.c_int32(0)
     _check(lib().clg_plan_region_of(plan, int(index), C.byref(r)))
     return r.value
+
+
+def clg_plan_read_ahead(plan, index):
+    """(bytes of later kernels' packed weights that the kernel reads ahead, workgroups that do it)."""
+    nbytes, groups = C.c_size_t(0), C.c_int32(0)
+    _check(lib().clg_plan_read_ahead(plan, int(index), C.byref(nbytes), C.byref(groups)))
+    return nbytes.value, groups.value
 
 
 STATIC_WORKSPACE_BYTES = 32 << 20

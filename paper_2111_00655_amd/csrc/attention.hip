@@ -239,32 +239,23 @@ int launch_as(const AttentionArgs &a, const R &r, dim3 grid, hipStream_t s) {
 }
 
 template <int D16, int MAXT, int RT, int CS>
-int launch_one(const AttentionArgs &a, const Ahead *ahead, hipStream_t s) {
-    constexpr int ROWS = kRows * RT;
-    const unsigned tiles = (unsigned)((a.Sq + ROWS - 1) / ROWS), own = tiles * (unsigned)a.B;
-    // Reading ahead: at most 64 workgroups, last, and only on compute units that have none of the others (one in the way of those
-    // made all of BERT-base on 512 rows 7 % slower).
-    const unsigned idle = own < (unsigned)kCUs && ahead && ahead->n ? std::min((unsigned)kCUs - own, 64u) : 0;
-    if (idle / tiles) return launch_as<D16, MAXT, RT, CS>(a, *ahead, dim3(tiles, (unsigned)a.B + idle / tiles), s);
-    return launch_as<D16, MAXT, RT, CS>(a, NoAhead{}, dim3(tiles, (unsigned)a.B), s);
+int launch_one(const AttentionArgs &a, const AttentionGrid &g, const Ahead *ahead, hipStream_t s) {
+    const dim3 grid((unsigned)g.tiles, (unsigned)a.B);
+    if (ahead && ahead->n && g.spare) return launch_as<D16, MAXT, RT, CS>(a, *ahead, dim3(grid.x, grid.y + (unsigned)(g.spare / g.tiles)), s);
+    return launch_as<D16, MAXT, RT, CS>(a, NoAhead{}, grid, s);
 }
 
 // Up to 128 keys a wave takes one column tile of the result (a short second product: adding eight partial results would be
-// the longer part); beyond, all columns of its own keys.  From 385 keys on a compute unit's registers hold one workgroup, below two:
-// more workgroups than that would be a second round, and two row tiles share each load of k and v (twelve heads, one and two
-// row tiles, us: 389 keys, heads of 64, 20.4 and 16.5, heads of 32 10.9 and 10.1; 512 keys 23.2 and 18.7).  Heads of 128 have no
-// registers for a second row tile.
+// the longer part); beyond, all columns of its own keys.
 template <int D16>
 int launch_heads(const AttentionArgs &a, const Ahead *r, hipStream_t s) {
     const int tiles = (a.Sk + 15) / 16;
-    const int64_t groups = (int64_t)((a.Sq + kRows - 1) / kRows) * a.B;
-    if (tiles <= kWaves) return launch_one<D16, 1, 1, D16>(a, r, s);
-    if (tiles <= 2 * kWaves) return launch_one<D16, 2, 1, 1>(a, r, s);
-    if constexpr (D16 <= 4) {
-        if (tiles <= 3 * kWaves && groups > 2 * kCUs) return launch_one<D16, 3, 2, 1>(a, r, s);
-        if (tiles > 3 * kWaves && groups > kCUs) return launch_one<D16, 4, 2, 1>(a, r, s);
-    }
-    return tiles <= 3 * kWaves ? launch_one<D16, 3, 1, 1>(a, r, s) : launch_one<D16, 4, 1, 1>(a, r, s);
+    const AttentionGrid g = attention_grid(a);
+    if (tiles <= kWaves) return launch_one<D16, 1, 1, D16>(a, g, r, s);
+    if (tiles <= 2 * kWaves) return launch_one<D16, 2, 1, 1>(a, g, r, s);
+    if constexpr (D16 <= 4)
+        if (g.rows == 2 * kRows) return tiles <= 3 * kWaves ? launch_one<D16, 3, 2, 1>(a, g, r, s) : launch_one<D16, 4, 2, 1>(a, g, r, s);
+    return tiles <= 3 * kWaves ? launch_one<D16, 3, 1, 1>(a, g, r, s) : launch_one<D16, 4, 1, 1>(a, g, r, s);
 }
 
 }  // namespace
@@ -272,6 +263,23 @@ int launch_heads(const AttentionArgs &a, const Ahead *r, hipStream_t s) {
 bool attention_shape_ok(const AttentionArgs &a) {
     return a.B >= 1 && a.B <= 65535 && a.Sq >= 1 && a.Sk >= 1 && a.Sk <= kMaxKeys &&
            (a.d == 32 || a.d == 64 || a.d == 128) && (int64_t)a.Sq * a.d < ((int64_t)1 << 31);
+}
+
+// From 385 keys on a compute unit's registers hold one workgroup, below two: more workgroups than that would be a second
+// round, and two row tiles share each load of k and v (twelve heads, one and two row tiles, us: 389 keys, heads of 64, 20.4 and
+// 16.5, heads of 32 10.9 and 10.1; 512 keys 23.2 and 18.7).  Heads of 128 have no registers for a second row tile.
+// Reading ahead: at most 64 workgroups, last, in whole rows of the grid, and only on compute units that have none of the others (one in
+// the way of those made all of BERT-base on 512 rows 7 % slower).
+AttentionGrid attention_grid(const AttentionArgs &a) {
+    const int keys = (a.Sk + 15) / 16;                       // key tiles
+    const int64_t groups = (int64_t)((a.Sq + kRows - 1) / kRows) * a.B;
+    const bool two = a.d <= 64 && keys > 2 * kWaves && groups > (keys <= 3 * kWaves ? 2 : 1) * kCUs;
+    AttentionGrid g;
+    g.rows = two ? 2 * kRows : kRows;
+    g.tiles = (a.Sq + g.rows - 1) / g.rows;
+    const int64_t own = (int64_t)g.tiles * a.B;
+    g.spare = own < kCUs ? (int32_t)std::min<int64_t>(kCUs - own, 64) / g.tiles * g.tiles : 0;
+    return g;
 }
 
 int launch_attention(const AttentionArgs &a, const Ahead *ahead, void *stream) {

@@ -604,6 +604,18 @@ int32_t clg_plan_num_launches(const clg_plan *plan, size_t *n) {
     return CLG_OK;
 }
 
+int32_t clg_plan_read_ahead(const clg_plan *plan, size_t index, size_t *bytes, int32_t *workgroups) {
+    NEED(plan); NEED(bytes); NEED(workgroups);
+    const Plan &p = plan->p;
+    if (index >= p.calls.size()) return fail(CLG_UNKNOWN_ID, "kernel index %zu", index);
+    *bytes = 0;
+    *workgroups = 0;
+    if (p.ahead.empty() || p.ahead[index].empty()) return CLG_OK;
+    for (int32_t j : p.ahead[index]) *bytes += p.calls[(size_t)j].pack_bytes;
+    *workgroups = p.calls[index].kind == CALL_ATTENTION ? attention_grid(p.calls[index].att).spare : kAheadWaves;
+    return CLG_OK;
+}
+
 int32_t clg_plan_region_of(const clg_plan *plan, size_t index, int32_t *region) {
     NEED(plan); NEED(region);
     if (index >= plan->p.calls.size()) return fail(CLG_UNKNOWN_ID, "kernel index %zu", index);

@@ -244,6 +244,9 @@ struct AttentionArgs {
 };
 static_assert(sizeof(AttentionArgs) <= 64, "a kernel's arguments are its first memory round trip: one cache line");
 bool attention_shape_ok(const AttentionArgs &a);       // d in {32, 64, 128}, Sk <= 512
+// The grid of one launch: `rows` query rows per workgroup, `tiles` workgroups per head, `spare` workgroups that can read ahead.
+struct AttentionGrid { int32_t rows, tiles, spare; };
+AttentionGrid attention_grid(const AttentionArgs &a);
 int launch_attention(const AttentionArgs &a, const Ahead *ahead, void *stream);       // ahead: null or what to read ahead
 
 // ---- contractions on the bf16 matrix cores, operands split exactly into three bf16 values (gemm_b3.h) ----
@@ -333,7 +336,8 @@ struct RowwiseArgs {
     const float *tab[3];
     const int32_t *gid[3];
 };
-bool rowwise_reads_ahead(const RowwiseArgs &a);        // the shape is that kernel's (pointer alignment aside)
+constexpr int kAheadWaves = 256;           // read-ahead workgroups (one wave each) of a layer norm
+bool rowwise_reads_ahead(const RowwiseArgs &a);        // shape and prologue are the one-round-trip layer norm's (pointer alignment aside)
 
 // ---- elementwise chain / gather --------------------------------------------------------------
 struct EltwiseArgs {

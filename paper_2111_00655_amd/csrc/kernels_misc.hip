@@ -206,7 +206,6 @@ __global__ __launch_bounds__(256) void rowwise_block_kernel(RowwiseArgs a) {
 // gathered table rows (an embedding).  Same arithmetic as above: mean, biased variance of the centred
 // values, scale and shift.  len % 4 == 0, len <= 256 * V4, all pointers 16-byte aligned.
 // R: Ahead (the first kAheadWaves workgroups read ahead; a constant, so that the others wait for nothing to know that they do not) or NoAhead.
-constexpr int kAheadWaves = 256;
 template <int V4, class R>
 __global__ __launch_bounds__(64) void ln_wave_kernel(RowwiseArgs a, EpiFast ef, R ra) {
     const int lane = threadIdx.x;
@@ -274,28 +273,36 @@ __global__ __launch_bounds__(64) void ln_wave_kernel(RowwiseArgs a, EpiFast ef, 
     }
 }
 
-bool rowwise_reads_ahead(const RowwiseArgs &a) {
-    return a.mode == 1 && a.len % 4 == 0 && a.len <= 256 * 8 && a.len >= 64 && a.rows <= 4096;
-}
-
-// Whether the one-round-trip layer norm takes these arguments; fills *ef with the prologue's common form.
-static bool ln_wave_ok(const RowwiseArgs &a, EpiFast *ef) {
-    if (!rowwise_reads_ahead(a)) return false;
-    auto al = [](const void *p) { return ((uintptr_t)p & 15) == 0; };
-    if (!al(a.y) || !al(a.gamma) || !al(a.beta)) return false;
+// Whether the one-round-trip layer norm takes the shape and the prologue; fills *ef with the prologue's common form.
+static bool ln_wave_shape_ok(const RowwiseArgs &a, EpiFast *ef) {
+    if (a.mode != 1 || a.len % 4 || a.len > 256 * 8 || a.len < 64 || a.rows > 4096) return false;
     ef->flags = 0;
     if (a.n_gather) {
         for (int k = 0; k < a.n_gather; ++k)
-            if (!al(a.tab[k]) || a.tab_rows[k] < 1) return false;
+            if (a.tab_rows[k] < 1) return false;
         return a.n_gather == 2 || a.n_gather == 3;
     }
     *ef = make_epi_fast(a.pro);
     if (ef->flags & ~(EF_BIAS | EF_ADD)) return false;
-    if (ef->flags & EF_BIAS) {
-        if (a.pro.bias_inner != 1 || a.pro.bias_c != a.len || !al(ef->bias)) return false;
+    return !(ef->flags & EF_BIAS) || (a.pro.bias_inner == 1 && a.pro.bias_c == a.len);
+}
+
+// ... and, with every pointer bound, the alignment.
+static bool ln_wave_ok(const RowwiseArgs &a, EpiFast *ef) {
+    if (!ln_wave_shape_ok(a, ef)) return false;
+    auto al = [](const void *p) { return ((uintptr_t)p & 15) == 0; };
+    if (!al(a.y) || !al(a.gamma) || !al(a.beta)) return false;
+    if (a.n_gather) {
+        for (int k = 0; k < a.n_gather; ++k)
+            if (!al(a.tab[k])) return false;
+        return true;
     }
-    if ((ef->flags & EF_ADD) && !al(ef->add)) return false;
-    return al(a.x);
+    return al(a.x) && (!(ef->flags & EF_BIAS) || al(ef->bias)) && (!(ef->flags & EF_ADD) || al(ef->add));
+}
+
+bool rowwise_reads_ahead(const RowwiseArgs &a) {
+    EpiFast ef{};
+    return ln_wave_shape_ok(a, &ef);
 }
 
 // Rows longer than 64 * 32: same arithmetic, the row is re-read per pass.

@@ -222,8 +222,11 @@ size_t plan_num_launches(const Plan &p) {
 // after pass; a larger one streams them from HBM (BERT-base: 340 MB), and each of its dense layers then takes 1.3 - 3.5 us longer than with its
 // weights in that cache.  Layer norms and attention leave most of the chip idle: workgroups of theirs read (64 bytes apart, nothing is
 // kept) what later kernels will stream.
-//  * How much: attention 2.4 MB per microsecond it takes itself (4 + flops / 37 GFLOP per ms on 12 heads of 64), a layer norm 16 MB, which make it
-//    1 us longer; more makes it longer than the dense layers gain (BERT-base, 389 rows: 14 MB more in a layer norm 1102 instead of 1077 us).
+//  * How much: a layer norm 16 MB, which make it 1 us longer; more makes it longer than the dense layers gain (BERT-base, 389 rows: 14 MB more in a
+//    layer norm 1102 instead of 1077 us).  Attention 2.4 MB per microsecond that it takes itself, and no more than 61 KB per read-ahead workgroup of its
+//    launch (17.7 MB in 8 us: on 36 workgroups, 288 rows, 853 us, with 3.5 MB instead 873; on 19, 304 rows, 948 and 879).  It takes 4 us, and the
+//    products of a workgroup at 270 GFLOP per second (heads of 64, measured alone and by this: 128 keys 5.4 and 5.9 us, 256 7.8 and 7.9, 389 16.5 and
+//    15.8, 512 18.7 and 19.5).
 //  * Where: attention with room for all that lies before the kernel after next that could read ahead takes all of it (389 rows: 1077 us, with
 //    a share in the layer norm 1099, without any 1123); otherwise the nearest one before that has room (256 rows: 795, attention first 820, without 864).
 //  * From 96 rows on: below, everything takes a few microseconds and reading ahead prolongs what it hides in (us without and with, all of BERT-base: 16 rows 435
@@ -240,8 +243,10 @@ static void plan_read_ahead(Plan *plan) {
     std::vector<int64_t> room(nc, 0);
     for (size_t i = 0; i < nc; ++i) {
         const KernelCall &c = plan->calls[i];
-        const AttentionArgs &a = c.att;
-        if (c.kind == CALL_ATTENTION && a.Sq >= kRows) room[i] = (int64_t)(2.4e6 * (4.0 + 4.0 * a.B * a.Sq * a.Sk * a.d / 37e6));
+        if (c.kind == CALL_ATTENTION && c.att.Sq >= kRows) {
+            const AttentionGrid grid = attention_grid(c.att);
+            room[i] = (int64_t)(std::min(2.4e6, 61e3 * grid.spare) * (4.0 + 4.0 * grid.rows * c.att.Sk * c.att.d / 270e3));
+        }
         if (c.kind == CALL_ROWWISE && c.row.rows >= kRows && rowwise_reads_ahead(c.row)) room[i] = 16000000;
     }
     std::vector<char> placed(nc, 0);
@@ -450,8 +455,8 @@ int32_t compile_plan(Context &ctx, Graph &g, const int32_t *ids, size_t n, Plan 
             }
         if (any && hipStreamSynchronize(nullptr) != hipSuccess)
             return fail(CLG_HIP_ERROR, "weight packing failed: %s", hipGetErrorString(hipGetLastError()));
-        plan_read_ahead(plan);
     }
+    plan_read_ahead(plan);
     return CLG_OK;
 }
 
@@ -788,13 +793,19 @@ int32_t execute_plan(Plan &p, const void *const *inputs, void *const *outputs, v
     };
     const bool fuse = p.max_lanes <= 1 && !p.handed.empty() && !p.regions.empty();
     Ahead ahead;
+    auto in_region = [&](size_t j) {                   // launched with a sibling: reads the region's copy of the weights
+        if (!fuse || p.region_of[j] < 0 || !p.handed[j]) return false;
+        int n = 0;
+        for (int32_t m : p.regions[(size_t)p.region_of[j]].members) n += p.handed[(size_t)m] ? 1 : 0;
+        return n >= 2;
+    };
     auto ahead_of = [&](size_t i, Ahead *out) -> const Ahead * {
         if (p.ahead.empty() || p.ahead[i].empty()) return nullptr;
         out->n = 0;
         for (int32_t j : p.ahead[i]) {
             const void *w = p.packed[(size_t)j];
             size_t bytes = p.calls[(size_t)j].pack_bytes;
-            if (fuse && p.region_of[(size_t)j] >= 0 && p.handed[(size_t)j]) {
+            if (in_region((size_t)j)) {
                 const Region &r = p.regions[(size_t)p.region_of[(size_t)j]];
                 for (size_t k = 0; k < r.members.size(); ++k)
                     if (r.members[k] == j && r.packed[k]) {

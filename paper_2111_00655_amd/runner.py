@@ -142,6 +142,10 @@ class Plan:
         """Region index of every kernel (-1: in none)."""
         return [B.clg_plan_region_of(self.h, i) for i in range(self.n_kernels)]
 
+    def read_ahead(self):
+        """(bytes, workgroups) of every kernel: the later kernels' packed weights that it reads ahead."""
+        return [B.clg_plan_read_ahead(self.h, i) for i in range(self.n_kernels)]
+
     def set_lanes(self, lanes):
         B.clg_plan_set_lanes(self.h, lanes)
         return self

@@ -508,3 +508,70 @@ def test_weight_streams_of_split_operand_kernels_fit_one_buffer_descriptor():
         s.match()
         assert ("_rfb3_" in s.compile([0]).kernels()[0]["name"]) == split_operand, cin
         s.close()
+
+
+def _encoder(rows, heads, layers, eps_tail=()):
+    """A transformer encoder with heads of 64 (weights that nobody reads: the plan is made on the host).  eps_tail: operators between a residual
+    add and its layer norm."""
+    hid = 64 * heads
+    d = wl.GraphDesc("encoder")
+    const = lambda *shape: d.const(np.zeros(shape, np.float32))
+    x = d.input(np.zeros((rows, hid), np.float32))
+
+    def dense(t, n_in, n_out, act=None):
+        y = d.op("bias_add", [d.op("dense", [t, const(n_out, n_in)]), const(n_out)], axis=-1)
+        return d.op(act, [y]) if act else y
+
+    def norm(t, residual):
+        y = d.op("add", [t, residual])
+        for op in eps_tail:
+            y = d.op(op, [y])
+        return d.op("layer_norm", [y, const(hid), const(hid)], eps=1e-12)
+
+    for _ in range(layers):
+        q, k, v = (d.op("transpose", [d.op("reshape", [dense(x, hid, hid)], dims=(rows, heads, 64))], dims=(1, 0, 2)) for _ in range(3))
+        p = d.op("softmax", [d.op("mul_scalar", [d.op("batch_matmul", [q, k], transpose_b=True)], scalar=0.125)])
+        c = d.op("transpose", [d.op("batch_matmul", [p, v], transpose_b=False)], dims=(1, 0, 2))
+        x = norm(dense(d.op("reshape", [c], dims=(rows, hid)), hid, hid), x)
+        x = norm(dense(dense(x, hid, 4 * hid, "gelu"), 4 * hid, hid), x)
+    d.mark_output(x)
+    return d
+
+
+def _read_ahead(d, extra=()):
+    s = clg.Session(d, wl.default_registry(("igemm_r16_sk",), attention=True) + list(extra), device=None)
+    n = len(s.match())
+    plan = s.compile(s.search([1] * n, 0)[1])                # equal costs: the fewest kernels
+    out = [(k["name"], *ra) for k, ra in zip(plan.kernels(), plan.read_ahead())]
+    s.close()
+    return out
+
+
+@pytest.mark.parametrize("heads,layers", [(8, 24), (12, 12), (16, 8)])
+def test_every_weight_that_is_read_ahead_has_workgroups_that_read_it(heads, layers):
+    """Lengths from where nothing is read ahead to where attention covers the compute units, in one and two row tiles: what a kernel is given to
+    read, its launch has workgroups for, and where attention has none the layer norms take what they have room for."""
+    weights = layers * 12 * (64 * heads) ** 2
+    for rows in (64, 95, 96, 128, 200, 256, 273, 288, 304, 305, 320, 334, 335, 352, 360, 384, 385, 389, 448, 512):
+        ks = _read_ahead(_encoder(rows, heads, layers))
+        assert sum("attention" in n for n, _, _ in ks) == layers and sum("layer_norm" in n for n, _, _ in ks) == 2 * layers, ks
+        for name, nbytes, groups in ks:
+            assert (nbytes > 0) == (groups > 0), (rows, name, nbytes, groups)
+            assert not nbytes or "attention" in name or "layer_norm" in name, name
+        got = sum(b for _, b, _ in ks)
+        if rows < 96:
+            assert got == 0, rows
+            continue
+        # fp32 kernels (below 160 rows) pack four bytes per weight, the split-operand ones six.  A layer norm takes 16 MB: at 512 wide all that lies
+        # between it and the next one, at 768 all but one feed-forward matrix of a layer, at 1024 the four projections.
+        assert got > {8: 0.9, 12: 0.6, 16: 0.25}[heads] * (6 if rows >= 160 else 4) * weights, (rows, got)
+
+
+def test_a_layer_norm_that_is_another_kernel_is_given_nothing_to_read_ahead():
+    """A relu in a layer norm's prologue keeps it from the kernel that reads ahead."""
+    extra = [("rowwise", P("layer_norm", P("relu", P("add", W, W)), W, W))]
+    for tail in ((), ("relu",)):
+        ks = _read_ahead(_encoder(384, 12, 12, tail), extra)
+        norms = [b for n, b, _ in ks if "layer_norm" in n]
+        assert len(norms) == 24 and sum("layer_norm_pro2" in n for n, _, _ in ks) == 24, ks         # [bias, add], or [add, relu]
+        assert all(b == 0 for b in norms) == bool(tail), ks
