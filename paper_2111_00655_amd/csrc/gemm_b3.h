@@ -324,9 +324,11 @@ __device__ __forceinline__ void b3_body(const B3Args &p) {
         } else if constexpr (DEPTH) {
             // block: (16 channels, depth tap); a plane before or behind the volume is zero
             const int blk = min(st * SC + c16l[u], p.nC - 1), c16 = (int)b3_div((uint32_t)blk, p.d_kd), kd = blk - c16 * p.KD;
-            const uint32_t so = (uint32_t)(c16 * 16 * p.cs) * 4;
-            const bool in = off[u] != kB3Out && st * SC + c16l[u] < blk_end && (uint32_t)(idu[u] + kd) < (uint32_t)p.D;
-            const uint32_t o = in ? off[u] + so + (uint32_t)(kd * p.HW * 4) : kB3Out;      // (off may lie in front of the volume)
+            // (the offset is masked, not selected, so that the scalar work in front of it stays out of a branch.  A slot of padding stays beyond the
+            // buffer; off may lie in front of the volume, the sum is in it where the plane is)
+            const uint32_t so = (uint32_t)(c16 * 16 * p.cs + kd * p.HW) * 4;
+            const bool in = st * SC + c16l[u] < blk_end && (uint32_t)(idu[u] + kd) < (uint32_t)p.D;
+            const uint32_t o = (off[u] + so) | (in ? 0u : kB3Out);
 #pragma unroll
             for (int i = 0; i < 8; ++i)
                 xv[u][i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsrc, (int)o, i * p.cs * 4, 0));
