@@ -216,6 +216,8 @@ bool b3_resolve(const GemmArgs &g, int tile, int epi_flags, int n_cus, bool spli
         }
         a.Cf = cin;
         a.nC = ceil_div(cin, 16) * a.KD;
+        // A slot of padding (kB3Out) stays beyond the buffer whatever channel block and depth tap are added to it: their offset has 31 bits too.
+        if (depth && (int64_t)(ceil_div(cin, 16) - 1) * 16 * a.cs + (int64_t)(a.KD - 1) * a.HW >= ((int64_t)1 << 29)) return false;
         // slot geometry: with one filter row (column) only the rows (columns) that are read get slots
         a.ys = a.KHe == 1 ? she : 1;
         a.ly = a.KHe == 1 ? 1 : she;

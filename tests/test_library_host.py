@@ -510,6 +510,19 @@ def test_weight_streams_of_split_operand_kernels_fit_one_buffer_descriptor():
         s.close()
 
 
+@pytest.mark.parametrize("cin,width,split_operand", [(72, 448, True), (72, 449, False), (64, 449, True)])
+def test_depth_taps_behind_a_buffer_of_two_gigabytes(cin, width, split_operand):
+    """Ten depth taps over one plane: the last block of 16 channels and the last tap lie 73 planes behind the first (57 with 64 channels).  From 2^29 values on
+    that offset, added to the mark of a padded slot, wraps around 2^32 to the front of the input, and the fp32 kernels run the layer."""
+    d = wl.GraphDesc("deep_filter")
+    d.mark_output(d.op("conv3d", [d.input(np.zeros((1, cin, 1, 16384, width), np.float32)), d.const(np.zeros((1, cin, 10, 3, 3), np.float32))],
+                       stride=(1, 1, 1), pad=(9, 1, 1)))
+    s = clg.Session(d, [("igemm_r32_sk", P("conv3d", W, W))], device=None)
+    s.match()
+    assert ("_rfb3_" in s.compile([0]).kernels()[0]["name"]) == split_operand
+    s.close()
+
+
 def _encoder(rows, heads, layers, eps_tail=()):
     """A transformer encoder with heads of 64 (weights that nobody reads: the plan is made on the host).  eps_tail: operators between a residual
     add and its layer norm."""
