@@ -523,6 +523,20 @@ def test_depth_taps_behind_a_buffer_of_two_gigabytes(cin, width, split_operand):
     s.close()
 
 
+@pytest.mark.parametrize("images,channels,plane,split_operand", [(1, 512, (2, 2), False), (2, 512, (2, 2), False), (1, 512, (1, 9), True), (1, 256, (2, 2), True)])
+def test_convolutions_of_few_positions_and_many_weights_stay_on_the_fp32_kernels(images, channels, plane, split_operand):
+    """Eight positions, nine, and fewer weights (16 MB as fp32 is the limit)."""
+    d = wl.GraphDesc("few_positions")
+    d.mark_output(d.op("conv3d", [d.input(np.zeros((images, channels, 1) + plane, np.float32)), d.const(np.zeros((channels, channels, 3, 3, 3), np.float32))],
+                       stride=(1, 1, 1), pad=(1, 1, 1)))
+    for be in ("igemm_r16_sk", "igemm_r16_sk_w4", "igemm_r32_sk"):
+        s = clg.Session(d, [(be, P("conv3d", W, W))], device=None)
+        s.match()
+        name = s.compile([0]).kernels()[0]["name"]
+        s.close()
+        assert "_rfb3_" not in name if not split_operand else be != "igemm_r16_sk" or "_rfb3_" in name, (be, name)
+
+
 def _encoder(rows, heads, layers, eps_tail=()):
     """A transformer encoder with heads of 64 (weights that nobody reads: the plan is made on the host).  eps_tail: operators between a residual
     add and its layer norm."""
