@@ -5,7 +5,8 @@
 // bound the register-fed kernel: 7x7 stride 2, 3 -> 64 channels at 224x224 and batch 32 took 206 us, for
 // 7.6 GFLOP and 122 MB.  Here k runs along an input row: for a fixed (channel, depth tap, filter row)
 // the eight values x[2 ow - pad .. + 7] are eight consecutive bf16 in LDS, which a lane reads with one
-// 16-byte load at a 4-byte aligned address; columns past the filter's width are cleared.
+// 16-byte load at a 4-byte aligned address; columns past the filter's width meet zero weights (an infinity or NaN among
+// them makes the result a NaN, and results that are not finite are computed again as a fp32 chain of the filter's own columns).
 // An MFMA takes two such rows (one per lane half).  A workgroup copies the input patch of its 128 (256) output
 // pixels once, split into the three planes; the patch is 2.5 times its output in values, so the split costs
 // little, and the kernel is bound by its stores (64 channels of output per 3 of input).
@@ -124,7 +125,7 @@ __global__ __launch_bounds__(256, 2) void b3_first_kernel(B3Args p) {
         if (st + 1 < p.stages) load(st + 1);
         lds_barrier();
         const uint32_t *P0 = b3_patch + buf * 3 * PL;
-        // filter rows 2 q and 2 q + 1 of the stage, as (plane, row); past the last one: cleared, as its weights are
+        // filter rows 2 q and 2 q + 1 of the stage, as (plane, row); past the last one: the last one again, with zero weights
         int kh0 = 0, r0 = 0, kh1 = 1, r1 = 1;
         if (p.KHe == 1) {
             kh1 = 0;
@@ -328,7 +329,7 @@ bool first_resolve(const GemmArgs &g, B3Args *out) {
         !b3_set_div(&a.d_do, a.DO, a.Nimg) || !b3_set_div(&a.d_pw, a.pxw / 2, pairs + 12 * 256) || !b3_set_div(&a.d_rpi, a.prow, pairs + 12 * 256) ||
         !b3_set_div(&a.d_tw, a.TW, bn))
         return false;
-    a.pack_steps = (int64_t)a.mtiles * a.stages * a.steps + kRing - 1;      // the ring reads ahead
+    a.pack_steps = (int64_t)a.mtiles * a.stages * a.steps;
     *out = a;
     return true;
 }
