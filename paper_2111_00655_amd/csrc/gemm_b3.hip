@@ -117,7 +117,7 @@ bool place(B3Args *a, int tile, int split_cus = 0) {
     // A wave's weights of its stages lie behind one buffer descriptor (11 million input channels of a 4x4 transposed filter are the first
     // that do not fit).
     ok = ok && (int64_t)a->stages_per * cw * a->taps * (3 * kWave * 16) < ((int64_t)1 << 31);
-    a->pack_steps = (int64_t)a->mtiles * ts.wk * a->stages * cw * a->taps;          // (no kernel reads behind its stream)
+    a->pack_steps = (int64_t)a->mtiles * ts.wk * a->stages * cw * a->taps + 4;      // (and four steps of zeros; no kernel reads behind its stream)
     return ok;
 }
 

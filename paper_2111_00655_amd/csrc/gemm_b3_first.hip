@@ -329,7 +329,7 @@ bool first_resolve(const GemmArgs &g, B3Args *out) {
         !b3_set_div(&a.d_do, a.DO, a.Nimg) || !b3_set_div(&a.d_pw, a.pxw / 2, pairs + 12 * 256) || !b3_set_div(&a.d_rpi, a.prow, pairs + 12 * 256) ||
         !b3_set_div(&a.d_tw, a.TW, bn))
         return false;
-    a.pack_steps = (int64_t)a.mtiles * a.stages * a.steps;
+    a.pack_steps = (int64_t)a.mtiles * a.stages * a.steps + kRing - 1;      // (and kRing - 1 steps of zeros; the kernel does not read behind its stream)
     *out = a;
     return true;
 }

@@ -48,15 +48,12 @@ def test_global_average(hw):
     np.testing.assert_allclose(got, ref, rtol=0, atol=4 * 2.0 ** -24 * (hw[0] * hw[1]) ** 0.5)
 
 
-@pytest.mark.parametrize("avg", [False, True], ids=["max", "avg"])
-@pytest.mark.parametrize("case", WINDOWS, ids=str)
+@pytest.mark.parametrize("case,avg", [(c, avg) for c in WINDOWS for avg in (False, True) if not (avg and len(c[0]) == 5)], ids=str)
 def test_windows_of_values_that_are_not_finite(case, avg):
     """A maximum passes over NaN (nothing but NaN: minus infinity) and takes infinities and the lowest float as they are; an average is of the pixels inside the image,
     whatever lies behind the edge."""
     shape, k, st, pad = case
     n = len(shape) - 2
-    if avg and n == 3:
-        pytest.skip("no 3-D average window pool")
     r = np.random.default_rng(len(shape) * 100 + k)
     lowest = np.finfo(np.float32).min
     xv = r.choice(np.array([-np.inf, lowest, -1, 2, np.nan] + ([] if avg else [np.inf]), np.float32), shape, p=[.2, .2, .3, .2, .1] if avg else [.3, .2, .1, .05, .3, .05])
