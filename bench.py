@@ -34,13 +34,13 @@ VARIANTS = ("igemm", "igemm_s", "igemm_s8", "igemm_s16", "igemm_m", "igemm_l", "
 
 # HBM-side traffic of the MFMA kernels of one step, from two rocprofv3 --pmc runs of this file with
 # --passes-only (FETCH_SIZE, then WRITE_SIZE; KiB per dispatch, summed over the MFMA-kernel dispatches and divided
-# by the warm-up + steps passes of the run: ResNet-50 57 such dispatches per pass - 52 convolution launches, one of
-# them a region of two, and 5 split-K reductions; BERT-base 60, attention with the weights that it reads ahead).  Scale factors from the 256 MiB plain device
+# by the warm-up + steps passes of the run: ResNet-50 55 such dispatches per pass - 52 convolution launches, one of
+# them a region of two, and 3 split-K reductions; BERT-base 60, attention with the weights that it reads ahead).  Scale factors from the 256 MiB plain device
 # copy of --calib-copy in the same runs: WRITE_SIZE read 262144.0 KiB for it (factor 1.000), FETCH_SIZE
 # 131083.5 KiB (factor 2.000).  profiles/*_pmc_summary.txt hold the runs.  The figures hold for the kernel sources
 # they were taken with; after any change to them `traffic` is reported as null.
-TRAFFIC = {"resnet50": {"sources": "6192ae5e80b38571", "fetch_bytes": 300.66e6, "write_bytes": 45.80e6},
-           "bert_base": {"sources": "6192ae5e80b38571", "fetch_bytes": 830.75e6, "write_bytes": 47.19e6}}
+TRAFFIC = {"resnet50": {"sources": "baee1fe07b0e5b27", "fetch_bytes": 300.14e6, "write_bytes": 45.40e6},
+           "bert_base": {"sources": "baee1fe07b0e5b27", "fetch_bytes": 830.75e6, "write_bytes": 47.19e6}}
 
 
 def kernel_sources_fingerprint():
