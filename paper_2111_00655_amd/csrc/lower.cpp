@@ -289,10 +289,11 @@ bool lower_b3(const Context &ctx, const Backend &be, const GemmArgs &a, const Ep
     // 13.0, 20.8 and 20.8; 192 rows 10.4 and 10.2, 16.4 and 16.5, 21.6 and 21.7; 224 rows 10.3 and 10.3, 17.4 and 17.3, 23.2 and 21.2)
     if (a.mode == GM_NT && a.M < kB3DenseRows) return false;
     // A convolution with eight output positions or fewer and many weights takes the time of its weights, half as many bytes again here, and a tile
-    // stages and multiplies rows that no image has.  Alone, over and over, it is 3 - 4 % faster all the same, so the search took it.  3x3x3 512 -> 512 in
-    // a chain of four, us here and on the fp32 kernels: 1x2x2 18.1 and 17.8, 1x3x3 16.9 and 19.4, 1x4x4 16.9 and 20.2.  All of 3D-ResNet50 with three such
-    // layers, us: 8x64x64 (four positions) 358 and 350, 24x64x64 (eight) 439 and 436, two clips of 8x64x64 (eight) 395 and 392, 8x80x80 (nine)
-    // 390 and 391.  Weights: of layers with 7 MB (256 -> 256) and less the search took none here.
+    // stages and multiplies rows that no image has.  Measured alone, 3x3x3 512 -> 512 on 1x2x2 takes 17.5 us here, 17.4 on the four-wave fp32 kernel of
+    // igemm_r16_sk_w4 and 16.6 on the sixteen-wave one of igemm_r16_sk, which is a candidate only where this one is not.  In a chain of four, us here and on
+    // the fp32 kernels: 1x2x2 18.1 and 17.8, 1x3x3 16.9 and 19.4, 1x4x4 16.9 and 20.2.  All of 3D-ResNet50 with three such layers, us: 8x64x64 (four
+    // positions) 358 and 350, 24x64x64 (eight) 439 and 436, two clips of 8x64x64 (eight) 395 and 392, 8x80x80 (nine) 390 and 391.  Weights: of
+    // layers with 7 MB (256 -> 256) and less the search took none here.
     if (a.mode == GM_CONV && a.N <= 8 && (int64_t)a.M * a.K >= ((int64_t)4 << 20)) return false;
     B3Args b;
     const int flags = epi_fast_flags(epi), tile = b3_tile(ctx, be, a);
