@@ -468,8 +468,10 @@ int32_t clg_evolve(size_t n, const clg_es_opts *opts, const uint32_t *rand,
  *    residual block; thread-per-output kernels (depthwise 3x3 / 5x5 / 7x7
  *    convolutions, window pools, with their fused tails; at most 8 per region)
  *    and one-kernel separable convolutions of one filter size and workgroup
- *    size (at most 4), e.g. the branches of a NasNet cell; the latter two
- *    kinds run unchanged inside a region, bit for bit.  The
+ *    size (at most 4), e.g. the branches of a NasNet cell; and, where they are
+ *    more than the siblings of one kind, all of these kinds and 1x1 convolutions
+ *    together (at most 8).  Thread-per-output kernels and separable convolutions
+ *    run unchanged inside a region, bit for bit.  The
  *    handed-over members of a region, if there are two or more, run as ONE
  *    launch of a kernel that works on several problems at once (all members in
  *    one common tile shape, that of the member with the most flops; members

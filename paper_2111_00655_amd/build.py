@@ -30,7 +30,7 @@ SOURCES = ["graph.cpp", "matcher.cpp", "search.cpp", "lower.cpp", "plan.cpp",
            "profiler.cpp", "rules.cpp", "evolve.cpp", "capi.cpp", "kernels_gemm.hip", "gemm_fast_mm.hip", "gemm_fast_conv.hip",
            "gemm_lean_mm.hip", "gemm_lean_conv.hip", "gemm_rf.hip",
            "gemm_b3.hip", "gemm_b3_point.hip", "gemm_b3_nine.hip", "gemm_b3_depth.hip", "gemm_b3_phase.hip", "gemm_b3_first.hip",
-           "kernels_misc.hip", "sepconv.hip", "attention.hip", "static_ws.hip"]
+           "kernels_misc.hip", "sepconv.hip", "region_mix.hip", "attention.hip", "static_ws.hip"]
 
 BUILD_SAN = os.path.join(HERE, "_build_san")
 LIB_SAN = os.path.join(HERE, "libcollage_mi_san.so")
@@ -39,6 +39,9 @@ SAN_FLAGS = ["-fsanitize=address", "-fsanitize=undefined"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 COMMON = ["-O3", "-std=c++17", "-fPIC", "-Wall", "-Wextra", "-Wno-unused-parameter",
           "-I", INCLUDE, "-I", CSRC]
+# region_mix.hip: the argument block stays in the kernel-argument segment only if the optimiser may look at all its (some 2000) uses, else every
+# lane gets a copy of it in scratch memory
+PER_SOURCE = {"region_mix.hip": ["-mllvm", "-instcombine-max-copied-from-constant-users=10000"]}
 # no packed-fp32 instructions: plain v_fma_f32 / v_add_f32 only
 DEVICE = ["--offload-arch=gfx950", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 
@@ -72,7 +75,7 @@ def _compile(src: str, force: bool, hdr_mtime: float, sanitize: bool = False) ->
         cmd += ["-x", "c++", "-D__HIP_PLATFORM_AMD__", "-I", "/opt/rocm/include"]
         if sanitize:
             cmd += SAN_FLAGS + ["-fno-omit-frame-pointer", "-g"]
-    cmd += ["-c", path, "-o", obj]
+    cmd += PER_SOURCE.get(src, []) + ["-c", path, "-o", obj]
     r = subprocess.run(cmd, capture_output=True, text=True)
     msgs = "\n".join(l for l in (r.stdout + r.stderr).splitlines()
                      if "packed-fp32-ops" not in l)

@@ -186,11 +186,13 @@ int32_t check_pattern(const Context &ctx, Pattern *p);
 int32_t generate_patterns(Context &ctx, Graph &g, int32_t backend, const clg_pattern_rule &rule, int32_t *n_added);
 
 // ---- plan -----------------------------------------------------------------------------
-// A region: kernels of the plan that do not depend on each other and run the same kind of
-// register-fed kernel, so that those of them that are handed over (clg_plan_set_handover) can
+// A region: kernels of the plan that do not depend on each other and of which a kernel for several
+// problems exists, so that those of them that are handed over (clg_plan_set_handover) can
 // share one launch.  Members are adjacent in the plan's order.
 struct Region {
+    bool mixed = false;                    // members of several kinds, or of several shapes of one (region_mix.hip)
     std::vector<int32_t> members;          // call indices, ascending
+    std::vector<int32_t> order;            // positions in members, in the order of a launch
     std::vector<KernelCall> fused;         // per member: the call lowered again for the region's common kernel shape
     std::vector<void *> packed;            // per member: weights packed for that shape (owned by the plan)
 };
@@ -201,6 +203,7 @@ struct Plan {
     bool counted = false;              // this plan is among graph->live_plans
     std::vector<KernelCall> calls;
     PlaneMultiArgs plane_args{};           // argument block of a region of thread-per-output kernels, refilled per launch
+    MixArgs mix_args{};                    // the same of a mixed region
     std::vector<int64_t> value_offset;     // node -> workspace byte offset, -1 none
     std::vector<int32_t> value_output;     // node -> index in outputs[] of the buffer it lives in, -1 none
     std::vector<int64_t> value_delta;      // node -> byte offset inside that output buffer (a piece of a concatenation)

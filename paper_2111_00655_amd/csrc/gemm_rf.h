@@ -109,8 +109,9 @@ struct RfMfma<16> {
 // with a relu on its input (the operand values are clamped on their way into the MFMA).  The depth code is
 // compiled into GEO 2 and 3 only: a few more kernel arguments and one division are a measurable
 // part of a four-microsecond kernel.
-// The body takes its tile number as (bx of gx) instead of reading blockIdx.x, so that one launch can
-// run the tiles of several convolutions (conv_rf_multi_kernel below); grid.y and grid.z are read as usual.
+// The body takes its tile, its image (or (image, output depth) pair, by), its K split or sub-pixel phase (bz), its thread number
+// among the WGK waves that share the tile and the LDS in which these meet as arguments, so that one launch can run the tiles of several
+// convolutions (conv_rf_multi_kernel below) and a workgroup several tiles (region_mix.hip).  live: false stores nothing.
 // Loads in flight per wave, in chunks: a wave that owns several chunks issues the loads of up to
 // rf_depth<TAPK, WGK>() of them before its first MFMA.  A kernel whose waves own one chunk each is
 // instantiated with PF = 1 instead: the deeper variant holds its extra operand registers whether it
@@ -121,14 +122,13 @@ constexpr int rf_depth() {
 }
 
 template <int TS, int TAPK, int WGK, int GEO, int PF>
-__device__ __forceinline__ void conv_rf_body(const GemmCore &p, const int bx, const int gx) {
+__device__ __forceinline__ void conv_rf_body(const GemmCore &p, const int tile, const int by, const int bz, const int tid, float *const red, const bool live = true) {
     using MF = RfMfma<TS>;
     typedef typename MF::acc_t acc_t;
     constexpr int NSLOT = MF::NSLOT, NACC = MF::NACC;
     constexpr int NT = WGK * kWave;
     constexpr int PER_WAVE = NACC * kWave;                  // outputs of a tile
     constexpr int EPT = (PER_WAVE + NT - 1) / NT;           // outputs finished per thread
-    extern __shared__ float red[];
     constexpr bool CONVT = GEO == 1;
     constexpr bool FOLD = GEO == 2;
     constexpr bool DEPTH = GEO == 2 || GEO == 3;
@@ -136,16 +136,15 @@ __device__ __forceinline__ void conv_rf_body(const GemmCore &p, const int bx, co
     constexpr bool D2S = GEO == 5;
 
     CLG_STAMP(0);                                            // entry
-    const int tid = threadIdx.x;
     const int lane = tid & (kWave - 1);
     const int w = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int r = lane % TS, s = lane / TS;
 
     // effective geometry: the convolution itself, or one phase of a transposed convolution
     int KHe = p.KH, KWe = p.KW, she = p.sh, swe = p.sw, phe = p.ph, pwe = p.pw, HOe = p.HO, WOe = p.WO;
-    int a_h = 0, a_w = 0, phase = 0, ks = blockIdx.z;
+    int a_h = 0, a_w = 0, phase = 0, ks = bz;
     if constexpr (CONVT) {
-        phase = blockIdx.z;
+        phase = bz;
         ks = 0;
         a_h = phase / p.sw;
         a_w = phase - a_h * p.sw;
@@ -167,7 +166,6 @@ __device__ __forceinline__ void conv_rf_body(const GemmCore &p, const int bx, co
     const int CoutE = D2S ? 4 * p.Cout : p.Cout;              // rows of the GEMM
     const int npix = HOe * WOe;
     const int tiles_m = (CoutE + TS - 1) / TS;
-    const int tile = xcd_remap(bx, gx);
     // neighbouring workgroups share the larger operand: weights rows (i-major) or pixels (j-major);
     // tile / rf_tile_div by multiply-high (an integer division costs some thirty instructions)
     const int t_hi = (int)(((uint64_t)(uint32_t)tile * p.rf_tile_magic) >> 32), t_lo = tile - t_hi * p.rf_tile_div;
@@ -175,11 +173,11 @@ __device__ __forceinline__ void conv_rf_body(const GemmCore &p, const int bx, co
     const int nt = p.rf_jmajor ? t_hi : t_lo;
     const int i0 = mt * TS, j0 = nt * TS;
     // grid.y: the image, or (image, output depth) of a 3-D convolution
-    int img = blockIdx.y, od = 0, DOe = 1;
+    int img = by, od = 0, DOe = 1;
     if constexpr (DEPTH) {
         DOe = p.DO;
-        img = blockIdx.y / p.DO;
-        od = blockIdx.y - img * p.DO;
+        img = by / p.DO;
+        od = by - img * p.DO;
     }
     const int id0 = DEPTH ? od * p.sd - p.pd : 0;            // input depth of depth tap 0
 
@@ -216,7 +214,7 @@ __device__ __forceinline__ void conv_rf_body(const GemmCore &p, const int bx, co
             const int e = tid + t * NT;                                                       \
             const int l = e % kWave, g = e / kWave;                                           \
             const int i = i0 + MF::row(g, l / TS), j = j0 + l % TS;                           \
-            e_off[t] = (e < PER_WAVE && i < CoutE && j < npix) ? (((int64_t)img * p.Cout + i) * DOe + od) * npix + j : -1;\
+            e_off[t] = (live && e < PER_WAVE && i < CoutE && j < npix) ? (((int64_t)img * p.Cout + i) * DOe + od) * npix + j : -1;\
             if (D2S && e_off[t] >= 0) {                                                       \
                 const int ohh = (int)(((uint64_t)(uint32_t)j * p.rf_wo_magic) >> 32), oww = j - ohh * WOe;\
                 e_off[t] = (((int64_t)img * p.Cout + (i >> 2)) * p.HO + 2 * ohh + ((i >> 1) & 1)) * p.WO + 2 * oww + (i & 1);\
@@ -465,7 +463,8 @@ __device__ __forceinline__ void conv_rf_body(const GemmCore &p, const int bx, co
 
 template <int TS, int TAPK, int WGK, int GEO, int PF>
 __global__ __launch_bounds__(WGK *kWave) void conv_rf_kernel(GemmArgs p) {
-    conv_rf_body<TS, TAPK, WGK, GEO, PF>(p, blockIdx.x, gridDim.x);
+    extern __shared__ float red[];
+    conv_rf_body<TS, TAPK, WGK, GEO, PF>(p, xcd_remap(blockIdx.x, gridDim.x), blockIdx.y, blockIdx.z, threadIdx.x, red);
 }
 
 // Several independent problems of one kernel shape in ONE launch (a region of sibling kernels,
@@ -479,9 +478,10 @@ __global__ __launch_bounds__(WGK *kWave) void conv_rf_multi_kernel(RfMultiArgs m
     const int bx = blockIdx.x;
     int k = 0;
 #pragma unroll
-    for (int i = 0; i + 1 < kMaxRegion; ++i) k += (i + 1 < m.n && bx >= m.tile_end[i]) ? 1 : 0;
+    for (int i = 0; i + 1 < kMaxRegion; ++i) k += bx >= m.tile_end[i] ? 1 : 0;
     const int start = k ? m.tile_end[k - 1] : 0;
-    conv_rf_body<TS, 1, WGK, GEO, rf_depth<1, WGK>()>(m.p[k], bx - start, m.tile_end[k] - start);
+    extern __shared__ float red[];
+    conv_rf_body<TS, 1, WGK, GEO, rf_depth<1, WGK>()>(m.p[k], xcd_remap(bx - start, m.tile_end[k] - start), blockIdx.y, blockIdx.z, threadIdx.x, red);
 }
 
 // ---- dense: y[m][n] = sum_k x[m][k] * w[n][k] -------------------------------------------------
@@ -624,7 +624,7 @@ __global__ __launch_bounds__(WGK *kWave) void dense_rf_multi_kernel(RfMultiArgs 
     const int bx = blockIdx.x;
     int k = 0;
 #pragma unroll
-    for (int i = 0; i + 1 < kMaxRegion; ++i) k += (i + 1 < m.n && bx >= m.tile_end[i]) ? 1 : 0;
+    for (int i = 0; i + 1 < kMaxRegion; ++i) k += bx >= m.tile_end[i] ? 1 : 0;
     const int start = k ? m.tile_end[k - 1] : 0;
     dense_rf_body<TS, WGK>(m.p[k], bx - start, m.tile_end[k] - start);
 }
@@ -750,7 +750,7 @@ __global__ __launch_bounds__(WGK *kWave) void dense_rf2_multi_kernel(RfMultiArgs
     const int bx = blockIdx.x;
     int k = 0;
 #pragma unroll
-    for (int i = 0; i + 1 < kMaxRegion; ++i) k += (i + 1 < m.n && bx >= m.tile_end[i]) ? 1 : 0;
+    for (int i = 0; i + 1 < kMaxRegion; ++i) k += bx >= m.tile_end[i] ? 1 : 0;
     const int start = k ? m.tile_end[k - 1] : 0;
     dense_rf2_body<WGK>(m.p[k], bx - start, m.tile_end[k] - start);
 }

@@ -216,6 +216,33 @@ struct SepMultiArgs {
 int sepconv_region_key(const SepConvArgs &a);
 int launch_sepconv_region(const SepConvArgs *members, int n, void *stream);
 
+// ---- kernels of several kinds in one launch (a region of siblings of unlike kinds, region_mix.hip) -----------------
+// kind: depthwise convolutions and window pools as above; separable convolutions with four or eight waves per 16 pixels (MIX_SEP4, MIX_SEP8 + filter
+// size, 0: none); register-fed 1x1 convolutions with 16x16 tiles and one to eight waves per tile (MIX_CONV + waves), the same with a relu on the
+// input (MIX_RCONV) and of channel counts that take the any-filter path (MIX_ANY).
+enum MixKind : int32_t { MIX_DW3 = 3, MIX_DW5 = 5, MIX_DW7 = 7, MIX_MAX = 10, MIX_AVG = 11, MIX_SEP4 = 20, MIX_SEP8 = 30, MIX_CONV = 40, MIX_RCONV = 50,
+                         MIX_ANY = 60 };
+constexpr int kMaxMixRegion = 8;
+union MixMember {
+    GemmCore conv;
+    SepConvArgs sep;
+    DirectConvArgs dw;
+    PoolArgs pool;
+};
+struct MixArgs {
+    int32_t n;                             // problems, 2..kMaxMixRegion
+    int32_t block_end[kMaxMixRegion];      // problem k owns workgroups block_end[k-1] .. block_end[k] - 1
+    int32_t kind[kMaxMixRegion];
+    int32_t pad_[3];
+    MixMember p[kMaxMixRegion];
+};
+static_assert(sizeof(MixArgs) <= 4096, "kernel arguments");
+// The kind under which a (resolved) problem runs, 0: it does not.
+int32_t mix_conv_kind(const GemmArgs &a);
+int32_t mix_sep_kind(const SepConvArgs &a);
+int32_t mix_weight(int32_t kind);          // what comes first in a launch: the larger
+int launch_mix_region(const MixArgs &m, void *stream);
+
 // ---- reading ahead -----------------------------------------------------------------------------
 // Packed weights of later kernels that workgroups behind a kernel's own ones read without using them, so that those kernels find them in
 // the memory-side cache (plan.cpp: plan_read_ahead says when).

@@ -2,6 +2,7 @@
 // disjoint matches covering G; Sec. 5.1: tensors are handed between backends
 // by pointer, without copies), and its execution on a HIP stream.
 #include <algorithm>
+#include <map>
 
 #include <hip/hip_runtime_api.h>
 
@@ -117,30 +118,95 @@ bool dense_region_b3(const Context &ctx, const std::vector<KernelCall> &calls, c
     return true;
 }
 
+// A 1x1 convolution, separable or depthwise convolution or window pool as member of a mixed region: the kind under which it runs there (0: it does
+// not).  *out: the call, a convolution lowered again for 16 x 16 tiles and at most eight waves per tile.
+int32_t mix_kind(const Context &ctx, const KernelCall &c, KernelCall *out) {
+    *out = c;
+    if (c.kind == CALL_SEPCONV) return mix_sep_kind(c.sep);
+    if (c.kind == CALL_DIRECT_CONV) return depthwise_fast_ok(c.dconv) ? c.dconv.KH : 0;
+    if (c.kind == CALL_POOL) return plane_region_pool_ok(c.pool) ? (c.pool.mode == 0 ? MIX_MAX : MIX_AVG) : 0;
+    if (c.kind != CALL_GEMM || !c.gemm.rf_ts || !c.pack_bytes || c.gemm.mode != GM_CONV || c.gemm.KH != 1 || c.gemm.KW != 1 || c.gemm.D > 1) return 0;
+    GemmArgs &a = out->gemm;
+    const int flags = epi_fast_flags(a.epi);
+    if (!rf_resolve(&a, 16, flags, ctx.n_cus, -8)) return 0;
+    out->pack_bytes = rf_pack_bytes(a);
+    out->scratch_bytes = 0;
+    return mix_conv_kind(a);
+}
+
+// Calls in order of their distance from the graph's inputs, if that brings together kernels that a mixed region can hold: a
+// region's members read nothing that its first kernel or a later one makes, and in the order of the sinks' depths a separable convolution of one
+// kernel (five operators deep) and a pool (one operator) that read the same tensor lie far apart.  Concatenations that can be aliases count nothing.
+void order_by_level(const Context &ctx, const Graph &g, std::vector<KernelCall> *calls) {
+    const size_t nc = calls->size();
+    std::vector<int32_t> level(nc, 0), at(g.nodes.size(), -1), order(nc);
+    std::map<int32_t, int32_t> kind_at;                      // level -> kind of the first member there
+    auto free_of_charge = [&](size_t i) { return (*calls)[i].kind == CALL_CONCAT && (*calls)[i].cat.outer == 1; };
+    bool mixed = false;
+    for (size_t i = 0; i < nc; ++i) {
+        for (int32_t v : operands_of((*calls)[i])) {
+            const int32_t j = at[v];
+            if (j >= 0) level[i] = std::max(level[i], level[(size_t)j] + (free_of_charge(i) ? 0 : 1));
+        }
+        at[(*calls)[i].out_node] = (int32_t)i;
+        order[i] = (int32_t)i;
+        KernelCall c;
+        const int32_t kind = mix_kind(ctx, (*calls)[i], &c);
+        if (kind && kind_at.emplace(level[i], kind).first->second != kind) mixed = true;
+    }
+    if (!mixed) return;
+    std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) {
+        return level[(size_t)a] != level[(size_t)b] ? level[(size_t)a] < level[(size_t)b] : free_of_charge((size_t)a) < free_of_charge((size_t)b);
+    });
+    std::vector<KernelCall> moved;
+    moved.reserve(nc);
+    for (int32_t i : order) moved.push_back(std::move((*calls)[(size_t)i]));
+    calls->swap(moved);
+}
+
 // Finds the regions of a freshly lowered kernel sequence and moves every member next to its region's
 // first one (a member only moves forward past kernels it does not depend on, so the order stays
 // topological).  Greedy and deterministic: scanning in order, a kernel of a fusable kind opens a
 // region; later kernels of the same family join when everything they read was produced before the
-// region's first kernel and the common kernel shape (that of the member with the most flops) takes them.
+// region's first kernel and the common kernel shape (that of the member with the most flops) takes them.  Where more kernels of
+// several kinds are free than of the opener's, they are a mixed region.
 void find_regions(const Context &ctx, const Graph &g, Plan *plan) {
     std::vector<KernelCall> &calls = plan->calls;
     const size_t nc = calls.size();
+    order_by_level(ctx, g, &calls);
     std::vector<int32_t> produced_at(g.nodes.size(), -1);
     for (size_t i = 0; i < nc; ++i) produced_at[calls[i].out_node] = (int32_t)i;
     std::vector<int32_t> reg_of(nc, -1);
-    struct Found { std::vector<int32_t> members; std::vector<KernelCall> fused; };
+    struct Found { std::vector<int32_t> members; std::vector<KernelCall> fused; bool mixed = false; };
+    std::vector<int32_t> kind(nc);
+    std::vector<KernelCall> as_mixed(nc);
+    for (size_t i = 0; i < nc; ++i) kind[i] = mix_kind(ctx, calls[i], &as_mixed[i]);
     std::vector<Found> found;
     for (size_t i = 0; i < nc; ++i) {
         const int cls = region_class(calls[i]);
-        if (reg_of[i] >= 0 || cls == RC_NONE) continue;
-        std::vector<int32_t> cand{(int32_t)i};
+        if (reg_of[i] >= 0 || (cls == RC_NONE && !kind[i])) continue;
+        std::vector<int32_t> cand{(int32_t)i}, mix;
         const size_t cap = cls == RC_PLANE ? (size_t)kMaxPlaneRegion : (cls >= RC_SEPCONV ? (size_t)kMaxSepRegion : (size_t)kMaxRegion);
-        for (size_t j = i + 1; j < nc && cand.size() < cap; ++j) {
-            if (reg_of[j] >= 0 || region_class(calls[j]) != cls) continue;
+        if (kind[i]) mix.push_back((int32_t)i);
+        for (size_t j = i + 1; j < nc; ++j) {
+            const bool like = cls != RC_NONE && region_class(calls[j]) == cls && cand.size() < cap, other = kind[i] && kind[j] && mix.size() < (size_t)kMaxMixRegion;
+            if (reg_of[j] >= 0 || (!like && !other)) continue;
             bool free = true;
             for (int32_t v : operands_of(calls[j]))
                 if (g.nodes[v].is_op() && produced_at[v] >= (int32_t)i) free = false;
-            if (free) cand.push_back((int32_t)j);
+            if (free && like) cand.push_back((int32_t)j);
+            if (free && other) mix.push_back((int32_t)j);
+        }
+        if (mix.size() > cand.size()) {
+            Found f;
+            f.mixed = true;
+            f.members = mix;                               // (in the plan's order; a launch takes them by weight)
+            for (int32_t c : mix) {
+                f.fused.push_back(as_mixed[(size_t)c]);
+                reg_of[(size_t)c] = (int32_t)found.size();
+            }
+            found.push_back(std::move(f));
+            continue;
         }
         if (cand.size() < 2) continue;
         int32_t lead = cand[0];
@@ -199,6 +265,16 @@ void find_regions(const Context &ctx, const Graph &g, Plan *plan) {
             plan->region_of[new_pos[c]] = (int32_t)plan->regions.size();
         }
         r.fused = std::move(f.fused);
+        r.mixed = f.mixed;
+        r.order.resize(r.members.size());
+        for (size_t k = 0; k < r.order.size(); ++k) r.order[k] = (int32_t)k;
+        if (r.mixed) {
+            auto weight = [&](int32_t k) {
+                KernelCall c;
+                return mix_weight(mix_kind(ctx, r.fused[(size_t)k], &c));
+            };
+            std::stable_sort(r.order.begin(), r.order.end(), [&](int32_t a, int32_t b) { return weight(a) > weight(b); });
+        }
         r.packed.assign(r.members.size(), nullptr);
         plan->regions.push_back(std::move(r));
     }
@@ -643,6 +719,39 @@ int32_t bind_gemm(const KernelCall &c, const void *a, const void *b, void *out, 
     return CLG_OK;
 }
 
+// One member of a mixed region with its pointers bound.
+static int32_t bind_mix(const KernelCall &c, const void *a, const void *b, const void *c3, void *out, const void *const *epi_ptrs, const void *packed,
+                        MixMember *m, int32_t *kind) {
+    auto bind = [&](Epilogue &e) {
+        for (int s = 0; s < e.n; ++s) e.s[s].ptr = (const float *)epi_ptrs[s];
+    };
+    if (c.pack_bytes && !packed) return fail(CLG_INVALID_ARG, "%s needs packed weights, none were prepared", c.name.c_str());
+    if (c.kind == CALL_SEPCONV) {
+        m->sep = c.sep;
+        m->sep.x = (const float *)a; m->sep.wp = (const float *)packed; m->sep.wd = (const float *)c3; m->sep.y = (float *)out;
+        bind(m->sep.epi);
+        *kind = mix_sep_kind(c.sep);
+    } else if (c.kind == CALL_DIRECT_CONV) {
+        m->dw = c.dconv;
+        m->dw.x = (const float *)a; m->dw.w = (const float *)b; m->dw.y = (float *)out;
+        bind(m->dw.epi);
+        *kind = c.dconv.KH;
+    } else if (c.kind == CALL_POOL) {
+        m->pool = c.pool;
+        m->pool.x = (const float *)a; m->pool.y = (float *)out;
+        bind(m->pool.epi);
+        *kind = c.pool.mode == 0 ? MIX_MAX : MIX_AVG;
+    } else {
+        GemmArgs k;
+        const int32_t rc = bind_gemm(c, a, b, out, epi_ptrs, nullptr, packed, &k);
+        if (rc != CLG_OK) return rc;
+        k.ef = make_epi_fast(k.epi);
+        m->conv = k;
+        *kind = mix_conv_kind(k);
+    }
+    return CLG_OK;
+}
+
 int32_t launch_call(const KernelCall &c, const void *a, const void *b, const void *c3, void *out,
                     const void *const *epi_ptrs, void *scratch, const void *packed, void *stream, const Ahead *ahead) {
     auto bind = [&](Epilogue e) {
@@ -829,22 +938,27 @@ int32_t execute_plan(Plan &p, const void *const *inputs, void *const *outputs, v
         if (fuse && done[i]) continue;
         if (fuse && p.region_of[i] >= 0 && p.handed[i]) {
             const Region &r = p.regions[(size_t)p.region_of[i]];
-            const bool sep = c.kind == CALL_SEPCONV;
+            const bool sep = !r.mixed && c.kind == CALL_SEPCONV;
             const bool b3 = r.fused[0].kind == CALL_B3;
-            const bool plane = r.fused[0].kind != CALL_GEMM && !sep && !b3;   // a region of thread-per-output kernels
+            const bool plane = !r.mixed && r.fused[0].kind != CALL_GEMM && !sep && !b3;   // a region of thread-per-output kernels
             GemmArgs members[kMaxRegion];
             B3Args bmembers[kMaxB3Region];
             SepConvArgs smembers[kMaxSepRegion];
             PlaneMultiArgs &pm = p.plane_args;           // (part of the plan: nothing this large goes on the stack per call)
+            MixArgs &mm = p.mix_args;
+            static_assert(kMaxMixRegion <= kMaxPlaneRegion && kMaxRegion <= kMaxPlaneRegion, "idx holds any region's members");
             size_t idx[kMaxPlaneRegion];
             int nm = 0;
-            for (size_t k = 0; k < r.members.size(); ++k) {
-                const size_t ci = (size_t)r.members[k];
+            for (size_t o = 0; o < r.members.size(); ++o) {
+                const size_t k = (size_t)r.order[o], ci = (size_t)r.members[k];
                 if (ci < i || !p.handed[ci]) continue;
                 const KernelCall &fc = r.fused[k];
                 const void *fepi[kMaxEpi];
                 for (int s = 0; s < kMaxEpi; ++s) fepi[s] = ptr_of(fc.epi_nodes[s]);
-                if (sep) {
+                if (r.mixed) {
+                    rc = bind_mix(fc, ptr_of(fc.a_node), ptr_of(fc.b_node), ptr_of(fc.c_node), const_cast<void *>(ptr_of(fc.out_node)), fepi,
+                                  r.packed[k] ? r.packed[k] : p.packed[ci], &mm.p[nm], &mm.kind[nm]);
+                } else if (sep) {
                     if (!p.packed[ci]) rc = fail(CLG_INVALID_ARG, "%s needs packed weights, none were prepared", fc.name.c_str());
                     SepConvArgs &k2 = smembers[nm];
                     k2 = fc.sep;
@@ -888,7 +1002,9 @@ int32_t execute_plan(Plan &p, const void *const *inputs, void *const *outputs, v
             if (nm >= 2) {
                 if (kernel_ns) (void)hipEventRecord(ev[2 * i], (hipStream_t)stream);
                 pm.n = nm;
-                const int err = sep ? launch_sepconv_region(smembers, nm, stream)
+                mm.n = nm;
+                const int err = r.mixed ? launch_mix_region(mm, stream)
+                                : sep ? launch_sepconv_region(smembers, nm, stream)
                                     : (plane ? launch_plane_region(pm, stream)
                                              : (b3 ? launch_b3_region(bmembers, nm, stream) : launch_gemm_region(members, nm, stream)));
                 if (kernel_ns) (void)hipEventRecord(ev[2 * i + 1], (hipStream_t)stream);

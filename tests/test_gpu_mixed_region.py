@@ -1,0 +1,88 @@
+"""Regions of siblings of unlike kinds in one launch: depthwise and separable convolutions of every filter size, window pools and 1x1 convolutions over one tensor, where a kind's tiles, waves and
+remainders can go wrong beside the others.  Against the oracle; the kinds that run unchanged (all but 1x1 convolutions) bit for bit as one by one."""
+import numpy as np
+import pytest
+
+import workloads as wl
+from workloads.patterns import P, W
+import paper_2111_00655_amd as clg
+from oracle.graph import Graph
+from parity_util import OP_TOL, check_outputs
+
+pytestmark = pytest.mark.gpu
+
+TAILS = [(), ("bias_add",), ("bias_add", "add"), ("bias_add", "relu")]
+CASES = [
+    # batch, channels, height, width, branches: (kind, filter, stride, relu in front, output channels, tail)
+    # one and two 16-pixel tiles per problem; channels that are not a multiple of four (the any-filter path), a wave per tile
+    (1, 11, 5, 5, [("dw", 3, 1, True, 0, ()), ("max", 3, 1, False, 0, ()), ("conv", 1, 1, False, 11, ("bias_add",)), ("sep", 3, 1, True, 11, ("bias_add",)),
+                   ("conv", 1, 2, False, 7, ("bias_add", "add"))]),
+    # every depthwise and separable filter size, four and eight waves, an odd number of pixel tiles, two images
+    (2, 44, 9, 11, [("dw", 7, 1, True, 0, ("bias_add",)), ("sep", 5, 1, True, 44, ("bias_add", "add")), ("sep", 7, 1, False, 20, ("bias_add",)), ("conv", 1, 1, True, 33, ("bias_add",)),
+                    ("avg", 3, 2, False, 0, ("add",)), ("dw", 5, 2, False, 0, ()), ("sep", 3, 2, True, 50, ())]),
+    # two, four and eight waves per tile of 1x1 convolutions (two to more than eight chunks), with and without a relu, without wide kinds
+    (1, 88, 14, 13, [("conv", 1, 1, False, 88, ("bias_add",)), ("conv", 1, 1, True, 90, ("bias_add", "add")), ("max", 3, 1, False, 0, ("add",)), ("sep", 3, 1, True, 88, ("bias_add",))]),
+    (3, 176, 7, 7, [("conv", 1, 1, False, 176, ("bias_add", "relu")), ("conv", 1, 2, True, 16, ("bias_add",)), ("dw", 3, 1, True, 0, ("bias_add", "add")), ("avg", 3, 1, False, 0, ())]),
+    (1, 600, 6, 4, [("conv", 1, 1, False, 40, ("bias_add",)), ("conv", 1, 1, True, 24, ()), ("dw", 5, 1, True, 0, ()), ("max", 2, 2, False, 0, ())]),
+    # long any-filter channel ranges; more branches than a region holds
+    (1, 90, 8, 8, [("conv", 1, 1, False, 18, ("bias_add",)), ("dw", 3, 1, False, 0, ()), ("dw", 7, 2, True, 0, ()), ("sep", 5, 2, True, 90, ("bias_add",)), ("avg", 5, 1, False, 0, ()),
+                   ("max", 3, 1, False, 0, ()), ("sep", 3, 1, False, 16, ()), ("conv", 1, 2, False, 90, ()), ("dw", 5, 1, False, 0, ("bias_add",)), ("conv", 1, 1, False, 5, ())]),
+]
+
+
+@pytest.mark.parametrize("ci", range(len(CASES)))
+def test_region_of_siblings_of_unlike_kinds(ci):
+    n_img, c, h, w, branches = CASES[ci]
+    r = np.random.default_rng([91, ci])
+    f32 = lambda *shape, scale=1.0: (r.standard_normal(shape) * scale).astype(np.float32)
+    d = wl.GraphDesc("region_mixed")
+    x = d.input(f32(n_img, c, h, w))
+    for kind, k, stride, pre, cout, tail in branches:
+        pad, ho, wo = (k - 1) // 2, (h + 2 * ((k - 1) // 2) - k) // stride + 1, (w + 2 * ((k - 1) // 2) - k) // stride + 1
+        cout = cout or c
+        y = d.op("relu", [x]) if pre else x
+        if kind in ("dw", "sep"):
+            y = d.op("conv2d", [y, d.const(f32(c, 1, k, k, scale=1.0 / k))], stride=(stride, stride), pad=(pad, pad), groups=c)
+        if kind in ("sep", "conv"):
+            s1 = stride if kind == "conv" else 1
+            y = d.op("conv2d", [y, d.const(f32(cout, c, 1, 1, scale=c ** -0.5))], stride=(s1, s1), pad=(0, 0), groups=1)
+        if kind in ("max", "avg"):
+            y = d.op(kind + "_pool2d", [x], kernel=(k, k), stride=(stride, stride), pad=(pad, pad))
+        for op in tail:
+            operand = [d.const(f32(cout))] if op == "bias_add" else ([d.input(f32(n_img, cout, ho, wo))] if op == "add" else [])
+            y = d.op(op, [y] + operand, **({"axis": 1} if op == "bias_add" else {}))
+        d.mark_output(y)
+
+    def tails(anchor):
+        out = []
+        for t in TAILS:
+            p = anchor
+            for op in t:
+                p = P(op, p, W) if op in ("bias_add", "add") else P(op, p)
+            out.append(p)
+        return out
+    dw = P("conv2d", P("relu", W), W)
+    reg = [("sepconv", p) for a in (P("conv2d", dw, W), P("conv2d", P("conv2d", W, W), W), dw) for p in tails(a)]
+    reg += [("direct", p) for p in tails(P("conv2d", W, W, groups=(c, c)))] + [("igemm_r16", p) for p in tails(P("conv2d", W, W, groups=(1, 1)))]
+    reg += [("direct", p) for k in ("avg_pool2d", "max_pool2d") for p in (P(k, W), P("add", P(k, W), W))]
+    reg += [("eltwise", P("relu", W)), ("eltwise", P("add", W, W)), ("eltwise", P("bias_add", W, W))]
+    s = clg.Session(d, reg, device=0)
+    ms = s.match()
+    _, ids = s.search([100] * len(ms), 0)                   # fewest kernels: every branch is one
+    plan = s.compile(ids).bind()
+    n, regions = plan.n_kernels, plan.regions()
+    names = [k["name"] for k in plan.kernels()]
+    assert n == len(branches), names
+    assert sum(g == 0 for g in regions) == min(n, 8), (regions, names)
+    ref = Graph(d).run()
+    one_by_one = plan.run()
+    check_outputs(one_by_one, ref, OP_TOL, (ci, "one by one"))
+    for digits in ([1] * n, [i % 2 for i in range(n)], [1, 1] + [0] * (n - 2), [0] * (n - 2) + [1, 1], [1] * n):
+        plan.set_handover(digits, lanes=1)
+        saved = sum(max(sum(dg for dg, g in zip(digits, regions) if g == q) - 1, 0) for q in range(max(regions) + 1))
+        assert plan.n_launches == n - saved, (digits, regions, plan.n_launches)
+        got = plan.run()
+        check_outputs(got, ref, OP_TOL, (ci, digits))
+        for k, (a, b) in enumerate(zip(got, one_by_one)):
+            assert branches[k][0] == "conv" or np.array_equal(a, b), (ci, digits, branches[k])
+    s.close()
