@@ -13,13 +13,15 @@
 // LDS and are the A operand of the second product (read 16 bytes per lane, the same index order).
 // Nothing but q, k, v and the result touches memory.
 //
-// What bounds it is latency and the L1: some 5 us of matrix work at most, and k and v pass through a compute unit's L1
-// once per workgroup.  So a wave keeps the same keys in both products, loads all its rows of k and of v at once
-// before the first MFMA, and reads v 16 bytes per lane as well: the columns of d are dealt out so that a lane's four
-// neighbouring ones belong to four column tiles.  Every wave has a partial result of all columns; they meet in LDS.
-// Twelve heads of 64, us, four waves with v read 4 bytes per lane behind the softmax against this: 16 keys 3.93 and 3.74; 128 keys
-// 6.1 and 5.35; 256 keys 10.5 and 7.8; 389 keys 19.6 and 16.5; 512 keys 23.7 and 18.7.  (Sixteen waves with two column tiles of v per
-// wave took 5.4, 11.2 and 18.4 at 128, 256 and 389 keys.)
+// What bounds it is the L1: some 5 us of matrix work at most, and k and v pass through a compute unit's L1 once per workgroup, where a wave's load of
+// 1 KB takes about 45 cycles wherever the data lie (time stamps; putting a head's tiles on one XCD changed nothing).  So a wave keeps the same keys in
+// both products, loads all its rows of k at once, and those of v, 16 bytes per lane as well (the columns of d are dealt out so that a lane's
+// four neighbouring ones belong to four column tiles), between the products of the scores, which wait for k only; the query rows are loaded once per
+// workgroup and shared through LDS.  Every wave has a partial result of all columns; they meet in LDS.
+// Twelve heads of 64, us: 128 keys 4.9, 256 keys 7.2, 389 keys 14.7, 512 keys 17.1.  With every wave loading the query rows and v before the first product
+// 5.4, 7.9, 16.6 and 19.0; of that, 16 bytes instead of 4 per LDS access of the softmax made 15.3 and 17.8 the last two.  Two workgroups of one row
+// tile per compute unit instead of one of two tiles: 389 keys 16.9.  (Sixteen waves with two column tiles of v per wave took 5.4, 11.2 and 18.4 at
+// 128, 256 and 389 keys.)
 #include <algorithm>
 #include <type_traits>
 
@@ -71,8 +73,10 @@ __global__ __launch_bounds__(kWaves * kWave) void attention_kernel(AttentionArgs
     constexpr int VG = MAXT * CS;                            // key tiles of a wave in it
     constexpr int VEC = VT < 4 ? VT : 4, NV = VT / VEC;      // columns of d per load of v, loads per row
     static_assert(kWaves % CS == 0 && D16 % CS == 0, "the waves share out the column tiles");
+    static_assert(CS == 1 || MAXT == 1, "a wave loads v's tile u with the scores of its key tile u");
     constexpr int LPR = kWave * kWaves / ROWS;               // lanes per row of the softmax
-    constexpr int CPL = kWaves * MAXT * 16 / LPR;            // columns per lane
+    constexpr int PPL = kWaves * MAXT * 4 / LPR;             // 16-byte parts of a row per lane
+    static_assert(PPL * LPR == kWaves * MAXT * 4, "a lane takes whole parts");
     typedef float vecv __attribute__((ext_vector_type(VEC)));
     typedef float vecu __attribute__((ext_vector_type(VEC), aligned(4)));      // (v may lie at any address of a float)
     extern __shared__ float lds[];                           // [ROWS][ldp]: scores, then probabilities; then [KS][ROWS][ldr]: partial results
@@ -93,12 +97,11 @@ __global__ __launch_bounds__(kWaves * kWave) void attention_kernel(AttentionArgs
 
     // ---- all loads: key tiles wave, wave + kWaves, ... of this wave (past the end: the last key row, not used)
     float4 qa[RT][D16], kb[MAXT][D16];
-#pragma unroll
-    for (int t = 0; t < RT; ++t) {
-        const float4 *qp = reinterpret_cast<const float4 *>(Q + (int64_t)min(q0 + 16 * t + r, a.Sq - 1) * d) + s;
-#pragma unroll
-        for (int g = 0; g < D16; ++g) qa[t][g] = qp[4 * g];
-    }
+    float *const lds_q = lds + ROWS * max(ldp, KS * ldr);    // [ROWS][ldr]
+    float4 q_own = make_float4(0.f, 0.f, 0.f, 0.f);
+    static_assert(ROWS * D16 * 4 <= kWaves * kWave, "16 bytes per lane");
+    const int q_row = tid / (D16 * 4), q_part = tid % (D16 * 4);
+    if (q_row < ROWS) q_own = reinterpret_cast<const float4 *>(Q + (int64_t)min(q0 + q_row, a.Sq - 1) * d)[q_part];
 #pragma unroll
     for (int u = 0; u < MAXT; ++u) {
         const float4 *kp = reinterpret_cast<const float4 *>(K + (int64_t)min((wave + kWaves * u) * 16 + r, a.Sk - 1) * d) + s;
@@ -109,19 +112,26 @@ __global__ __launch_bounds__(kWaves * kWave) void attention_kernel(AttentionArgs
     constexpr bool EARLY_V = D16 <= 4;
     const int ks = wave / CS, c0 = wave % CS * VT * 16;      // key tiles ks, ks + KS, ... and first column in the second product
     vecv vb[VG][4][NV];                                      // row 4s + q of the tile, columns c0 + 16 VEC c + VEC r ..
-    auto load_v = [&] {
+    auto load_v = [&](int u, int q) {
+#pragma unroll
+        for (int c = 0; c < NV; ++c)
+            vb[u][q][c] = *reinterpret_cast<const vecu *>(V + (int64_t)min((ks + KS * u) * 16 + 4 * s + q, a.Sk - 1) * d + c0 + 16 * VEC * c + VEC * r);
+    };
+    auto load_all_v = [&] {
 #pragma unroll
         for (int u = 0; u < VG; ++u)
 #pragma unroll
-            for (int q = 0; q < 4; ++q)
-#pragma unroll
-                for (int c = 0; c < NV; ++c)
-                    vb[u][q][c] = *reinterpret_cast<const vecu *>(V + (int64_t)min((ks + KS * u) * 16 + 4 * s + q, a.Sk - 1) * d + c0 + 16 * VEC * c + VEC * r);
+            for (int q = 0; q < 4; ++q) load_v(u, q);
     };
-    if constexpr (EARLY_V) {
-        load_v();
-        __builtin_amdgcn_sched_barrier(0);                   // every load leaves before the first MFMA waits
-    }
+    constexpr bool LATE_V = EARLY_V && MAXT > 1;             // v's loads between the products of the scores
+    if constexpr (EARLY_V && !LATE_V) load_all_v();
+    __builtin_amdgcn_sched_barrier(0);                       // every load leaves before anything waits
+    if (q_row < ROWS) *reinterpret_cast<float4 *>(lds_q + q_row * ldr + 4 * q_part) = q_own;
+    lds_barrier();
+#pragma unroll
+    for (int t = 0; t < RT; ++t)
+#pragma unroll
+        for (int g = 0; g < D16; ++g) qa[t][g] = *reinterpret_cast<const float4 *>(lds_q + (16 * t + r) * ldr + 16 * g + 4 * s);
     // ---- scores; accumulator g of a lane: row 4s + g, column r of the tile
 #pragma unroll
     for (int u = 0; u < MAXT; ++u) {
@@ -133,12 +143,19 @@ __global__ __launch_bounds__(kWaves * kWave) void attention_kernel(AttentionArgs
 #pragma unroll
             for (int g = 0; g < D16; g += 2)
 #pragma unroll
-                for (int q = 0; q < 4; ++q)
+                for (int q = 0; q < 4; ++q) {
+                    if constexpr (LATE_V) {
+                        if (g == 0) {
+                            load_v(u, q);
+                            __builtin_amdgcn_sched_barrier(0);
+                        }
+                    }
 #pragma unroll
                     for (int e = 0; e < 2; ++e)
 #pragma unroll
                         for (int t = 0; t < RT; ++t)
                             acc[t][e] = __builtin_amdgcn_mfma_f32_16x16x4f32((&qa[t][g + e].x)[q], (&kb[u][g + e].x)[q], acc[t][e], 0, 0, 0);
+                }
             const int col = kt * 16 + r;
 #pragma unroll
             for (int t = 0; t < RT; ++t)
@@ -147,36 +164,36 @@ __global__ __launch_bounds__(kWaves * kWave) void attention_kernel(AttentionArgs
                     lds[(16 * t + 4 * s + g) * ldp + col] = col < a.Sk ? (acc[t][0][g] + acc[t][1][g]) * a.scale : -INFINITY;
         }
     }
-    if constexpr (!EARLY_V) load_v();
+    if constexpr (!EARLY_V) load_all_v();
     lds_barrier();                                           // (LDS only: the v operands stay in flight)
 
-    // ---- softmax: LPR lanes per row, a lane takes the columns c, c + LPR, ...
+    // ---- softmax: LPR lanes per row, a lane takes the parts c, c + LPR, ...
     {
-        const int c = tid % LPR, cols = nct * 16;
-        float *row = lds + tid / LPR * ldp;
-        float v[CPL];
+        const int c = tid % LPR, parts = nct * 4;            // 16-byte parts of a row
+        float4 *row = reinterpret_cast<float4 *>(lds + tid / LPR * ldp);
+        float4 v[PPL];
         float mx = -INFINITY;
 #pragma unroll
-        for (int i = 0; i < CPL; ++i) {
-            v[i] = c + LPR * i < cols ? row[c + LPR * i] : -INFINITY;
-            mx = fmaxf(mx, v[i]);
+        for (int i = 0; i < PPL; ++i) {
+            v[i] = c + LPR * i < parts ? row[c + LPR * i] : make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
+            mx = fmaxf(mx, fmaxf(fmaxf(v[i].x, v[i].y), fmaxf(v[i].z, v[i].w)));
         }
         mx = row16_max(mx);
 #pragma unroll
         for (int o = 16; o < LPR; o *= 2) mx = fmaxf(mx, __shfl_xor(mx, o));
         float sum = 0.f;
 #pragma unroll
-        for (int i = 0; i < CPL; ++i) {
-            v[i] = c + LPR * i < cols ? __expf(v[i] - mx) : 0.f;           // exp(-inf) = 0 for the padded columns
-            sum += v[i];
+        for (int i = 0; i < PPL; ++i) {                      // exp(-inf) = 0 for the padded columns
+            v[i] = make_float4(__expf(v[i].x - mx), __expf(v[i].y - mx), __expf(v[i].z - mx), __expf(v[i].w - mx));
+            sum += c + LPR * i < parts ? (v[i].x + v[i].y) + (v[i].z + v[i].w) : 0.f;
         }
         sum = row16_sum(sum);
 #pragma unroll
         for (int o = 16; o < LPR; o *= 2) sum += __shfl_xor(sum, o);
         const float inv = 1.0f / sum;
 #pragma unroll
-        for (int i = 0; i < CPL; ++i)
-            if (c + LPR * i < cols) row[c + LPR * i] = v[i] * inv;
+        for (int i = 0; i < PPL; ++i)
+            if (c + LPR * i < parts) row[c + LPR * i] = make_float4(v[i].x * inv, v[i].y * inv, v[i].z * inv, v[i].w * inv);
     }
     lds_barrier();
 
@@ -228,7 +245,7 @@ __global__ __launch_bounds__(kWaves * kWave) void attention_kernel(AttentionArgs
 template <int D16, int MAXT, int RT, int CS, class R>
 int launch_as(const AttentionArgs &a, const R &r, dim3 grid, hipStream_t s) {
     constexpr int ROWS = kRows * RT;
-    const size_t lds = (size_t)ROWS * std::max((a.Sk + 15) / 16 * 16 + 4, kWaves / CS * (D16 * 16 + 4)) * sizeof(float);
+    const size_t lds = (size_t)ROWS * (std::max((a.Sk + 15) / 16 * 16 + 4, kWaves / CS * (D16 * 16 + 4)) + D16 * 16 + 4) * sizeof(float);
     if (lds > 64 * 1024) {
         static LdsLimit limit;
         const hipError_t e = limit.raise((const void *)attention_kernel<D16, MAXT, RT, CS, R>);
@@ -265,9 +282,9 @@ bool attention_shape_ok(const AttentionArgs &a) {
            (a.d == 32 || a.d == 64 || a.d == 128) && (int64_t)a.Sq * a.d < ((int64_t)1 << 31);
 }
 
-// From 385 keys on a compute unit's registers hold one workgroup, below two: more workgroups than that would be a second
-// round, and two row tiles share each load of k and v (twelve heads, one and two row tiles, us: 389 keys, heads of 64, 20.4 and
-// 16.5, heads of 32 10.9 and 10.1; 512 keys 23.2 and 18.7).  Heads of 128 have no registers for a second row tile.
+// Two row tiles share each load of k and v, where single ones would be more than one workgroup per compute unit from 385 keys on, more
+// than two below (twelve heads, one and two row tiles, us: 389 keys, heads of 64, 16.9 and 14.7, heads of 32 10.6 and 8.9; 512 keys 19.7 and
+// 17.1).  Heads of 128 have no registers for a second row tile.
 // Reading ahead: at most 64 workgroups, last, in whole rows of the grid, and only on compute units that have none of the others (one in
 // the way of those made all of BERT-base on 512 rows 7 % slower).
 AttentionGrid attention_grid(const AttentionArgs &a) {
