@@ -13,15 +13,15 @@
 // LDS and are the A operand of the second product (read 16 bytes per lane, the same index order).
 // Nothing but q, k, v and the result touches memory.
 //
-// What bounds it is the L1: some 5 us of matrix work at most, and k and v pass through a compute unit's L1 once per workgroup, where a wave's load of
-// 1 KB takes about 45 cycles wherever the data lie (time stamps; putting a head's tiles on one XCD changed nothing).  So a wave keeps the same keys in
-// both products, loads all its rows of k at once, and those of v, 16 bytes per lane as well (the columns of d are dealt out so that a lane's
-// four neighbouring ones belong to four column tiles), between the products of the scores, which wait for k only; the query rows are loaded once per
-// workgroup and shared through LDS.  Every wave has a partial result of all columns; they meet in LDS.
-// Twelve heads of 64, us: 128 keys 4.9, 256 keys 7.2, 389 keys 14.7, 512 keys 17.1.  With every wave loading the query rows and v before the first product
-// 5.4, 7.9, 16.6 and 19.0; of that, 16 bytes instead of 4 per LDS access of the softmax made 15.3 and 17.8 the last two.  Two workgroups of one row
-// tile per compute unit instead of one of two tiles: 389 keys 16.9.  (Sixteen waves with two column tiles of v per wave took 5.4, 11.2 and 18.4 at
-// 128, 256 and 389 keys.)
+// What bounds it is the L1: some 5 us of matrix work at most, and k and v pass through a compute unit's L1 once per workgroup.  So a wave keeps the
+// same keys in both products, loads all its rows of k at once, and those of v, 16 bytes per lane as well (the columns of d are dealt out so that
+// a lane's four neighbouring ones belong to four column tiles), between the products of the scores, which wait for k only.  The lanes of an MFMA's
+// operand hold 16 bytes of 16 rows each, and a load in that pattern takes the L1 27 ns instead of the 7 of a contiguous one: q (once per
+// workgroup) and k are loaded in the order of memory and change lanes through LDS.  Every wave has a partial result of all columns; they meet in LDS.
+// Twelve heads of 64, us: 128 keys 4.8, 256 keys 6.8, 389 keys 14.3, 512 keys 16.4.  With k loaded as the MFMA wants it 4.9, 7.2, 14.7 and 17.1; with
+// every wave loading the query rows so as well, and v before the first product, 5.4, 7.9, 16.6 and 19.0 (of that, 16 bytes instead of 4 per LDS
+// access of the softmax made 0.6 at 389 and 512 keys).  A head's tiles on one XCD: no change.  Sixteen waves with two column tiles of v per wave: 5.4, 11.2 and
+// 18.4 at 128, 256 and 389 keys.
 #include <algorithm>
 #include <type_traits>
 
@@ -96,18 +96,21 @@ __global__ __launch_bounds__(kWaves * kWave) void attention_kernel(AttentionArgs
     const float *V = a.v + (int64_t)h * a.Sk * d;
 
     // ---- all loads: key tiles wave, wave + kWaves, ... of this wave (past the end: the last key row, not used)
-    float4 qa[RT][D16], kb[MAXT][D16];
+    // (in the order of memory: 64 lanes of one load that read 16 bytes of 16 rows each take 64 cycles of the L1, neighbouring ones 17.  The lanes that
+    // multiply them get q and k through LDS, k through the wave's own part of it.)
+    floatx4 qa[RT][D16], ko[MAXT][D16];
     float *const lds_q = lds + ROWS * max(ldp, KS * ldr);    // [ROWS][ldr]
-    float4 q_own = make_float4(0.f, 0.f, 0.f, 0.f);
-    static_assert(ROWS * D16 * 4 <= kWaves * kWave, "16 bytes per lane");
-    const int q_row = tid / (D16 * 4), q_part = tid % (D16 * 4);
-    if (q_row < ROWS) q_own = reinterpret_cast<const float4 *>(Q + (int64_t)min(q0 + q_row, a.Sq - 1) * d)[q_part];
+    float *const lds_k = lds_q + (ROWS + 16 * wave) * ldr;   // [16][ldr]
+    constexpr int PPR = 4 * D16;                             // 16-byte parts of a row of q, k
+    floatx4 q_own = {0.f, 0.f, 0.f, 0.f};
+    static_assert(ROWS * PPR <= kWaves * kWave && kWave % PPR == 0, "16 bytes per lane, whole rows per load");
+    const int q_row = tid / PPR, q_part = tid % PPR, k_row = lane / PPR, k_part = lane % PPR;
+    if (q_row < ROWS) q_own = reinterpret_cast<const floatx4 *>(Q + (int64_t)min(q0 + q_row, a.Sq - 1) * d)[q_part];
 #pragma unroll
-    for (int u = 0; u < MAXT; ++u) {
-        const float4 *kp = reinterpret_cast<const float4 *>(K + (int64_t)min((wave + kWaves * u) * 16 + r, a.Sk - 1) * d) + s;
+    for (int u = 0; u < MAXT; ++u)
 #pragma unroll
-        for (int g = 0; g < D16; ++g) kb[u][g] = kp[4 * g];
-    }
+        for (int i = 0; i < D16; ++i)
+            ko[u][i] = reinterpret_cast<const floatx4 *>(K + (int64_t)min((wave + kWaves * u) * 16 + i * (kWave / PPR) + k_row, a.Sk - 1) * d)[k_part];
     // (heads of 128 leave no registers for v before the scores are done)
     constexpr bool EARLY_V = D16 <= 4;
     const int ks = wave / CS, c0 = wave % CS * VT * 16;      // key tiles ks, ks + KS, ... and first column in the second product
@@ -126,17 +129,22 @@ __global__ __launch_bounds__(kWaves * kWave) void attention_kernel(AttentionArgs
     constexpr bool LATE_V = EARLY_V && MAXT > 1;             // v's loads between the products of the scores
     if constexpr (EARLY_V && !LATE_V) load_all_v();
     __builtin_amdgcn_sched_barrier(0);                       // every load leaves before anything waits
-    if (q_row < ROWS) *reinterpret_cast<float4 *>(lds_q + q_row * ldr + 4 * q_part) = q_own;
+    if (q_row < ROWS) *reinterpret_cast<floatx4 *>(lds_q + q_row * ldr + 4 * q_part) = q_own;
     lds_barrier();
 #pragma unroll
     for (int t = 0; t < RT; ++t)
 #pragma unroll
-        for (int g = 0; g < D16; ++g) qa[t][g] = *reinterpret_cast<const float4 *>(lds_q + (16 * t + r) * ldr + 16 * g + 4 * s);
+        for (int g = 0; g < D16; ++g) qa[t][g] = *reinterpret_cast<const floatx4 *>(lds_q + (16 * t + r) * ldr + 16 * g + 4 * s);
     // ---- scores; accumulator g of a lane: row 4s + g, column r of the tile
 #pragma unroll
     for (int u = 0; u < MAXT; ++u) {
         const int kt = wave + kWaves * u;
         if (kt < nct) {                                      // uniform over the wave
+            floatx4 kb[D16];
+#pragma unroll
+            for (int i = 0; i < D16; ++i) *reinterpret_cast<floatx4 *>(lds_k + (i * (kWave / PPR) + k_row) * ldr + 4 * k_part) = ko[u][i];
+#pragma unroll
+            for (int g = 0; g < D16; ++g) kb[g] = *reinterpret_cast<const floatx4 *>(lds_k + r * ldr + 16 * g + 4 * s);
             floatx4 acc[RT][2];                              // even and odd groups of d apart: shorter chains
 #pragma unroll
             for (int t = 0; t < RT; ++t) acc[t][0] = acc[t][1] = floatx4{0.f, 0.f, 0.f, 0.f};
@@ -154,7 +162,7 @@ __global__ __launch_bounds__(kWaves * kWave) void attention_kernel(AttentionArgs
                     for (int e = 0; e < 2; ++e)
 #pragma unroll
                         for (int t = 0; t < RT; ++t)
-                            acc[t][e] = __builtin_amdgcn_mfma_f32_16x16x4f32((&qa[t][g + e].x)[q], (&kb[u][g + e].x)[q], acc[t][e], 0, 0, 0);
+                            acc[t][e] = __builtin_amdgcn_mfma_f32_16x16x4f32(qa[t][g + e][q], kb[g + e][q], acc[t][e], 0, 0, 0);
                 }
             const int col = kt * 16 + r;
 #pragma unroll
@@ -245,7 +253,7 @@ __global__ __launch_bounds__(kWaves * kWave) void attention_kernel(AttentionArgs
 template <int D16, int MAXT, int RT, int CS, class R>
 int launch_as(const AttentionArgs &a, const R &r, dim3 grid, hipStream_t s) {
     constexpr int ROWS = kRows * RT;
-    const size_t lds = (size_t)ROWS * (std::max((a.Sk + 15) / 16 * 16 + 4, kWaves / CS * (D16 * 16 + 4)) + D16 * 16 + 4) * sizeof(float);
+    const size_t lds = (size_t)ROWS * (std::max((a.Sk + 15) / 16 * 16 + 4, kWaves / CS * (D16 * 16 + 4)) + (D16 * 16 + 4) * (1 + 16 * kWaves / ROWS)) * sizeof(float);
     if (lds > 64 * 1024) {
         static LdsLimit limit;
         const hipError_t e = limit.raise((const void *)attention_kernel<D16, MAXT, RT, CS, R>);
@@ -283,8 +291,8 @@ bool attention_shape_ok(const AttentionArgs &a) {
 }
 
 // Two row tiles share each load of k and v, where single ones would be more than one workgroup per compute unit from 385 keys on, more
-// than two below (twelve heads, one and two row tiles, us: 389 keys, heads of 64, 16.9 and 14.7, heads of 32 10.6 and 8.9; 512 keys 19.7 and
-// 17.1).  Heads of 128 have no registers for a second row tile.
+// than two below (twelve heads, one and two row tiles, us: 389 keys, heads of 64, 15.1 and 14.3, heads of 32 9.3 and 9.0; 512 keys 17.6 and
+// 16.4).  Heads of 128 have no registers for a second row tile.
 // Reading ahead: at most 64 workgroups, last, in whole rows of the grid, and only on compute units that have none of the others (one in
 // the way of those made all of BERT-base on 512 rows 7 % slower).
 AttentionGrid attention_grid(const AttentionArgs &a) {
