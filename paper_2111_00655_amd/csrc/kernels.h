@@ -113,6 +113,7 @@ struct GemmCore {
                                            //    over the input whose 4 * Cout rows are (channel, sub-pixel phase)
     int32_t bias_on_row;                   // 1: channel = i (conv), 0: channel = j (dense)
     int32_t gemv;                          // 1: GM_NT with at most 8 rows runs the matrix-vector kernel (a wave per column)
+    int32_t gemv16;                        // 1: the same with shorter rows (sixteen lanes per column)
     int32_t patch_sz;                      // 3x3 kernel: floats per channel of the LDS input patch
     int64_t strideA, strideB, strideC;     // per batch, in elements
     // 3-D convolution on the register-fed kernels: one grid.y slice per (image, output depth);
@@ -426,5 +427,6 @@ int epi_fast_flags(const Epilogue &e);
 bool lean_mm_shape_ok(const GemmArgs &a, int epi_flags);
 // Whether the matrix-vector kernel takes these sizes (pointer alignment aside).
 bool gemv_shape_ok(const GemmArgs &a, int epi_flags);
+bool gemv16_shape_ok(const GemmArgs &a, int epi_flags);
 
 }  // namespace clg

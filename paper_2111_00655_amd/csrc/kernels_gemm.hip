@@ -421,6 +421,58 @@ bool gemv_shape_ok(const GemmArgs &a, int epi_flags) {
            a.ldb % 4 == 0 && a.cs_len == 0 && !(epi_flags & EF_GENERIC);
 }
 
+// The same for shorter rows (64 <= K < 512), which leave lanes of a wave idle: sixteen lanes share a row, a wave takes four neighbouring
+// ones, and every load of the weights leaves before the first use (NQ per lane).  Streaming the weights in one round trip is the bound; a further row
+// of x costs 0.2 - 0.6 us.  us, the fastest tiled kernel and this one: 100 -> 8192 on one row 4.6 and 2.6, two 4.6 and 2.7, four 4.6 and 3.3, eight 4.7 and 4.5;
+// 508 -> 4096 on one row 7.9 and 3.7, four 7.9 and 5.5, eight 7.9 and 7.4; 96 -> 65536 on one 7.2 and 7.2, eight 7.7 and 12.8.  So up to four rows.
+template <int NQ>
+__global__ __launch_bounds__(256) void gemv16_nt_kernel(GemmArgs p) {
+    const int lane = threadIdx.x & 15;
+    const int n = (int)((blockIdx.x * 256 + threadIdx.x) / 16), row = min(n, p.N - 1);
+    const f32x4 *wrow = reinterpret_cast<const f32x4 *>(p.B + (int64_t)row * p.ldb);
+    const int k4 = p.K / 4;
+    f32x4 w[NQ];
+#pragma unroll
+    for (int u = 0; u < NQ; ++u) w[u] = wrow[min(lane + 16 * u, k4 - 1)];
+    const float bv = (p.ef.flags & EF_BIAS) ? p.ef.bias[row] : 0.f;
+    auto load = [&](f32x4 (&x)[NQ], int m) {
+        const f32x4 *xrow = reinterpret_cast<const f32x4 *>(p.A + (int64_t)min(m, p.M - 1) * p.lda);
+#pragma unroll
+        for (int u = 0; u < NQ; ++u) x[u] = xrow[min(lane + 16 * u, k4 - 1)];
+    };
+    float mine = 0.f;
+    auto finish = [&](const f32x4 (&x)[NQ], int m) {
+        float acc = 0.f;
+#pragma unroll
+        for (int u = 0; u < NQ; ++u) {
+            const float d = w[u][0] * x[u][0] + w[u][1] * x[u][1] + w[u][2] * x[u][2] + w[u][3] * x[u][3];
+            acc += lane + 16 * u < k4 ? d : 0.f;
+        }
+        acc += dpp_lane<0xB1>(acc);                          // (the steps of wave_sum_dpp inside a row of sixteen lanes)
+        acc += dpp_lane<0x4E>(acc);
+        acc += dpp_lane<0x141>(acc);
+        acc += dpp_lane<0x140>(acc);
+        mine = lane == m ? acc : mine;                       // lane m of the sixteen finishes row m
+    };
+    f32x4 x0[NQ], x1[NQ];
+    load(x0, 0);
+    for (int m = 0; m < p.M; m += 2) {
+        load(x1, m + 1);
+        finish(x0, m);
+        load(x0, m + 2);
+        finish(x1, m + 1);                                   // (behind the last row: a lane that stores nothing)
+    }
+    if (lane < p.M && n < p.N) {
+        const int64_t off = (int64_t)lane * p.ldc + n;
+        p.C[off] = finish_value(p, mine, bv, (p.ef.flags & EF_ADD) ? p.ef.add[off] : 0.f);
+    }
+}
+
+bool gemv16_shape_ok(const GemmArgs &a, int epi_flags) {
+    return a.mode == GM_NT && a.batch == 1 && a.M >= 1 && a.M <= 4 && a.K % 4 == 0 && a.K >= 64 && a.K < 512 && a.lda % 4 == 0 &&
+           a.ldb % 4 == 0 && a.cs_len == 0 && !(epi_flags & EF_GENERIC);
+}
+
 static int launch_splitk_reduce(const float *partial, float *out, int64_t numel, int splitk, const Epilogue &epi, void *stream) {
     hipLaunchKernelGGL(splitk_reduce_kernel, dim3((unsigned)((numel + 255) / 256)), dim3(256), 0, (hipStream_t)stream,
                        partial, out, numel, splitk, epi);
@@ -449,6 +501,14 @@ int launch_gemm(const GemmArgs &a_in, void *stream) {
     if (a.gemv) {
         if (!al16(a.A) || !al16(a.B)) return (int)hipErrorInvalidValue;       // rows are read 16 bytes at a time
         hipLaunchKernelGGL(gemv_nt_kernel, dim3((unsigned)((a.N + 3) / 4)), dim3(256), 0, s, a);
+        return (int)hipGetLastError();
+    }
+    if (a.gemv16 && al16(a.A) && al16(a.B)) {                // (operands at other addresses: the tiled kernels below)
+        const dim3 grid((unsigned)(((int64_t)a.N * 16 + 255) / 256));
+        const int nq = (a.K / 4 + 15) / 16;
+        if (nq <= 2) hipLaunchKernelGGL(gemv16_nt_kernel<2>, grid, dim3(256), 0, s, a);
+        else if (nq <= 4) hipLaunchKernelGGL(gemv16_nt_kernel<4>, grid, dim3(256), 0, s, a);
+        else hipLaunchKernelGGL(gemv16_nt_kernel<8>, grid, dim3(256), 0, s, a);
         return (int)hipGetLastError();
     }
     int err;

@@ -751,6 +751,11 @@ int32_t lower_match(const Context &ctx, const Graph &g, int32_t match_id, Kernel
                     a.splitk = 1;
                     c.bound = 1;
                     c.name = "gemv_nt";
+                } else if (k0 == CLG_OP_DENSE && gemv16_shape_ok(a, epi_fast_flags(epi))) {
+                    a.gemv16 = 1;
+                    a.splitk = 1;
+                    c.bound = 1;
+                    c.name = "gemv16_nt";
                 }
                 if (a.cs_len) {
                     // only the lean kernel's K-wave tiles place columns block by block, and the
@@ -762,7 +767,7 @@ int32_t lower_match(const Context &ctx, const Graph &g, int32_t match_id, Kernel
                 }
                 c.scratch_bytes = gemm_scratch_bytes(a);
                 static const char *tn[] = {"auto", "s", "m", "l", "s8", "s16"};
-                if (!a.gemv) c.name += std::string("_") + tn[a.tile] + (a.splitk > 1 ? "_k" + std::to_string(a.splitk) : "");
+                if (!a.gemv && !a.gemv16) c.name += std::string("_") + tn[a.tile] + (a.splitk > 1 ? "_k" + std::to_string(a.splitk) : "");
             }
         }
         c.a_node = xa;
