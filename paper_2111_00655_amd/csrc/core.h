@@ -197,6 +197,12 @@ struct Region {
     std::vector<void *> packed;            // per member: weights packed for that shape (owned by the plan)
 };
 
+// Neighbouring kernels of the plan, each reading what the one before it made, that share launches (unless they are timed one by one or the plan
+// has several lanes): a split contraction and the layer norm behind it, which adds up the partial results itself.
+struct Join {
+    int32_t first, n;
+};
+
 struct Plan {
     Context *ctx = nullptr;
     Graph *graph = nullptr;            // read at every execution: the graph outlives its plans, unchanged
@@ -212,6 +218,8 @@ struct Plan {
     std::vector<void *> packed;            // call -> re-packed weights (device memory owned by the plan) or null
     std::vector<Region> regions;
     std::vector<int32_t> region_of;        // call -> index into regions, -1 none
+    std::vector<Join> joins;
+    std::vector<int32_t> join_of;          // call -> index into joins, -1 none
     std::vector<char> fuse_mark;           // per call, scratch of an execution: 1 launched with its region, 2 carried its region
     std::vector<std::vector<int32_t>> ahead;   // call -> later calls whose packed weights it reads ahead
     size_t workspace_bytes = 0;

@@ -456,7 +456,7 @@ int launch_b3_pack(const B3Args &a, const float *w, void *dst, void *stream) {
     return (int)hipGetLastError();
 }
 
-int launch_b3(const B3Args &a_in, void *stream) {
+int launch_b3(const B3Args &a_in, void *stream, bool reduce) {
     B3Args a = a_in;
     hipStream_t s = (hipStream_t)stream;
     a.ef = make_epi_fast(a.epi);
@@ -468,7 +468,7 @@ int launch_b3(const B3Args &a_in, void *stream) {
     else if (a.taps == 9) e = a.KD > 1 ? b3_launch_tile<9, true, false>(a, s) : b3_launch_tile<9, false, false>(a, s);
     else if (a.taps == 4) e = b3_launch_tile<4, false, false>(a, s);
     else e = (int)hipErrorInvalidValue;
-    if (e || a.splitk <= 1) return e;
+    if (e || a.splitk <= 1 || !reduce) return e;
     return launch_b3_reduce(a, s);
 }
 

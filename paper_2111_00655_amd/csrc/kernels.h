@@ -331,7 +331,7 @@ bool b3_resolve(const GemmArgs &a, int tile, int epi_flags, int n_cus, bool spli
 size_t b3_pack_bytes(const B3Args &a);
 size_t b3_scratch_bytes(const B3Args &a);
 int launch_b3_pack(const B3Args &a, const float *w, void *dst, void *stream);
-int launch_b3(const B3Args &a, void *stream);
+int launch_b3(const B3Args &a, void *stream, bool reduce = true);      // reduce: partial results are added up as well
 // The kernel of `n` dense layers of one shape and tail in one launch; members differ in pointers only.
 bool b3_region_resolve(const GemmArgs *members, int n, int n_cus, B3Args *out);
 int launch_b3_region(const B3Args *members, int n, void *stream);
@@ -364,6 +364,13 @@ struct RowwiseArgs {
     const float *tab[3];
     const int32_t *gid[3];
 };
+// In the place of x of a layer norm: partial results [splitk][rows * len] of a split contraction, to which its reduction would add bias and residual.
+struct SplitSum {
+    const float *partial;
+    const float *bias, *add;               // or null
+    int32_t splitk, numel;
+};
+struct NoSum {};
 constexpr int kAheadWaves = 256;           // read-ahead workgroups (one wave each) of a layer norm
 bool rowwise_reads_ahead(const RowwiseArgs &a);        // shape and prologue are the one-round-trip layer norm's (pointer alignment aside)
 
@@ -394,6 +401,10 @@ int launch_gemm(const GemmArgs &a, void *stream);
 int launch_direct_conv(const DirectConvArgs &a, void *stream);
 int launch_pool(const PoolArgs &a, void *stream);
 int launch_rowwise(const RowwiseArgs &a, const Ahead *ahead, void *stream);   // ahead: null or what the one-round-trip layer norm reads ahead
+// The one-round-trip layer norm of partial results (a.x unused): whether it takes shape and prologue, and the pointers once they are bound.
+bool rowwise_sums_shape_ok(const RowwiseArgs &a);
+bool rowwise_sums_ok(const RowwiseArgs &a, const SplitSum &s);
+int launch_rowwise_sum(const RowwiseArgs &a, const SplitSum &sum, const Ahead *ahead, void *stream);
 int launch_eltwise(const EltwiseArgs &a, void *stream);
 int launch_layout(const LayoutArgs &a, void *stream);
 int launch_concat(const ConcatArgs &a, void *stream);

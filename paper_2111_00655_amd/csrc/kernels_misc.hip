@@ -207,8 +207,11 @@ __global__ __launch_bounds__(256) void rowwise_block_kernel(RowwiseArgs a) {
 // gathered table rows (an embedding).  Same arithmetic as above: mean, biased variance of the centred
 // values, scale and shift.  len % 4 == 0, len <= 256 * V4, all pointers 16-byte aligned.
 // R: Ahead (the first kAheadWaves workgroups read ahead; a constant, so that the others wait for nothing to know that they do not) or NoAhead.
-template <int V4, class R>
-__global__ __launch_bounds__(64) void ln_wave_kernel(RowwiseArgs a, EpiFast ef, R ra) {
+// P: SplitSum (x is the sum of a split contraction's partial results, in slice order, and its bias and residual, which saves the launch that would
+// add them: 4.8 us between two kernels on 389 rows of 768) or NoSum.
+template <int V4, class R, class P>
+__global__ __launch_bounds__(64) void ln_wave_kernel(RowwiseArgs a, EpiFast ef, R ra, P parts) {
+    constexpr bool SUM = std::is_same_v<P, SplitSum>;
     const int lane = threadIdx.x;
     int row = blockIdx.x;
     if constexpr (std::is_same_v<R, Ahead>) {
@@ -229,7 +232,8 @@ __global__ __launch_bounds__(64) void ln_wave_kernel(RowwiseArgs a, EpiFast ef, 
         p1 = row_of(1);
         if (a.n_gather > 2) p2 = row_of(2);
     } else {
-        p0 = reinterpret_cast<const float4 *>(a.x + (int64_t)row * a.len);
+        if constexpr (SUM) p0 = reinterpret_cast<const float4 *>(parts.partial + (int64_t)row * a.len);
+        else p0 = reinterpret_cast<const float4 *>(a.x + (int64_t)row * a.len);
         if (ef.flags & EF_BIAS) p1 = reinterpret_cast<const float4 *>(ef.bias);
         if (ef.flags & EF_ADD) p2 = reinterpret_cast<const float4 *>(ef.add + (int64_t)row * a.len);
     }
@@ -239,12 +243,46 @@ __global__ __launch_bounds__(64) void ln_wave_kernel(RowwiseArgs a, EpiFast ef, 
         const int c = lane + kWave * q;
         const bool in = c < len4;
         const int cc = in ? c : 0;
-        v[q] = p0[cc];
+        if constexpr (!SUM) v[q] = p0[cc];
         t1[q] = p1 ? p1[cc] : zero;
         t2[q] = p2 ? p2[cc] : zero;
         ga[q] = g4[cc];
         be[q] = b4[cc];
         if (!in) v[q] = t1[q] = t2[q] = zero;
+    }
+    if constexpr (SUM) {                                     // the reduction's own order: slice after slice, then bias, then residual
+        float4 db[V4], da[V4];
+        const float4 *d1 = reinterpret_cast<const float4 *>(parts.bias), *d2 = parts.add ? reinterpret_cast<const float4 *>(parts.add + (int64_t)row * a.len) : nullptr;
+#pragma unroll
+        for (int q = 0; q < V4; ++q) {
+            const int cc = lane + kWave * q < len4 ? lane + kWave * q : 0;
+            db[q] = d1 ? d1[cc] : zero;
+            da[q] = d2 ? d2[cc] : zero;
+            v[q] = zero;
+        }
+        constexpr int F = V4 <= 4 ? 4 : 2;                   // slices in flight
+        const uint32_t step = (uint32_t)parts.numel / 4;
+        for (int k = 0; k < parts.splitk; k += F) {
+            float4 s[F][V4];
+#pragma unroll
+            for (int e = 0; e < F; ++e)
+#pragma unroll
+                for (int q = 0; q < V4; ++q) {
+                    const int c = lane + kWave * q;
+                    s[e][q] = p0[(uint32_t)min(k + e, parts.splitk - 1) * step + (uint32_t)(c < len4 ? c : 0)];
+                }
+#pragma unroll
+            for (int e = 0; e < F; ++e)
+#pragma unroll
+                for (int q = 0; q < V4; ++q)
+                    if (k + e < parts.splitk) { v[q].x += s[e][q].x; v[q].y += s[e][q].y; v[q].z += s[e][q].z; v[q].w += s[e][q].w; }
+        }
+#pragma unroll
+        for (int q = 0; q < V4; ++q) {
+            v[q].x = v[q].x + db[q].x + da[q].x; v[q].y = v[q].y + db[q].y + da[q].y;
+            v[q].z = v[q].z + db[q].z + da[q].z; v[q].w = v[q].w + db[q].w + da[q].w;
+            if (lane + kWave * q >= len4) v[q] = zero;
+        }
     }
     float sum = 0.f;
 #pragma unroll
@@ -337,13 +375,33 @@ __global__ __launch_bounds__(256) void rowwise_long_kernel(RowwiseArgs a) {
     }
 }
 
-template <class R>
-static void launch_ln_wave(const RowwiseArgs &a, const EpiFast &ef, const R &r, int waves, hipStream_t s) {
+template <class R, class P>
+static void launch_ln_wave(const RowwiseArgs &a, const EpiFast &ef, const R &r, const P &p, int waves, hipStream_t s) {
     const int v4 = (a.len / 4 + kWave - 1) / kWave;
-    if (v4 <= 1) hipLaunchKernelGGL((ln_wave_kernel<1, R>), dim3(waves), dim3(kWave), 0, s, a, ef, r);
-    else if (v4 <= 2) hipLaunchKernelGGL((ln_wave_kernel<2, R>), dim3(waves), dim3(kWave), 0, s, a, ef, r);
-    else if (v4 <= 4) hipLaunchKernelGGL((ln_wave_kernel<4, R>), dim3(waves), dim3(kWave), 0, s, a, ef, r);
-    else hipLaunchKernelGGL((ln_wave_kernel<8, R>), dim3(waves), dim3(kWave), 0, s, a, ef, r);
+    if (v4 <= 1) hipLaunchKernelGGL((ln_wave_kernel<1, R, P>), dim3(waves), dim3(kWave), 0, s, a, ef, r, p);
+    else if (v4 <= 2) hipLaunchKernelGGL((ln_wave_kernel<2, R, P>), dim3(waves), dim3(kWave), 0, s, a, ef, r, p);
+    else if (v4 <= 4) hipLaunchKernelGGL((ln_wave_kernel<4, R, P>), dim3(waves), dim3(kWave), 0, s, a, ef, r, p);
+    else hipLaunchKernelGGL((ln_wave_kernel<8, R, P>), dim3(waves), dim3(kWave), 0, s, a, ef, r, p);
+}
+
+bool rowwise_sums_shape_ok(const RowwiseArgs &a) {
+    EpiFast ef{};
+    return !a.n_gather && ln_wave_shape_ok(a, &ef);
+}
+
+bool rowwise_sums_ok(const RowwiseArgs &a, const SplitSum &s) {
+    RowwiseArgs b = a;
+    b.x = s.partial;
+    EpiFast ef{};
+    return !a.n_gather && ln_wave_ok(b, &ef) && ((uintptr_t)s.bias & 15) == 0 && ((uintptr_t)s.add & 15) == 0;
+}
+
+int launch_rowwise_sum(const RowwiseArgs &a, const SplitSum &sum, const Ahead *ahead, void *stream) {
+    const EpiFast ef = make_epi_fast(a.pro);
+    if (!rowwise_sums_ok(a, sum)) return (int)hipErrorInvalidValue;
+    if (ahead && ahead->n) launch_ln_wave(a, ef, *ahead, sum, a.rows + kAheadWaves, (hipStream_t)stream);
+    else launch_ln_wave(a, ef, NoAhead{}, sum, a.rows, (hipStream_t)stream);
+    return (int)hipGetLastError();
 }
 
 int launch_rowwise(const RowwiseArgs &a, const Ahead *ahead, void *stream) {
@@ -354,8 +412,8 @@ int launch_rowwise(const RowwiseArgs &a, const Ahead *ahead, void *stream) {
     EpiFast ef{};
     if (ln_wave_ok(a, &ef)) {                                      // layer norm in one memory round trip
         // (read-ahead waves first, so that theirs are the first loads to leave: behind the rows all of BERT-base, 200 rows, took 797 instead of 785 us)
-        if (ahead && ahead->n) launch_ln_wave(a, ef, *ahead, a.rows + kAheadWaves, s);
-        else launch_ln_wave(a, ef, NoAhead{}, a.rows, s);
+        if (ahead && ahead->n) launch_ln_wave(a, ef, *ahead, NoSum{}, a.rows + kAheadWaves, s);
+        else launch_ln_wave(a, ef, NoAhead{}, NoSum{}, a.rows, s);
         return (int)hipGetLastError();
     }
     if (a.n_gather) return (int)hipErrorInvalidValue;              // only the kernel above gathers

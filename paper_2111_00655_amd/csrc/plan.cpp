@@ -280,6 +280,36 @@ void find_regions(const Context &ctx, const Graph &g, Plan *plan) {
     }
 }
 
+// Finds the joins of a sequence in its final order.
+void find_joins(const Graph &g, Plan *plan) {
+    const std::vector<KernelCall> &calls = plan->calls;
+    const size_t nc = calls.size();
+    plan->joins.clear();
+    plan->join_of.assign(nc, -1);
+    std::vector<int32_t> readers(g.nodes.size(), 0);
+    for (const KernelCall &c : calls)
+        for (int32_t v : operands_of(c)) ++readers[v];
+    auto add = [&](const Join &j) {
+        for (int32_t k = 0; k < j.n; ++k) plan->join_of[j.first + k] = (int32_t)plan->joins.size();
+        plan->joins.push_back(j);
+    };
+    auto alone = [&](size_t i, int32_t kind) { return i < nc && calls[i].kind == kind && plan->region_of[i] < 0 && plan->join_of[i] < 0; };
+    for (size_t i = 0; i < nc; ++i) {
+        // a split dense layer whose result only the layer norm behind it reads, as what is normalised
+        if (!alone(i, CALL_B3) || !alone(i + 1, CALL_ROWWISE)) continue;
+        const KernelCall &c = calls[i], &n = calls[i + 1];
+        const B3Args &b = c.b3;
+        if (!b.dense || b.splitk < 2 || n.a_node != c.out_node || readers[c.out_node] != 1 || g.is_output[c.out_node]) continue;
+        if (n.row.mode != 1 || n.row.rows != b.Nrows || n.row.len != b.Cout || b.ldy != b.Cout || !rowwise_sums_shape_ok(n.row)) continue;
+        const int flags = epi_fast_flags(b.epi);
+        if (flags & ~(EF_BIAS | EF_ADD) || ((flags & EF_BIAS) && (b.epi.bias_inner > 1 || b.epi.bias_c != b.Cout))) continue;
+        Join j{};
+        j.first = (int32_t)i;
+        j.n = 2;
+        add(j);
+    }
+}
+
 }  // namespace
 
 size_t plan_num_launches(const Plan &p) {
@@ -390,6 +420,7 @@ int32_t compile_plan(Context &ctx, Graph &g, const int32_t *ids, size_t n, Plan 
         plan->calls.push_back(std::move(c));
     }
     find_regions(ctx, g, plan);
+    find_joins(g, plan);
 
     // every operand must be a leaf or the sink of an earlier group
     const size_t nc = plan->calls.size();
@@ -458,6 +489,7 @@ int32_t compile_plan(Context &ctx, Graph &g, const int32_t *ids, size_t n, Plan 
         if (root[v] == v && release_at[v] >= 0 && g.nodes[v].is_op() && plan->value_output[v] < 0)
             releases[(size_t)release_at[v]].push_back(v);
     Arena arena;
+    const std::vector<int64_t> no_offset(n_nodes, -1);
     auto place_output = [&](size_t i) {
         const int32_t v = plan->calls[i].out_node, r = root[v];
         if (plan->value_output[r] >= 0) {
@@ -472,24 +504,44 @@ int32_t compile_plan(Context &ctx, Graph &g, const int32_t *ids, size_t n, Plan 
     };
     // The members of a region may run as one launch: all their results are placed before any of them
     // runs, and what they read is released only after the last of them.  The plan so made holds for
-    // every choice of digits (members run one by one use the same buffers in the same order).
-    for (size_t i = 0; i < nc; ++i) {
-        const KernelCall &c = plan->calls[i];
-        const int32_t ri = plan->region_of[i];
-        const bool first_of_region = ri >= 0 && plan->regions[ri].members.front() == (int32_t)i;
-        const bool last_of_region = ri >= 0 && plan->regions[ri].members.back() == (int32_t)i;
-        if (ri < 0) place_output(i);
-        else if (first_of_region)
-            for (int32_t m : plan->regions[ri].members) place_output((size_t)m);
-        if (c.scratch_bytes) {
-            plan->scratch_offset[i] = arena.alloc((int64_t)c.scratch_bytes);
-            arena.release(plan->scratch_offset[i]);
-        }
-        if (ri < 0) {
-            for (int32_t r2 : releases[i]) arena.release(plan->value_offset[r2]);
-        } else if (last_of_region) {
-            for (int32_t m : plan->regions[ri].members)
+    // every choice of digits (members run one by one use the same buffers in the same order).  So it is with a join,
+    // whose last kernel also reads the first one's scratch.
+    auto plan_memory = [&] {
+        arena = Arena{};
+        plan->value_offset = no_offset;
+        for (size_t i = 0; i < nc; ++i) {
+            const KernelCall &c = plan->calls[i];
+            const int32_t ri = plan->region_of[i], ji = plan->join_of[i];
+            std::vector<int32_t> only{(int32_t)i};
+            if (ji >= 0) {
+                only.clear();
+                for (int32_t k = 0; k < plan->joins[ji].n; ++k) only.push_back(plan->joins[ji].first + k);
+            }
+            const std::vector<int32_t> &together = ri >= 0 ? plan->regions[ri].members : only;
+            if (together.front() == (int32_t)i)
+                for (int32_t m : together) place_output((size_t)m);
+            if (c.scratch_bytes) {
+                plan->scratch_offset[i] = arena.alloc((int64_t)c.scratch_bytes);
+                if (ji < 0) arena.release(plan->scratch_offset[i]);
+            }
+            if (together.back() != (int32_t)i) continue;
+            for (int32_t m : together) {
+                if (ji >= 0 && plan->calls[m].scratch_bytes) arena.release(plan->scratch_offset[m]);
                 for (int32_t r2 : releases[(size_t)m]) arena.release(plan->value_offset[r2]);
+            }
+        }
+        return arena.peak;
+    };
+    if (plan_memory() > (int64_t)CLG_STATIC_WORKSPACE_BYTES && !plan->joins.empty()) {
+        // joins keep a little more at a time: not where that alone keeps a plan out of the fixed workspace
+        std::vector<Join> joins = std::move(plan->joins);
+        std::vector<int32_t> join_of = std::move(plan->join_of);
+        plan->joins.clear();
+        plan->join_of.assign(nc, -1);
+        if (plan_memory() > (int64_t)CLG_STATIC_WORKSPACE_BYTES) {
+            plan->joins = std::move(joins);
+            plan->join_of = std::move(join_of);
+            (void)plan_memory();
         }
     }
     plan->workspace_bytes = (size_t)arena.peak;
@@ -843,6 +895,41 @@ int32_t launch_call(const KernelCall &c, const void *a, const void *b, const voi
     return CLG_OK;
 }
 
+// The launches of a join, operands by `ptr_of`; *done = false: the addresses are such that they run one by one.
+template <class F>
+static int32_t launch_join(const Plan &p, const Join &j, const F &ptr_of, void *scratch, const Ahead *ahead, void *stream, bool *done) {
+    const size_t first = (size_t)j.first, last = first + (size_t)j.n - 1;
+    auto in = [&](int32_t v) { return (const float *)ptr_of(v); };
+    auto out = [&](size_t i) { return (float *)const_cast<void *>(ptr_of(p.calls[i].out_node)); };
+    auto bind = [&](Epilogue e, const KernelCall &c) {
+        for (int s = 0; s < e.n; ++s) e.s[s].ptr = in(c.epi_nodes[s]);
+        return e;
+    };
+    for (size_t i = first; i <= last; ++i)
+        for (int32_t v : {p.calls[i].a_node, p.calls[i].b_node, p.calls[i].c_node})
+            if (v >= 0 && !ptr_of(v)) return fail(CLG_INVALID_ARG, "constant node %d has no device pointer", v);
+    int err;
+    *done = true;
+    const KernelCall &c = p.calls[first], &n = p.calls[last];
+    if (!p.packed[first]) return fail(CLG_INVALID_ARG, "%s needs packed weights, none were prepared", c.name.c_str());
+    B3Args k = c.b3;
+    k.x = in(c.a_node); k.w = p.packed[first]; k.y = out(first); k.partial = (float *)scratch;
+    k.epi = bind(c.b3.epi, c);
+    const EpiFast ef = make_epi_fast(k.epi);
+    RowwiseArgs r = n.row;
+    r.gamma = in(n.b_node); r.beta = in(n.c_node); r.y = out(last);
+    r.pro = bind(n.row.pro, n);
+    const SplitSum sum{k.partial, ef.flags & EF_BIAS ? ef.bias : nullptr, ef.flags & EF_ADD ? ef.add : nullptr, k.splitk, (int32_t)k.c_numel};
+    if (!rowwise_sums_ok(r, sum)) {
+        *done = false;
+        return CLG_OK;
+    }
+    err = launch_b3(k, stream, false);
+    if (!err) err = launch_rowwise_sum(r, sum, ahead, stream);
+    if (err != 0) return fail(CLG_HIP_ERROR, "launch of %s and what follows it failed: %s", p.calls[first].name.c_str(), hipGetErrorString((hipError_t)err));
+    return CLG_OK;
+}
+
 int32_t execute_plan(Plan &p, const void *const *inputs, void *const *outputs, void *workspace,
                      size_t ws_bytes, void *stream, int64_t *kernel_ns) {
     Context &ctx = *p.ctx;
@@ -936,6 +1023,17 @@ int32_t execute_plan(Plan &p, const void *const *inputs, void *const *outputs, v
     for (size_t i = 0; i < p.calls.size() && rc == CLG_OK; ++i) {
         const KernelCall &c = p.calls[i];
         if (fuse && done[i]) continue;
+        if (!lanes && !kernel_ns && p.join_of[i] >= 0 && p.joins[(size_t)p.join_of[i]].first == (int32_t)i) {
+            const Join &j = p.joins[(size_t)p.join_of[i]];
+            bool joined = false;
+            rc = launch_join(p, j, ptr_of, p.scratch_offset[i] >= 0 ? (char *)workspace + p.scratch_offset[i] : nullptr,
+                             ahead_of(i + (size_t)j.n - 1, &ahead), stream, &joined);
+            if (rc != CLG_OK) break;
+            if (joined) {
+                i += (size_t)j.n - 1;
+                continue;
+            }
+        }
         if (fuse && p.region_of[i] >= 0 && p.handed[i]) {
             const Region &r = p.regions[(size_t)p.region_of[i]];
             const bool sep = !r.mixed && c.kind == CALL_SEPCONV;
