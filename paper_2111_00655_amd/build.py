@@ -30,7 +30,7 @@ SOURCES = ["graph.cpp", "matcher.cpp", "search.cpp", "lower.cpp", "plan.cpp",
            "profiler.cpp", "rules.cpp", "evolve.cpp", "capi.cpp", "kernels_gemm.hip", "gemm_fast_mm.hip", "gemm_fast_conv.hip",
            "gemm_lean_mm.hip", "gemm_lean_conv.hip", "gemm_rf.hip",
            "gemm_b3.hip", "gemm_b3_point.hip", "gemm_b3_nine.hip", "gemm_b3_depth.hip", "gemm_b3_phase.hip", "gemm_b3_first.hip",
-           "kernels_misc.hip", "sepconv.hip", "region_mix.hip", "attention.hip", "static_ws.hip"]
+           "kernels_misc.hip", "sepconv.hip", "region_mix.hip", "classifier.hip", "attention.hip", "static_ws.hip"]
 
 BUILD_SAN = os.path.join(HERE, "_build_san")
 LIB_SAN = os.path.join(HERE, "libcollage_mi_san.so")

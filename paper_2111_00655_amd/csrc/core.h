@@ -197,10 +197,12 @@ struct Region {
     std::vector<void *> packed;            // per member: weights packed for that shape (owned by the plan)
 };
 
-// Neighbouring kernels of the plan, each reading what the one before it made, that share launches (unless they are timed one by one or the plan
-// has several lanes): a split contraction and the layer norm behind it, which adds up the partial results itself.
+// Neighbouring kernels of the plan, each reading what the one before it made, that share launches (unless they are timed one by one): JOIN_CLASSIFIER [global average pool,] dense layer and softmax in one; JOIN_NORM a split contraction and the layer norm behind it, which
+// adds up the partial results itself.
+enum JoinKind : int32_t { JOIN_CLASSIFIER = 1, JOIN_NORM };
 struct Join {
-    int32_t first, n;
+    int32_t kind, first, n;
+    ClassifierArgs classifier;             // pointers null
 };
 
 struct Plan {

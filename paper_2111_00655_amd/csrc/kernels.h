@@ -374,6 +374,20 @@ struct NoSum {};
 constexpr int kAheadWaves = 256;           // read-ahead workgroups (one wave each) of a layer norm
 bool rowwise_reads_ahead(const RowwiseArgs &a);        // shape and prologue are the one-round-trip layer norm's (pointer alignment aside)
 
+// ---- the end of a classifier in one kernel (classifier.hip): [global average pool] -> dense -> softmax ------------------------
+struct ClassifierArgs {
+    const float *x;                        // [rows][K][hw], or [rows][lda] where nothing is pooled (hw = 0)
+    float *pooled;                         // [rows][lda]
+    const float *w;                        // [N][ldb], or packed for the register-fed kernel (ts = 32 | 16, ngtot)
+    float *logits;                         // [rows][ldc]
+    float *prob;                           // [rows][N]
+    EpiFast ef;                            // of the dense layer
+    int32_t rows, K, N, hw, lda, ldb, ldc, ts, ngtot;
+};
+// Fills `a` from the calls' arguments (pool may be null); false: the kernel does not take them.
+bool classifier_resolve(const PoolArgs *pool, const GemmArgs &dense, const RowwiseArgs &softmax, ClassifierArgs *a);
+int launch_classifier(const ClassifierArgs &a, void *stream);
+
 // ---- elementwise chain / gather --------------------------------------------------------------
 struct EltwiseArgs {
     const float *x;                        // source tensor, or the table when ids != null

@@ -289,12 +289,26 @@ void find_joins(const Graph &g, Plan *plan) {
     std::vector<int32_t> readers(g.nodes.size(), 0);
     for (const KernelCall &c : calls)
         for (int32_t v : operands_of(c)) ++readers[v];
+    auto reads = [](const KernelCall &c, int32_t v) {
+        const std::vector<int32_t> in = operands_of(c);
+        return std::count(in.begin(), in.end(), v);
+    };
     auto add = [&](const Join &j) {
         for (int32_t k = 0; k < j.n; ++k) plan->join_of[j.first + k] = (int32_t)plan->joins.size();
         plan->joins.push_back(j);
     };
     auto alone = [&](size_t i, int32_t kind) { return i < nc && calls[i].kind == kind && plan->region_of[i] < 0 && plan->join_of[i] < 0; };
     for (size_t i = 0; i < nc; ++i) {
+        for (size_t d : {i + 1, i}) {                        // the dense layer: behind a pool, or the first
+            if (plan->join_of[i] >= 0 || !alone(i, d == i ? CALL_GEMM : CALL_POOL) || !alone(d, CALL_GEMM) || !alone(d + 1, CALL_ROWWISE)) continue;
+            const KernelCall &dense = calls[d], &soft = calls[d + 1];
+            if (dense.gemm_swap || soft.a_node != dense.out_node || (d != i && (dense.a_node != calls[i].out_node || reads(dense, calls[i].out_node) != 1))) continue;
+            Join j{};
+            j.kind = JOIN_CLASSIFIER;
+            j.first = (int32_t)i;
+            j.n = (int32_t)(d + 2 - i);
+            if (classifier_resolve(d == i ? nullptr : &calls[i].pool, dense.gemm, soft.row, &j.classifier)) add(j);
+        }
         // a split dense layer whose result only the layer norm behind it reads, as what is normalised
         if (!alone(i, CALL_B3) || !alone(i + 1, CALL_ROWWISE)) continue;
         const KernelCall &c = calls[i], &n = calls[i + 1];
@@ -304,6 +318,7 @@ void find_joins(const Graph &g, Plan *plan) {
         const int flags = epi_fast_flags(b.epi);
         if (flags & ~(EF_BIAS | EF_ADD) || ((flags & EF_BIAS) && (b.epi.bias_inner > 1 || b.epi.bias_c != b.Cout))) continue;
         Join j{};
+        j.kind = JOIN_NORM;
         j.first = (int32_t)i;
         j.n = 2;
         add(j);
@@ -315,6 +330,7 @@ void find_joins(const Graph &g, Plan *plan) {
 size_t plan_num_launches(const Plan &p) {
     size_t n = 0;
     for (size_t i = 0; i < p.calls.size(); ++i) n += p.elided[i] ? 0 : 1;
+    for (const Join &j : p.joins) n -= j.kind == JOIN_CLASSIFIER ? (size_t)j.n - 1 : 0;      // (a split layer's join saves its reduction, which counts as none)
     if (p.max_lanes > 1 || p.handed.empty()) return n;
     for (const Region &r : p.regions) {
         size_t in = 0;
@@ -690,6 +706,13 @@ void schedule_lanes(Plan *plan) {
     std::vector<int32_t> last(lanes, -1);            // last call queued on each lane
     for (size_t j = 0; j < nc; ++j) {
         int pick = (!plan->handed.empty() && !plan->handed[j]) ? 0 : -1;   // not handed over: the caller's stream
+        if (plan->join_of[j] >= 0) {                       // a join runs on one lane, the caller's stream if any of its kernels has to
+            const Join &jn = plan->joins[(size_t)plan->join_of[j]];
+            if (jn.first < (int32_t)j) pick = plan->lane[(size_t)jn.first];
+            else
+                for (int32_t k = 0; k < jn.n && !plan->handed.empty(); ++k)
+                    if (!plan->handed[j + (size_t)k]) pick = 0;
+        }
         const int home = deps[j].empty() ? 0 : plan->lane[deps[j].back()];
         if (pick < 0 && depends(j, last[home])) pick = home;
         for (int l = 0; l < lanes && pick < 0; ++l)
@@ -910,22 +933,41 @@ static int32_t launch_join(const Plan &p, const Join &j, const F &ptr_of, void *
             if (v >= 0 && !ptr_of(v)) return fail(CLG_INVALID_ARG, "constant node %d has no device pointer", v);
     int err;
     *done = true;
-    const KernelCall &c = p.calls[first], &n = p.calls[last];
-    if (!p.packed[first]) return fail(CLG_INVALID_ARG, "%s needs packed weights, none were prepared", c.name.c_str());
-    B3Args k = c.b3;
-    k.x = in(c.a_node); k.w = p.packed[first]; k.y = out(first); k.partial = (float *)scratch;
-    k.epi = bind(c.b3.epi, c);
-    const EpiFast ef = make_epi_fast(k.epi);
-    RowwiseArgs r = n.row;
-    r.gamma = in(n.b_node); r.beta = in(n.c_node); r.y = out(last);
-    r.pro = bind(n.row.pro, n);
-    const SplitSum sum{k.partial, ef.flags & EF_BIAS ? ef.bias : nullptr, ef.flags & EF_ADD ? ef.add : nullptr, k.splitk, (int32_t)k.c_numel};
-    if (!rowwise_sums_ok(r, sum)) {
-        *done = false;
-        return CLG_OK;
+    if (j.kind == JOIN_CLASSIFIER) {
+        const size_t d = last - 1;
+        const KernelCall &c = p.calls[d];
+        ClassifierArgs a = j.classifier;
+        if (c.pack_bytes && !p.packed[d]) return fail(CLG_INVALID_ARG, "%s needs packed weights, none were prepared", c.name.c_str());
+        a.x = in(p.calls[first].a_node);
+        a.pooled = d > first ? out(first) : nullptr;
+        a.w = c.pack_bytes ? (const float *)p.packed[d] : in(c.b_node);
+        a.logits = out(d);
+        a.prob = out(last);
+        a.ef = make_epi_fast(bind(c.gemm.epi, c));
+        // (an image is read while results of others are written)
+        const uintptr_t x0 = (uintptr_t)a.x, x1 = x0 + 4 * (uintptr_t)a.rows * (a.hw ? (uintptr_t)a.K * a.hw : (uintptr_t)a.lda);
+        for (const float *y : {a.logits, a.prob})
+            if ((uintptr_t)y < x1 && x0 < (uintptr_t)y + 4 * (uintptr_t)a.rows * a.N) *done = false;
+        if (!*done) return CLG_OK;
+        err = launch_classifier(a, stream);
+    } else {
+        const KernelCall &c = p.calls[first], &n = p.calls[last];
+        if (!p.packed[first]) return fail(CLG_INVALID_ARG, "%s needs packed weights, none were prepared", c.name.c_str());
+        B3Args k = c.b3;
+        k.x = in(c.a_node); k.w = p.packed[first]; k.y = out(first); k.partial = (float *)scratch;
+        k.epi = bind(c.b3.epi, c);
+        const EpiFast ef = make_epi_fast(k.epi);
+        RowwiseArgs r = n.row;
+        r.gamma = in(n.b_node); r.beta = in(n.c_node); r.y = out(last);
+        r.pro = bind(n.row.pro, n);
+        const SplitSum sum{k.partial, ef.flags & EF_BIAS ? ef.bias : nullptr, ef.flags & EF_ADD ? ef.add : nullptr, k.splitk, (int32_t)k.c_numel};
+        if (!rowwise_sums_ok(r, sum)) {
+            *done = false;
+            return CLG_OK;
+        }
+        err = launch_b3(k, stream, false);
+        if (!err) err = launch_rowwise_sum(r, sum, ahead, stream);
     }
-    err = launch_b3(k, stream, false);
-    if (!err) err = launch_rowwise_sum(r, sum, ahead, stream);
     if (err != 0) return fail(CLG_HIP_ERROR, "launch of %s and what follows it failed: %s", p.calls[first].name.c_str(), hipGetErrorString((hipError_t)err));
     return CLG_OK;
 }
@@ -1023,14 +1065,24 @@ int32_t execute_plan(Plan &p, const void *const *inputs, void *const *outputs, v
     for (size_t i = 0; i < p.calls.size() && rc == CLG_OK; ++i) {
         const KernelCall &c = p.calls[i];
         if (fuse && done[i]) continue;
-        if (!lanes && !kernel_ns && p.join_of[i] >= 0 && p.joins[(size_t)p.join_of[i]].first == (int32_t)i) {
+        if (!kernel_ns && p.join_of[i] >= 0 && p.joins[(size_t)p.join_of[i]].first == (int32_t)i) {
             const Join &j = p.joins[(size_t)p.join_of[i]];
+            const size_t end = i + (size_t)j.n;
+            void *st = stream_of(i);
+            if (lanes)
+                for (size_t k = i; k < end; ++k)
+                    for (int32_t w : p.waits[k])             // (no kernel of the join is on another lane)
+                        if (hipStreamWaitEvent((hipStream_t)st, (hipEvent_t)p.events[w], 0) != hipSuccess)
+                            rc = fail(CLG_HIP_ERROR, "hipStreamWaitEvent failed");
+            if (rc != CLG_OK) break;
             bool joined = false;
-            rc = launch_join(p, j, ptr_of, p.scratch_offset[i] >= 0 ? (char *)workspace + p.scratch_offset[i] : nullptr,
-                             ahead_of(i + (size_t)j.n - 1, &ahead), stream, &joined);
+            rc = launch_join(p, j, ptr_of, p.scratch_offset[i] >= 0 ? (char *)workspace + p.scratch_offset[i] : nullptr, ahead_of(end - 1, &ahead), st, &joined);
             if (rc != CLG_OK) break;
             if (joined) {
-                i += (size_t)j.n - 1;
+                for (size_t k = i; k < end; ++k)
+                    if (lanes && p.signals[k] && hipEventRecord((hipEvent_t)p.events[k], (hipStream_t)st) != hipSuccess)
+                        rc = fail(CLG_HIP_ERROR, "hipEventRecord failed");
+                i = end - 1;
                 continue;
             }
         }

@@ -1,4 +1,5 @@
-"""A split dense layer whose partial results the layer norm behind it adds up: one by one (timed) and joined."""
+"""Kernels that share launches with what reads them: [global average pool,] dense layer and softmax in one, and a split dense layer whose partial results
+the layer norm behind it adds up."""
 import numpy as np
 import pytest
 import torch
@@ -11,13 +12,80 @@ from paper_2111_00655_amd import binding as B
 pytestmark = pytest.mark.gpu
 
 
-def both(plan):
-    """Outputs of a joined execution and of one kernel after the other."""
-    got = plan.run()
-    ns = plan.execute_timed()
+def timed(plan):
+    """Outputs of an execution that times its kernels."""
+    ns = np.asarray(plan.execute_timed())
     torch.cuda.synchronize()
-    assert (np.asarray(ns) > 0).all()
-    return got, [t.cpu().numpy() for t in plan._out]
+    assert (ns > 0).all()                                    # one by one
+    return [t.cpu().numpy() for t in plan._out]
+
+
+def same_on_two_lanes(plan, got):
+    plan.set_lanes(2)
+    assert all(np.array_equal(a, b) for a, b in zip(plan.run(), got))
+    n = plan.n_kernels
+    for digits in ([0] + [1] * (n - 1), [1] * (n - 1) + [0]):
+        plan.set_handover(digits, lanes=2)
+        assert all(np.array_equal(a, b) for a, b in zip(plan.run(), got))
+
+
+# classes and channels at the ends of what the kernel takes, images of all remainders of four and eight loads, weights as they lie and in both packed orders
+@pytest.mark.parametrize("backend", ["igemm_s8", "igemm_r16", "igemm_r32", "igemm_r16x2_w4"])
+@pytest.mark.parametrize("n,c,h,w,classes", [(1, 32, 32, 32, 10), (3, 16, 7, 9, 64), (2, 256, 2, 3, 8), (1, 48, 1, 1, 1), (5, 128, 4, 6, 33), (2, 130, 9, 9, 63), (1, 3, 130, 130, 5)])
+def test_classifier(n, c, h, w, classes, backend):
+    r = np.random.default_rng(n * c + h)
+    xv, wv, bv = r.standard_normal((n, c, h, w)).astype(np.float32) + 1, r.standard_normal((classes, c)).astype(np.float32), r.standard_normal(classes).astype(np.float32)
+    d = wl.GraphDesc("classifier")
+    y = d.op("dense", [d.op("global_avg_pool2d", [d.input(xv)]), d.const(wv)])
+    logits = d.op("bias_add", [y, d.const(bv)], axis=-1)
+    d.mark_output(logits)
+    d.mark_output(d.op("softmax", [logits]))
+    s = clg.Session(d, [("direct", P("global_avg_pool2d", W)), (backend, P("bias_add", P("dense", W, W), W)), ("rowwise", P("softmax", W))], device=0)
+    plan = s.compile(list(range(len(s.match()))))
+    assert plan.n_kernels == 3 and plan.n_launches == 1
+    p = xv.astype(np.float64).mean((2, 3))
+    want = p @ wv.T.astype(np.float64) + bv
+    # means of up to 17000 values, added 8 ways and over the lanes (60 terms in a chain at most), then products of 256 terms, 16 in a chain
+    bound = 140 * 2.0 ** -24 * (np.abs(xv).astype(np.float64).mean((2, 3)) @ np.abs(wv).T.astype(np.float64) + np.abs(bv))
+    e = np.exp(want - want.max(-1, keepdims=True))
+    prob = e / e.sum(-1, keepdims=True)
+    got = plan.run()
+    for y in (got, timed(plan)):
+        assert (np.abs(y[0] - want) <= bound).all()
+        assert (np.abs(y[1] - prob) <= prob * (4 * bound.max(-1, keepdims=True) + 80 * 2.0 ** -24)).all()
+    same_on_two_lanes(plan, got)
+    s.close()
+
+
+def test_classifier_without_a_pool_and_with_outputs_over_its_input():
+    r = np.random.default_rng(2)
+    xv, wv = r.standard_normal((6, 20)).astype(np.float32), r.standard_normal((20, 20)).astype(np.float32)
+    d = wl.GraphDesc("dense_softmax")
+    d.mark_output(d.op("softmax", [d.op("dense", [d.input(xv), d.const(wv)])]))
+    s = clg.Session(d, [("igemm_s", P("dense", W, W)), ("rowwise", P("softmax", W))], device=0)
+    plan = s.compile(list(range(len(s.match()))))
+    assert plan.n_launches == 1
+    e = np.exp(xv.astype(np.float64) @ wv.T.astype(np.float64))
+    want = e / e.sum(-1, keepdims=True)
+    assert np.allclose(plan.run()[0], want, rtol=1e-5, atol=0)
+    plan._in[0].copy_(torch.from_numpy(xv))
+    plan._out[0] = plan._in[0]                               # the softmax of all rows over the input: the kernels run one by one
+    plan.execute()
+    torch.cuda.synchronize()
+    assert np.allclose(plan._out[0].cpu().numpy(), want, rtol=1e-5, atol=0)
+    s.close()
+
+
+def test_what_is_no_small_classifier():
+    for classes, c, hw in ((65, 16, 4), (10, 260, 4), (10, 32, 2052)):
+        d = wl.GraphDesc("large")
+        y = d.op("dense", [d.op("global_avg_pool2d", [d.input(np.ones((1, c, hw, 1), np.float32))]), d.const(np.ones((classes, c), np.float32))])
+        d.mark_output(d.op("softmax", [y]))
+        s = clg.Session(d, [("direct", P("global_avg_pool2d", W)), ("igemm_s8", P("dense", W, W)), ("rowwise", P("softmax", W))], device=0)
+        plan = s.compile(list(range(len(s.match()))))
+        assert plan.n_launches == (2 if hw == 2052 else 3), (classes, c, hw)
+        assert np.allclose(plan.run()[0], 1 / classes, rtol=1e-5, atol=0)
+        s.close()
 
 
 # rows and lengths with partly empty tiles and waves, two to sixteen slices, one to eight loads per lane; bias and residual before and in the layer norm's prologue
@@ -40,9 +108,10 @@ def test_layer_norm_of_partial_results(rows, k, hid, head, pro, backend):
     d.mark_output(d.op("layer_norm", [y, d.const(f(hid)), d.const(f(hid))], eps=1e-5))
     s = clg.Session(d, [(backend, pat), ("rowwise", P("layer_norm", npat, W, W))], device=0)
     plan = s.compile(list(range(len(s.match()))))
-    got, apart = both(plan)
+    got = plan.run()
     assert plan.n_kernels == 2
-    assert np.array_equal(got[0], apart[0])                  # the same sums in the same order
+    assert np.array_equal(got[0], timed(plan)[0])            # one by one: the same sums in the same order
+    same_on_two_lanes(plan, got)
     # operands at addresses that 16-byte loads do not take: one by one
     if "add" in pro:
         n = len(plan._in) - 1
