@@ -436,6 +436,8 @@ int32_t clg_plan_reads_constant(const clg_plan *plan, int32_t node, int32_t *rea
     for (const Region &r : p.regions)
         for (size_t k = 0; k < r.members.size(); ++k)
             if (r.packed[k] && r.fused[k].b_node == node) packed += r.fused[k].pack_bytes;
+    for (const Join &j : p.joins)
+        if (j.packed && j.split.b_node == node) packed += j.split.pack_bytes;
     if (packed_bytes) *packed_bytes = packed;
     return CLG_OK;
     CLG_CATCH

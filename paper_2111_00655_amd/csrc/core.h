@@ -203,6 +203,10 @@ enum JoinKind : int32_t { JOIN_CLASSIFIER = 1, JOIN_NORM };
 struct Join {
     int32_t kind, first, n;
     ClassifierArgs classifier;             // pointers null
+    bool lowered;                          // JOIN_NORM: the dense layer is lowered again for the join
+    KernelCall split;                      // ... to this call,
+    void *packed;                          // with weights packed for it (owned by the plan; null: the call's own copy is the same)
+    int64_t scratch_offset;
 };
 
 struct Plan {

@@ -283,7 +283,7 @@ int launch_rf_multi(const GemmArgs *members, int n, hipStream_t s) {
                          : launch_rf_multi_wgk<16>(m, a.rf_wgk, rf_geo(a), gy, s);
 }
 
-bool rf_resolve_dense(GemmArgs *a, int ts, int epi_flags, int n_cus, int waves, int nb) {
+bool rf_resolve_dense(GemmArgs *a, int ts, int epi_flags, int n_cus, int waves, int nb, int splitk) {
     (void)n_cus;
     if (a->mode != GM_NT || a->batch != 1 || (epi_flags & EF_GENERIC)) return false;
     if (nb != 1 && !(nb == 2 && ts == 16)) return false;
@@ -294,13 +294,14 @@ bool rf_resolve_dense(GemmArgs *a, int ts, int epi_flags, int n_cus, int waves, 
     const int ng = a->K / (4 * nslot);                       // weight groups (4 MFMAs each)
     const int nc = (ng + 3) / 4;                             // chunks per tile
     const int wtiles = nb == 2 ? ((a->N + ts - 1) / ts + 1) / 2 : (a->N + ts - 1) / ts;      // tiles (or pairs of tiles) of weight rows
-    const int wgk = pick_waves(nc, (int64_t)((a->M + ts - 1) / ts) * wtiles, waves, true);
+    if (splitk < 1 || (splitk > 1 && (nb != 1 || a->cs_len))) return false;
+    const int wgk = pick_waves((nc + splitk - 1) / splitk, (int64_t)((a->M + ts - 1) / ts) * wtiles * splitk, waves, true);
     a->rf_ts = ts;
     a->rf_nb = nb;
     a->rf_tapk = -1;
     a->rf_wgk = wgk;
-    a->rf_nch = (nc + wgk - 1) / wgk;
-    a->splitk = 1;
+    a->rf_nch = (nc + wgk * splitk - 1) / (wgk * splitk);
+    a->splitk = (nc + wgk * a->rf_nch - 1) / (wgk * a->rf_nch);
     a->rf_ngtot = wgk * a->splitk * a->rf_nch * 4;
     a->rf_nm = ng * 4;
     a->rf_jmajor = a->M > a->N ? 1 : 0;

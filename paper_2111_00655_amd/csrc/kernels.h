@@ -411,7 +411,7 @@ struct LayoutArgs {
 
 // Launchers: enqueue on `stream` (a hipStream_t) and return the hipError_t
 // of the launch as an int (0 = success).
-int launch_gemm(const GemmArgs &a, void *stream);
+int launch_gemm(const GemmArgs &a, void *stream, bool reduce = true);    // reduce: partial results are added up as well
 int launch_direct_conv(const DirectConvArgs &a, void *stream);
 int launch_pool(const PoolArgs &a, void *stream);
 int launch_rowwise(const RowwiseArgs &a, const Ahead *ahead, void *stream);   // ahead: null or what the one-round-trip layer norm reads ahead
@@ -441,7 +441,8 @@ size_t gemm_scratch_bytes(const GemmArgs &a);
 bool rf_resolve(GemmArgs *a, int ts, int epi_flags, int n_cus, int waves = 0, bool split = false);
 // The same for GM_NT dense (A = activations [M,K], B = weights [N,K], no batch).
 // nb = 2 (ts = 16 only): a wave computes two weight tiles against one tile of activation rows.
-bool rf_resolve_dense(GemmArgs *a, int ts, int epi_flags, int n_cus, int waves = 0, int nb = 1);
+// splitk: K split across that many workgroups per tile (at most; nb = 1).
+bool rf_resolve_dense(GemmArgs *a, int ts, int epi_flags, int n_cus, int waves = 0, int nb = 1, int splitk = 1);
 // The same for GM_CONVT (kernel and output sizes divisible by the stride).
 bool rf_resolve_convt(GemmArgs *a, int ts, int epi_flags, int n_cus, int waves = 0);
 size_t rf_pack_bytes(const GemmArgs &a);

@@ -489,13 +489,13 @@ int launch_gemm_region(const GemmArgs *members, int n, void *stream) {
     return launch_rf_multi(local, n, (hipStream_t)stream);
 }
 
-int launch_gemm(const GemmArgs &a_in, void *stream) {
+int launch_gemm(const GemmArgs &a_in, void *stream, bool reduce) {
     hipStream_t s = (hipStream_t)stream;
     GemmArgs a = a_in;
     a.ef = make_epi_fast(a.epi);
     if (a.rf_ts) {
         const int e = launch_rf_conv(a, s);
-        if (e || a.splitk <= 1 || a.rf_convt) return e;      // (a transposed convolution's grid.z counts phases)
+        if (e || a.splitk <= 1 || a.rf_convt || !reduce) return e;      // (a transposed convolution's grid.z counts phases)
         return launch_splitk_reduce(a.partial, a.C, a.c_numel, a.splitk, a.epi, stream);
     }
     if (a.gemv) {
@@ -534,7 +534,7 @@ int launch_gemm(const GemmArgs &a_in, void *stream) {
     default: err = launch_mode<GM_CONVT>(a, s); break;
     }
     if (err) return err;
-    return a.splitk > 1 ? launch_splitk_reduce(a.partial, a.C, a.c_numel, a.splitk, a.epi, stream) : 0;
+    return a.splitk > 1 && reduce ? launch_splitk_reduce(a.partial, a.C, a.c_numel, a.splitk, a.epi, stream) : 0;
 }
 
 }  // namespace clg

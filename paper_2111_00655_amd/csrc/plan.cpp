@@ -280,8 +280,26 @@ void find_regions(const Context &ctx, const Graph &g, Plan *plan) {
     }
 }
 
+// Lowers a register-fed dense layer in front of a layer norm again, with K split four ways in workgroups of four waves, where that shares out long
+// rows better: the layer norm adds up the partial results at no launch of its own.  All of BERT-base (3072 -> 768), us, unsplit and split, by the number T
+// of 16 x 16 tiles on 256 compute units: T = 48 438 and 403, 96 450 and 438, 144 473 and 475, 192 492 and 497, 240 512 and 529 (one round of tiles either way);
+// 288 589 and 575, 336 610 and 603, 384 628 and 622, 432 650 and 657, 480 658 and 674 (two rounds of tiles, five to eight of quarters).  Split 2, 3, 6
+// and 12 ways, or in workgroups of eight and sixteen waves, it is up to 4 % slower than so; 768 -> 768 as well 1 - 2 % slower.
+bool split_for_norm(const Context &ctx, const KernelCall &own, KernelCall *c) {
+    *c = own;
+    GemmArgs a = own.gemm;
+    const int64_t tiles = (int64_t)((a.M + 15) / 16) * ((a.N + 15) / 16), n = ctx.n_cus;
+    if (a.K < 2048 || !(tiles * 2 <= n || (tiles > n && tiles * 2 <= 3 * n))) return false;
+    if (!rf_resolve_dense(&a, 16, epi_fast_flags(a.epi), ctx.n_cus, -4, 1, 4) || a.splitk < 2) return false;
+    c->gemm = a;
+    c->pack_bytes = rf_pack_bytes(a);
+    c->scratch_bytes = gemm_scratch_bytes(a);
+    c->name = "dense_rf16_w" + std::to_string(a.rf_wgk) + "_k" + std::to_string(a.splitk);
+    return true;
+}
+
 // Finds the joins of a sequence in its final order.
-void find_joins(const Graph &g, Plan *plan) {
+void find_joins(const Context &ctx, const Graph &g, Plan *plan) {
     const std::vector<KernelCall> &calls = plan->calls;
     const size_t nc = calls.size();
     plan->joins.clear();
@@ -309,16 +327,20 @@ void find_joins(const Graph &g, Plan *plan) {
             j.n = (int32_t)(d + 2 - i);
             if (classifier_resolve(d == i ? nullptr : &calls[i].pool, dense.gemm, soft.row, &j.classifier)) add(j);
         }
-        // a split dense layer whose result only the layer norm behind it reads, as what is normalised
-        if (!alone(i, CALL_B3) || !alone(i + 1, CALL_ROWWISE)) continue;
+        // a dense layer whose result only the layer norm behind it reads, as what is normalised: split already, or to be split for that
+        if (!(alone(i, CALL_B3) || alone(i, CALL_GEMM)) || !alone(i + 1, CALL_ROWWISE)) continue;
         const KernelCall &c = calls[i], &n = calls[i + 1];
-        const B3Args &b = c.b3;
-        if (!b.dense || b.splitk < 2 || n.a_node != c.out_node || readers[c.out_node] != 1 || g.is_output[c.out_node]) continue;
-        if (n.row.mode != 1 || n.row.rows != b.Nrows || n.row.len != b.Cout || b.ldy != b.Cout || !rowwise_sums_shape_ok(n.row)) continue;
-        const int flags = epi_fast_flags(b.epi);
-        if (flags & ~(EF_BIAS | EF_ADD) || ((flags & EF_BIAS) && (b.epi.bias_inner > 1 || b.epi.bias_c != b.Cout))) continue;
+        const bool b3 = c.kind == CALL_B3;
+        const Epilogue &e = b3 ? c.b3.epi : c.gemm.epi;
+        const int rows = b3 ? c.b3.Nrows : c.gemm.M, len = b3 ? c.b3.Cout : c.gemm.N, ld = b3 ? c.b3.ldy : c.gemm.ldc, flags = epi_fast_flags(e);
+        if (b3 ? !c.b3.dense || c.b3.splitk < 2 : c.gemm.rf_tapk != -1 || !c.gemm.rf_ts || c.gemm.cs_len || c.gemm_swap) continue;
+        if (n.a_node != c.out_node || readers[c.out_node] != 1 || g.is_output[c.out_node]) continue;
+        if (n.row.mode != 1 || n.row.rows != rows || n.row.len != len || ld != len || !rowwise_sums_shape_ok(n.row)) continue;
+        if (flags & ~(EF_BIAS | EF_ADD) || ((flags & EF_BIAS) && (e.bias_inner > 1 || e.bias_c != len))) continue;
         Join j{};
         j.kind = JOIN_NORM;
+        j.lowered = !b3;
+        if (!b3 && !split_for_norm(ctx, c, &j.split)) continue;
         j.first = (int32_t)i;
         j.n = 2;
         add(j);
@@ -436,7 +458,7 @@ int32_t compile_plan(Context &ctx, Graph &g, const int32_t *ids, size_t n, Plan 
         plan->calls.push_back(std::move(c));
     }
     find_regions(ctx, g, plan);
-    find_joins(g, plan);
+    find_joins(ctx, g, plan);
 
     // every operand must be a leaf or the sink of an earlier group
     const size_t nc = plan->calls.size();
@@ -536,11 +558,14 @@ int32_t compile_plan(Context &ctx, Graph &g, const int32_t *ids, size_t n, Plan 
             const std::vector<int32_t> &together = ri >= 0 ? plan->regions[ri].members : only;
             if (together.front() == (int32_t)i)
                 for (int32_t m : together) place_output((size_t)m);
+            Join *const low = ji >= 0 && plan->joins[ji].lowered ? &plan->joins[ji] : nullptr;
+            if (low && low->first == (int32_t)i) low->scratch_offset = arena.alloc((int64_t)low->split.scratch_bytes);
             if (c.scratch_bytes) {
                 plan->scratch_offset[i] = arena.alloc((int64_t)c.scratch_bytes);
                 if (ji < 0) arena.release(plan->scratch_offset[i]);
             }
             if (together.back() != (int32_t)i) continue;
+            if (low) arena.release(low->scratch_offset);
             for (int32_t m : together) {
                 if (ji >= 0 && plan->calls[m].scratch_bytes) arena.release(plan->scratch_offset[m]);
                 for (int32_t r2 : releases[(size_t)m]) arena.release(plan->value_offset[r2]);
@@ -599,6 +624,19 @@ int32_t compile_plan(Context &ctx, Graph &g, const int32_t *ids, size_t n, Plan 
                 if (rc != CLG_OK) return rc;
                 any = true;
             }
+        // (nor does a join's call always read the packed copy that its kernel has alone)
+        for (Join &j : plan->joins) {
+            const KernelCall &own = plan->calls[(size_t)j.first], &c = j.split;
+            if (!j.lowered || (own.gemm.rf_ts == c.gemm.rf_ts && own.gemm.rf_ngtot == c.gemm.rf_ngtot && own.pack_bytes >= c.pack_bytes)) continue;
+            if (hipMalloc(&j.packed, c.pack_bytes) != hipSuccess) {
+                (void)hipGetLastError();
+                j.packed = nullptr;
+                return fail(CLG_OUT_OF_MEMORY, "allocation of %zu bytes for packed weights failed", c.pack_bytes);
+            }
+            const int32_t rc = pack_weights(c, g.nodes[c.b_node].dev_ptr, j.packed, nullptr);
+            if (rc != CLG_OK) return rc;
+            any = true;
+        }
         if (any && hipStreamSynchronize(nullptr) != hipSuccess)
             return fail(CLG_HIP_ERROR, "weight packing failed: %s", hipGetErrorString(hipGetLastError()));
     }
@@ -613,6 +651,8 @@ Plan::~Plan() {
     for (Region &r : regions)
         for (void *p : r.packed)
             if (p) (void)hipFree(p);
+    for (Join &j : joins)
+        if (j.packed) (void)hipFree(j.packed);
     for (void *e : events)
         if (e) (void)hipEventDestroy((hipEvent_t)e);
     for (void *e : ev_end)
@@ -680,6 +720,10 @@ void schedule_lanes(Plan *plan) {
                              plan->value_offset[c.out_node] + round_up(4 * g.nodes[c.out_node].shape.numel())});
         if (plan->scratch_offset[i] >= 0)
             wr[i].push_back({plan->scratch_offset[i], plan->scratch_offset[i] + round_up((int64_t)c.scratch_bytes)});
+        if (plan->join_of[i] >= 0 && plan->joins[(size_t)plan->join_of[i]].lowered) {
+            const Join &j = plan->joins[(size_t)plan->join_of[i]];
+            wr[i].push_back({j.scratch_offset, j.scratch_offset + round_up((int64_t)j.split.scratch_bytes)});
+        }
         produced_at[c.out_node] = (int32_t)i;
     }
     // direct dependencies and their transitive closure (bit sets over calls)
@@ -920,7 +964,7 @@ int32_t launch_call(const KernelCall &c, const void *a, const void *b, const voi
 
 // The launches of a join, operands by `ptr_of`; *done = false: the addresses are such that they run one by one.
 template <class F>
-static int32_t launch_join(const Plan &p, const Join &j, const F &ptr_of, void *scratch, const Ahead *ahead, void *stream, bool *done) {
+static int32_t launch_join(const Plan &p, const Join &j, const F &ptr_of, void *workspace, const Ahead *ahead, void *stream, bool *done) {
     const size_t first = (size_t)j.first, last = first + (size_t)j.n - 1;
     auto in = [&](int32_t v) { return (const float *)ptr_of(v); };
     auto out = [&](size_t i) { return (float *)const_cast<void *>(ptr_of(p.calls[i].out_node)); };
@@ -931,6 +975,7 @@ static int32_t launch_join(const Plan &p, const Join &j, const F &ptr_of, void *
     for (size_t i = first; i <= last; ++i)
         for (int32_t v : {p.calls[i].a_node, p.calls[i].b_node, p.calls[i].c_node})
             if (v >= 0 && !ptr_of(v)) return fail(CLG_INVALID_ARG, "constant node %d has no device pointer", v);
+    void *scratch = p.scratch_offset[first] >= 0 ? (char *)workspace + p.scratch_offset[first] : nullptr;
     int err;
     *done = true;
     if (j.kind == JOIN_CLASSIFIER) {
@@ -951,21 +996,34 @@ static int32_t launch_join(const Plan &p, const Join &j, const F &ptr_of, void *
         if (!*done) return CLG_OK;
         err = launch_classifier(a, stream);
     } else {
-        const KernelCall &c = p.calls[first], &n = p.calls[last];
-        if (!p.packed[first]) return fail(CLG_INVALID_ARG, "%s needs packed weights, none were prepared", c.name.c_str());
-        B3Args k = c.b3;
-        k.x = in(c.a_node); k.w = p.packed[first]; k.y = out(first); k.partial = (float *)scratch;
-        k.epi = bind(c.b3.epi, c);
-        const EpiFast ef = make_epi_fast(k.epi);
+        const KernelCall &c = j.lowered ? j.split : p.calls[first], &n = p.calls[last];
+        const void *w = j.packed ? j.packed : p.packed[first];
+        if (!w) return fail(CLG_INVALID_ARG, "%s needs packed weights, none were prepared", c.name.c_str());
+        if (j.lowered) scratch = (char *)workspace + j.scratch_offset;
+        const bool b3 = c.kind == CALL_B3;
+        const EpiFast ef = make_epi_fast(bind(b3 ? c.b3.epi : c.gemm.epi, c));
         RowwiseArgs r = n.row;
         r.gamma = in(n.b_node); r.beta = in(n.c_node); r.y = out(last);
         r.pro = bind(n.row.pro, n);
-        const SplitSum sum{k.partial, ef.flags & EF_BIAS ? ef.bias : nullptr, ef.flags & EF_ADD ? ef.add : nullptr, k.splitk, (int32_t)k.c_numel};
+        const SplitSum sum{(const float *)scratch, ef.flags & EF_BIAS ? ef.bias : nullptr, ef.flags & EF_ADD ? ef.add : nullptr, b3 ? c.b3.splitk : c.gemm.splitk,
+                           (int32_t)(b3 ? c.b3.c_numel : c.gemm.c_numel)};
         if (!rowwise_sums_ok(r, sum)) {
             *done = false;
             return CLG_OK;
         }
-        err = launch_b3(k, stream, false);
+        if (b3) {
+            B3Args k = c.b3;
+            k.x = in(c.a_node); k.w = w; k.y = out(first); k.partial = (float *)scratch;
+            k.epi = bind(c.b3.epi, c);
+            err = launch_b3(k, stream, false);
+        } else {
+            const void *epi[kMaxEpi];
+            for (int s = 0; s < kMaxEpi; ++s) epi[s] = c.epi_nodes[s] >= 0 ? ptr_of(c.epi_nodes[s]) : nullptr;
+            GemmArgs k;
+            const int32_t rc = bind_gemm(c, in(c.a_node), in(c.b_node), out(first), epi, scratch, w, &k);
+            if (rc != CLG_OK) return rc;
+            err = launch_gemm(k, stream, false);
+        }
         if (!err) err = launch_rowwise_sum(r, sum, ahead, stream);
     }
     if (err != 0) return fail(CLG_HIP_ERROR, "launch of %s and what follows it failed: %s", p.calls[first].name.c_str(), hipGetErrorString((hipError_t)err));
@@ -1053,6 +1111,11 @@ int32_t execute_plan(Plan &p, const void *const *inputs, void *const *outputs, v
                         bytes = r.fused[k].pack_bytes;
                     }
             }
+            if (p.join_of[(size_t)j] >= 0 && p.joins[(size_t)p.join_of[(size_t)j]].packed) {
+                const Join &jn = p.joins[(size_t)p.join_of[(size_t)j]];
+                w = jn.packed;
+                bytes = jn.split.pack_bytes;
+            }
             out->p[out->n] = w;
             out->lines[out->n++] = (uint32_t)(bytes / kAheadLine);
         }
@@ -1076,7 +1139,7 @@ int32_t execute_plan(Plan &p, const void *const *inputs, void *const *outputs, v
                             rc = fail(CLG_HIP_ERROR, "hipStreamWaitEvent failed");
             if (rc != CLG_OK) break;
             bool joined = false;
-            rc = launch_join(p, j, ptr_of, p.scratch_offset[i] >= 0 ? (char *)workspace + p.scratch_offset[i] : nullptr, ahead_of(end - 1, &ahead), st, &joined);
+            rc = launch_join(p, j, ptr_of, workspace, ahead_of(end - 1, &ahead), st, &joined);
             if (rc != CLG_OK) break;
             if (joined) {
                 for (size_t k = i; k < end; ++k)

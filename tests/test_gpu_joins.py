@@ -1,5 +1,5 @@
-"""Kernels that share launches with what reads them: [global average pool,] dense layer and softmax in one, and a split dense layer whose partial results
-the layer norm behind it adds up."""
+"""Kernels that share launches with what reads them: [global average pool,] dense layer and softmax in one, and a dense layer with K split whose partial
+results the layer norm behind it adds up."""
 import numpy as np
 import pytest
 import torch
@@ -121,4 +121,40 @@ def test_layer_norm_of_partial_results(rows, k, hid, head, pro, backend):
         plan.execute()
         torch.cuda.synchronize()
         assert np.allclose(plan._out[0].cpu().numpy(), got[0], rtol=1e-4, atol=1e-5)
+    s.close()
+
+
+# fp32 dense layers that are split for the layer norm behind them: both ends of both ranges of tiles, a last slice that is short (33 chunks, three per wave: eleven waves of twelve), other tiles and K that stay
+@pytest.mark.parametrize("rows,k,hid,head,pro,slices", [(1, 2048, 64, (), ("bias_add", "add"), 4), (16, 3072, 768, ("bias_add",), ("add",), 4), (42, 2048, 656, ("bias_add", "add"), (), 4),
+                                                        (17, 2064, 68, (), ("add",), 3), (96, 2560, 720, (), ("bias_add", "add"), 4), (128, 3072, 768, (), ("add",), 4),
+                                                        (64, 3072, 768, (), ("add",), 1), (144, 3072, 768, (), ("add",), 1), (16, 1536, 768, (), ("add",), 1)])
+@pytest.mark.parametrize("backend", ["igemm_r16", "igemm_r16x2_w8", "igemm_r32_w4"])
+def test_dense_layers_split_for_a_layer_norm(rows, k, hid, head, pro, slices, backend):
+    r = np.random.default_rng(rows + hid)
+    f = lambda *sh: r.standard_normal(sh).astype(np.float32)
+    d = wl.GraphDesc("split_for_norm")
+    pat, npat = P("dense", W, W), W
+    xv, wv = f(rows, k), f(hid, k) / np.float32(k ** 0.5)
+    y, ref = d.op("dense", [d.input(xv), d.const(wv)]), xv.astype(np.float64) @ wv.T.astype(np.float64)
+    for n, op in enumerate(head + pro):
+        t = f(hid) if op == "bias_add" else f(rows, hid)
+        ref = ref + t
+        y = d.op("bias_add", [y, d.const(t)], axis=-1) if op == "bias_add" else d.op("add", [y, d.input(t)])
+        if n < len(head):
+            pat = P(op, pat, W)
+        else:
+            npat = P(op, npat, W)
+    g, b = 1 + f(hid) / 8, f(hid)
+    d.mark_output(d.op("layer_norm", [y, d.const(g), d.const(b)], eps=1e-5))
+    c = ref - ref.mean(-1, keepdims=True)
+    ref = c / np.sqrt((c * c).mean(-1, keepdims=True) + 1e-5) * g + b
+    s = clg.Session(d, [(backend, pat), ("rowwise", P("layer_norm", npat, W, W))], device=0)
+    plan = s.compile(list(range(len(s.match()))))
+    got = plan.run()
+    # a chain of up to 2048 / 4 products per K-wave and slice, at random: 1e-6 of the values; their spread is about one
+    assert np.linalg.norm(got[0] - ref) < 2e-6 * np.linalg.norm(ref)
+    apart = timed(plan)[0]                                   # the kernel that the layer has alone
+    assert np.linalg.norm(apart - ref) < 2e-6 * np.linalg.norm(ref)
+    assert plan.ws_bytes >= slices * rows * hid * 4 and (slices == 1) == np.array_equal(apart, got[0])
+    same_on_two_lanes(plan, got)
     s.close()
