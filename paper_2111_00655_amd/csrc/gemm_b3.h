@@ -75,7 +75,7 @@ struct B3Cfg {
 using B3L = B3Cfg<4, 2, 1, 2, 4>;    // 128 x 128, eight waves
 using B3LM = B3Cfg<2, 2, 1, 2>;      // 64 x 128
 using B3M = B3Cfg<2, 1, 2, 2>;       // 64 x 64, two K-waves
-using B3M8 = B3Cfg<2, 1, 4, 2, 1>;   // 64 x 64, four K-waves (1x1 filters and dense layers)
+using B3M8 = B3Cfg<2, 1, 4, 2, 1>;   // 64 x 64, four K-waves
 using B3M12 = B3Cfg<3, 1, 4, 2, 3>;  // 96 x 64, four K-waves (dense layers)
 using B3S = B3Cfg<1, 1, 4, 2>;       // 32 x 64, four K-waves
 using B3SS = B3Cfg<1, 1, 4, 1>;      // 32 x 32, four K-waves
@@ -706,7 +706,7 @@ int b3_launch_one(const B3Args &a, hipStream_t s) {
         case B3_LM: return b3_launch_one<B3LM, TAPS, DEPTH, DENSE>(a, s);                  \
         case B3_M: return b3_launch_one<B3M, TAPS, DEPTH, DENSE>(a, s);                    \
         case B3_M8:                                                                       \
-            if constexpr (TAPS == 1) return b3_launch_one<B3M8, TAPS, DEPTH, DENSE>(a, s); \
+            if constexpr (!DEPTH) return b3_launch_one<B3M8, TAPS, DEPTH, DENSE>(a, s);    \
             else return (int)hipErrorInvalidValue;                                        \
         case B3_M12:                                                                      \
             if constexpr (DENSE) return b3_launch_one<B3M12, TAPS, DEPTH, DENSE>(a, s);    \

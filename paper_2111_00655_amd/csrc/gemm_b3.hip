@@ -255,6 +255,19 @@ bool b3_resolve(const GemmArgs &g, int tile, int epi_flags, int n_cus, bool spli
             return true;
         }
     }
+    // So it is with 3x3 and 2x2 taps where a tile's K is long, from 256 channels on, and not split (us, four and eight waves: 3x3 512 -> 512 on 32 7x7
+    // 46.2 and 41.9, on 24 45.8 and 41.5, 256 -> 256 on 16 14x14 24.3 and 22.3, on 20 25.9 and 24.4; 4x4 transposed, stride 2, 512 -> 256 on 64 4x4 37.5 and
+    // 35.9, 256 -> 128 on 32 8x8 18.1 and 17.2.  128 -> 128 on eight 28x28 17.1 and 17.3; split, 512 -> 512 on five 7x7 14.5 and 18.9).
+    if (tile == B3_M && split && a.taps != 1 && a.KD == 1 && a.nC >= 16) {
+        B3Args b = a;
+        if (place(&b, B3_M8)) {
+            const int64_t tiles = (int64_t)b.mgroups * b.ntiles;
+            if (tiles <= n_cus && tiles * 2 > n_cus) {
+                *out = b;
+                return true;
+            }
+        }
+    }
     if (tile != B3_NONE) {
         if (!place(&a, tile, split ? n_cus : 0)) return false;
     } else {
