@@ -43,7 +43,7 @@ __global__ __launch_bounds__(kThreads) void classifier_kernel(ClassifierArgs a, 
         const float *wp = a.w + ((nn / a.ts) * a.ngtot * kWave + nn % a.ts) * 4 + l16 % 4;
 #pragma unroll
         for (int u = 0; u < kPerLane; ++u) {
-            const int part = min((l16 >> 2) + 4 * u, a.K / 4 - 1);       // (such a layer has K % 8 = 0)
+            const int part = min((l16 >> 2) + 4 * u, a.K / 4 - 1);       // (such a layer has K % 4 = 0)
             w[u] = wp[((part >> sh) * kWave + (part & (slots - 1)) * a.ts) * 4];
         }
     } else {

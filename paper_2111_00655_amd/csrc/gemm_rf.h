@@ -507,7 +507,10 @@ struct RfPark<16> {
     static __device__ __forceinline__ int of(int row, int col) { return at(row % 4, row / 4, col); }
 };
 
-template <int TS, int WGK>
+// RAG: K is a multiple of 4 only.  What a lane loads of the last group behind K is the row's last 16 bytes again, and zero to the MFMA (as its weights are: an
+// infinity would make that NaN); rows may lie at any address of a float.
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+template <int TS, int WGK, bool RAG = false>
 __device__ __forceinline__ void dense_rf_body(const GemmCore &p, const int bx, const int gx) {
     using MF = RfMfma<TS>;
     using PK = RfPark<TS>;
@@ -533,16 +536,18 @@ __device__ __forceinline__ void dense_rf_body(const GemmCore &p, const int bx, c
     // addresses are "uniform base + 32-bit lane offset" (no 64-bit vector arithmetic per load)
     const f32x4 *const Ab = reinterpret_cast<const f32x4 *>(p.B) + (int64_t)mt * p.rf_ngtot * kWave;
     const f32x4 *const Xb = reinterpret_cast<const f32x4 *>(p.A);
+    const float *x_row = nullptr;                            // RAG: this lane's row
     const uint32_t lane_u = (uint32_t)lane;
     // The 16 bytes lane (slot s, column r) needs lie at row r, k-part s.  Loaded by that lane itself, neighbouring
     // lanes would touch different rows; instead lane l loads row l / NSLOT, part l % NSLOT (neighbouring lanes
     // read neighbouring addresses) and the values change lanes afterwards (ds_bpermute: no memory access).
     const int lrow = lane / NSLOT, lpart = lane % NSLOT;
     const uint32_t x_lane = (uint32_t)(min(j0 + lrow, p.M - 1) * (p.lda / 4) + lpart);      // in 16-byte units
+    if constexpr (RAG) x_row = p.A + (int64_t)min(j0 + lrow, p.M - 1) * p.lda;
     const int src_lane4 = (r * NSLOT + s) * 4;                                            // byte address for ds_bpermute
     const int nch = p.rf_nch;
     const int c0 = (ks * WGK + w) * nch;
-    const int g_last = p.K / (4 * NSLOT) - 1;
+    const int g_last = (p.K + 4 * NSLOT - 1) / (4 * NSLOT) - 1, q_end = p.K / 4;     // last group; 16-byte parts of a row
 
     // outputs this thread finishes: row (n) runs fastest over the threads
     const int tile_base = p.cs_len ? (i0 / p.cs_len) * (int)p.cs_stride + i0 % p.cs_len : i0;
@@ -560,13 +565,18 @@ __device__ __forceinline__ void dense_rf_body(const GemmCore &p, const int bx, c
     do {                                                                                      \
         const int ch_ = min((c), nch - 1) + c0;                                               \
         _Pragma("unroll") for (int u = 0; u < 4; ++u) a[set][u] = (Ab + (uint32_t)(ch_ * 4 + u) * kWave)[lane_u]; \
-        _Pragma("unroll") for (int u = 0; u < 4; ++u) b[set][u] = (Xb + (uint32_t)min(ch_ * 4 + u, g_last) * NSLOT)[x_lane]; \
+        _Pragma("unroll") for (int u = 0; u < 4; ++u) {                                       \
+            const int g_ = min(ch_ * 4 + u, g_last);                                          \
+            if constexpr (RAG) b[set][u] = *reinterpret_cast<const f32x4_any *>(x_row + 4 * min(g_ * NSLOT + lpart, q_end - 1)); \
+            else b[set][u] = (Xb + (uint32_t)g_ * NSLOT)[x_lane];                             \
+        }                                                                                     \
         __builtin_amdgcn_sched_barrier(0);                                                    \
     } while (0)
-#define CLG_RFD_MMA(set)                                                                      \
+#define CLG_RFD_MMA(set, c)                                                                   \
     do {                                                                                      \
         _Pragma("unroll") for (int u = 0; u < 16; ++u) {                                      \
-            const float own_ = b[set][u / 4][u % 4];      /* (a copy: not the vector element itself) */ \
+            float own_ = b[set][u / 4][u % 4];            /* (a copy: not the vector element itself) */ \
+            if constexpr (RAG) own_ = ((c) + c0) * 4 + u / 4 >= g_last && ((c) + c0) * 4 * NSLOT + u / 4 * NSLOT + lpart >= q_end ? 0.f : own_; \
             const float bv_ = __int_as_float(__builtin_amdgcn_ds_bpermute(src_lane4, __float_as_int(own_))); \
             acc = MF::mma(a[set][u / 4][u % 4], bv_, acc);                                    \
         }                                                                                     \
@@ -589,11 +599,11 @@ __device__ __forceinline__ void dense_rf_body(const GemmCore &p, const int bx, c
     int c = 0;
     for (; c + 1 < nch; c += 2) {
         CLG_RFD_LOAD(1, c + 1);
-        CLG_RFD_MMA(0);
+        CLG_RFD_MMA(0, c);
         CLG_RFD_LOAD(0, c + 2);
-        CLG_RFD_MMA(1);
+        CLG_RFD_MMA(1, c + 1);
     }
-    if (c < nch) CLG_RFD_MMA(0);
+    if (c < nch) CLG_RFD_MMA(0, c);
 #undef CLG_RFD_LOAD
 #undef CLG_RFD_MMA
 
@@ -612,9 +622,9 @@ __device__ __forceinline__ void dense_rf_body(const GemmCore &p, const int bx, c
     }
 }
 
-template <int TS, int WGK>
+template <int TS, int WGK, bool RAG>
 __global__ __launch_bounds__(WGK *kWave) void dense_rf_kernel(GemmArgs p) {
-    dense_rf_body<TS, WGK>(p, blockIdx.x, gridDim.x);
+    dense_rf_body<TS, WGK, RAG>(p, blockIdx.x, gridDim.x);
 }
 
 // Several dense problems in one launch (see conv_rf_multi_kernel): e.g. the query, key and value

@@ -110,17 +110,22 @@ int launch_rfd2_multi_wgk(const RfMultiArgs &m, int wgk, hipStream_t s) {
     }
 }
 
-template <int TS, int WGK>
-int launch_rfd_one(const GemmArgs &a, hipStream_t s) {
+template <int TS, int WGK, bool RAG>
+int launch_rfd_as(const GemmArgs &a, hipStream_t s) {
     const int tiles = ((a.N + TS - 1) / TS) * ((a.M + TS - 1) / TS);
     const size_t lds = (size_t)WGK * RfPark<TS>::PERW * sizeof(float);
     if (lds > 64 * 1024) {
         static LdsLimit limit;
-        const hipError_t e = limit.raise((const void *)dense_rf_kernel<TS, WGK>);
+        const hipError_t e = limit.raise((const void *)dense_rf_kernel<TS, WGK, RAG>);
         if (e != hipSuccess) return (int)e;
     }
-    hipLaunchKernelGGL((dense_rf_kernel<TS, WGK>), dim3(tiles, 1, a.splitk), dim3(WGK * kWave), lds, s, a);
+    hipLaunchKernelGGL((dense_rf_kernel<TS, WGK, RAG>), dim3(tiles, 1, a.splitk), dim3(WGK * kWave), lds, s, a);
     return (int)hipGetLastError();
+}
+
+template <int TS, int WGK>
+int launch_rfd_one(const GemmArgs &a, hipStream_t s) {
+    return a.rf_ragged ? launch_rfd_as<TS, WGK, true>(a, s) : launch_rfd_as<TS, WGK, false>(a, s);
 }
 
 template <int TS>
@@ -243,7 +248,7 @@ void rf_set_stamps(long long *dev) { (void)hipMemcpyToSymbol(HIP_SYMBOL(g_rf_sta
 
 int launch_rf_conv(const GemmArgs &a, hipStream_t s) {
     if (a.rf_tapk == -1) {
-        if (((uintptr_t)a.A & 15) != 0) return (int)hipErrorInvalidValue;      // activations are read 16 bytes at a time
+        if (((uintptr_t)a.A & (a.rf_ragged ? 3 : 15)) != 0) return (int)hipErrorInvalidValue;      // activations are read 16 bytes at a time
         if (a.rf_nb == 2) return a.rf_ts == 16 && a.splitk == 1 ? launch_rfd2_wgk(a, s) : (int)hipErrorInvalidValue;
         return a.rf_ts == 32 ? launch_rfd_wgk<32>(a, s) : launch_rfd_wgk<16>(a, s);
     }
@@ -253,7 +258,7 @@ int launch_rf_conv(const GemmArgs &a, hipStream_t s) {
 bool rf_same_launch_shape(const GemmArgs &a, const GemmArgs &b) {
     if (!a.rf_ts || a.rf_ts != b.rf_ts || a.rf_tapk != b.rf_tapk || a.rf_wgk != b.rf_wgk) return false;
     if (a.splitk != 1 || b.splitk != 1) return false;
-    if (a.rf_tapk == -1) return a.rf_nb == b.rf_nb;           // dense: grid.y = grid.z = 1
+    if (a.rf_tapk == -1) return a.rf_nb == b.rf_nb && !a.rf_ragged && !b.rf_ragged;           // dense: grid.y = grid.z = 1
     if (a.rf_tapk != 1) return false;                         // of the convolutions the 1x1 path is built as a region kernel
     const int ga = rf_geo(a), gb = rf_geo(b);
     if (ga != gb || (ga != 0 && ga != 3 && ga != 4)) return false;
@@ -288,16 +293,20 @@ bool rf_resolve_dense(GemmArgs *a, int ts, int epi_flags, int n_cus, int waves, 
     if (a->mode != GM_NT || a->batch != 1 || (epi_flags & EF_GENERIC)) return false;
     if (nb != 1 && !(nb == 2 && ts == 16)) return false;
     const int nslot = ts == 32 ? 2 : 4;
-    if (a->K % (4 * nslot) || a->lda % 4) return false;
+    // K a multiple of 4 only: the kernel variant that masks the last group (us, the fastest LDS-tiled kernel and it: 100 -> 8192 on 5 rows 4.65 and 3.45, 64
+    // 6.0 and 4.7, 150 9.7 and 8.2, 256 10.4 and 11.3; 1028 -> 512 on 64 rows 9.4 and 6.2; 772 -> 768 on 128 9.9 and 7.0; 2100 -> 2000 on 700 74 and 71).
+    const bool ragged = a->K % (4 * nslot) != 0 || a->lda % 4;
+    if (ragged && (a->K % 4 || a->K < 16 || nb != 1 || splitk != 1)) return false;
     if ((int64_t)a->M * a->lda >= ((int64_t)1 << 31)) return false;     // 32-bit lane offsets
     if (a->cs_len && a->cs_len % ts) return false;           // a tile's columns must stay within one block of the split
-    const int ng = a->K / (4 * nslot);                       // weight groups (4 MFMAs each)
+    const int ng = (a->K + 4 * nslot - 1) / (4 * nslot);     // weight groups (4 MFMAs each)
     const int nc = (ng + 3) / 4;                             // chunks per tile
     const int wtiles = nb == 2 ? ((a->N + ts - 1) / ts + 1) / 2 : (a->N + ts - 1) / ts;      // tiles (or pairs of tiles) of weight rows
     if (splitk < 1 || (splitk > 1 && (nb != 1 || a->cs_len))) return false;
     const int wgk = pick_waves((nc + splitk - 1) / splitk, (int64_t)((a->M + ts - 1) / ts) * wtiles * splitk, waves, true);
     a->rf_ts = ts;
     a->rf_nb = nb;
+    a->rf_ragged = ragged;
     a->rf_tapk = -1;
     a->rf_wgk = wgk;
     a->rf_nch = (nc + wgk * splitk - 1) / (wgk * splitk);

@@ -107,6 +107,7 @@ struct GemmCore {
     int32_t cs_len, ldb;
     int32_t mode, tile, batch;
     int32_t rf_ts, rf_tapk, rf_wgk;        // tile edge 32|16, tap mode 1|9|4|0 (-1: dense), K-waves per workgroup
+    int32_t rf_ragged;                     // dense: the last group of k is partly empty (K a multiple of 4 only)
     int32_t rf_nb;                         // dense: 16-row weight tiles per wave (1, or 2 sharing the activation operand)
     int32_t rf_convt;                      // 1: transposed convolution, one sub-pixel phase per grid.z slice
     int32_t rf_d2s;                        // 1: k4 s2 p1 transposed convolution with few output channels as ONE 3x3 convolution

@@ -607,9 +607,13 @@ int32_t lower_match(const Context &ctx, const Graph &g, int32_t match_id, Kernel
                 }
                 c.name = "gemm_nt";
                 b3 = g.nodes[wb].kind == NODE_CONST && lower_b3(ctx, be, a, epi, "dense", &c);
-                if (!b3 && want_rf && g.nodes[wb].kind == NODE_CONST)
-                    rf = rf_resolve_dense(&a, a.tile == TILE_R32 ? 32 : 16, epi_fast_flags(epi), ctx.n_cus, rfw,
-                                           a.tile == TILE_R16X2 ? 2 : 1);
+                if (!b3 && want_rf && g.nodes[wb].kind == NODE_CONST) {
+                    const int flags = epi_fast_flags(epi);
+                    GemmArgs t = a;
+                    rf = rf_resolve_dense(&t, a.tile == TILE_R32 ? 32 : 16, flags, ctx.n_cus, rfw, a.tile == TILE_R16X2 ? 2 : 1) &&
+                         !(t.rf_ragged && (gemv_shape_ok(a, flags) || gemv16_shape_ok(a, flags)));      // a handful of ragged rows: the matrix-vector kernels
+                    if (rf) a = t;
+                }
                 if (rf) c.pack_bytes = rf_pack_bytes(a);
             } else if (k0 == CLG_OP_BATCH_MATMUL) {
                 const bool tb = anchor.attrs.transpose_b != 0;
@@ -738,7 +742,7 @@ int32_t lower_match(const Context &ctx, const Graph &g, int32_t match_id, Kernel
                 c.gemm_swap = false;
             } else if (rf) {
                 c.scratch_bytes = gemm_scratch_bytes(a);
-                c.name = (a.rf_tapk == -1 ? "dense_rf" + std::to_string(a.rf_ts) + (a.rf_nb == 2 ? "x2" : "")
+                c.name = (a.rf_tapk == -1 ? (a.rf_ragged ? "dense4_rf" : "dense_rf") + std::to_string(a.rf_ts) + (a.rf_nb == 2 ? "x2" : "")
                                           : std::string((a.rf_convt || a.rf_d2s) ? "convt_rf" : (a.D > 1 ? "conv3d_rf" : "conv_rf")) + std::to_string(a.rf_ts) + "_t" +
                                                 std::to_string(a.rf_tapk)) +
                          "_w" + std::to_string(a.rf_wgk) + (a.cs_len ? "_split" : "") + (a.splitk > 1 ? "_k" + std::to_string(a.splitk) : "");

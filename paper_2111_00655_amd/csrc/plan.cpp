@@ -62,7 +62,7 @@ int region_class(const KernelCall &c) {
     if (c.kind == CALL_B3) return c.b3.dense ? RC_DENSE : RC_NONE;
     if (c.kind != CALL_GEMM || !c.gemm.rf_ts || c.gemm.splitk != 1 || !c.pack_bytes) return RC_NONE;
     const GemmArgs &a = c.gemm;
-    if (a.rf_tapk == -1) return RC_DENSE;
+    if (a.rf_tapk == -1) return a.rf_ragged ? RC_NONE : RC_DENSE;
     return a.rf_tapk == 1 && !a.rf_convt && !a.rf_fold ? RC_CONV1X1 : RC_NONE;
 }
 
@@ -333,7 +333,7 @@ void find_joins(const Context &ctx, const Graph &g, Plan *plan) {
         const bool b3 = c.kind == CALL_B3;
         const Epilogue &e = b3 ? c.b3.epi : c.gemm.epi;
         const int rows = b3 ? c.b3.Nrows : c.gemm.M, len = b3 ? c.b3.Cout : c.gemm.N, ld = b3 ? c.b3.ldy : c.gemm.ldc, flags = epi_fast_flags(e);
-        if (b3 ? !c.b3.dense || c.b3.splitk < 2 : c.gemm.rf_tapk != -1 || !c.gemm.rf_ts || c.gemm.cs_len || c.gemm_swap) continue;
+        if (b3 ? !c.b3.dense || c.b3.splitk < 2 : c.gemm.rf_tapk != -1 || !c.gemm.rf_ts || c.gemm.rf_ragged || c.gemm.cs_len || c.gemm_swap) continue;
         if (n.a_node != c.out_node || readers[c.out_node] != 1 || g.is_output[c.out_node]) continue;
         if (n.row.mode != 1 || n.row.rows != rows || n.row.len != len || ld != len || !rowwise_sums_shape_ok(n.row)) continue;
         if (flags & ~(EF_BIAS | EF_ADD) || ((flags & EF_BIAS) && (e.bias_inner > 1 || e.bias_c != len))) continue;
