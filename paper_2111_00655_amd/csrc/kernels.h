@@ -107,14 +107,12 @@ struct GemmCore {
     int32_t cs_len, ldb;
     int32_t mode, tile, batch;
     int32_t rf_ts, rf_tapk, rf_wgk;        // tile edge 32|16, tap mode 1|9|4|0 (-1: dense), K-waves per workgroup
-    int32_t rf_ragged;                     // dense: the last group of k is partly empty (K a multiple of 4 only)
     int32_t rf_nb;                         // dense: 16-row weight tiles per wave (1, or 2 sharing the activation operand)
     int32_t rf_convt;                      // 1: transposed convolution, one sub-pixel phase per grid.z slice
     int32_t rf_d2s;                        // 1: k4 s2 p1 transposed convolution with few output channels as ONE 3x3 convolution
                                            //    over the input whose 4 * Cout rows are (channel, sub-pixel phase)
     int32_t bias_on_row;                   // 1: channel = i (conv), 0: channel = j (dense)
     int32_t gemv;                          // 1: GM_NT with at most 8 rows runs the matrix-vector kernel (a wave per column)
-    int32_t gemv16;                        // 1: the same with shorter rows (sixteen lanes per column)
     int32_t patch_sz;                      // 3x3 kernel: floats per channel of the LDS input patch
     int64_t strideA, strideB, strideC;     // per batch, in elements
     // 3-D convolution on the register-fed kernels: one grid.y slice per (image, output depth);
@@ -128,6 +126,9 @@ struct GemmCore {
 };
 struct GemmArgs : GemmCore {
     Epilogue epi;
+    // read on the host only
+    int32_t gemv16;                        // 1: as gemv with shorter rows (sixteen lanes per column)
+    int32_t rf_ragged;                     // dense: the last group of k is partly empty (K a multiple of 4 only)
 };
 
 // Several register-fed problems of one kernel shape in one launch (a region of sibling kernels).
