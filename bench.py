@@ -39,8 +39,8 @@ VARIANTS = ("igemm", "igemm_s", "igemm_s8", "igemm_s16", "igemm_m", "igemm_l", "
 # copy of --calib-copy in the same runs: WRITE_SIZE read 262144.0 KiB for it (factor 1.000), FETCH_SIZE
 # 131083.5 KiB (factor 2.000).  profiles/*_pmc_summary.txt hold the runs.  The figures hold for the kernel sources
 # they were taken with; after any change to them `traffic` is reported as null.
-TRAFFIC = {"resnet50": {"sources": "baee1fe07b0e5b27", "fetch_bytes": 300.14e6, "write_bytes": 45.40e6},
-           "bert_base": {"sources": "baee1fe07b0e5b27", "fetch_bytes": 830.75e6, "write_bytes": 47.19e6}}
+TRAFFIC = {"resnet50": {"sources": "3affa27178308ef2", "fetch_bytes": 300.03e6, "write_bytes": 45.40e6},
+           "bert_base": {"sources": "3affa27178308ef2", "fetch_bytes": 830.72e6, "write_bytes": 61.34e6}}
 
 
 def kernel_sources_fingerprint():
