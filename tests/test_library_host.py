@@ -377,6 +377,21 @@ def test_concat_of_kernel_results_is_planned_without_a_copy():
         s.close()
 
 
+@pytest.mark.parametrize("batch,image,mixed", [(1, 224, True), (6, 256, True), (8, 256, False), (10, 224, False), (12, 224, True)])
+def test_regions_of_unlike_kinds_keep_no_plan_out_of_the_fixed_workspace(batch, image, mixed):
+    """NasNet-A with the fewest kernels.  Executed level by level more values live at once: where only the order of the sinks fits the fixed workspace, the plan
+    keeps that order and regions of one kind; where neither does (36.4 MB in that order), its regions are the ones that save the most launches."""
+    s = clg.Session(wl.nasnet_a(0, batch=batch, image=image), wl.default_registry(("igemm_r16",), sepconv=True), device=None)
+    plan = s.compile(s.search([1] * len(s.match()), 0)[1])
+    assert (plan.ws_bytes <= B.STATIC_WORKSPACE_BYTES) == (batch < 12)
+    members = {}
+    for k, r in zip(plan.kernels(), plan.regions()):
+        members.setdefault(r, set()).add(k["name"].split("_")[0])
+    del members[-1]
+    assert any(len(m) > 2 for m in members.values()) == mixed, members
+    s.close()
+
+
 def test_a_graph_with_plans_can_neither_go_nor_change():
     d = wl.tiny_cnn(0, image=8)
     s = clg.Session(d, wl.default_registry(), device=None)

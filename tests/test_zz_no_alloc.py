@@ -72,6 +72,19 @@ def test_static_workspace_gives_the_bits_of_clg_execute_on_two_calls_in_a_row():
     s2.close()
 
 
+def test_static_workspace_with_regions_of_unlike_kinds():
+    """Kernels in order of their level, and the members of a region in one launch."""
+    d = wl.nasnet_a(0, image=48, stem=8, filters=8, cells=1, classes=5, batch=2)
+    s = clg.Session(d, wl.default_registry(("igemm_r16",), sepconv=True), device=0)
+    plan = s.compile(s.search([1] * len(s.match()), 0)[1]).bind()
+    plan.set_handover([1] * plan.n_kernels, lanes=1)
+    assert plan.n_launches < plan.n_kernels - 20
+    want, got = _both_ways(plan)
+    assert all(np.array_equal(a, b) for a, b in zip(want, got))
+    assert max(norm_err(a, b) for a, b in zip(got, Graph(d).run())) <= 1e-3
+    s.close()
+
+
 def test_static_workspace_refuses_what_does_not_fit():
     r = np.random.default_rng(3)
     d = wl.GraphDesc("too_big")
