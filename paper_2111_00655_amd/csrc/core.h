@@ -229,6 +229,7 @@ struct Plan {
     std::vector<char> fuse_mark;           // per call, scratch of an execution: 1 launched with its region, 2 carried its region
     std::vector<std::vector<int32_t>> ahead;   // call -> later calls whose packed weights it reads ahead
     size_t workspace_bytes = 0;
+    int32_t missing_const = -1;            // a constant without device memory that a kernel reads (any operand), -1 none: not executed
     // concurrent lanes: kernels of independent branches go to different HIP streams
     int32_t max_lanes = 1;                 // 1 = everything on the caller's stream (default: see clg_plan_set_lanes)
     int32_t n_lanes = 1;                   // lanes the schedule uses

@@ -651,6 +651,10 @@ int32_t compile_plan(Context &ctx, Graph &g, const int32_t *ids, size_t n, Plan 
             return fail(CLG_HIP_ERROR, "weight packing failed: %s", hipGetErrorString(hipGetLastError()));
     }
     plan_read_ahead(plan);
+    plan->missing_const = -1;
+    for (const KernelCall &c : plan->calls)
+        for (int32_t v : operands_of(c))
+            if (g.nodes[v].kind == NODE_CONST && !g.nodes[v].dev_ptr) plan->missing_const = v;
     return CLG_OK;
 }
 
@@ -982,9 +986,6 @@ static int32_t launch_join(const Plan &p, const Join &j, const F &ptr_of, void *
         for (int s = 0; s < e.n; ++s) e.s[s].ptr = in(c.epi_nodes[s]);
         return e;
     };
-    for (size_t i = first; i <= last; ++i)
-        for (int32_t v : {p.calls[i].a_node, p.calls[i].b_node, p.calls[i].c_node})
-            if (v >= 0 && !ptr_of(v)) return fail(CLG_INVALID_ARG, "constant node %d has no device pointer", v);
     void *scratch = p.scratch_offset[first] >= 0 ? (char *)workspace + p.scratch_offset[first] : nullptr;
     int err;
     *done = true;
@@ -1054,6 +1055,7 @@ int32_t execute_plan(Plan &p, const void *const *inputs, void *const *outputs, v
         if (!inputs[i]) return fail(CLG_INVALID_ARG, "input %d is null", i);
     for (size_t i = 0; i < g.outputs.size(); ++i)
         if (!outputs[i]) return fail(CLG_INVALID_ARG, "output %zu is null", i);
+    if (p.missing_const >= 0) return fail(CLG_INVALID_ARG, "constant node %d has no device pointer", p.missing_const);
 
     auto ptr_of = [&](int32_t v) -> const void * {
         if (v < 0) return nullptr;
@@ -1240,9 +1242,6 @@ int32_t execute_plan(Plan &p, const void *const *inputs, void *const *outputs, v
         }
         const void *epi[kMaxEpi];
         for (int s = 0; s < kMaxEpi; ++s) epi[s] = ptr_of(c.epi_nodes[s]);
-        for (int32_t v : {c.a_node, c.b_node, c.c_node})
-            if (v >= 0 && !ptr_of(v)) rc = fail(CLG_INVALID_ARG, "constant node %d has no device pointer", v);
-        if (rc != CLG_OK) break;
         void *scratch = p.scratch_offset[i] >= 0 ? (char *)workspace + p.scratch_offset[i] : nullptr;
         void *st = stream_of(i);
         if (lanes)

@@ -2,10 +2,12 @@
 remainders can go wrong beside the others.  Against the oracle; the kinds that run unchanged (all but 1x1 convolutions) bit for bit as one by one."""
 import numpy as np
 import pytest
+import torch
 
 import workloads as wl
 from workloads.patterns import P, W
 import paper_2111_00655_amd as clg
+from paper_2111_00655_amd import binding as B
 from oracle.graph import Graph
 from parity_util import OP_TOL, check_outputs
 
@@ -86,3 +88,42 @@ def test_region_of_siblings_of_unlike_kinds(ci):
         for k, (a, b) in enumerate(zip(got, one_by_one)):
             assert branches[k][0] == "conv" or np.array_equal(a, b), (ci, digits, branches[k])
     s.close()
+
+
+@pytest.mark.parametrize("missing", ["weights", "bias"])
+def test_a_constant_without_device_memory_is_refused_in_a_region_too(missing):
+    """Depthwise convolutions and a pool over one tensor: the members of a region are checked as kernels launched one by one are, and so are the operands of
+    fused tails (host-side checks: nothing is launched)."""
+    r = np.random.default_rng(5)
+    d = wl.GraphDesc("no_memory")
+    x = d.input(r.standard_normal((1, 8, 6, 6)).astype(np.float32))
+    w, b = d.const(r.standard_normal((8, 1, 3, 3)).astype(np.float32)), d.const(r.standard_normal(8).astype(np.float32))
+    d.mark_output(d.op("bias_add", [d.op("conv2d", [x, w], stride=(1, 1), pad=(1, 1), groups=8), b], axis=1))
+    d.mark_output(d.op("max_pool2d", [x], kernel=(3, 3), stride=(1, 1), pad=(1, 1)))
+    reg = [("direct", P("bias_add", P("conv2d", W, W), W)), ("direct", P("max_pool2d", W))]
+    ctx = B.clg_create(0)
+    g = B.clg_graph_create(ctx)
+    for be, pat in reg:
+        B.clg_register_pattern(ctx, B.clg_register_backend(ctx, be), pat)
+    keep = {n: torch.from_numpy(t).to("cuda:0") for n, t in d.tensors.items() if n in (w, b)}
+    for n, nd in enumerate(d.nodes):
+        if nd["kind"] == "input":
+            B.clg_graph_input(g, B.F32, nd["shape"])
+        elif nd["kind"] == "const":
+            B.clg_graph_const(g, B.F32, d.tensors[n].shape, 0 if n == (w if missing == "weights" else b) else keep[n].data_ptr())
+        else:
+            B.clg_graph_op(g, nd["kind"], nd["inputs"], B.make_attrs(**nd["attrs"]))
+    for o in d.outputs:
+        B.clg_graph_mark_output(g, o)
+    plan = B.clg_compile(ctx, g, list(range(len(B.clg_match_all(ctx, g)))))
+    xs = torch.zeros(1, 8, 6, 6, device="cuda:0")
+    outs = [torch.zeros(1, 8, 6, 6, device="cuda:0") for _ in d.outputs]
+    for digits in ([0, 0], [1, 1]):
+        B.clg_plan_set_handover(plan, digits, 1)
+        assert B.clg_plan_num_launches(plan) == 2 - digits[0]
+        with pytest.raises(clg.ClgError, match="device pointer") as e:
+            B.clg_execute(plan, [xs.data_ptr()], [t.data_ptr() for t in outs], 0, 0, torch.cuda.current_stream().cuda_stream)
+        assert e.value.status == "INVALID_ARG"
+    B.clg_plan_destroy(plan)
+    B.clg_graph_destroy(g)
+    B.clg_destroy(ctx)
