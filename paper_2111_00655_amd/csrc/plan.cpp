@@ -976,7 +976,13 @@ int32_t launch_call(const KernelCall &c, const void *a, const void *b, const voi
     return CLG_OK;
 }
 
-// The launches of a join, operands by `ptr_of`; *done = false: the addresses are such that they run one by one.
+// Whether two arrays of floats share memory (a null one shares none).
+static bool meet(const float *p, int64_t n, const float *q, int64_t m) {
+    return p && q && (uintptr_t)p < (uintptr_t)q + 4 * (uintptr_t)m && (uintptr_t)q < (uintptr_t)p + 4 * (uintptr_t)n;
+}
+
+// The launches of a join, operands by `ptr_of`; *done = false: the addresses are such that they run one by one (a caller's output buffer may lie over an
+// input, or over another output, which kernels that run one after the other take as long as each reads before a later one writes).
 template <class F>
 static int32_t launch_join(const Plan &p, const Join &j, const F &ptr_of, void *workspace, const Ahead *ahead, void *stream, bool *done) {
     const size_t first = (size_t)j.first, last = first + (size_t)j.n - 1;
@@ -1000,10 +1006,16 @@ static int32_t launch_join(const Plan &p, const Join &j, const F &ptr_of, void *
         a.logits = out(d);
         a.prob = out(last);
         a.ef = make_epi_fast(bind(c.gemm.epi, c));
-        // (an image is read while results of others are written)
-        const uintptr_t x0 = (uintptr_t)a.x, x1 = x0 + 4 * (uintptr_t)a.rows * (a.hw ? (uintptr_t)a.K * a.hw : (uintptr_t)a.lda);
-        for (const float *y : {a.logits, a.prob})
-            if ((uintptr_t)y < x1 && x0 < (uintptr_t)y + 4 * (uintptr_t)a.rows * a.N) *done = false;
+        // (rows are read, weights and bias included, while results of others are written)
+        const int64_t rows = a.rows;
+        const struct { const float *p; int64_t n; } outs[] = {{a.pooled, rows * a.lda}, {a.logits, rows * a.N}, {a.prob, rows * a.N}},
+            ins[] = {{a.x, rows * (a.hw ? (int64_t)a.K * a.hw : a.lda)}, {c.pack_bytes ? nullptr : a.w, (int64_t)a.N * a.ldb}, {a.ef.flags & EF_BIAS ? a.ef.bias : nullptr, a.N}};
+        for (const auto &o : outs) {
+            for (const auto &i : ins)
+                if (meet(o.p, o.n, i.p, i.n)) *done = false;
+            for (const auto &o2 : outs)
+                if (&o2 != &o && meet(o.p, o.n, o2.p, o2.n)) *done = false;
+        }
         if (!*done) return CLG_OK;
         err = launch_classifier(a, stream);
     } else {
@@ -1018,7 +1030,9 @@ static int32_t launch_join(const Plan &p, const Join &j, const F &ptr_of, void *
         r.pro = bind(n.row.pro, n);
         const SplitSum sum{(const float *)scratch, ef.flags & EF_BIAS ? ef.bias : nullptr, ef.flags & EF_ADD ? ef.add : nullptr, b3 ? c.b3.splitk : c.gemm.splitk,
                            (int32_t)(b3 ? c.b3.c_numel : c.gemm.c_numel)};
-        if (!rowwise_sums_ok(r, sum)) {
+        // (a wave reads its row of the residual before it writes the same row; bias and other rows are read while it does)
+        const int64_t numel = (int64_t)r.rows * r.len;
+        if (!rowwise_sums_ok(r, sum) || meet(r.y, numel, sum.bias, r.len) || (r.y != sum.add && meet(r.y, numel, sum.add, numel))) {
             *done = false;
             return CLG_OK;
         }

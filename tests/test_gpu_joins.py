@@ -158,3 +158,71 @@ def test_dense_layers_split_for_a_layer_norm(rows, k, hid, head, pro, slices, ba
     assert plan.ws_bytes >= slices * rows * hid * 4 and (slices == 1) == np.array_equal(apart, got[0])
     same_on_two_lanes(plan, got)
     s.close()
+
+
+def over(plan, k, shift, n):
+    """Puts the plan's output 0 into the memory of its input k, `shift` floats behind the input's begin; returns the call that fills the inputs."""
+    base = torch.zeros(shift + max(plan._in[k].numel(), n), device="cuda:0")
+    value, shape = plan._in[k].clone(), plan._in[k].shape
+    plan._in[k] = base[:value.numel()].view(shape)
+    out = plan._out[0]
+    plan._out[0] = base[shift:shift + out.numel()].view(out.shape)
+    return lambda: plan._in[k].copy_(value)
+
+
+# the softmax over the input, over weights and over a bias that are inputs, and over the logits one row further on: rows that run beside each other would overwrite
+# what others read
+@pytest.mark.parametrize("where", ["input", "weights", "bias", "logits"])
+def test_classifier_with_outputs_over_what_other_rows_read(where):
+    r = np.random.default_rng(4)
+    m, k, n = 40, 48, 24
+    xv, wv, bv = r.standard_normal((m, k)).astype(np.float32), r.standard_normal((n, k)).astype(np.float32), r.standard_normal(n).astype(np.float32)
+    d = wl.GraphDesc("outputs_over_inputs")
+    logits = d.op("bias_add", [d.op("dense", [d.input(xv), d.input(wv)]), d.input(bv)], axis=-1)
+    d.mark_output(d.op("softmax", [logits]))
+    if where == "logits":
+        d.mark_output(logits)
+    s = clg.Session(d, [("igemm_s", P("bias_add", P("dense", W, W), W)), ("rowwise", P("softmax", W))], device=0)
+    plan = s.compile(list(range(len(s.match())))).bind()
+    assert plan.n_launches == 1
+    z = xv.astype(np.float64) @ wv.T.astype(np.float64) + bv
+    e = np.exp(z - z.max(-1, keepdims=True))
+    want = e / e.sum(-1, keepdims=True)
+    fill = lambda: None
+    if where == "logits":
+        both = torch.zeros((m + 1) * n, device="cuda:0")
+        plan._out = [both[n:].view(m, n), both[:m * n].view(m, n)]
+    else:
+        fill = over(plan, ("input", "weights", "bias").index(where), 8, m * n)
+    for _ in range(3):
+        fill()
+        plan.execute()
+        torch.cuda.synchronize()
+        assert np.allclose(plan._out[0].cpu().numpy(), want, rtol=1e-4, atol=1e-7)
+    s.close()
+
+
+# the layer norm's result over the residual of the dense layer in front of it (its own row: joined; a row further on: not) and over its bias
+@pytest.mark.parametrize("where,shift", [(1, 0), (1, 260), (2, 0)], ids=["residual", "residual a row on", "bias"])
+@pytest.mark.parametrize("backend,rows", [("igemm_r16_sk", 200), ("igemm_r16", 16)], ids=["split", "split for it"])
+def test_layer_norm_over_what_its_dense_layer_adds(backend, rows, where, shift):
+    r = np.random.default_rng(6)
+    f = lambda *sh: r.standard_normal(sh).astype(np.float32)
+    k, hid = 2048, 260
+    xv, av, bv, wv, g, b = f(rows, k), f(rows, hid), f(hid), f(hid, k) / np.float32(k ** 0.5), f(hid), f(hid)
+    d = wl.GraphDesc("norm_over_inputs")
+    x, a, bias = d.input(xv), d.input(av), d.input(bv)
+    y = d.op("add", [d.op("bias_add", [d.op("dense", [x, d.const(wv)]), bias], axis=-1), a])
+    d.mark_output(d.op("layer_norm", [y, d.const(g), d.const(b)], eps=1e-5))
+    s = clg.Session(d, [(backend, P("add", P("bias_add", P("dense", W, W), W), W)), ("rowwise", P("layer_norm", W, W, W))], device=0)
+    plan = s.compile(list(range(len(s.match())))).bind()
+    z = xv.astype(np.float64) @ wv.T.astype(np.float64) + bv + av
+    z -= z.mean(-1, keepdims=True)
+    want = z / np.sqrt((z * z).mean(-1, keepdims=True) + 1e-5) * g + b
+    fill = over(plan, where, shift, rows * hid)
+    for _ in range(3):
+        fill()
+        plan.execute()
+        torch.cuda.synchronize()
+        assert np.linalg.norm(plan._out[0].cpu().numpy() - want) < 2e-6 * np.linalg.norm(want)       # (as below)
+    s.close()
