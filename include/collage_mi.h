@@ -516,7 +516,8 @@ int32_t clg_plan_measure(clg_plan *plan, const void *const *inputs,
                          const clg_measure_opts *opts, int64_t *ns);
 /* (Joins: the layer norm behind a dense layer with K split adds up its partial
  * results, and [a global average pool,] a dense layer of at most 64 classes and
- * 256 channels and a softmax behind each other are one launch, on whichever lane.
+ * 256 channels and a softmax behind each other, on no more rows than one launch
+ * holds without a loss, are one launch, on whichever lane.
  * clg_execute_timed runs their kernels one by one; a classifier's results then
  * agree to rounding, others bit for bit.) */
 int32_t clg_plan_num_launches(const clg_plan *plan, size_t *n);

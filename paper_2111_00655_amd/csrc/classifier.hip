@@ -111,10 +111,15 @@ __global__ __launch_bounds__(kThreads) void classifier_kernel(ClassifierArgs a, 
 
 // An image up to 256 KB: one compute unit sums it in the time that a launch costs (45x45: GPU time of the network 17.8 -> 16.9 us); larger ones are
 // summed by all of them, and only dense layer and softmax are joined (55x55 19.3 -> 18.6, 96x96 27.1 -> 26.5).
-bool classifier_resolve(const PoolArgs *pool, const GemmArgs &d, const RowwiseArgs &sm, ClassifierArgs *out) {
+// Images: a workgroup each, and a round of workgroups costs as much as the first however little each has to do, while the tiles of a dense layer grow with the rows
+// slowly.  So no more rows than compute units, or than twice as many where a pool is joined as well, from 32 channels on.  us, launches apart and joined, on 256 compute units: 256 -> 64
+// on 256 rows 5.0 and 4.7, 384 5.0 and 7.7, 4096 7.3 and 50; 32 -> 10 on 256 5.4 and 3.6, 384 5.5 and 5.6, 1024 5.5 and 9.6; with a pool 64 channels of 4x4 on 256 rows 8.5 and 4.9, 512 10.0
+// and 8.2, 768 11.3 and 11.4; 32 channels of 16x16 on 512 10.0 and 8.4, 1024 12.8 and 15.2; 256 channels of 7x7 on 512 20.7 and 10.3; 16 channels of 8x8 on 256 7.4 and 5.0, 257 7.5 and 7.7.
+bool classifier_resolve(const PoolArgs *pool, const GemmArgs &d, const RowwiseArgs &sm, int n_cus, ClassifierArgs *out) {
     const int flags = epi_fast_flags(d.epi);
     if (d.mode != GM_NT || d.batch != 1 || d.cs_len || (flags & ~EF_BIAS)) return false;
-    if (d.N < 1 || d.N > kMaxClasses || d.K < 1 || d.K > kMaxChannels || (int64_t)d.N * d.ldb >= ((int64_t)1 << 30) || d.M < 1 || d.M > 65535) return false;
+    if (d.N < 1 || d.N > kMaxClasses || d.K < 1 || d.K > kMaxChannels || (int64_t)d.N * d.ldb >= ((int64_t)1 << 30) || d.M < 1) return false;
+    if (d.M > (pool && d.K >= 32 ? 2 * n_cus : n_cus)) return false;
     if (sm.mode != 0 || sm.n_gather || sm.pro.n || sm.rows != d.M || sm.len != d.N || d.ldc != d.N) return false;
     ClassifierArgs a{};
     if (pool) {

@@ -387,7 +387,7 @@ struct ClassifierArgs {
     int32_t rows, K, N, hw, lda, ldb, ldc, ts, ngtot;
 };
 // Fills `a` from the calls' arguments (pool may be null); false: the kernel does not take them.
-bool classifier_resolve(const PoolArgs *pool, const GemmArgs &dense, const RowwiseArgs &softmax, ClassifierArgs *a);
+bool classifier_resolve(const PoolArgs *pool, const GemmArgs &dense, const RowwiseArgs &softmax, int n_cus, ClassifierArgs *a);
 int launch_classifier(const ClassifierArgs &a, void *stream);
 
 // ---- elementwise chain / gather --------------------------------------------------------------

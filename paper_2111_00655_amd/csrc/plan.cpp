@@ -325,7 +325,7 @@ void find_joins(const Context &ctx, const Graph &g, Plan *plan) {
             j.kind = JOIN_CLASSIFIER;
             j.first = (int32_t)i;
             j.n = (int32_t)(d + 2 - i);
-            if (classifier_resolve(d == i ? nullptr : &calls[i].pool, dense.gemm, soft.row, &j.classifier)) add(j);
+            if (classifier_resolve(d == i ? nullptr : &calls[i].pool, dense.gemm, soft.row, ctx.n_cus, &j.classifier)) add(j);
         }
         // a dense layer whose result only the layer norm behind it reads, as what is normalised: split already, or to be split for that
         if (!(alone(i, CALL_B3) || alone(i, CALL_GEMM)) || !alone(i + 1, CALL_ROWWISE)) continue;

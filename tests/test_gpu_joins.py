@@ -88,6 +88,24 @@ def test_what_is_no_small_classifier():
         s.close()
 
 
+# both sides of the row counts up to which a workgroup per row pays: compute units, twice as many with a pool of 32 channels and more
+@pytest.mark.parametrize("c,hw,rows,joined", [(40, 0, 1, 1), (40, 0, 0, 2), (40, 5, 1, 1), (40, 5, 2, 1), (40, 5, 3, 3), (31, 5, 1, 1), (31, 5, 0, 3)])
+def test_classifier_rows(c, hw, rows, joined):
+    n_cus = torch.cuda.get_device_properties(0).multi_processor_count
+    m = {0: n_cus + 1, 1: n_cus, 2: 2 * n_cus, 3: 2 * n_cus + 1}[rows]
+    r = np.random.default_rng(m)
+    xv, wv = r.standard_normal((m, c, hw, 1) if hw else (m, c)).astype(np.float32), r.standard_normal((10, c)).astype(np.float32)
+    d = wl.GraphDesc("classifier_rows")
+    x = d.input(xv)
+    d.mark_output(d.op("softmax", [d.op("dense", [d.op("global_avg_pool2d", [x]) if hw else x, d.const(wv)])]))
+    s = clg.Session(d, [("direct", P("global_avg_pool2d", W)), ("igemm_s8", P("dense", W, W)), ("rowwise", P("softmax", W))], device=0)
+    plan = s.compile(list(range(len(s.match()))))
+    assert plan.n_launches == joined
+    e = np.exp((xv.astype(np.float64).mean((2, 3)) if hw else xv.astype(np.float64)) @ wv.T.astype(np.float64))
+    assert np.allclose(plan.run()[0], e / e.sum(-1, keepdims=True), rtol=1e-4, atol=0)
+    s.close()
+
+
 # rows and lengths with partly empty tiles and waves, two to sixteen slices, one to eight loads per lane; bias and residual before and in the layer norm's prologue
 @pytest.mark.parametrize("rows,k,hid,head,pro", [(389, 3072, 768, (), ("bias_add", "add")), (161, 2048, 64, ("bias_add",), ("add",)), (200, 512, 260, ("bias_add", "add"), ()),
                                                  (160, 4096, 128, (), ()), (333, 1024, 516, ("bias_add",), ("add",)), (170, 1024, 1028, (), ("add",)), (162, 2048, 2048, ("bias_add",), ("add",))])
