@@ -18,10 +18,13 @@
 // a lane's four neighbouring ones belong to four column tiles), between the products of the scores, which wait for k only.  The lanes of an MFMA's
 // operand hold 16 bytes of 16 rows each, and a load in that pattern takes the L1 27 ns instead of the 7 of a contiguous one: q (once per
 // workgroup) and k are loaded in the order of memory and change lanes through LDS.  Every wave has a partial result of all columns; they meet in LDS.
-// Twelve heads of 64, us: 128 keys 4.8, 256 keys 6.8, 389 keys 14.3, 512 keys 16.4.  With k loaded as the MFMA wants it 4.9, 7.2, 14.7 and 17.1; with
-// every wave loading the query rows so as well, and v before the first product, 5.4, 7.9, 16.6 and 19.0 (of that, 16 bytes instead of 4 per LDS
-// access of the softmax made 0.6 at 389 and 512 keys).  A head's tiles on one XCD: no change.  Sixteen waves with two column tiles of v per wave: 5.4, 11.2 and
-// 18.4 at 128, 256 and 389 keys.
+// Twelve heads of 64, us: 128 keys 4.3, 256 keys 6.1, 389 keys 13.1, 512 keys 14.7; with k loaded as the MFMA wants it, every wave loading the query rows so
+// as well, and v before the first product, 5.1, 7.5, 16.1 and 17.9 (of that, 16 bytes instead of 4 per LDS access of the softmax made 0.6 at 389 and 512 keys).
+// k passes through LDS in slices of 32 columns, in the place of the partial results: with whole rows in a place of their own a compute unit held one workgroup
+// of 128-wide heads instead of two to four.  384 heads, us, k as the MFMA wants it, whole rows and slices: heads of 128, 16 keys 6.0, 8.3 and 6.0, 64 keys 22.4, 30.8 and 22.0, 128 keys 67, 76
+// and 65, 256 keys 215, 222 and 180; heads of 64, 64 keys 14.6, 12.4 and 12.5, 200 keys 70, 72 and 63, 300 keys 177, 149 and 118; heads of 32, 512 keys 163, 201 and 161.  Seven keys
+// are 0.1 - 0.2 us slower for the barrier that query rows in LDS need.
+// A head's tiles on one XCD: no change.  Sixteen waves with two column tiles of v per wave: slower from 128 to 389 keys.
 #include <algorithm>
 #include <type_traits>
 
@@ -64,9 +67,9 @@ constexpr int kWaves = 8;
 constexpr int kCUs = 256;          // compute units of an MI355X
 
 // D16 = head size / 16; MAXT = key tiles per wave (kWaves * MAXT tiles cover the keys); RT = row tiles; CS = column
-// splits of the second product.
+// splits of the second product; SL = columns of k that a wave passes through LDS at a time.
 // R: Ahead (workgroups behind the heads read ahead) or NoAhead.
-template <int D16, int MAXT, int RT, int CS, class R>
+template <int D16, int MAXT, int RT, int CS, int SL, class R>
 __global__ __launch_bounds__(kWaves * kWave) void attention_kernel(AttentionArgs a, R ra) {
     constexpr int ROWS = kRows * RT, d = D16 * 16, ldr = d + 4;
     constexpr int KS = kWaves / CS, VT = D16 / CS;           // key splits of the second product, column tiles of a wave
@@ -79,7 +82,7 @@ __global__ __launch_bounds__(kWaves * kWave) void attention_kernel(AttentionArgs
     static_assert(PPL * LPR == kWaves * MAXT * 4, "a lane takes whole parts");
     typedef float vecv __attribute__((ext_vector_type(VEC)));
     typedef float vecu __attribute__((ext_vector_type(VEC), aligned(4)));      // (v may lie at any address of a float)
-    extern __shared__ float lds[];                           // [ROWS][ldp]: scores, then probabilities; then [KS][ROWS][ldr]: partial results
+    extern __shared__ float lds[];                           // [ROWS][ldp]: scores, then probabilities, behind them lds_q and lds_k; then [KS][ROWS][ldr]: partial results
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r = lane & 15, s = lane >> 4;
@@ -96,21 +99,26 @@ __global__ __launch_bounds__(kWaves * kWave) void attention_kernel(AttentionArgs
     const float *V = a.v + (int64_t)h * a.Sk * d;
 
     // ---- all loads: key tiles wave, wave + kWaves, ... of this wave (past the end: the last key row, not used)
-    // (in the order of memory: 64 lanes of one load that read 16 bytes of 16 rows each take 64 cycles of the L1, neighbouring ones 17.  The lanes that
-    // multiply them get q and k through LDS, k through the wave's own part of it.)
+    // (in the order of memory, whole lines: 64 lanes of one load that read 16 bytes of 16 rows each take 64 cycles of the L1, neighbouring ones 17.  The
+    // lanes that multiply them get q and k through LDS, k through the wave's own part of it, slice after slice.)
     floatx4 qa[RT][D16], ko[MAXT][D16];
-    float *const lds_q = lds + ROWS * max(ldp, KS * ldr);    // [ROWS][ldr]
-    float *const lds_k = lds_q + (ROWS + 16 * wave) * ldr;   // [16][ldr]
-    constexpr int PPR = 4 * D16;                             // 16-byte parts of a row of q, k
+    constexpr int GS = SL / 16, lks = SL + 4;
+    constexpr int LC = 32, PPL_K = LC / 4, RPL = kWave / PPL_K;          // columns, 16-byte parts and rows of one load of k
+    constexpr bool Q_LATE = D16 >= 4 && RT == 1;             // query rows read from LDS again for every key tile: fewer registers
+    static_assert(d % LC == 0 && LC % SL == 0 && SL % 16 == 0, "whole slices per load");
+    float *const lds_q = lds + ROWS * ldp;                   // [ROWS][ldr]
+    float *const lds_k = lds_q + ROWS * ldr + 16 * wave * lks;           // [16][lks]
+    constexpr int PPR = 4 * D16;                             // 16-byte parts of a row of q
     floatx4 q_own = {0.f, 0.f, 0.f, 0.f};
-    static_assert(ROWS * PPR <= kWaves * kWave && kWave % PPR == 0, "16 bytes per lane, whole rows per load");
-    const int q_row = tid / PPR, q_part = tid % PPR, k_row = lane / PPR, k_part = lane % PPR;
+    static_assert(ROWS * PPR <= kWaves * kWave, "16 bytes per lane");
+    const int q_row = tid / PPR, q_part = tid % PPR, k_row = lane / PPL_K, k_part = lane % PPL_K;
     if (q_row < ROWS) q_own = reinterpret_cast<const floatx4 *>(Q + (int64_t)min(q0 + q_row, a.Sq - 1) * d)[q_part];
 #pragma unroll
     for (int u = 0; u < MAXT; ++u)
+        if (!(D16 == 8 && MAXT == 1) || wave < nct)          // (heads of 128, 16 keys: loads of the other waves took 0.2 of 4.6 us)
 #pragma unroll
         for (int i = 0; i < D16; ++i)
-            ko[u][i] = reinterpret_cast<const floatx4 *>(K + (int64_t)min((wave + kWaves * u) * 16 + i * (kWave / PPR) + k_row, a.Sk - 1) * d)[k_part];
+            ko[u][i] = reinterpret_cast<const floatx4 *>(K + (int64_t)min((wave + kWaves * u) * 16 + i % (LC / 16) * RPL + k_row, a.Sk - 1) * d)[i / (LC / 16) * PPL_K + k_part];
     // (heads of 128 leave no registers for v before the scores are done)
     constexpr bool EARLY_V = D16 <= 4;
     const int ks = wave / CS, c0 = wave % CS * VT * 16;      // key tiles ks, ks + KS, ... and first column in the second product
@@ -131,39 +139,54 @@ __global__ __launch_bounds__(kWaves * kWave) void attention_kernel(AttentionArgs
     __builtin_amdgcn_sched_barrier(0);                       // every load leaves before anything waits
     if (q_row < ROWS) *reinterpret_cast<floatx4 *>(lds_q + q_row * ldr + 4 * q_part) = q_own;
     lds_barrier();
+    auto load_q = [&](int g) {
 #pragma unroll
-    for (int t = 0; t < RT; ++t)
+        for (int t = 0; t < RT; ++t) qa[t][g] = *reinterpret_cast<const floatx4 *>(lds_q + (16 * t + r) * ldr + 16 * g + 4 * s);
+    };
+    if constexpr (!Q_LATE) {
 #pragma unroll
-        for (int g = 0; g < D16; ++g) qa[t][g] = *reinterpret_cast<const floatx4 *>(lds_q + (16 * t + r) * ldr + 16 * g + 4 * s);
+        for (int g = 0; g < D16; ++g) load_q(g);
+    }
     // ---- scores; accumulator g of a lane: row 4s + g, column r of the tile
 #pragma unroll
     for (int u = 0; u < MAXT; ++u) {
         const int kt = wave + kWaves * u;
         if (kt < nct) {                                      // uniform over the wave
-            floatx4 kb[D16];
-#pragma unroll
-            for (int i = 0; i < D16; ++i) *reinterpret_cast<floatx4 *>(lds_k + (i * (kWave / PPR) + k_row) * ldr + 4 * k_part) = ko[u][i];
-#pragma unroll
-            for (int g = 0; g < D16; ++g) kb[g] = *reinterpret_cast<const floatx4 *>(lds_k + r * ldr + 16 * g + 4 * s);
             floatx4 acc[RT][2];                              // even and odd groups of d apart: shorter chains
 #pragma unroll
             for (int t = 0; t < RT; ++t) acc[t][0] = acc[t][1] = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int g = 0; g < D16; g += 2)
+            for (int g0 = 0; g0 < D16; g0 += GS) {
+                floatx4 kb[GS];
+                constexpr int LPB = LC / 16;                 // loads per block of LC columns
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    if constexpr (LATE_V) {
-                        if (g == 0) {
-                            load_v(u, q);
-                            __builtin_amdgcn_sched_barrier(0);
-                        }
-                    }
+                for (int i = 0; i < LPB; ++i)
+                    if (LC == SL || k_part / (SL / 4) == g0 / GS % (LC / SL))
+                        *reinterpret_cast<floatx4 *>(lds_k + (i * RPL + k_row) * lks + 4 * (k_part % (SL / 4))) = ko[u][g0 / LPB * LPB + i];
 #pragma unroll
-                    for (int e = 0; e < 2; ++e)
+                for (int g = 0; g < GS; ++g) kb[g] = *reinterpret_cast<const floatx4 *>(lds_k + r * lks + 16 * g + 4 * s);
+                if constexpr (Q_LATE) {
 #pragma unroll
-                        for (int t = 0; t < RT; ++t)
-                            acc[t][e] = __builtin_amdgcn_mfma_f32_16x16x4f32(qa[t][g + e][q], kb[g + e][q], acc[t][e], 0, 0, 0);
+                    for (int g = 0; g < GS; ++g) load_q(g0 + g);
                 }
+                constexpr int E = GS < 2 ? 1 : 2;            // groups side by side
+#pragma unroll
+                for (int g = 0; g < GS; g += E)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        if constexpr (LATE_V) {
+                            if (g0 + g == 0) {
+                                load_v(u, q);
+                                __builtin_amdgcn_sched_barrier(0);
+                            }
+                        }
+#pragma unroll
+                        for (int e = 0; e < E; ++e)
+#pragma unroll
+                            for (int t = 0; t < RT; ++t)
+                                acc[t][(g0 + e) % 2] = __builtin_amdgcn_mfma_f32_16x16x4f32(qa[t][g0 + g + e][q], kb[g + e][q], acc[t][(g0 + e) % 2], 0, 0, 0);
+                    }
+            }
             const int col = kt * 16 + r;
 #pragma unroll
             for (int t = 0; t < RT; ++t)
@@ -250,24 +273,30 @@ __global__ __launch_bounds__(kWaves * kWave) void attention_kernel(AttentionArgs
     }
 }
 
-template <int D16, int MAXT, int RT, int CS, class R>
+template <int D16, int MAXT, int RT, int CS, int SL>
+size_t lds_bytes(int Sk) {
+    constexpr int ROWS = kRows * RT, ldr = D16 * 16 + 4;
+    const int ldp = (Sk + 15) / 16 * 16 + 4;
+    return (size_t)std::max(ROWS * (ldp + ldr) + 16 * kWaves * (SL + 4), kWaves / CS * ROWS * ldr) * sizeof(float);
+}
+
+template <int D16, int MAXT, int RT, int CS, int SL, class R>
 int launch_as(const AttentionArgs &a, const R &r, dim3 grid, hipStream_t s) {
-    constexpr int ROWS = kRows * RT;
-    const size_t lds = (size_t)ROWS * (std::max((a.Sk + 15) / 16 * 16 + 4, kWaves / CS * (D16 * 16 + 4)) + (D16 * 16 + 4) * (1 + 16 * kWaves / ROWS)) * sizeof(float);
+    const size_t lds = lds_bytes<D16, MAXT, RT, CS, SL>(a.Sk);
     if (lds > 64 * 1024) {
         static LdsLimit limit;
-        const hipError_t e = limit.raise((const void *)attention_kernel<D16, MAXT, RT, CS, R>);
+        const hipError_t e = limit.raise((const void *)attention_kernel<D16, MAXT, RT, CS, SL, R>);
         if (e != hipSuccess) return (int)e;
     }
-    hipLaunchKernelGGL((attention_kernel<D16, MAXT, RT, CS, R>), grid, dim3(kWaves * kWave), lds, s, a, r);
+    hipLaunchKernelGGL((attention_kernel<D16, MAXT, RT, CS, SL, R>), grid, dim3(kWaves * kWave), lds, s, a, r);
     return (int)hipGetLastError();
 }
 
-template <int D16, int MAXT, int RT, int CS>
+template <int D16, int MAXT, int RT, int CS, int SL = 32>
 int launch_one(const AttentionArgs &a, const AttentionGrid &g, const Ahead *ahead, hipStream_t s) {
     const dim3 grid((unsigned)g.tiles, (unsigned)a.B);
-    if (ahead && ahead->n && g.spare) return launch_as<D16, MAXT, RT, CS>(a, *ahead, dim3(grid.x, grid.y + (unsigned)(g.spare / g.tiles)), s);
-    return launch_as<D16, MAXT, RT, CS>(a, NoAhead{}, grid, s);
+    if (ahead && ahead->n && g.spare) return launch_as<D16, MAXT, RT, CS, SL>(a, *ahead, dim3(grid.x, grid.y + (unsigned)(g.spare / g.tiles)), s);
+    return launch_as<D16, MAXT, RT, CS, SL>(a, NoAhead{}, grid, s);
 }
 
 // Up to 128 keys a wave takes one column tile of the result (a short second product: adding eight partial results would be
@@ -278,6 +307,10 @@ int launch_heads(const AttentionArgs &a, const Ahead *r, hipStream_t s) {
     const AttentionGrid g = attention_grid(a);
     if (tiles <= kWaves) return launch_one<D16, 1, 1, D16>(a, g, r, s);
     if (tiles <= 2 * kWaves) return launch_one<D16, 2, 1, 1>(a, g, r, s);
+    // Registers hold two of these workgroups per compute unit, LDS from 449 keys on only with narrower slices of k, which otherwise take 2 % longer (512 keys, slices
+    // of 32 and 16 columns, us: 192 heads 102 and 83, 24 heads 17.8 and 15.8, 16 heads 9.5 and 9.7).
+    if constexpr (D16 == 2)
+        if (g.rows == 2 * kRows && (int64_t)g.tiles * a.B > kCUs && lds_bytes<2, 4, 2, 1, 32>(a.Sk) > 80 * 1024) return launch_one<2, 4, 2, 1, 16>(a, g, r, s);
     if constexpr (D16 <= 4)
         if (g.rows == 2 * kRows) return tiles <= 3 * kWaves ? launch_one<D16, 3, 2, 1>(a, g, r, s) : launch_one<D16, 4, 2, 1>(a, g, r, s);
     return tiles <= 3 * kWaves ? launch_one<D16, 3, 1, 1>(a, g, r, s) : launch_one<D16, 4, 1, 1>(a, g, r, s);

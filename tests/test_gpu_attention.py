@@ -13,7 +13,9 @@ pytestmark = pytest.mark.gpu
 
 # heads, queries, keys, head size
 CASES = [(12, 128, 128, 64), (12, 129, 129, 64), (12, 336, 336, 64), (12, 337, 389, 64), (12, 512, 512, 64), (1, 7, 130, 64),
-         (17, 250, 300, 32), (40, 100, 512, 32), (3, 40, 97, 32), (9, 470, 144, 128), (2, 31, 128, 128), (300, 17, 3, 64)]
+         (17, 250, 300, 32), (40, 100, 512, 32), (3, 40, 97, 32), (9, 470, 144, 128), (2, 31, 128, 128), (300, 17, 3, 64),
+         # more workgroups than compute units: slices of k of both widths (heads of 32, on both sides of 448 keys), every count of key tiles per wave
+         (80, 100, 470, 32), (80, 100, 512, 32), (80, 100, 448, 32), (300, 5, 9, 128), (40, 130, 70, 128), (40, 130, 250, 128), (30, 150, 300, 128), (70, 150, 250, 64)]
 
 
 @pytest.mark.parametrize("merged", [False, True])
