@@ -281,15 +281,24 @@ void find_regions(const Context &ctx, const Graph &g, bool allow_mixed, Plan *pl
 }
 
 // Lowers a register-fed dense layer in front of a layer norm again, with K split four ways in workgroups of four waves, where that shares out long
-// rows better: the layer norm adds up the partial results at no launch of its own.  All of BERT-base (3072 -> 768), us, unsplit and split, by the number T
-// of 16 x 16 tiles on 256 compute units: T = 48 438 and 403, 96 450 and 438, 144 473 and 475, 192 492 and 497, 240 512 and 529 (one round of tiles either way);
-// 288 589 and 575, 336 610 and 603, 384 628 and 622, 432 650 and 657, 480 658 and 674 (two rounds of tiles, five to eight of quarters).  Split 2, 3, 6
-// and 12 ways, or in workgroups of eight and sixteen waves, it is up to 4 % slower than so; 768 -> 768 as well 1 - 2 % slower.
+// rows better: the layer norm adds up the partial results at no launch of its own.  The lines were drawn by whole encoders under one placement, unsplit and split, by the
+// number T of 16 x 16 tiles on 256 compute units (us; layers written K -> N):
+//  * T <= half the compute units, from K = 2048 on.  3072 -> 768 T = 48 434 and 401, 96 460 and 448; 4096 -> 1024 64 327 and 292, 128 363 and 348; 2048 -> 512 64 321 and 311, 128 349 and 345;
+//    3584 -> 896 56 357 and 330; 6144 -> 1536 96 238 and 229; 2816 -> 704 44 432 and 399; 2560 -> 768 96 447 and 447; the one loss 2560 -> 640 120 416 and 422.
+//  * One round of tiles and up to half a second: nothing to gain (3072 -> 768 144, 192 and 240: 476 and 476, 497 and 496, 511 and 513).
+//  * Between one round of tiles and one and a quarter, where K's chunks share out evenly over slices and waves (K % 1024 = 0) and the layer norm has four slices in flight
+//    (N <= 1024): 3072 -> 768 288 589 and 575, 4096 -> 768 288 643 and 630, 4096 -> 1024 320 475 and 469, 3072 -> 1024 320 433 and 423, 3072 -> 512 288 760 and 719; otherwise 2560 -> 640 320 547 and 562,
+//    3584 -> 896 280 498 and 506, 3072 -> 1152 288 351 and 355.  From K = 3072 on: 2048 -> 768 288 490 and 517, 2048 -> 512 320 496 and 496.
+//  * Up to one and a half rounds, as long as K is below 4096: 3072 -> 768 384 627 and 620, 3072 -> 1024 384 449 and 441, 3072 -> 896 336 486 and 481, but 4096 -> 1024 384 486 and 490, 4096 -> 768
+//    336 655 and 655, 384 675 and 681.  More tiles: 3072 -> 768 432 650 and 657, 480 658 and 674.
+// Split 2, 3, 6 and 12 ways, or in workgroups of eight and sixteen waves, 3072 -> 768 is up to 4 % slower than so; 768 -> 768 as well 1 - 2 % slower.
 bool split_for_norm(const Context &ctx, const KernelCall &own, KernelCall *c) {
     *c = own;
     GemmArgs a = own.gemm;
     const int64_t tiles = (int64_t)((a.M + 15) / 16) * ((a.N + 15) / 16), n = ctx.n_cus;
-    if (a.K < 2048 || !(tiles * 2 <= n || (tiles > n && tiles * 2 <= 3 * n))) return false;
+    const bool few = a.K >= 2048 && tiles * 2 <= n;
+    const bool more = a.K >= 3072 && a.K % 1024 == 0 && a.N <= 1024 && tiles > n && tiles * 4 <= (a.K < 4096 ? 6 : 5) * n;
+    if (!few && !more) return false;
     if (!rf_resolve_dense(&a, 16, epi_fast_flags(a.epi), ctx.n_cus, -4, 1, 4) || a.splitk < 2) return false;
     c->gemm = a;
     c->pack_bytes = rf_pack_bytes(a);

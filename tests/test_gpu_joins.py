@@ -142,9 +142,11 @@ def test_layer_norm_of_partial_results(rows, k, hid, head, pro, backend):
     s.close()
 
 
-# fp32 dense layers that are split for the layer norm behind them: both ends of both ranges of tiles, a last slice that is short (33 chunks, three per wave: eleven waves of twelve), other tiles and K that stay
+# fp32 dense layers that are split for the layer norm behind them: both ends of both ranges of tiles, a last slice that is short (33 chunks, three per wave: eleven waves of twelve), other tiles, K and
+# widths that stay
 @pytest.mark.parametrize("rows,k,hid,head,pro,slices", [(1, 2048, 64, (), ("bias_add", "add"), 4), (16, 3072, 768, ("bias_add",), ("add",), 4), (42, 2048, 656, ("bias_add", "add"), (), 4),
-                                                        (17, 2064, 68, (), ("add",), 3), (96, 2560, 720, (), ("bias_add", "add"), 4), (128, 3072, 768, (), ("add",), 4),
+                                                        (17, 2064, 68, (), ("add",), 3), (96, 3072, 720, (), ("bias_add", "add"), 4), (80, 4096, 1024, (), ("add",), 4), (96, 2560, 720, (), ("add",), 1),
+                                                        (96, 2048, 720, (), ("add",), 1), (96, 4096, 1024, (), ("add",), 1), (64, 3072, 1028, (), ("add",), 1), (128, 3072, 768, (), ("add",), 4),
                                                         (64, 3072, 768, (), ("add",), 1), (144, 3072, 768, (), ("add",), 1), (16, 1536, 768, (), ("add",), 1)])
 @pytest.mark.parametrize("backend", ["igemm_r16", "igemm_r16x2_w8", "igemm_r32_w4"])
 def test_dense_layers_split_for_a_layer_norm(rows, k, hid, head, pro, slices, backend):
