@@ -518,8 +518,11 @@ int32_t clg_plan_measure(clg_plan *plan, const void *const *inputs,
  * results, and [a global average pool,] a dense layer of at most 64 classes and
  * 256 channels and a softmax behind each other, on no more rows than one launch
  * holds without a loss, are one launch, on whichever lane.
- * clg_execute_timed runs their kernels one by one; a classifier's results then
- * agree to rounding, others bit for bit.) */
+ * clg_execute_timed runs their kernels one by one, and so does clg_execute where
+ * operands are not aligned to 16 bytes or an output lies over what a join reads.
+ * Results then agree to rounding with those of the join if it is a classifier or
+ * if the dense layer has K split for the join only (clg_plan_kernel_info names the
+ * kernel that it has alone), otherwise bit for bit.) */
 int32_t clg_plan_num_launches(const clg_plan *plan, size_t *n);
 int32_t clg_plan_region_of(const clg_plan *plan, size_t index, int32_t *region);
 /* Reading ahead: where a plan's packed weights exceed the memory-side cache, layer
