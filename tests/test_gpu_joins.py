@@ -1,5 +1,7 @@
 """Kernels that share launches with what reads them: [global average pool,] dense layer and softmax in one, and a dense layer with K split whose partial
 results the layer norm behind it adds up."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -18,6 +20,19 @@ def timed(plan):
     torch.cuda.synchronize()
     assert (ns > 0).all()                                    # one by one
     return [t.cpu().numpy() for t in plan._out]
+
+
+def launches(plan):
+    """Kernels that one execution launches, counted in a graph that it is captured into."""
+    with open("/proc/self/maps") as f:
+        hip = ctypes.CDLL(next(line.split()[-1] for line in f if "libamdhip64.so" in line))
+    plan.execute()                                           # (what a first call sets up)
+    torch.cuda.synchronize()
+    g, st, n = torch.cuda.CUDAGraph(keep_graph=True), torch.cuda.Stream(), ctypes.c_size_t()
+    with torch.cuda.stream(st), torch.cuda.graph(g, stream=st):
+        plan.execute()
+    assert hip.hipGraphGetNodes(ctypes.c_void_p(g.raw_cuda_graph()), None, ctypes.byref(n)) == 0
+    return n.value
 
 
 def same_on_two_lanes(plan, got):
@@ -106,39 +121,51 @@ def test_classifier_rows(c, hw, rows, joined):
     s.close()
 
 
-# rows and lengths with partly empty tiles and waves, two to sixteen slices, one to eight loads per lane; bias and residual before and in the layer norm's prologue
-@pytest.mark.parametrize("rows,k,hid,head,pro", [(389, 3072, 768, (), ("bias_add", "add")), (161, 2048, 64, ("bias_add",), ("add",)), (200, 512, 260, ("bias_add", "add"), ()),
-                                                 (160, 4096, 128, (), ()), (333, 1024, 516, ("bias_add",), ("add",)), (170, 1024, 1028, (), ("add",)), (162, 2048, 2048, ("bias_add",), ("add",))])
+# rows and lengths with partly empty tiles and waves, two to sixteen slices, one to eight loads per lane; bias and residual before and in the layer norm's prologue.  igemm_r32_sk has tiles
+# that are not split: no join, the same results
+@pytest.mark.parametrize("rows,k,hid,head,pro,slices", [(389, 3072, 768, (), ("bias_add", "add"), 3), (161, 2048, 64, ("bias_add",), ("add",), 16), (200, 512, 260, ("bias_add", "add"), (), 4),
+                                                        (160, 4096, 128, (), (), 16), (333, 1024, 516, ("bias_add",), ("add",), 4), (170, 1024, 1028, (), ("add",), 4),
+                                                        (162, 2048, 2048, ("bias_add",), ("add",), 2)])
 @pytest.mark.parametrize("backend", ["igemm_r16_sk", "igemm_r32_sk"])
-def test_layer_norm_of_partial_results(rows, k, hid, head, pro, backend):
+def test_layer_norm_of_partial_results(rows, k, hid, head, pro, slices, backend):
     r = np.random.default_rng(rows + hid)
     f = lambda *sh: r.standard_normal(sh).astype(np.float32)
     d = wl.GraphDesc("split_norm")
-    pat = P("dense", W, W)
-    y = d.op("dense", [d.input(f(rows, k)), d.const(f(hid, k) / k ** 0.5)])
-    for op in head:
-        y = d.op("bias_add", [y, d.const(f(hid))], axis=-1) if op == "bias_add" else d.op("add", [y, d.input(f(rows, hid))])
-        pat = P(op, pat, W)
-    npat = W
-    for op in pro:
-        y = d.op("bias_add", [y, d.const(f(hid))], axis=-1) if op == "bias_add" else d.op("add", [y, d.input(f(rows, hid))])
-        npat = P(op, npat, W)
-    d.mark_output(d.op("layer_norm", [y, d.const(f(hid)), d.const(f(hid))], eps=1e-5))
+    pat, npat = P("dense", W, W), W
+    xv, wv = f(rows, k), f(hid, k) / np.float32(k ** 0.5)
+    y, ref = d.op("dense", [d.input(xv), d.const(wv)]), xv.astype(np.float64) @ wv.T.astype(np.float64)
+    for n, op in enumerate(head + pro):
+        t = f(hid) if op == "bias_add" else f(rows, hid)
+        ref = ref + t
+        y = d.op("bias_add", [y, d.const(t)], axis=-1) if op == "bias_add" else d.op("add", [y, d.input(t)])
+        if n < len(head):
+            pat = P(op, pat, W)
+        else:
+            npat = P(op, npat, W)
+    g, b = f(hid), f(hid)
+    d.mark_output(d.op("layer_norm", [y, d.const(g), d.const(b)], eps=1e-5))
+    c = ref - ref.mean(-1, keepdims=True)
+    ref = c / np.sqrt((c * c).mean(-1, keepdims=True) + 1e-5) * g + b
     s = clg.Session(d, [(backend, pat), ("rowwise", P("layer_norm", npat, W, W))], device=0)
     plan = s.compile(list(range(len(s.match()))))
+    split = backend == "igemm_r16_sk"
+    assert plan.kernels()[0]["name"].endswith(f"_k{slices}") == split
     got = plan.run()
-    assert plan.n_kernels == 2
+    assert plan.n_kernels == 2 and launches(plan) == 2
+    assert np.linalg.norm(got[0] - ref) < 2e-6 * np.linalg.norm(ref)      # (chains of 1024 products and less: as below)
     assert np.array_equal(got[0], timed(plan)[0])            # one by one: the same sums in the same order
     same_on_two_lanes(plan, got)
+    plan.set_lanes(1)
     # operands at addresses that 16-byte loads do not take: one by one
     if "add" in pro:
         n = len(plan._in) - 1
         odd = torch.empty(rows * hid + 1, device="cuda:0")[1:].view(rows, hid)
         odd.copy_(plan._in[n])
         plan._in[n] = odd
+        assert launches(plan) == (3 if split else 2)
         plan.execute()
         torch.cuda.synchronize()
-        assert np.allclose(plan._out[0].cpu().numpy(), got[0], rtol=1e-4, atol=1e-5)
+        assert np.linalg.norm(plan._out[0].cpu().numpy() - ref) < 2e-6 * np.linalg.norm(ref)
     s.close()
 
 
