@@ -9,7 +9,7 @@ from workloads.patterns import P, W
 import paper_2111_00655_amd as clg
 from paper_2111_00655_amd import binding as B
 from oracle.graph import Graph
-from parity_util import OP_TOL, check_outputs
+from parity_util import OP_TOL, check_outputs, norm_err
 
 pytestmark = pytest.mark.gpu
 
@@ -87,6 +87,49 @@ def test_region_of_siblings_of_unlike_kinds(ci):
         check_outputs(got, ref, OP_TOL, (ci, digits))
         for k, (a, b) in enumerate(zip(got, one_by_one)):
             assert branches[k][0] == "conv" or np.array_equal(a, b), (ci, digits, branches[k])
+    s.close()
+
+
+# 1x1 convolutions of grouped channels (whole tiles, several groups per tile, groups that take the any-filter path) and with padding, beside pools
+def test_grouped_and_padded_convolutions_in_a_region_of_unlike_kinds():
+    r = np.random.default_rng(17)
+    f32 = lambda *shape: r.standard_normal(shape).astype(np.float32)
+    c, d = 48, wl.GraphDesc("region_grouped")
+    x = d.input(f32(2, c, 9, 7))
+    for cout, groups, stride, pad in ((48, 3, 1, 0), (48, 12, 2, 0), (32, 16, 1, 0), (20, 1, 2, 1), (96, 3, 1, 1)):
+        y = d.op("conv2d", [x, d.const(f32(cout, c // groups, 1, 1))], stride=(stride, stride), pad=(pad, pad), groups=groups)
+        d.mark_output(d.op("bias_add", [y, d.const(f32(cout))], axis=1))
+    d.mark_output(d.op("max_pool2d", [x], kernel=(3, 3), stride=(1, 1), pad=(1, 1)))
+    d.mark_output(d.op("avg_pool2d", [x], kernel=(3, 3), stride=(2, 2), pad=(1, 1)))
+    s = clg.Session(d, [("igemm_r16", P("bias_add", P("conv2d", W, W), W)), ("direct", P("max_pool2d", W)), ("direct", P("avg_pool2d", W))], device=0)
+    plan = s.compile(list(range(len(s.match())))).bind()
+    assert plan.regions() == [0] * 7
+    ref = Graph(d).run()
+    one_by_one = plan.run()
+    check_outputs(one_by_one, ref, OP_TOL, "one by one")
+    plan.set_handover([1] * 7, lanes=1)
+    assert plan.n_launches == 1
+    got = plan.run()
+    check_outputs(got, ref, OP_TOL, "one launch")
+    assert all(np.array_equal(a, b) for a, b in zip(got[5:], one_by_one[5:]))
+    s.close()
+
+
+# in the order of their levels, with and without digits, on several streams: the kernels of the sequence, bit for bit
+def test_order_by_level_on_several_lanes():
+    d = wl.nasnet_a(0, image=48, stem=8, filters=8, cells=1, classes=5, batch=2)
+    s = clg.Session(d, wl.default_registry(("igemm_r16",), sepconv=True), device=0)
+    plan = s.compile(s.search([1] * len(s.match()), 0)[1]).bind()
+    n = plan.n_kernels
+    want = plan.run()
+    assert max(norm_err(a, b) for a, b in zip(want, Graph(d).run())) <= 1e-3
+    for lanes, digits in ((2, [1] * n), (4, [1] * n), (4, [i % 2 for i in range(n)]), (3, [int(i % 3 > 0) for i in range(n)])):
+        plan.set_handover(digits, lanes=lanes)
+        assert plan.n_launches >= n - sum(k["name"].endswith("_alias") for k in plan.kernels()) - 2, "regions share launches on one lane only"
+        for _ in range(3):
+            assert all(np.array_equal(a, b) for a, b in zip(plan.run(), want)), (lanes, digits)
+    plan.set_lanes(4)
+    assert all(np.array_equal(a, b) for a, b in zip(plan.run(), want))
     s.close()
 
 
