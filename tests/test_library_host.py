@@ -6,6 +6,8 @@ call is made: contexts are host-only (device = -1).
 import ctypes
 import os
 import re
+import struct
+import subprocess
 
 import numpy as np
 import pytest
@@ -375,6 +377,27 @@ def test_concat_of_kernel_results_is_planned_without_a_copy():
         # aliased: the three pieces live inside the result's 3 x 512 bytes; copied: two pieces + the result
         assert ws == (1536 if not with_input else 1024 + 1536), ws
         s.close()
+
+
+def test_a_region_of_unlike_kinds_reads_its_arguments_where_they_lie(tmp_path):
+    """The 3.6 KB argument block of the kernel is indexed by problem; a compiler that does not see through that gives every lane a copy in scratch memory."""
+    with open(B.LIB_PATH, "rb") as f:
+        blob = f.read()
+    magic, sizes = b"__CLANG_OFFLOAD_BUNDLE__", {}
+    at = blob.find(magic)
+    while at >= 0:
+        p = at + len(magic) + 8
+        for _ in range(struct.unpack_from("<Q", blob, at + len(magic))[0]):
+            start, size, n = struct.unpack_from("<QQQ", blob, p)
+            if b"gfx950" in blob[p + 24:p + 24 + n]:
+                (tmp_path / "code").write_bytes(blob[at + start:at + start + size])
+                if b"mix_kernel" in blob[at + start:at + start + size]:
+                    notes = subprocess.run(["/opt/rocm/llvm/bin/llvm-readelf", "--notes", str(tmp_path / "code")], capture_output=True, text=True, check=True).stdout
+                    for name, scratch in re.findall(r"\.name: +(\S*mix_kernel\S*).*?\.private_segment_fixed_size: (\d+)", notes, re.S):
+                        sizes[name] = int(scratch)
+            p += 24 + n
+        at = blob.find(magic, at + 1)
+    assert len(sizes) == 2 and not any(sizes.values()), sizes
 
 
 @pytest.mark.parametrize("batch,image,mixed", [(1, 224, True), (6, 256, True), (8, 256, False), (10, 224, False), (12, 224, True)])
