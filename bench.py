@@ -255,54 +255,59 @@ def ablation(desc, variants, opts, cost_log, steps, warmup):
     return out
 
 
-def kernel_table(plan, reps=20):
-    """Per-kernel durations (HIP events around every launch, on the launch
-    stream), averaged over `reps` passes."""
+def kernel_table(plan, digits, reps=20):
+    """Per-launch durations (HIP events around every launch, on the launch stream), averaged over `reps` passes: one row
+    per kernel, and one for the kernels of a region that are handed over (`digits`, on one lane) and so share a launch.
+    Joins (a dense layer with the layer norm behind it, the end of a small classifier) are timed as the kernels that
+    they consist of, one by one, which is not how a step runs them."""
     import numpy as np
     plan.execute_timed()
     acc = np.zeros(plan.n_kernels)
     for _ in range(reps):
         acc += plan.execute_timed()
     ns = acc / reps
+    kernels, region = plan.kernels(), plan.regions()
+    launches = {}
+    for i, (q, handed) in enumerate(zip(region, digits)):
+        launches.setdefault(("region", q) if q >= 0 and handed else i, []).append(i)
     rows = []
-    for k, t in zip(plan.kernels(), ns):
-        r = dict(k)
-        r["ns"] = float(t)
-        r["tflops"] = k["flops"] / t / 1e3 if t > 0 else 0.0
-        r["gbps"] = k["bytes"] / t if t > 0 else 0.0
-        rows.append(r)
+    for mem in launches.values():                  # in the order of their first kernels
+        ks = [kernels[i] for i in mem]
+        names = sorted({k["name"] for k in ks})
+        mf = [k for k in ks if k["bound"] == "mfma"]
+        rows.append(dict(name=("" if len(ks) == 1 else f"{len(ks)}x ") + names[0] if len(names) == 1 else f"region of {len(ks)}: " + " ".join(names),
+                         bound="mfma" if mf else ks[0]["bound"],             # a launch with a contraction in it is one
+                         kernels=mem, ns=float(sum(ns[i] for i in mem)), flops=sum(k["flops"] for k in ks), bytes=sum(k["bytes"] for k in ks),
+                         ns_at_peak=sum(k["flops"] / mfma_peak(k) / 1e3 for k in mf), split_operand=any(mfma_peak(k) != PEAK_MFMA_F32_TFLOPS for k in mf)))
     return rows
 
 
-def mfma_peak(row):
+def mfma_peak(kernel):
     """Matrix-core peak of the kernel that runs a contraction, in fp32 flops (the plan names split-operand kernels
     ..._rfb3_...; members of a region by the kernel that each runs alone)."""
-    return PEAK_SPLIT_TFLOPS if "_rfb3_" in row["name"] else PEAK_MFMA_F32_TFLOPS
+    return PEAK_SPLIT_TFLOPS if "_rfb3_" in kernel["name"] else PEAK_MFMA_F32_TFLOPS
 
 
 def roofline_of(rows, step_ns=None):
-    """Dominant kernel family = the MFMA kernels (convolutions / GEMMs):
+    """Dominant kernel family = the MFMA kernels (convolutions / GEMMs), regions that hold one included with all their time:
     algorithmic flops of all their launches in one step over the summed launch
-    durations; peak = those flops over the time they take with each launch at its own kernel's matrix-core peak.  An event pair around every kernel serialises the stream and
-    lengthens each launch (their sum exceeds the step time measured without
-    them), so with `step_ns` given the per-kernel event durations are scaled to
-    add up to that undisturbed step time; the rocprofv3 kernel trace of the
-    same command gives the same per-kernel averages."""
+    durations; peak = those flops over the time they take with each contraction at its own kernel's matrix-core peak.  An event pair around every
+    launch serialises the stream and lengthens each one (their sum exceeds the step time measured without
+    them), so with `step_ns` given the event durations are scaled to
+    add up to that undisturbed step time (joins as their kernels one by one: kernel_table)."""
     total = sum(r["ns"] for r in rows)
     scale = step_ns / total if step_ns and total > 0 else 1.0
     mf = [r for r in rows if r["bound"] == "mfma"]
     t = sum(r["ns"] for r in mf) * scale
     fl = sum(r["flops"] for r in mf)
     achieved = fl / t / 1e3 if t > 0 else 0.0
-    at_peak = sum(r["flops"] / mfma_peak(r) for r in mf)
-    peak = fl / at_peak if at_peak > 0 else PEAK_MFMA_F32_TFLOPS
-    split = sum(1 for r in mf if r["ns"] > 0 and mfma_peak(r) != PEAK_MFMA_F32_TFLOPS)
-    n_launch = sum(1 for r in mf if r["ns"] > 0)       # the members of a fused region count once (the first carries the time)
+    at_peak = sum(r["ns_at_peak"] for r in mf)
+    peak = fl / at_peak / 1e3 if at_peak > 0 else PEAK_MFMA_F32_TFLOPS
     return dict(bound="mfma", achieved=round(achieved, 3), peak=round(peak, 1), unit="TFLOP/s",
                 frac=round(achieved / peak, 5), traffic=None,
-                kernel="MFMA convolution / GEMM kernels (all their launches of one step; fp32 MFMA, or bf16 MFMA with fp32 operands "
-                       "split in three)", launches=n_launch, split_operand_launches=split,
-                avg_launch_us=round(t / max(n_launch, 1) / 1e3, 3),
+                kernel="MFMA convolution / GEMM kernels (all their launches of one step, with joined kernels one by one; fp32 MFMA, or bf16 MFMA "
+                       "with fp32 operands split in three)", launches=len(mf), split_operand_launches=sum(r["split_operand"] for r in mf),
+                avg_launch_us=round(t / max(len(mf), 1) / 1e3, 3),
                 share_of_kernel_time=round(t / max(total * scale, 1), 4))
 
 
@@ -444,7 +449,7 @@ def main():
             f.write("".join(str(int(b)) for b in gl_main["digits"]) + "\n")
     timing["graph_level_s"] = gl_main["search_s"]
     ms_per_step = time_steps(plan, args.steps, args.warmup)
-    rows = kernel_table(plan)
+    rows = kernel_table(plan, gl_main["digits"])
     roof = roofline_of(rows, ms_per_step * 1e6)
     roof["algorithmic_bytes"] = int(sum(r["bytes"] for r in rows if r["bound"] == "mfma"))
     roof["algorithmic_flops"] = int(sum(r["flops"] for r in rows if r["bound"] == "mfma"))
@@ -467,7 +472,7 @@ def main():
             s2, p2, _, _, t2 = optimise(d2, reg, opts, "", rules)
             gl2 = graph_level(p2, max(20, args.steps // 2), args.warmup)
             ms2 = time_steps(p2, max(20, args.steps // 2), args.warmup)
-            r2 = kernel_table(p2, reps=5)
+            r2 = kernel_table(p2, gl2["digits"], reps=5)
             roof2 = roofline_of(r2, ms2 * 1e6)
             roof2["algorithmic_bytes"] = int(sum(r["bytes"] for r in r2 if r["bound"] == "mfma"))
             roof2["algorithmic_flops"] = int(sum(r["flops"] for r in r2 if r["bound"] == "mfma"))
@@ -524,10 +529,13 @@ def main():
         scale = ms_per_step * 1e6 / sum(r["ns"] for r in rows)
         cpu_us = None
         if not args.no_cpu:
-            cpu_us = oracle_us_per_group(desc, [list(s.matches[r["match"]].nodes[:s.matches[r["match"]].n_nodes]) for r in rows])
-        lines = [f"{args.model} batch 1 fp32, one MI355X: the {len(rows)} fused kernels of one step in execution order.",
+            ks = [s.matches[k["match"]] for k in plan.kernels()]
+            us = oracle_us_per_group(desc, [list(m.nodes[:m.n_nodes]) for m in ks])
+            cpu_us = [sum(us[i] for i in r["kernels"]) for r in rows]
+        lines = [f"{args.model} batch 1 fp32, one MI355X: the {plan.n_kernels} fused kernels of one step in execution order, kernels that share a launch in one line.",
                  f"Durations: HIP event pair around every launch, scaled by {scale:.3f} so that they add up to the step time "
-                 f"measured without the events ({ms_per_step * 1e3:.1f} us).",
+                 f"measured without the events ({ms_per_step * 1e3:.1f} us).  Joins (a dense layer with the layer norm behind it, the end of a small "
+                 "classifier) run as one in a step and are timed here as the kernels that they consist of.",
                  f"Peaks: fp32 MFMA {PEAK_MFMA_F32_TFLOPS} TFLOP/s (split-operand kernels, _rfb3_: {PEAK_SPLIT_TFLOPS:.1f}), HBM {PEAK_HBM_GBPS} GB/s.  flops / bytes are the operator's own "
                  "(no padding or tile waste; every operand and the output once).",
                  ] + (["oracle us: the CPU oracle's time for the same fused group (sum over its operators, all host cores)."]
@@ -546,22 +554,24 @@ def main():
                 a["bytes"] += r["bytes"]
                 a["cpu"] += cpu_us[i] if cpu_us else 0.0
             lines = lines[:-1]
-            lines[0] = f"{args.model} batch 1 fp32, one MI355X: the {len(rows)} fused kernels of one step summed by kernel name."
+            lines[0] = f"{args.model} batch 1 fp32, one MI355X: the {len(rows)} launches of one step summed by name."
             lines.append(f"{'kernel':34s} {'bound':5s} {'count':>5s} {'sum us':>8s} {'avg us':>7s} {'MFLOP':>9s} {'KB':>10s} "
                          f"{'TFLOP/s':>8s} {'GB/s':>8s}" + (f" {'oracle us':>10s}" if cpu_us else ""))
             for name, a in sorted(agg.items(), key=lambda kv: -kv[1]["ns"]):
                 t = max(a["ns"], 1.0)
                 lines.append(f"{name[:34]:34s} {a['bound']:5s} {a['n']:5d} {a['ns'] / 1e3:8.1f} {a['ns'] / a['n'] / 1e3:7.2f} "
                              f"{a['flops'] / 1e6:9.1f} {a['bytes'] / 1e3:10.1f} {a['flops'] / t / 1e3:8.3f} {a['bytes'] / t:8.1f}"
-                             + (f" {a['cpu']:10.0f}" if cpu_us else ""))
+                             + (f" {a['cpu']:10.0f}" if cpu_us else "")
+                             + (f"  {name}" if len(name) > 34 else ""))
         else:
             for i, r in enumerate(rows):
                 t = r["ns"] * scale
                 tf, gb = (r["flops"] / t / 1e3, r["bytes"] / t) if t > 0 else (0.0, 0.0)
-                frac = tf / mfma_peak(r) if r["bound"] == "mfma" else gb / PEAK_HBM_GBPS
+                frac = (r["ns_at_peak"] / t if t > 0 else 0.0) if r["bound"] == "mfma" else gb / PEAK_HBM_GBPS
                 lines.append(f"{i:3d} {r['name'][:34]:34s} {r['bound']:5s} {t / 1e3:7.2f} {r['flops'] / 1e6:9.1f} "
                              f"{r['bytes'] / 1e3:9.1f} {tf:8.2f} {gb:8.1f} {frac:8.4f}"
-                             + (f" {cpu_us[i]:10.0f}" if cpu_us else ""))
+                             + (f" {cpu_us[i]:10.0f}" if cpu_us else "")
+                             + (f"  {r['name']}" if len(r["name"]) > 34 else ""))
         if cpu_us and len(rows) > 150:
             lines.append(f"{'sum':34s} {'':5s} {len(rows):5d} {sum(r['ns'] for r in rows) * scale / 1e3:8.1f} {'':7s} {'':9s} {'':10s} {'':8s} {'':8s} "
                          f"{sum(cpu_us):10.0f}")
