@@ -40,7 +40,9 @@ __device__ __forceinline__ void mix_sep(const SepConvArgs &a, const int local, f
 }
 
 // WIDE: with the kinds of more than 128 registers (7x7 depthwise convolutions, separable ones of 5x5 and 7x7); a launch without them has
-// four resident waves per SIMD instead of two.
+// four resident waves per SIMD instead of two.  All of NasNet-A under one placement, every region in one launch, us: 4 x 231x231 971 with the wide kernel for
+// all regions and 921 with this rule; 1 x 224x224 534 and 534, 2 x 101x101 530 and 528, where launches hardly fill a round.  Wide kinds stay members all the same
+// (out of such regions 589, 541 and 905, 13 - 5 launches more; where the members of a large one lose by it, the search turns their digits off).
 constexpr bool mix_wide(int32_t kind) {
     return kind == MIX_DW7 || kind == MIX_SEP4 + 5 || kind == MIX_SEP4 + 7 || kind == MIX_SEP8 + 5 || kind == MIX_SEP8 + 7;
 }
