@@ -324,8 +324,10 @@ bool attention_shape_ok(const AttentionArgs &a) {
 }
 
 // Two row tiles share each load of k and v, where single ones would be more than one workgroup per compute unit from 385 keys on, more
-// than two below (twelve heads, one and two row tiles, us: 389 keys, heads of 64, 15.1 and 14.3, heads of 32 9.3 and 9.0; 512 keys 17.6 and
-// 16.4).  Heads of 128 have no registers for a second row tile.
+// than two below (twelve heads, one and two row tiles, us: 389 keys, heads of 64, 14.1 and 13.7, heads of 32 9.0 and 8.8; 512 keys 16.1 and 15.4, 10.3 and 9.9; 384
+// heads of 64, 300 keys, 126 and 118).  The line is drawn at twelve heads, where both are one round: from 385 keys on a compute unit holds two workgroups with one row tile
+// but one with two, and many heads take longer with two (24 heads, 389 keys, heads of 64 20.1 and 26.1, of 32 12.1 and 14.0; 96 heads 57 and 65, 32 and 31; 384 heads
+// 206 and 241, 112 and 112).  Heads of 128 have no registers for a second row tile.
 // Reading ahead: at most 64 workgroups, last, in whole rows of the grid, and only on compute units that have none of the others (one in
 // the way of those made all of BERT-base on 512 rows 7 % slower).
 AttentionGrid attention_grid(const AttentionArgs &a) {

@@ -378,8 +378,8 @@ size_t plan_num_launches(const Plan &p) {
 //  * How much: a layer norm 16 MB, which make it 1 us longer; more makes it longer than the dense layers gain (BERT-base, 389 rows: 14 MB more in a
 //    layer norm 1102 instead of 1077 us).  Attention 2.4 MB per microsecond that it takes itself, and no more than 61 KB per read-ahead workgroup of its
 //    launch (17.7 MB in 8 us: on 36 workgroups, 288 rows, 853 us, with 3.5 MB instead 873; on 19, 304 rows, 948 and 879).  It takes 4 us, and the
-//    products of a workgroup at 310 GFLOP per second (heads of 64, measured alone and by this: 128 keys 4.8 and 5.7 us, 256 6.8 and 7.4, 389 14.3 and
-//    14.3, 512 16.4 and 17.5).
+//    products of a workgroup at 310 GFLOP per second (heads of 64, measured alone and by this: 128 keys 4.8 and 5.7 us, 256 6.6 and 7.4, 389 13.7 and
+//    14.3, 512 15.4 and 17.5).
 //  * Where: attention with room for all that lies before the kernel after next that could read ahead takes all of it (389 rows: 1077 us, with
 //    a share in the layer norm 1099, without any 1123); otherwise the nearest one before that has room (256 rows: 795, attention first 820, without 864).
 //  * From 96 rows on: below, everything takes a few microseconds and reading ahead prolongs what it hides in (us without and with, all of BERT-base: 16 rows 435
