@@ -285,7 +285,7 @@ void find_regions(const Context &ctx, const Graph &g, bool allow_mixed, Plan *pl
 // number T of 16 x 16 tiles on 256 compute units (us; layers written K -> N):
 //  * T <= half the compute units, from K = 2048 on.  3072 -> 768 T = 48 434 and 401, 96 460 and 448; 4096 -> 1024 64 327 and 292, 128 363 and 348; 2048 -> 512 64 321 and 311, 128 349 and 345;
 //    3584 -> 896 56 357 and 330; 6144 -> 1536 96 238 and 229; 2816 -> 704 44 432 and 399; 2560 -> 768 96 447 and 447; the one loss 2560 -> 640 120 416 and 422.
-//  * One round of tiles and up to half a second: nothing to gain (3072 -> 768 144, 192 and 240: 476 and 476, 497 and 496, 511 and 513).
+//  * From half a round of tiles to one: nothing to gain (3072 -> 768 144, 192 and 240: 476 and 476, 497 and 496, 511 and 513).
 //  * Between one round of tiles and one and a quarter, where K's chunks share out evenly over slices and waves (K % 1024 = 0) and the layer norm has four slices in flight
 //    (N <= 1024): 3072 -> 768 288 589 and 575, 4096 -> 768 288 643 and 630, 4096 -> 1024 320 475 and 469, 3072 -> 1024 320 433 and 423, 3072 -> 512 288 760 and 719; otherwise 2560 -> 640 320 547 and 562,
 //    3584 -> 896 280 498 and 506, 3072 -> 1152 288 351 and 355.  From K = 3072 on: 2048 -> 768 288 490 and 517, 2048 -> 512 320 496 and 496.
